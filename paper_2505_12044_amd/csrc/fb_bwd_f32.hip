@@ -1,254 +1,357 @@
-// fp32 backward of attention with a factorised additive bias: all arithmetic in fp32 FMA, the
-// full-precision companion of fb_fwd_f32.hip (gfx950's fp32 matrix rate equals its fp32 vector
-// rate, so there is nothing to gain from MFMA here).
+// fp32 backward of attention with a factorised (or materialised) additive bias, every product and sum in
+// fp32 (v_mfma_f32_32x32x2_f32); the full-precision companion of fb_fwd_f32.hip.
 //
 // With S = [q*scale | phi_q] . [k | phi_k]^T (FlashBias Eq. 3), P = exp(S - lse) and
 // D_i = sum_c dout_ic out_ic, the gradient of the scores is dS = P o (dout V^T - D), and
-//   [dq / scale | dphi_q] = dS   [k | phi_k]          (query-side kernel, one pass over the keys)
-//   [dk | dphi_k]         = dS^T [q*scale | phi_q]    (key-side kernel, one pass over the queries)
+//   [dq / scale | dphi_q] = dS   [k | phi_k]          (query-side launch, one pass over the keys)
+//   [dk / scale | dphi_k / 1] = dS^T [q | phi_q]      (key-side launch, one pass over the queries)
 //   dv                    = P^T  dout
 // so the factor gradients are the trailing R columns of the contractions that give dq and dk
-// (Sec. 3.2 "Speed up training").  Nothing N x N is stored; each kernel recomputes S from the
-// operand rows.  Deterministic: every output element is summed by one thread in a fixed order.
+// (Sec. 3.2 "Speed up training").  Nothing N x N is stored; each launch recomputes S and dP.
+// Deterministic: every output element is summed in a fixed order, without atomics.
 //
-// Work split: a workgroup of 256 threads owns 64 rows (queries in the first kernel, keys in the
-// second), four threads per row, thread t of a row holding the channels c = t (mod 4) of the row's
-// operands and accumulators (at most (2 (C + RP) + 2 C) / 4 = 160 registers of state).  The rows
-// of the other side pass through LDS in tiles of 32; all threads read the same tile row at the
-// same time (a broadcast), and the two dot products of a score are finished with two
-// cross-lane additions.  The query-side kernel also writes D (one float per query row) into the
-// caller's workspace for the key-side kernel, which runs after it on the same stream.
+// One wave owns 32 rows of its side (lanes), the streamed side comes in blocks of 32 rows (accumulator
+// registers): S and dP take the streamed rows as row operands (16 bytes a lane) and their results are,
+// register for register, the second operand of the output contractions, whose first operand is the
+// streamed rows read down their columns (4 bytes a lane, 128 bytes in a row).  Both come straight from
+// global memory into registers ahead of their use (rows: NPF chunks of four k-steps, columns: one tile of
+// sixteen k-steps); a k-step holds the matrix pipe for 64 cycles, so the vector cache keeps up
+// and the loop has no barrier and no LDS.  Bound: the matrix pipe.  The query-side launch also writes D
+// into the caller's workspace for the key-side launch behind it.
+// Measured, B 2, H 8, N 1500, C 64, R 8: 874 -> 169 us (query side) and 955 -> 253 us (key side, whose accumulators
+// leave one wave per SIMD) against the four-threads-per-row FMA kernel this replaced.
+// Where the tiles are too few to fill the chip, KW waves share one and take every KW-th block each; their
+// sums meet in LDS at the end.
 #include <hip/hip_runtime.h>
 
+#include "fb_f32_tiles.h"
 #include "fb_launch.h"
 #include "fb_params.h"
 
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kRows = kThreads / 4;   // rows per workgroup
-constexpr int kTile = 32;             // rows of the other side per LDS tile
+constexpr int BT = 32;       // streamed rows per block
+constexpr int OPITCH = 36;   // row pitch of an output tile in LDS (floats)
 
-__device__ __forceinline__ float quad_sum(float x) {
-    x += __shfl_xor(x, 1);
-    x += __shfl_xor(x, 2);
-    return x;
-}
+template <int C, int RP, bool KEYSIDE>
+struct Cfg {
+    static constexpr int W = C + RP;
+    static constexpr int NCH = W / 8, NC2 = C / 8;         // row chunks of S and of dP
+    static constexpr int NALL = NCH + NC2;
+    static constexpr int NPF = NALL < 6 ? NALL : 6;        // row chunks in flight
+    static constexpr int TA = (W + 31) / 32;               // 32-column tiles of d[x | phi]
+    static constexpr int TE = KEYSIDE ? (C + 31) / 32 : 0; // ... of dv
+    static constexpr int kRegs = (W + C) / 2 + 16 * (TA + TE) + 32 + 4 * NPF + 32 + (KEYSIDE ? 32 : 0);
+    static constexpr int kMinWaves = kRegs <= (C == 16 ? 190 : 225) ? 2 : 1;      // waves per SIMD the registers allow
+};
 
-// KEYSIDE = false: rows are queries, tiles are keys; outputs dq, dphi_q, D (and dBias when DENSE).
-// KEYSIDE = true:  rows are keys, tiles are queries; outputs dk, dv, dphi_k.
-// DENSE: the bias is a materialised [N, M] matrix per head, added to the scores (the training-side
-// baseline of Sec. 4.3); its gradient dBias = dS is written by the query-side pass, zero where masked.
+// KEYSIDE = false: lanes are queries, keys are streamed; outputs dq, dphi_q, D (and dBias when DENSE).
+// KEYSIDE = true:  lanes are keys, queries are streamed; outputs dk, dv, dphi_k.
+// DENSE: the bias is a materialised [N, M] matrix per head, the start value of the score chain (the
+// training-side baseline of Sec. 4.3); dBias = dS is written by the query-side launch, zero where masked.
 template <int C, int RP, bool KEYSIDE, bool DENSE = false>
-__global__ __launch_bounds__(kThreads) void bwd_f32_kernel(BwdParams p, float* __restrict__ Dws) {
-    constexpr int W = C + RP;
-    constexpr int WQ = W / 4, CQ = C / 4;
-    static_assert(W % 4 == 0 && C % 4 == 0, "four threads per row");
-    __shared__ float ts[kTile][W + 1];       // tile rows [x | phi] of the other side (queries: x = q*scale)
-    __shared__ float tv[kTile][C + 1];       // tile rows v (query side) or dout (key side)
-    __shared__ float tl[kTile], td[kTile];   // key side: lse and D of the tile's queries
-    // dense bias of (this workgroup's rows) x (the tile's rows): [own row][tile row] on the query side,
-    // [tile row][own row] on the key side, so that both are filled along the key index (coalesced)
-    __shared__ float tb[DENSE ? (KEYSIDE ? kTile : kRows) : 1][DENSE ? (KEYSIDE ? kRows : kTile) + 1 : 1];
+__global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bwd_f32_kernel(BwdParams p, float* __restrict__ Dws, int kw_log2) {
+    using K = Cfg<C, RP, KEYSIDE>;
+    __shared__ __align__(16) float otile[kThreads / 64][32 * OPITCH];
+    const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);      // contiguous runs of units per XCD
+    if (L >= p.total_tiles) return;
+    const int bh = L / p.n_tiles;                          // p.n_tiles: workgroups per (b, h)
+    const int u0 = L - bh * p.n_tiles;
+    const int u = (p.causal && !KEYSIDE) ? p.n_tiles - 1 - u0 : u0;      // causal: long tiles first
+    const int b = bh / p.H, h = bh - b * p.H;
+    const int N = p.N, M = p.M, R = p.R;                   // N queries, M keys
+    const int NL = KEYSIDE ? M : N;                        // rows on the lane side
+    const int NO = KEYSIDE ? N : M;                        // rows on the streamed side
 
-    const int tid = threadIdx.x;
-    const int t = tid & 3;
-    const int bh = blockIdx.x / p.n_tiles;
-    const int rt = blockIdx.x % p.n_tiles;
-    const int b = bh / p.H, h = bh % p.H;
-    const int N = p.N, M = p.M, R = p.R;       // N queries, M keys (M = N unless cross-attention)
-    const int NL = KEYSIDE ? M : N;            // rows on this kernel's own side
-    const int NO = KEYSIDE ? N : M;            // rows on the streamed side
-    const int row = rt * kRows + (tid >> 2);
-    const bool valid = row < NL;
-    const int rowc = valid ? row : NL - 1;    // clamped: finite values, never stored
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int KW = 1 << kw_log2;
+    const int part = wave & (KW - 1);
+    const int tile = u * ((kThreads / 64) >> kw_log2) + (wave >> kw_log2);
+    const int row0 = tile * 32;
+    const int row = row0 + l32;
+    const int rowc = min(row, NL - 1);                     // rows past the end compute on the last row and are not stored
 
-    const size_t base = (size_t)bh * N * C;    // query-side tensors
-    const size_t kbase = (size_t)bh * M * C;   // key-side tensors
-    const float* qg = (const float*)p.q + base;
+    const size_t qbase = (size_t)bh * N * C, kbase = (size_t)bh * M * C;
+    const float* pq = RP > 0 ? (const float*)p.phi_q + (size_t)b * p.phi_bstride + (size_t)h * N * R : nullptr;
+    const float* pk = RP > 0 ? (const float*)p.phi_k + (size_t)b * p.phik_bstride + (size_t)h * M * R : nullptr;
+    const float* qg = (const float*)p.q + qbase;
     const float* kg = (const float*)p.k + kbase;
     const float* vg = (const float*)p.v + kbase;
-    const float* og = (const float*)p.out + base;
-    const float* dog = (const float*)p.dout + base;
+    const float* dog = (const float*)p.dout + qbase;
     const float* lseg = p.lse + (size_t)bh * N;
     float* Dg = Dws + (size_t)bh * N;
+    // lane-side rows
+    const float* xrow = (KEYSIDE ? kg : qg) + (size_t)rowc * C;
+    const float* prow = RP > 0 ? (KEYSIDE ? pk : pq) + (size_t)rowc * R : nullptr;
+    const float* erow = (KEYSIDE ? vg : dog) + (size_t)rowc * C;
+    // streamed arrays
+    F32Rows oth;
+    oth.x = make_buf(KEYSIDE ? qg : kg, (size_t)NO * C * 4);
+    oth.phi = RP > 0 ? make_buf(KEYSIDE ? pq : pk, (size_t)NO * R * 4) : oth.x;
+    oth.R = R;
+    const f32_buf eoth = make_buf(KEYSIDE ? dog : vg, (size_t)NO * C * 4);
+    const f32_buf lbuf = make_buf(lseg, (size_t)N * 4), dbuf = make_buf(Dg, (size_t)N * 4);
     const float* bg = nullptr;
     float* dbg = nullptr;
     if (DENSE) {
         bg = (const float*)p.bias + (size_t)b * p.bias_bstride + (size_t)h * N * M;
         dbg = (float*)p.dbias + (size_t)bh * N * M;
     }
-    const float* pqg = nullptr;
-    const float* pkg = nullptr;
-    if (RP > 0) {
-        pqg = (const float*)p.phi_q + (size_t)b * p.phi_bstride + (size_t)h * N * R;
-        pkg = (const float*)p.phi_k + (size_t)b * p.phik_bstride + (size_t)h * M * R;
-    }
 
-    // this thread's channels of its row: a[u] <-> column t + 4u of [x | phi], e[u] <-> channel t + 4u
-    float a[WQ], e[CQ];
-    float acc_a[WQ], acc_e[KEYSIDE ? CQ : 1];
+    // ---- lane-side operands: the scale sits on the lane side's x columns ----
+    f32x4 ar[K::NCH], er[K::NC2];
+#pragma unroll
+    for (int i = 0; i < K::NCH; i++) {
+        ar[i] = own_chunk<C>(xrow, prow, R, i, hf);
+        if (8 * i < C) ar[i] *= p.scale;
+    }
+#pragma unroll
+    for (int i = 0; i < K::NC2; i++) er[i] = *(const f32x4*)(erow + 8 * i + 4 * hf);
     float lse_r = 0.f, d_r = 0.f;
-#pragma unroll
-    for (int u = 0; u < WQ; u++) {
-        const int c = t + 4 * u;
-        float x = 0.f;
-        if (c < C) x = KEYSIDE ? kg[(size_t)rowc * C + c] : qg[(size_t)rowc * C + c] * p.scale;
-        else if (c - C < R) x = KEYSIDE ? pkg[(size_t)rowc * R + (c - C)] : pqg[(size_t)rowc * R + (c - C)];
-        a[u] = x;
-        acc_a[u] = 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < CQ; u++) {
-        const int c = t + 4 * u;
-        e[u] = KEYSIDE ? vg[(size_t)rowc * C + c] : dog[(size_t)rowc * C + c];
-        if (KEYSIDE) acc_e[u] = 0.f;
-    }
     if (!KEYSIDE) {
-        float part = 0.f;
+        const float* orow = (const float*)p.out + qbase + (size_t)rowc * C;
+        float sum = 0.f;
 #pragma unroll
-        for (int u = 0; u < CQ; u++) part = fmaf(e[u], og[(size_t)rowc * C + t + 4 * u], part);
-        d_r = quad_sum(part);
+        for (int i = 0; i < K::NC2; i++) {
+            const f32x4 x = *(const f32x4*)(orow + 8 * i + 4 * hf);
+#pragma unroll
+            for (int e = 0; e < 4; e++) sum = fmaf(er[i][e], x[e], sum);
+        }
+        d_r = half_sum(sum);
         lse_r = lseg[rowc];
-        if (valid && t == 0) Dg[row] = d_r;
+        if (part == 0 && hf == 0 && row < NL) Dg[row] = d_r;
     }
 
-    // range of the other side this workgroup's rows can see
-    int o_begin = 0, o_end = NO;
-    if (p.causal) {                                              // (N = M)
-        if (KEYSIDE) o_begin = (rt * kRows / kTile) * kTile;      // queries i >= j
-        else o_end = min(NO, (rt + 1) * kRows);                  // keys j <= i
+    f32x16 acca[K::TA], acce[K::TE > 0 ? K::TE : 1];
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+#pragma unroll
+        for (int t = 0; t < K::TA; t++) acca[t][r] = 0.f;
+#pragma unroll
+        for (int t = 0; t < (K::TE > 0 ? K::TE : 1); t++) acce[t][r] = 0.f;
     }
 
-    for (int o0 = o_begin; o0 < o_end; o0 += kTile) {
-        __syncthreads();
-        for (int x = tid; x < kTile * W; x += kThreads) {
-            const int rr = x / W, c = x % W;
-            const int orow = o0 + rr;
-            float val = 0.f;
-            if (orow < NO) {
-                if (c < C) val = KEYSIDE ? qg[(size_t)orow * C + c] * p.scale : kg[(size_t)orow * C + c];
-                else if (c - C < R) val = KEYSIDE ? pqg[(size_t)orow * R + (c - C)] : pkg[(size_t)orow * R + (c - C)];
+    // ---- streamed blocks [b0, b1): with a causal mask (N = M) the tile's own block is the diagonal one ----
+    const int nall = (NO + BT - 1) / BT;
+    int b0 = 0, b1 = nall;
+    if (p.causal) {
+        if (KEYSIDE) b0 = min(tile, nall);
+        else b1 = min(nall, tile + 1);
+    }
+    if (row0 >= NL) b1 = b0 = 0;
+
+    // row operands, chunk n of a block: S chunks, then dP chunks
+    f32x4 rc[K::NPF];
+    auto load_row = [&](int blk, int n) __attribute__((always_inline)) {
+        const unsigned r = (unsigned)(blk * BT + l32);
+        return n < K::NCH ? row_chunk<C>(oth, r, n, hf) : buf_f32x4(eoth, r * (C * 4u) + 16u * hf + 32u * (n - K::NCH));
+    };
+    // column operands, tile t of a block: dv tiles (of the streamed dout rows), then d[x | phi] tiles.  Columns
+    // past C + R read some real element (computed, never stored).
+    constexpr int NT = K::TE + K::TA;
+    float cc[2][16];
+    auto load_cols = [&](int blk, int t) __attribute__((always_inline)) {
+        const unsigned r0 = (unsigned)(blk * BT + 4 * hf);
+        const int c0 = (t < K::TE ? t : t - K::TE) * 32;
+        if (t < K::TE || c0 < C) {
+            const unsigned off = r0 * (C * 4u) + 4u * (l32 & (C < 32 ? C - 1 : 31)) + 4u * c0;
+#pragma unroll
+            for (int r = 0; r < 16; r++) cc[t & 1][r] = buf_f32(t < K::TE ? eoth : oth.x, off + (8 * (r / 4) + r % 4) * (C * 4u));
+        }
+        if (RP > 0 && t >= K::TE && c0 + 32 > C) {
+            const int pc = min(max(c0 + l32 - C, 0), R - 1);
+            unsigned off = (r0 * (unsigned)R + (unsigned)pc) * 4u;
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const float x = buf_f32(oth.phi, off);
+                cc[t & 1][r] = c0 < C && l32 < C ? cc[t & 1][r] : x;      // (head dimension 16: a tile of both)
+                off += (r & 3) == 3 ? 20u * (unsigned)R : 4u * (unsigned)R;
             }
-            ts[rr][c] = val;
         }
-        for (int x = tid; x < kTile * C; x += kThreads) {
-            const int rr = x / C, c = x % C;
-            const int orow = o0 + rr;
-            tv[rr][c] = orow < NO ? (KEYSIDE ? dog[(size_t)orow * C + c] : vg[(size_t)orow * C + c]) : 0.f;
+    };
+    float lq[KEYSIDE ? 16 : 1], dqv[KEYSIDE ? 16 : 1];      // key side: lse and D of the streamed queries
+    auto load_vec = [&](int blk) __attribute__((always_inline)) {
+        if (!KEYSIDE) return;
+        const unsigned off = (unsigned)(blk * BT + 4 * hf) * 4u;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            lq[r % (KEYSIDE ? 16 : 1)] = buf_f32(lbuf, off + (8 * (r / 4) + r % 4) * 4u);
+            dqv[r % (KEYSIDE ? 16 : 1)] = buf_f32(dbuf, off + (8 * (r / 4) + r % 4) * 4u);
         }
-        if (KEYSIDE && tid < kTile) {
-            const int orow = o0 + tid;
-            tl[tid] = orow < NO ? lseg[orow] : 0.f;
-            td[tid] = orow < NO ? Dg[orow] : 0.f;
-        }
-        if (DENSE) {
-            if (KEYSIDE) {       // tb[query of the tile][key of this workgroup]
-                for (int x = tid; x < kTile * kRows; x += kThreads) {
-                    const int rr = x / kRows, cc = x % kRows;
-                    const int qi = o0 + rr, kj = rt * kRows + cc;
-                    tb[rr][cc] = (qi < N && kj < M) ? bg[(size_t)qi * M + kj] : 0.f;
+    };
+    float bv[DENSE ? 16 : 1];
+    const bool vec_m = DENSE && (M & 3) == 0;
+    auto load_bias = [&](int blk) __attribute__((always_inline)) {
+        if (!DENSE) return;
+        if (KEYSIDE) {
+#pragma unroll
+            for (int r = 0; r < 16; r++)
+                bv[r % (DENSE ? 16 : 1)] = bg[(size_t)min(blk * BT + acc_row(r, hf), N - 1) * M + rowc];
+        } else {
+            const float* brow = bg + (size_t)rowc * M;
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const int j = blk * BT + 8 * g + 4 * hf;
+                if (vec_m) {
+                    const f32x4 t = *(const f32x4*)(brow + min(j, M - 4));
+#pragma unroll
+                    for (int x = 0; x < 4; x++) bv[(4 * g + x) % (DENSE ? 16 : 1)] = t[x];
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 4; x++) bv[(4 * g + x) % (DENSE ? 16 : 1)] = brow[min(j + x, M - 1)];
                 }
-            } else {             // tb[query of this workgroup][key of the tile]
-                for (int x = tid; x < kRows * kTile; x += kThreads) {
-                    const int rr = x / kTile, cc = x % kTile;
-                    const int qi = rt * kRows + rr, kj = o0 + cc;
-                    tb[rr][cc] = (qi < N && kj < M) ? bg[(size_t)qi * M + kj] : 0.f;
+            }
+        }
+    };
+
+    if (b0 + part < b1) {
+        const int blk = b0 + part;
+#pragma unroll
+        for (int n = 0; n < K::NPF; n++) rc[n] = load_row(blk, n);
+        load_vec(blk);
+        load_bias(blk);
+        load_cols(blk, 0);
+    }
+    for (int blk = b0 + part; blk < b1; blk += KW) {
+        const int nxt = min(blk + KW, b1 - 1);
+        if (NT > 1) load_cols(blk, 1);
+        __builtin_amdgcn_sched_barrier(0);      // requests stay ahead of the chains they land under
+        f32x16 s, dp;
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            s[r] = DENSE ? bv[r % (DENSE ? 16 : 1)] : 0.f;
+            dp[r] = 0.f;
+        }
+#pragma unroll
+        for (int n = 0; n < K::NALL; n++) {
+            const f32x4 a = rc[n % K::NPF];
+            if (n + K::NPF < K::NALL) rc[n % K::NPF] = load_row(blk, n + K::NPF);
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                if (n < K::NCH) s = mfma32f(a[e], ar[n][e], s);
+                else dp = mfma32f(a[e], er[n - K::NCH][e], dp);
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < K::NPF; n++) rc[n] = load_row(nxt, n);
+        load_bias(nxt);
+        __builtin_amdgcn_sched_barrier(0);
+        // P in s, dS in dp
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            s[r] = fast_exp2((s[r] - (KEYSIDE ? lq[r % (KEYSIDE ? 16 : 1)] : lse_r)) * kLog2e);
+            dp[r] = s[r] * (dp[r] - (KEYSIDE ? dqv[r % (KEYSIDE ? 16 : 1)] : d_r));
+        }
+        if (blk * BT + BT > NO || (p.causal && blk == tile)) {
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                const int o = blk * BT + acc_row(r, hf);
+                if (o >= NO || (p.causal && (KEYSIDE ? o < row : o > row))) { s[r] = 0.f; dp[r] = 0.f; }
+            }
+        }
+        load_vec(nxt);
+        if (DENSE && !KEYSIDE && row < NL) {
+            float* drow = dbg + (size_t)row * M;
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const int j = blk * BT + 8 * g + 4 * hf;
+                if (vec_m) {
+                    if (j < M) *(f32x4*)(drow + j) = f32x4{dp[4 * g], dp[4 * g + 1], dp[4 * g + 2], dp[4 * g + 3]};
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 4; x++)
+                        if (j + x < M) drow[j + x] = dp[4 * g + x];
                 }
             }
         }
-        __syncthreads();
-
-#pragma unroll 2
-        for (int rr = 0; rr < kTile; rr++) {
-            const int orow = o0 + rr;
-            float sp = 0.f, dpp = 0.f;
 #pragma unroll
-            for (int u = 0; u < WQ; u++) sp = fmaf(a[u], ts[rr][t + 4 * u], sp);
+        for (int t = 0; t < NT; t++) {
 #pragma unroll
-            for (int u = 0; u < CQ; u++) dpp = fmaf(e[u], tv[rr][t + 4 * u], dpp);
-            float s = quad_sum(sp);
-            if (DENSE) s += KEYSIDE ? tb[rr][tid >> 2] : tb[tid >> 2][rr];
-            const float dp = quad_sum(dpp);     // dout_i . v_j
-            // query i and key j of this pair
-            const int qi = KEYSIDE ? orow : row;
-            const int kj = KEYSIDE ? row : orow;
-            const bool live = orow < NO && valid && !(p.causal && kj > qi);
-            const float lse_i = KEYSIDE ? tl[rr] : lse_r;
-            const float d_i = KEYSIDE ? td[rr] : d_r;
-            const float pr = live ? expf(s - lse_i) : 0.f;
-            const float ds = pr * (dp - d_i);
-            // dBias = dS: the four threads of a row take turns over the tile's keys
-            if (DENSE && !KEYSIDE && valid && orow < NO && (rr & 3) == t) dbg[(size_t)row * M + orow] = ds;
-#pragma unroll
-            for (int u = 0; u < WQ; u++) acc_a[u] = fmaf(ds, ts[rr][t + 4 * u], acc_a[u]);
-            if (KEYSIDE) {
-#pragma unroll
-                for (int u = 0; u < CQ; u++) acc_e[u] = fmaf(pr, tv[rr][t + 4 * u], acc_e[u]);
+            for (int r = 0; r < 16; r++) {
+                if (t < K::TE) acce[t < K::TE ? t : 0] = mfma32f(cc[t & 1][r], s[r], acce[t < K::TE ? t : 0]);
+                else acca[t < K::TE ? 0 : t - K::TE] = mfma32f(cc[t & 1][r], dp[r], acca[t < K::TE ? 0 : t - K::TE]);
             }
+            if (t + 2 < NT) load_cols(blk, t + 2);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        load_cols(nxt, 0);
+    }
+    if (DENSE && !KEYSIDE && p.causal && row < NL) {
+        // keys past the tile's diagonal block were never visited: their dBias entries are zero
+        float* drow = dbg + (size_t)row * M;
+        for (int blk = b1 + part; blk < nall; blk += KW)
+            for (int x = hf; x < BT; x += 2)
+                if (blk * BT + x < M) drow[blk * BT + x] = 0.f;
     }
 
-    if (DENSE && !KEYSIDE && p.causal) {
-        // the keys past this workgroup's last query were never visited: their dBias entries are zero
-        const int k0 = ((o_end + kTile - 1) / kTile) * kTile;
-        const int w = M - k0;
-        if (w > 0) {
-            for (long long x = tid; x < (long long)kRows * w; x += kThreads) {
-                const int rr = (int)(x / w), cc = (int)(x % w);
-                const int qi = rt * kRows + rr;
-                if (qi < N) dbg[(size_t)qi * M + k0 + cc] = 0.f;
-            }
-        }
-    }
-    if (!valid) return;
-    float* dxg = (float*)(KEYSIDE ? p.dk : p.dq) + (KEYSIDE ? kbase : base);
+    // ---- epilogue: tile by tile through LDS, where the KW partial sums meet; rows leave 16 bytes a thread ----
+    float* dxg = (float*)(KEYSIDE ? p.dk : p.dq) + (KEYSIDE ? kbase : qbase);
+    float* dvg = KEYSIDE ? (float*)p.dv + kbase : nullptr;
     float* dphig = (float*)(KEYSIDE ? p.dphi_k : p.dphi_q);      // [B,H,N or M,R], per batch element; may be NULL
     if (dphig) dphig += (size_t)bh * NL * R;
 #pragma unroll
-    for (int u = 0; u < WQ; u++) {
-        const int c = t + 4 * u;
-        // the tile rows carried q*scale (key side) resp. k (query side): dk = dS^T (q*scale), dq = scale dS k
-        if (c < C) dxg[(size_t)row * C + c] = KEYSIDE ? acc_a[u] : acc_a[u] * p.scale;
-        else if (c - C < R && dphig) dphig[(size_t)row * R + (c - C)] = acc_a[u];
-    }
-    if (KEYSIDE) {
-        float* dvg = (float*)p.dv + kbase;
+    for (int t = 0; t < NT; t++) {
+        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < CQ; u++) dvg[(size_t)row * C + t + 4 * u] = acc_e[u];
+        for (int g = 0; g < 4; g++) {
+            f32x4 w;
+#pragma unroll
+            for (int x = 0; x < 4; x++) w[x] = t < K::TE ? acce[t < K::TE ? t : 0][4 * g + x] : acca[t < K::TE ? 0 : t - K::TE][4 * g + x];
+            *(f32x4*)(&otile[wave][l32 * OPITCH + 8 * g + 4 * hf]) = w;
+        }
+        __syncthreads();
+        for (int e = part * 64 + lane; e < 32 * 8; e += KW * 64) {
+            const int rr = e >> 3, c4 = (e & 7) * 4;
+            if (row0 + rr >= NL) break;
+            f32x4 w = {0.f, 0.f, 0.f, 0.f};
+            for (int x = 0; x < KW; x++) w += *(const f32x4*)(&otile[wave - part + x][rr * OPITCH + c4]);
+            const int c = (t < K::TE ? t : t - K::TE) * 32 + c4;
+            const size_t orow = (size_t)(row0 + rr);
+            if (t < K::TE) {
+                if (c < C) *(f32x4*)(dvg + orow * C + c) = w;
+            } else if (c < C) {
+                w *= p.scale;
+                *(f32x4*)(dxg + orow * C + c) = w;
+            } else if (dphig) {
+#pragma unroll
+                for (int x = 0; x < 4; x++)
+                    if (c + x - C < R) dphig[orow * R + (c + x - C)] = w[x];
+            }
+        }
     }
 }
 
-template <int C, int RP>
-int launch(const BwdParams& pin, hipStream_t stream) {
+template <int C, int RP, bool KEYSIDE, bool DENSE>
+int launch_side(const BwdParams& pin, hipStream_t stream) {
     BwdParams p = pin;
-    float* Dws = (float*)p.workspace;
-    p.n_tiles = (p.N + kRows - 1) / kRows;         // query-side pass: tiles of query rows
+    const int rows = KEYSIDE ? p.M : p.N, other = KEYSIDE ? p.N : p.M;
+    const int tiles = (rows + 31) / 32;
+    const int kw = f32_split((long long)p.B * p.H * tiles, (other + BT - 1) / BT, 4);
+    int kw_log2 = 0;
+    while ((1 << kw_log2) < kw) kw_log2++;
+    const int qw = (kThreads / 64) / kw;
+    p.n_tiles = (tiles + qw - 1) / qw;
     p.total_tiles = p.B * p.H * p.n_tiles;
-    hipLaunchKernelGGL((bwd_f32_kernel<C, RP, false>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p, Dws);
-    if (hipGetLastError() != hipSuccess) return 1;
-    p.n_tiles = (p.M + kRows - 1) / kRows;         // key-side pass: tiles of key rows
-    p.total_tiles = p.B * p.H * p.n_tiles;
-    hipLaunchKernelGGL((bwd_f32_kernel<C, RP, true>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p, Dws);
+    p.tiles_per_xcd = (p.total_tiles + 7) / 8;
+    hipLaunchKernelGGL((bwd_f32_kernel<C, RP, KEYSIDE, DENSE>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
+                       (float*)p.workspace, kw_log2);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
-template <int C>
-int launch_dense(const BwdParams& pin, hipStream_t stream) {
-    BwdParams p = pin;
-    float* Dws = (float*)p.workspace;
-    p.n_tiles = (p.N + kRows - 1) / kRows;
-    p.total_tiles = p.B * p.H * p.n_tiles;
-    hipLaunchKernelGGL((bwd_f32_kernel<C, 0, false, true>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p, Dws);
-    if (hipGetLastError() != hipSuccess) return 1;
-    hipLaunchKernelGGL((bwd_f32_kernel<C, 0, true, true>), dim3(p.total_tiles), dim3(kThreads), 0, stream, p, Dws);
-    return hipGetLastError() == hipSuccess ? 0 : 1;
+template <int C, int RP, bool DENSE = false>
+int launch(const BwdParams& p, hipStream_t stream) {
+    const int rc = launch_side<C, RP, false, DENSE>(p, stream);      // also leaves D for the key side
+    return rc != 0 ? rc : launch_side<C, RP, true, DENSE>(p, stream);
 }
 
 template <int C>
 int dispatch_c(const BwdParams& p, hipStream_t stream) {
     if (p.R == 0) return launch<C, 0>(p, stream);
     if (p.R <= 8) return launch<C, 8>(p, stream);
+    if (p.R <= 16) return launch<C, 16>(p, stream);
     if (p.R <= 32) return launch<C, 32>(p, stream);
     return launch<C, 64>(p, stream);
 }
@@ -273,10 +376,10 @@ int fb_launch_bwd_f32(const BwdParams& p, int C, hipStream_t stream) {
 int fb_launch_bwd_dense_f32(const BwdParams& p, int C, hipStream_t stream) {
     if (p.N != p.M) return -1;
     switch (C) {
-        case 16: return launch_dense<16>(p, stream);
-        case 32: return launch_dense<32>(p, stream);
-        case 64: return launch_dense<64>(p, stream);
-        case 128: return launch_dense<128>(p, stream);
+        case 16: return launch<16, 0, true>(p, stream);
+        case 32: return launch<32, 0, true>(p, stream);
+        case 64: return launch<64, 0, true>(p, stream);
+        case 128: return launch<128, 0, true>(p, stream);
         default: return -1;
     }
 }

@@ -289,6 +289,15 @@ int fb_lowrank_xattn_bwd(const void* q, const void* k, const void* v,
                          fb_dtype dtype, fb_dtype phi_dtype, int phi_batch_broadcast,
                          float scale, void* workspace, size_t workspace_bytes, void* stream);
 
+/*
+ * Gradient of tensors that are shared over the batch (factors, a dense bias) from the per-batch-element
+ * gradients the backward entry points return: dst0[i] = sum_b src0[b * n0 + i] for i < n0, and the same for a
+ * second tensor of the same type (n1 = 0: none; src1, dst1 are then ignored).  fp32 sums in a fixed order,
+ * one rounding to `dtype` (FB_BF16 or FB_F32).  B >= 1; pointers aligned to the element size.
+ */
+int fb_fold_batch(const void* src0, void* dst0, long long n0, const void* src1, void* dst1, long long n1, int B,
+                  fb_dtype dtype, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

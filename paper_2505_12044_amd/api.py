@@ -27,6 +27,7 @@ EXPORTS = (
     "fb_lowrank_mulbias_attn_fwd_workspace_bytes", "fb_lowrank_mulbias_attn_fwd",
     "fb_lowrank_mulbias_attn_bwd_workspace_bytes", "fb_lowrank_mulbias_attn_bwd",
     "fb_alibi_attn_bwd_workspace_bytes", "fb_alibi_attn_bwd", "fb_lowrank_attn_bwd_noalloc",
+    "fb_fold_batch",
 )
 
 FB_STATIC_SCRATCH_BYTES = 64 << 20     # include/flashbias.h
@@ -88,6 +89,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.fb_alibi_attn_bwd_workspace_bytes.argtypes = [ci] * 4 + [ci]
     lib.fb_alibi_attn_bwd.restype = ci
     lib.fb_alibi_attn_bwd.argtypes = [vp] * 11 + [ci] * 5 + [ci, cf, vp, sz, vp]
+    lib.fb_fold_batch.restype = ci
+    lib.fb_fold_batch.argtypes = [vp, vp, ctypes.c_longlong, vp, vp, ctypes.c_longlong, ci, ci, vp]
     if path is None:
         _lib_handle = lib
     return lib
@@ -425,3 +428,21 @@ def fb_dense_bias_attn_bwd(q, k, v, bias, out, lse, dout, causal=False, scale: f
                                     workspace.numel() * workspace.element_size(), _stream(stream))
     _check(st, "fb_dense_bias_attn_bwd")
     return dq, dk, dv, dbias
+
+
+def fb_fold_batch(*grads, stream=None):
+    """Sums over the batch (dimension 0, kept) of one or two contiguous gradient tensors of one dtype and
+    batch size, in one launch: fp32 sums, one rounding to the tensors' dtype."""
+    lib = load_library()
+    if not 1 <= len(grads) <= 2:
+        raise FlashBiasError("one or two tensors")
+    B, dtype = grads[0].shape[0], _dtype_code(grads[0])
+    if any(g.shape[0] != B or _dtype_code(g) != dtype for g in grads):
+        raise FlashBiasError("the tensors must have one batch size and dtype")
+    outs = tuple(torch.empty((1,) + tuple(g.shape[1:]), dtype=g.dtype, device=g.device) for g in grads)
+    args = []
+    for i in range(2):
+        args += [_ptr(grads[i]), _ptr(outs[i]), outs[i].numel()] if i < len(grads) else [None, None, 0]
+    st = lib.fb_fold_batch(*args, B, dtype, _stream(stream))
+    _check(st, "fb_fold_batch")
+    return outs

@@ -7,11 +7,10 @@ the outputs of token-wise networks (neural type) without any other change to the
 
 Nothing is computed here except what autograd's own bookkeeping needs: tensors are made
 contiguous, the forward entry point is called, its inputs and (out, lse) are saved, and the
-backward entry point is called on the upstream gradient.  The only arithmetic outside the
-kernels is the chain rule of broadcasting: when factors (or a dense bias, or the ALiBi slopes)
-are shared over the batch, the per-batch-element gradients the kernels return are summed over
-the batch dimension with torch.sum.  There is no fallback path: without the shared library
-every call raises.
+backward entry point is called on the upstream gradient.  When factors (or a dense bias) are shared over
+the batch, the per-batch-element gradients the kernels return are summed over the batch dimension by
+fb_fold_batch; the only arithmetic outside the kernels is the same sum for the ALiBi slopes.
+There is no fallback path: without the shared library every call raises.
 """
 from __future__ import annotations
 
@@ -26,13 +25,20 @@ def _c(t: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
     return None if t is None else t.contiguous()
 
 
-def _fold_batch(g: Optional[torch.Tensor], like: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
-    """Gradient of a tensor that was broadcast over the batch: sum of the per-element gradients."""
-    if g is None or like is None:
-        return None
-    if like.shape[0] == 1 and g.shape[0] > 1:
-        return g.sum(dim=0, keepdim=True, dtype=torch.float32).to(like.dtype)
-    return g
+def _fold_batch(*pairs):
+    """Gradients of tensors that were broadcast over the batch: the sums of the per-element gradients, in one
+    launch for both tensors of a factor pair.  pairs: (gradient per batch element, tensor)."""
+    out = [g for g, _ in pairs]
+    todo = [i for i, (g, like) in enumerate(pairs)
+            if g is not None and like is not None and like.shape[0] == 1 and g.shape[0] > 1]
+    if len({(pairs[i][0].dtype, pairs[i][0].shape[0]) for i in todo}) > 1:
+        groups = [[i] for i in todo]
+    else:
+        groups = [todo] if todo else []
+    for idx in groups:
+        for i, f in zip(idx, api.fb_fold_batch(*(pairs[i][0] for i in idx))):
+            out[i] = f.to(pairs[i][1].dtype)
+    return out
 
 
 class _LowRank(torch.autograd.Function):
@@ -62,7 +68,7 @@ class _LowRank(torch.autograd.Function):
         else:
             dq, dk, dv, dpq, dpk = api.fb_lowrank_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout,
                                                            causal=causal, scale=scale)
-        return dq, dk, dv, _fold_batch(dpq, phi_q), _fold_batch(dpk, phi_k), None, None
+        return (dq, dk, dv, *_fold_batch((dpq, phi_q), (dpk, phi_k)), None, None)
 
 
 class _MulBias(torch.autograd.Function):
@@ -82,7 +88,7 @@ class _MulBias(torch.autograd.Function):
         causal, scale = ctx.cfg
         dq, dk, dv, dpq, dpk = api.fb_lowrank_mulbias_attn_bwd(q, k, v, phi_q, phi_k, out, lse, _c(dout),
                                                                causal=causal, scale=scale)
-        return dq, dk, dv, _fold_batch(dpq, phi_q), _fold_batch(dpk, phi_k), None, None
+        return (dq, dk, dv, *_fold_batch((dpq, phi_q), (dpk, phi_k)), None, None)
 
 
 class _Alibi(torch.autograd.Function):
@@ -126,7 +132,7 @@ class _DenseBias(torch.autograd.Function):
         causal, scale = ctx.cfg
         dq, dk, dv, dbias = api.fb_dense_bias_attn_bwd(q, k, v, bias, out, lse, _c(dout), causal=causal,
                                                        scale=scale)
-        return dq, dk, dv, _fold_batch(dbias, bias), None, None
+        return (dq, dk, dv, *_fold_batch((dbias, bias)), None, None)
 
 
 def lowrank_bias_attention(q, k, v, phi_q=None, phi_k=None, causal: bool = False, scale: float = 0.0):

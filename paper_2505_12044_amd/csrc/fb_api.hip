@@ -535,5 +535,19 @@ int fb_lowrank_xattn_bwd(const void* q, const void* k, const void* v,
                             stream);
 }
 
+int fb_fold_batch(const void* src0, void* dst0, long long n0, const void* src1, void* dst1, long long n1, int B,
+                  fb_dtype dtype, void* stream) {
+    if (B <= 0 || n0 <= 0 || n1 < 0) return FB_ERR_SHAPE;
+    if (n0 >= (1LL << 40) || n1 >= (1LL << 40)) return FB_ERR_SHAPE;
+    if (!src0 || !dst0 || (n1 > 0 && (!src1 || !dst1))) return FB_ERR_NULL;
+    if (dtype != FB_BF16 && dtype != FB_F32) return FB_ERR_UNSUPPORTED;
+    if (n1 == 0) { src1 = src0; dst1 = dst0; }
+    const uintptr_t mask = dtype == FB_F32 ? 3u : 1u;
+    const void* ptrs[] = {src0, dst0, src1, dst1};
+    for (const void* ptr : ptrs) if ((reinterpret_cast<uintptr_t>(ptr) & mask) != 0) return FB_ERR_ALIGN;
+    const int rc = fb_launch_fold_batch(src0, dst0, n0, src1, dst1, n1, B, dtype == FB_F32, (hipStream_t)stream);
+    return rc == 0 ? FB_OK : (rc < 0 ? FB_ERR_SHAPE : FB_ERR_LAUNCH);
+}
+
 }  // extern "C"
 #pragma GCC visibility pop

@@ -36,6 +36,10 @@ int fb_launch_mulbias_fold(const void* x, const void* phi, const void* g_head, c
                            void* dphi, int B, long long rows_per_batch, int C, int R, int phi_f32,
                            long long phi_bstride, float mul, hipStream_t stream);
 
+// d0[i] = sum_b s0[b * n0 + i] for i < n0, and the same for (s1, d1, n1); n1 = 0: one tensor only.
+int fb_launch_fold_batch(const void* s0, void* d0, long long n0, const void* s1, void* d1, long long n1, int B, bool f32,
+                         hipStream_t stream);
+
 // A kernel's dynamic-LDS limit is an attribute of the (kernel, device) pair: raise it on the
 // first launch on each device.  Racing first launches all set the same value; the flag is
 // published only after the attribute call has returned.

@@ -115,6 +115,20 @@ int fb_lowrank_xattn_fwd(const void* q, const void* k, const void* v,
                          float scale, void* stream);
 
 /*
+ * fb_lowrank_xattn_fwd with device scratch: where a few queries meet many keys (decode), the keys of a head are
+ * split over the GPU and the partial results pass through `workspace` (16-byte aligned, at least as large as the
+ * query below says; 0 where nothing is needed).  Without one (NULL, or too small), as in fb_lowrank_xattn_fwd, a
+ * head stays in one workgroup.
+ */
+size_t fb_lowrank_xattn_fwd_workspace_bytes(int B, int H, int N, int M, int C, int R, fb_dtype dtype);
+
+int fb_lowrank_xattn_fwd_ws(const void* q, const void* k, const void* v,
+                            const void* phi_q, const void* phi_k, void* out, float* lse,
+                            int B, int H, int N, int M, int C, int R,
+                            fb_dtype dtype, fb_dtype phi_dtype, int phi_batch_broadcast,
+                            float scale, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Forward with the ALiBi bias b_ij = -m_h (i - j) (0-based positions, every (i, j); the
  * causal mask is separate) generated inside the kernel from the per-head slopes: the rank-2
  * factors of Example 3.4 are computed from tile indices, so no factor tensor is read

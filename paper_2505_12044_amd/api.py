@@ -27,7 +27,7 @@ EXPORTS = (
     "fb_lowrank_mulbias_attn_fwd_workspace_bytes", "fb_lowrank_mulbias_attn_fwd",
     "fb_lowrank_mulbias_attn_bwd_workspace_bytes", "fb_lowrank_mulbias_attn_bwd",
     "fb_alibi_attn_bwd_workspace_bytes", "fb_alibi_attn_bwd", "fb_lowrank_attn_bwd_noalloc",
-    "fb_fold_batch",
+    "fb_fold_batch", "fb_lowrank_xattn_fwd_workspace_bytes", "fb_lowrank_xattn_fwd_ws",
 )
 
 FB_STATIC_SCRATCH_BYTES = 64 << 20     # include/flashbias.h
@@ -89,6 +89,10 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.fb_alibi_attn_bwd_workspace_bytes.argtypes = [ci] * 4 + [ci]
     lib.fb_alibi_attn_bwd.restype = ci
     lib.fb_alibi_attn_bwd.argtypes = [vp] * 11 + [ci] * 5 + [ci, cf, vp, sz, vp]
+    lib.fb_lowrank_xattn_fwd_workspace_bytes.restype = sz
+    lib.fb_lowrank_xattn_fwd_workspace_bytes.argtypes = [ci] * 7
+    lib.fb_lowrank_xattn_fwd_ws.restype = ci
+    lib.fb_lowrank_xattn_fwd_ws.argtypes = [vp] * 7 + [ci] * 6 + [ci, ci, ci, cf, vp, sz, vp]
     lib.fb_fold_batch.restype = ci
     lib.fb_fold_batch.argtypes = [vp, vp, ctypes.c_longlong, vp, vp, ctypes.c_longlong, ci, ci, vp]
     if path is None:
@@ -180,9 +184,13 @@ def fb_lowrank_xattn_fwd(q, k, v, phi_q, phi_k, out=None, lse=None, scale: float
     if lse is None:
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     phi_code = _dtype_code(phi_q) if phi_q is not None else _dtype_code(q)
-    st = lib.fb_lowrank_xattn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(phi_q), _ptr(phi_k), _ptr(out),
-                                  _ptr(lse), B, H, N, M, C, R, _dtype_code(q), phi_code,
-                                  int(bool(phi_batch_broadcast)), float(scale), _stream(stream))
+    # only a few queries against many keys ever need scratch
+    need = int(lib.fb_lowrank_xattn_fwd_workspace_bytes(B, H, N, M, C, R, _dtype_code(q))) if N <= 8 else 0
+    workspace = _scratch(need, q.device, stream) if need else None
+    st = lib.fb_lowrank_xattn_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(phi_q), _ptr(phi_k), _ptr(out),
+                                     _ptr(lse), B, H, N, M, C, R, _dtype_code(q), phi_code,
+                                     int(bool(phi_batch_broadcast)), float(scale), _ptr(workspace), need,
+                                     _stream(stream))
     _check(st, "fb_lowrank_xattn_fwd")
     return out, lse
 

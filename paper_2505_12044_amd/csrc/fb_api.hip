@@ -126,7 +126,7 @@ static int lowrank_fwd_impl(const void* q, const void* k, const void* v,
                             const void* phi_q, const void* phi_k, void* out, float* lse,
                             int B, int H, int N, int M, int C, int R, int causal,
                             fb_dtype dtype, fb_dtype phi_dtype, int phi_batch_broadcast,
-                            float scale, void* stream) {
+                            float scale, void* workspace, size_t workspace_bytes, void* stream) {
     if (!q || !k || !v || !out || !lse) return FB_ERR_NULL;
     if (int st = check_common(B, H, N > M ? N : M, C, R)) return st;
     if (N <= 0 || M <= 0) return FB_ERR_SHAPE;
@@ -155,6 +155,11 @@ static int lowrank_fwd_impl(const void* q, const void* k, const void* v,
     int rc;
     if (dtype == FB_F32) {
         rc = fb_launch_fwd_f32(p, C, false, (hipStream_t)stream);
+    } else if (g_fwd_qb.load(std::memory_order_relaxed) == 0 && fb_few_queries((long long)B * H, N, M, R)) {
+        // a workspace too small for the splits is left alone
+        const bool split = workspace != nullptr && aligned16(workspace) &&
+                           workspace_bytes >= fb_few_workspace_bytes((long long)B * H, N, M, C);
+        rc = fb_launch_fwd_bf16_few(p, C, split ? workspace : nullptr, (hipStream_t)stream);
     } else {
         int qb = pick_qb(B, H, N, C, rp, false, causal != 0);
         if (N != M && qb != 2) qb = 1;     // only the four-wave kernel takes N != M
@@ -169,7 +174,7 @@ int fb_lowrank_attn_fwd(const void* q, const void* k, const void* v,
                         fb_dtype dtype, fb_dtype phi_dtype, int phi_batch_broadcast,
                         float scale, void* stream) {
     return lowrank_fwd_impl(q, k, v, phi_q, phi_k, out, lse, B, H, N, N, C, R, causal, dtype, phi_dtype,
-                            phi_batch_broadcast, scale, stream);
+                            phi_batch_broadcast, scale, nullptr, 0, stream);
 }
 
 int fb_lowrank_xattn_fwd(const void* q, const void* k, const void* v,
@@ -178,7 +183,22 @@ int fb_lowrank_xattn_fwd(const void* q, const void* k, const void* v,
                          fb_dtype dtype, fb_dtype phi_dtype, int phi_batch_broadcast,
                          float scale, void* stream) {
     return lowrank_fwd_impl(q, k, v, phi_q, phi_k, out, lse, B, H, N, M, C, R, 0, dtype, phi_dtype,
-                            phi_batch_broadcast, scale, stream);
+                            phi_batch_broadcast, scale, nullptr, 0, stream);
+}
+
+size_t fb_lowrank_xattn_fwd_workspace_bytes(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
+    if (B <= 0 || H <= 0 || N <= 0 || M <= 0 || R < 0 || (C != 16 && C != 32 && C != 64 && C != 128)) return 0;
+    if (dtype != FB_BF16 || !fb_few_queries((long long)B * H, N, M, R)) return 0;
+    return fb_few_workspace_bytes((long long)B * H, N, M, C);
+}
+
+int fb_lowrank_xattn_fwd_ws(const void* q, const void* k, const void* v,
+                            const void* phi_q, const void* phi_k, void* out, float* lse,
+                            int B, int H, int N, int M, int C, int R,
+                            fb_dtype dtype, fb_dtype phi_dtype, int phi_batch_broadcast,
+                            float scale, void* workspace, size_t workspace_bytes, void* stream) {
+    return lowrank_fwd_impl(q, k, v, phi_q, phi_k, out, lse, B, H, N, M, C, R, 0, dtype, phi_dtype,
+                            phi_batch_broadcast, scale, workspace, workspace_bytes, stream);
 }
 
 int fb_dense_bias_attn_fwd(const void* q, const void* k, const void* v, const void* bias,

@@ -14,6 +14,11 @@ int fb_launch_fwd_f32(const FwdParams& p, int C, bool dense, hipStream_t stream)
 int fb_launch_fwd_bf16(const FwdParams& p, int C, int rp, bool dense, int qb, hipStream_t stream);
 // ALiBi factors generated in the kernel from p.slopes (p.phi_q / p.phi_k unused); qb = 1 or 2.
 int fb_launch_fwd_bf16_alibi(const FwdParams& p, int C, int qb, hipStream_t stream);
+// Few queries against many keys (no mask).  fb_few_queries: whether that kernel takes the call; ws: device scratch of
+// fb_few_workspace_bytes(B*H, N, M, C) bytes for the partial results of a head's splits, or NULL (no splits).
+bool fb_few_queries(long long BH, int N, int M, int R);
+size_t fb_few_workspace_bytes(long long BH, int N, int M, int C);
+int fb_launch_fwd_bf16_few(const FwdParams& p, int C, void* ws, hipStream_t stream);
 // p.workspace points at fb_bwd_workspace_bytes(B*H*N, B*H*M, C, R) bytes of device scratch.
 int fb_launch_bwd_bf16(const BwdParams& p, int C, int rp, hipStream_t stream);
 size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R);

@@ -1,0 +1,90 @@
+"""The few-query forward (decode) at its edges: query counts of and between its instantiations, key counts around one
+step of a wave and of a workgroup, with and without the split over the grid, each factor form, against the float64
+oracle at the forward's bounds, and against the tile kernel it stands beside."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fb_oracle as O
+from paper_2505_12044_amd import api, workloads as W
+from tests._gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(B, H, N, M, C, R, phi, shared, seed):
+    rng = np.random.default_rng(seed)
+    mk = lambda *s: W.round_bf16(rng.standard_normal(s).astype(np.float32))
+    q, k, v = mk(B, H, N, C), mk(B, H, M, C), mk(B, H, M, C)
+    pq = pk = None
+    if R:
+        Bp = 1 if shared else B
+        pq, pk = mk(Bp, H, N, R), mk(Bp, H, M, R)
+        if phi == "f32":
+            pq, pk = (x + 1e-3 * rng.standard_normal(x.shape).astype(np.float32) for x in (pq, pk))
+    return q, k, v, pq, pk
+
+
+def _check(B, H, N, M, C, R, phi, shared=True):
+    q, k, v, pq, pk = _case(B, H, N, M, C, R, phi, shared, seed=N * 1000 + M + C + R)
+    d = [dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16")] + [None if x is None else dev(x, phi) for x in (pq, pk)]
+    out, lse = api.fb_lowrank_xattn_fwd(*d)
+    try:
+        api.fb_tune_set("fwd_qb", 1)
+        out_t, lse_t = api.fb_lowrank_xattn_fwd(*d)
+    finally:
+        api.fb_tune_set("fwd_qb", 0)
+    torch.cuda.synchronize()
+    for b in range(B):
+        for h in range(H):
+            fq = pq[min(b, pq.shape[0] - 1), h] if R else np.zeros((N, 0))
+            fk = pk[min(b, pk.shape[0] - 1), h] if R else np.zeros((M, 0))
+            ro, rl = O.attention_lowrank(q[b, h], k[b, h], v[b, h], fq, fk)
+            for o, l in ((out, lse), (out_t, lse_t)):
+                assert np.abs(host(o[b, h]) - ro).max() <= 2e-2 and np.abs(host(l[b, h]) - rl).max() <= 2e-2
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("C,R,phi", [(128, 2, "f32"), (64, 0, "f32"), (32, 9, "f32"), (16, 5, "bf16"), (128, 16, "bf16"), (64, 8, "bf16")])
+def test_few_queries(N, C, R, phi):
+    for M in (N + 1, 129, 1111):
+        _check(2, 2, N, M, C, R, phi, shared=N % 2 == 0)
+
+
+@pytest.mark.parametrize("N,M", [(1, 31), (1, 32), (1, 33), (1, 127), (1, 128), (1, 129), (2, 257), (4, 63), (4, 65), (8, 16), (8, 17)])
+def test_few_queries_key_edges(N, M):
+    _check(1, 2, N, M, 128, 2, "f32")
+
+
+def test_few_queries_one_workgroup_per_head():
+    # 600 heads: no split; without a workspace: no split either
+    _check(75, 8, 1, 300, 16, 2, "f32")
+    q, k, v, pq, pk = _case(2, 3, 1, 5000, 64, 2, "f32", True, seed=5)
+    d = [dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), dev(pq, "f32"), dev(pk, "f32")]
+    a, la = api.fb_lowrank_xattn_fwd(*d)
+    b, lb = torch.empty_like(a), torch.empty_like(la)
+    st = api.load_library().fb_lowrank_xattn_fwd(*(t.data_ptr() for t in d), b.data_ptr(), lb.data_ptr(), 2, 3, 1, 5000, 64, 2,
+                                                 api.FB_BF16, api.FB_F32, 1, 0.0, torch.cuda.current_stream().cuda_stream or None)
+    assert st == 0
+    torch.cuda.synchronize()
+    # the same fp32 sums in another grouping, rounded to bf16
+    assert float((a.float() - b.float()).abs().max()) <= 2.0 ** -7 * float(a.float().abs().max())
+    assert float((la - lb).abs().max()) <= 1e-5
+
+
+def test_few_queries_decoder_positions():
+    # ALiBi at the end of a long cache: the factors are absolute positions, the bias near the diagonal is small
+    B, H, M, C = 1, 4, 16384, 64
+    rng = np.random.default_rng(3)
+    mk = lambda *s: W.round_bf16(rng.standard_normal(s).astype(np.float32))
+    q, k, v = mk(B, H, 1, C), mk(B, H, M, C), mk(B, H, M, C)
+    m = W.alibi_slopes_f32(H)
+    pq = np.zeros((1, H, 1, 2), np.float32); pk = np.zeros((1, H, M, 2), np.float32)
+    for h in range(H):
+        pq[0, h, 0] = (-m[h] * np.float32(M - 1), m[h])
+        pk[0, h, :, 0] = 1.0
+        pk[0, h, :, 1] = np.arange(M, dtype=np.float32)
+    out, lse = api.fb_lowrank_xattn_fwd(dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), dev(pq, "f32"), dev(pk, "f32"))
+    torch.cuda.synchronize()
+    ro, rl = O.batched_attention_lowrank(q, k, v, pq, pk)
+    assert np.abs(host(out) - ro).max() <= 2e-2 and np.abs(host(lse) - rl).max() <= 2e-3

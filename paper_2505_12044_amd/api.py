@@ -117,8 +117,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:      # the raw handle of the current device's current stream, without a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) or None
     h = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     return h or None
 
@@ -444,13 +444,20 @@ def fb_fold_batch(*grads, stream=None):
     lib = load_library()
     if not 1 <= len(grads) <= 2:
         raise FlashBiasError("one or two tensors")
-    B, dtype = grads[0].shape[0], _dtype_code(grads[0])
-    if any(g.shape[0] != B or _dtype_code(g) != dtype for g in grads):
+    g0 = grads[0]
+    g1 = grads[1] if len(grads) == 2 else None
+    shape0 = g0.shape
+    B, dtype = shape0[0], _dtype_code(g0)
+    o0 = g0.new_empty((1, *shape0[1:]))
+    n0 = o0.numel()
+    if g1 is None:
+        st = lib.fb_fold_batch(_ptr(g0), o0.data_ptr(), n0, None, None, 0, B, dtype, _stream(stream))
+        _check(st, "fb_fold_batch")
+        return (o0,)
+    shape1 = g1.shape
+    if shape1[0] != B or g1.dtype != g0.dtype:
         raise FlashBiasError("the tensors must have one batch size and dtype")
-    outs = tuple(torch.empty((1,) + tuple(g.shape[1:]), dtype=g.dtype, device=g.device) for g in grads)
-    args = []
-    for i in range(2):
-        args += [_ptr(grads[i]), _ptr(outs[i]), outs[i].numel()] if i < len(grads) else [None, None, 0]
-    st = lib.fb_fold_batch(*args, B, dtype, _stream(stream))
+    o1 = g1.new_empty((1, *shape1[1:]))
+    st = lib.fb_fold_batch(_ptr(g0), o0.data_ptr(), n0, _ptr(g1), o1.data_ptr(), o1.numel(), B, dtype, _stream(stream))
     _check(st, "fb_fold_batch")
-    return outs
+    return o0, o1

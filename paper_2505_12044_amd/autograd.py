@@ -25,20 +25,23 @@ def _c(t: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
     return None if t is None else t.contiguous()
 
 
-def _fold_batch(*pairs):
-    """Gradients of tensors that were broadcast over the batch: the sums of the per-element gradients, in one
-    launch for both tensors of a factor pair.  pairs: (gradient per batch element, tensor)."""
-    out = [g for g, _ in pairs]
-    todo = [i for i, (g, like) in enumerate(pairs)
-            if g is not None and like is not None and like.shape[0] == 1 and g.shape[0] > 1]
-    if len({(pairs[i][0].dtype, pairs[i][0].shape[0]) for i in todo}) > 1:
-        groups = [[i] for i in todo]
-    else:
-        groups = [todo] if todo else []
-    for idx in groups:
-        for i, f in zip(idx, api.fb_fold_batch(*(pairs[i][0] for i in idx))):
-            out[i] = f.to(pairs[i][1].dtype)
-    return out
+def _is_shared(g: Optional[torch.Tensor], like: Optional[torch.Tensor]) -> bool:
+    return g is not None and like is not None and like.shape[0] == 1 and g.shape[0] > 1
+
+
+def _fold_batch(g: Optional[torch.Tensor], like: Optional[torch.Tensor]) -> Optional[torch.Tensor]:
+    """Gradient of a tensor that was broadcast over the batch: sum of the per-element gradients."""
+    if not _is_shared(g, like):
+        return g
+    f, = api.fb_fold_batch(g)
+    return f if f.dtype == like.dtype else f.to(like.dtype)
+
+
+def _fold_pair(gq, like_q, gk, like_k):
+    """_fold_batch of both tensors of a factor pair, in one launch where both are shared."""
+    if _is_shared(gq, like_q) and _is_shared(gk, like_k) and gq.dtype == like_q.dtype == gk.dtype == like_k.dtype:
+        return api.fb_fold_batch(gq, gk)
+    return _fold_batch(gq, like_q), _fold_batch(gk, like_k)
 
 
 class _LowRank(torch.autograd.Function):
@@ -68,7 +71,7 @@ class _LowRank(torch.autograd.Function):
         else:
             dq, dk, dv, dpq, dpk = api.fb_lowrank_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout,
                                                            causal=causal, scale=scale)
-        return (dq, dk, dv, *_fold_batch((dpq, phi_q), (dpk, phi_k)), None, None)
+        return (dq, dk, dv, *_fold_pair(dpq, phi_q, dpk, phi_k), None, None)
 
 
 class _MulBias(torch.autograd.Function):
@@ -88,7 +91,7 @@ class _MulBias(torch.autograd.Function):
         causal, scale = ctx.cfg
         dq, dk, dv, dpq, dpk = api.fb_lowrank_mulbias_attn_bwd(q, k, v, phi_q, phi_k, out, lse, _c(dout),
                                                                causal=causal, scale=scale)
-        return (dq, dk, dv, *_fold_batch((dpq, phi_q), (dpk, phi_k)), None, None)
+        return (dq, dk, dv, *_fold_pair(dpq, phi_q, dpk, phi_k), None, None)
 
 
 class _Alibi(torch.autograd.Function):
@@ -132,7 +135,7 @@ class _DenseBias(torch.autograd.Function):
         causal, scale = ctx.cfg
         dq, dk, dv, dbias = api.fb_dense_bias_attn_bwd(q, k, v, bias, out, lse, _c(dout), causal=causal,
                                                        scale=scale)
-        return (dq, dk, dv, *_fold_batch((dbias, bias)), None, None)
+        return dq, dk, dv, _fold_batch(dbias, bias), None, None
 
 
 def lowrank_bias_attention(q, k, v, phi_q=None, phi_k=None, causal: bool = False, scale: float = 0.0):

@@ -45,8 +45,7 @@ namespace {
 constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
 constexpr int BT = 32;       // streamed rows per block
-constexpr int NSLOT = 4;       // ring slots of the dq kernel
-constexpr int NSLOT_DKV = 5;   // ring slots of the dkv kernel (a block is used in two iterations)
+constexpr int NSLOT = 4;       // ring slots of the kernels that use a block in one iteration
 
 FB_DEV int swz64(int r) { return (((r >> 1) & 1) << 2) | ((r >> 2) & 3); }
 FB_DEV int swz32(int r) { return (r >> 2) & 3; }
@@ -113,6 +112,14 @@ struct Cfg {
     using T1 = Tile<W>;
     using T2 = Tile<C>;
     static constexpr int kVecBytes = 1024;             // (lse2, D) of 32 rows in the first 256 bytes
+    // Form of the dkv kernel.  Up to 128 operand columns its accumulators leave room for two waves per SIMD (three
+    // at C = 32), which fill each other's gaps as they do in the dq kernel; above, one wave per SIMD overlaps
+    // matrix and vector work of two blocks in its own instruction stream (PIPE).  PIPE against plain, one launch:
+    // B 4, H 16, N 4096, C 64, 64 extra columns 1079 -> 867 us; B 8, H 12, N 1024, C 64, R 32 105 -> 87 us and
+    // with a dense bias 109 -> 82 us; B 384, H 4, N 384, C 32, R 16 140 -> 116 us; B 1, H 8, N 32186, C 16, R 9
+    // fp32 equal (its vector work, not the overlap, bounds it).
+    static constexpr bool PIPE = C >= 128 || C + RP > 128;
+    static constexpr int NSLOT_DKV = PIPE ? 5 : NSLOT;         // ring slots (PIPE: a block is used in two iterations)
     static constexpr size_t kEpiLds = (size_t)kWaves * 32 * (RP2 + 1) * sizeof(float);
 };
 
@@ -553,11 +560,13 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     // With eight or more dV MFMAs (C = 128) the dS arithmetic of a block (sub, mul, convert: 40
     // instructions) fits under them, which leaves only the exponentials under the S / dP chains;
     // smaller head dimensions have too few dV MFMAs and keep everything under the first half.
-    constexpr bool LAZY_DS = DKV && NO2 >= 8;
+    constexpr bool PIPE = DKV && K::PIPE;
+    constexpr int NSLOT_DKV = K::NSLOT_DKV;
+    constexpr bool LAZY_DS = PIPE && NO2 >= 8;
     constexpr int NOPS = NA + NO1 + NO2;
     // LDS operand reads run LA MFMAs ahead of their use; the first half never reads past its own block
     // (measured: look-ahead 2..4 for dq and 5..12 for dkv all run within 1 %)
-    constexpr int LA_WANT = DKV ? 6 : 3;
+    constexpr int LA_WANT = PIPE ? 6 : 3;
     constexpr int LA_CAP = (NO1 + NO2) < NA ? (NO1 + NO2) : NA;
     constexpr int LA = LA_CAP < LA_WANT ? LA_CAP : LA_WANT;
     bf16x8 opr[LA + 1];
@@ -612,8 +621,8 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         dsb[r / 8][r % 8] = (bf16_t)ds;
     };
 
-    if constexpr (DKV) {
-        // One wave per SIMD (the accumulators alone take 144 registers), so the overlap of
+    if constexpr (PIPE) {
+        // One wave per SIMD (at C = 128 the accumulators alone take 144 registers), so the overlap of
         // matrix and vector work is written into the instruction stream: while the S and dP
         // chains of block i+1 run, the exponentials and dS of block i are computed, one
         // accumulator element per MFMA.  Iteration i:
@@ -635,10 +644,10 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         // behind an inner link of a chain would read it too early (seen as a wrong dK at C = 128,
         // R = 9 fp32 factors; those instantiations keep the compiler's forms).
         constexpr bool SV = !DENSE && C + RP <= 144;
+        static_assert(!SV || C != 32, "a chain's last link carries its wait states: it must not be a dead step");
         // one link of the S (n < KS) or dP chain of a block into the VGPR tiles st / dt
         auto chain_link = [&](int n, f32x16& st, f32x16& dt, bf16x8 o) __attribute__((always_inline)) {
-            constexpr int CS = NA - K::KS;
-            // the last live link of each chain (head dimension 16: the second link of each chain is dead)
+            // the last link of each chain
             const bool last_s = n == K::KS - 1, last_d = n == NA - 1;
             if (n < K::KS) {
                 if (n == 0) mfma32_vdst_first(st, o, l1reg[n]);
@@ -649,7 +658,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                 else if (last_d) mfma32_vdst_last(dt, o, l2reg[n - K::KS]);
                 else mfma32_vdst(dt, o, l2reg[n - K::KS]);
             }
-            (void)CS;
         };
         static_assert(K::KS >= 2 && NA - K::KS >= 2, "a first and a last link per chain");
         issue_block(0, 0); issue_bias(0, 0);
@@ -668,8 +676,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
             for (int n = 0; n < NA; n++) {
                 const bf16x8 o = read_op(r0, t0, n);
-                // (SV: a chain's last link carries its wait states, so it is issued even when it adds zeros)
-                if (dead_step(n) && !(SV && (n == NA - 1 || n == K::KS - 1))) continue;
+                if (dead_step(n)) continue;
                 if (SV) {
                     chain_link(n, sA, dA, o);
                 } else {
@@ -714,7 +721,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
             for (int n = 0; n < NA; n++) {
                 opr[(n + LA) % (LA + 1)] = read_op(rb1, tb0, n + LA);   // past NA: output operands of block i
-                if (!dead_step(n) || (SV && (n == NA - 1 || n == K::KS - 1))) {
+                if (!dead_step(n)) {
                     if (SV) {
                         chain_link(n, sn, dn, opr[n % (LA + 1)]);
                     } else {
@@ -797,7 +804,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             dA = dB;
         }
     } else {
-        // Two waves per SIMD: the other workgroup's wave fills the gaps.  Iteration i:
+        // Two or three waves per SIMD: another workgroup's wave fills the gaps.  Iteration i:
         //     S, dP chains of block i | P, dS | wait, barrier | issue block i+3 |
         //     output chains of block i, first operand reads of block i+1
         issue_block(0, 0); issue_bias(0, 0);
@@ -807,7 +814,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         // D = rowsum(dO o O) and lse log2 e itself and leaves the pair for the dkv kernel, which is
         // launched behind it (no separate pass over out and dO).  Placed here so that the row loads
         // are in flight together with the first blocks.
-        {
+        if (!DKV) {
             const bf16_t* og = (const bf16_t*)p.out + (lbase + rc) * p.Cg;
             float dsum = 0.f;
 #pragma unroll
@@ -827,7 +834,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         __syncthreads();
         RowBase rb0 = mk_row(0);
         bf16_t* dbg = nullptr;      // dBias rows of this (b, h)
-        if (DENSE) dbg = (bf16_t*)p.dbias + (size_t)bh * p.N * p.M;
+        if (DENSE && !DKV) dbg = (bf16_t*)p.dbias + (size_t)bh * p.N * p.M;
 #pragma unroll
         for (int n = 0; n < LA; n++) opr[n] = read_op(rb0, TrBase{}, n);
 
@@ -851,20 +858,36 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             }
             // ---------------- P and dS in accumulator layout ----------------
             bf16x8 pb[2], dsb[2];
+            if (DKV) {
+                const unsigned char* vp = smem + (slot * kSlotBytes + kOffVec + 32 * hf);
 #pragma unroll
-            for (int r = 0; r < 16; r++) elem(r, s, dp, my_lse2, my_d, false, sb0, pb, dsb);
-            if ((sb0 + BT > NS) || (CAUSAL && sb0 + BT - 1 > rw0)) {
+                for (int g = 0; g < 4; g++) {
+                    const float4 x0 = *(const float4*)(vp + 64 * g);
+                    const float4 x1 = *(const float4*)(vp + 64 * g + 16);
+                    elem(4 * g + 0, s, dp, x0.x, x0.y, false, sb0, pb, dsb);
+                    elem(4 * g + 1, s, dp, x0.z, x0.w, false, sb0, pb, dsb);
+                    elem(4 * g + 2, s, dp, x1.x, x1.y, false, sb0, pb, dsb);
+                    elem(4 * g + 3, s, dp, x1.z, x1.w, false, sb0, pb, dsb);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; r++) elem(r, s, dp, my_lse2, my_d, false, sb0, pb, dsb);
+            }
+            if ((sb0 + BT > NS) || (CAUSAL && (DKV ? sb0 < rw0 + 31 : sb0 + BT - 1 > rw0))) {
                 // rare (diagonal blocks, sequence end): zero the dead elements behind a real branch
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
                     const int srow = sb0 + 8 * (r / 4) + 4 * hf + (r % 4);
-                    if (srow >= NS || (CAUSAL && srow > ri)) dsb[r / 8][r % 8] = (bf16_t)0.f;
+                    if (srow >= NS || (CAUSAL && (DKV ? srow < ri : srow > ri))) {
+                        dsb[r / 8][r % 8] = (bf16_t)0.f;
+                        if (DKV) pb[r / 8][r % 8] = (bf16_t)0.f;
+                    }
                 }
             }
             // ---------------- dBias = dS, straight from the packed operand registers ----------------
             int nstores = 0;
-            if (DENSE) {
+            if (DENSE && !DKV) {
                 const int Mk = p.M;
                 if (ri < NL) {
                     bf16_t* drow = dbg + (size_t)ri * Mk + sb0 + 4 * hf;
@@ -892,13 +915,14 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                 if (n + LA < NOPS) opr[(n + LA) % (LA + 1)] = read_op(rb0, tb0, n + LA);
                 else nxt[n + LA - NOPS] = read_op(rbn, tb0, n + LA - NOPS);
                 const int m = n - NA;
-                acc1[m >> 1] = mfma32(opr[n % (LA + 1)], dsb[m & 1], acc1[m >> 1]);
+                if (m < NO1) acc1[m >> 1] = mfma32(opr[n % (LA + 1)], dsb[m & 1], acc1[m >> 1]);
+                else acc2[(m - NO1) >> 1] = mfma32(opr[n % (LA + 1)], pb[(m - NO1) & 1], acc2[(m - NO1) >> 1]);
             }
 #pragma unroll
             for (int n = 0; n < LA; n++) opr[n] = nxt[n];
             rb0 = rbn;
         }
-        if (DENSE && CAUSAL && ri < NL) {
+        if (DENSE && !DKV && CAUSAL && ri < NL) {
             // key blocks above the diagonal are never visited: their dBias is zero
             for (int blk = b_end; blk < nblk_all; blk++) {
                 bf16_t* drow = dbg + (size_t)ri * p.M + blk * BT + 4 * hf;
@@ -981,7 +1005,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 // Work units: one 128-row tile per workgroup, or when causal the tile pair (n-1-u, u), whose
 // streamed ranges add up to the same length for every u (no tail of heavy tiles).
 template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE = false>
-__global__ __launch_bounds__(kThreads, (DKV || DENSE || C + RP > 160) ? 1 : 2) void bwd_main_kernel(BwdParams p, MainArgs a) {
+__global__ __launch_bounds__(kThreads, (DKV ? Cfg<C, RP>::PIPE : (DENSE || C + RP > 160)) ? 1 : 2) void bwd_main_kernel(BwdParams p, MainArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);
     if (L >= p.total_tiles) return;
@@ -1008,7 +1032,7 @@ int launch(const BwdParams& pin, hipStream_t stream) {
     using K = Cfg<C, RP>;
     constexpr size_t slot = K::T1::BYTES + K::T2::BYTES + (DENSE ? (size_t)kWaves * 32 * 32 * 2 : 0);
     constexpr size_t ring_dq = (size_t)NSLOT * slot;
-    constexpr size_t ring_dkv = (size_t)NSLOT_DKV * (slot + K::kVecBytes);
+    constexpr size_t ring_dkv = (size_t)K::NSLOT_DKV * (slot + K::kVecBytes);
     constexpr size_t lds_dq = ring_dq > K::kEpiLds ? ring_dq : K::kEpiLds;
     constexpr size_t lds_dkv = ring_dkv > K::kEpiLds ? ring_dkv : K::kEpiLds;
     auto kdq = bwd_main_kernel<C, RP, CAUSAL, false, DENSE>;

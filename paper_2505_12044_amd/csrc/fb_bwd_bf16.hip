@@ -101,17 +101,30 @@ struct Tile {
     }
 };
 
-template <int C, int RP>
+// LIMB: the factors are fp32 (or generated), i.e. bf16 limb columns.  Set only where it changes something, see
+// FOLD and DL.  CG: channels of the caller's rows, 16 on the 32-channel tiles of head dimension 16, else C.
+template <int C, int RP, bool LIMB = false, int CG = C>
 struct Cfg {
     static constexpr int RP2 = (RP + 31) / 32 * 32;    // factor columns kept in the workspace rows (0, 32 or 64)
     static constexpr int W = C + RP2;
-    static constexpr int KS = (C + RP) / 16;           // k-steps of the score contraction
-    static constexpr int CS = C / 16;                  // k-steps of the dP contraction
-    static constexpr int MB = W / 32;                  // 32-column blocks of dAq / dAk
+    static constexpr int KS = (CG + RP) / 16;          // k-steps of the score contraction (channels CG.. are zero: no step)
+    static constexpr int CS = CG / 16;                 // k-steps of the dP contraction
+    // DL: six to ten fp32 ranks.  A rank's six product columns are kept as three and three, 32 columns apart: the
+    // first three pair (a1, b3) (a2, b2) (a3, b1), so they hold every limb of either side once and are all that the
+    // factor gradients need: one 32-column output block instead of two (B 1, H 8, N 32186, C 16, R 9: of 12 + 15
+    // matrix instructions a block 2 + 2).
+    static constexpr bool DL = LIMB && RP == 64;
+    // FOLD: the forward at C = 32 carries log2 e on its query columns where the factors are fp32.  Formed the same
+    // way here, the exponent of P needs no multiply-add (the score chain starts at -lse log2 e), and the scores round
+    // as the forward's did (gradients against 64 bits, N 3001, R 9: 3.3e-3 -> 3.0e-3).  Not at head dimension 16,
+    // whose q scale is exact at the default scale: log2 e would round it (dk 2.5e-3 -> 3.6e-3).
+    static constexpr bool FOLD = LIMB && C == 32 && CG == C;
+    static constexpr int MBP = DL ? 1 : RP2 / 32;      // 32-column blocks of the factor gradients
+    static constexpr int MB = C / 32 + MBP;            // 32-column blocks of dAq / dAk
     static constexpr int MBC = C / 32;
     using T1 = Tile<W>;
     using T2 = Tile<C>;
-    static constexpr int kVecBytes = 1024;             // (lse2, D) of 32 rows in the first 256 bytes
+    static constexpr int kVecBytes = 1024;             // -lse2 of 32 rows, then their -D, in the first 256 bytes
     // Form of the dkv kernel.  Up to 128 operand columns its accumulators leave room for two waves per SIMD (three
     // at C = 32), which fill each other's gaps as they do in the dq kernel; above, one wave per SIMD overlaps
     // matrix and vector work of two blocks in its own instruction stream (PIPE).  PIPE against plain, one launch:
@@ -120,7 +133,7 @@ struct Cfg {
     // fp32 equal (its vector work, not the overlap, bounds it).
     static constexpr bool PIPE = C >= 128 || C + RP > 128;
     static constexpr int NSLOT_DKV = PIPE ? 5 : NSLOT;         // ring slots (PIPE: a block is used in two iterations)
-    static constexpr size_t kEpiLds = (size_t)kWaves * 32 * (RP2 + 1) * sizeof(float);
+    static constexpr size_t kEpiLds = (size_t)kWaves * 32 * (MBP * 32 + 1) * sizeof(float);
 };
 
 // ------------------------------------------------------------------------------------------
@@ -141,8 +154,10 @@ constexpr int kPrepRows = 256 / ((SPLIT ? Cfg<C, RP>::RP2 : Cfg<C, RP>::W) / 8);
 // fmul: factor of the factor columns (1, or 1/scale on the query side of a launch whose q columns
 // carry no scale: q k^T scale + phi_q phi_k^T = scale (q k^T + (phi_q / scale) phi_k^T); applied to fp32
 // factors before the limb split, as the forward does, and to bf16 factors only as a power of two).
-template <int C, int RP, bool QSIDE, bool SPLIT>
-FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const unsigned block, const float fmul) {
+// qscale: factor of the q columns.
+template <int C, int RP, bool QSIDE, bool SPLIT, bool DL>
+FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const unsigned block, const float fmul,
+                           const float qscale) {
     using K = Cfg<C, RP>;
     static_assert(!SPLIT || (RP > 0 && C % 64 == 0), "split rows: whole 64-column panels of channels, and factor columns to write");
     constexpr int CPR = (SPLIT ? K::RP2 : K::W) / 8;
@@ -167,7 +182,7 @@ FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const u
         }
         if (QSIDE) {
 #pragma unroll
-            for (int e = 0; e < 8; e++) a[e] = (bf16_t)((float)x[e] * p.scale);
+            for (int e = 0; e < 8; e++) a[e] = (bf16_t)((float)x[e] * qscale);
         } else {
             a = x;
         }
@@ -199,6 +214,8 @@ FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const u
                 u32x4 raw = u32x4{0u, 0u, 0u, 0u};
                 if (pc * 8 < p.R) raw = *(const u32x4*)(src + pc * 16);
                 a = as_bf16x8(raw);
+            } else if (DL) {
+                a = phi_chunk_dl_switch<QSIDE>((const float*)src, pc, p.R, fmul);
             } else {
                 a = phi_chunk_switch<QSIDE>(src, pc, p.R, f32, fmul);
             }
@@ -213,14 +230,14 @@ FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const u
 
 // The whole pre-pass in one launch: the first nb_q workgroups write the query-side rows, the rest the
 // key-side rows.  SQ, SK: that side is written in the split form (factor columns only).
-template <int C, int RP, bool SQ = false, bool SK = false>
+template <int C, int RP, bool DL, bool SQ = false, bool SK = false>
 __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, bf16_t* __restrict__ aq, bf16_t* __restrict__ ak,
-                                                      unsigned nb_q, float qmul) {
+                                                      unsigned nb_q, float qmul, float qscale) {
     const unsigned blk = blockIdx.x;
     if (blk < nb_q) {
-        bwd_prep_block<C, RP, true, SQ>(p, aq, blk, qmul);
+        bwd_prep_block<C, RP, true, SQ, DL>(p, aq, blk, qmul, qscale);
     } else {
-        bwd_prep_block<C, RP, false, SK>(p, ak, blk - nb_q, 1.f);
+        bwd_prep_block<C, RP, false, SK, DL>(p, ak, blk - nb_q, 1.f, 1.f);
     }
 }
 
@@ -241,7 +258,7 @@ __global__ __launch_bounds__(256) void bwd_pad16_kernel(const bf16_t* __restrict
 // acc[mb] holds columns mb*32 + 8*g + 4*hf + x (register 4*g + x) for row l32.
 // raw: the R columns are written as float without any limb summing (gradients of bf16 columns
 // kept in fp32 for a later reduction).
-template <int RP2, bool QSIDE>
+template <int RP2, bool QSIDE, bool DL>
 FB_DEV void store_dphi(const f32x16* acc_phi /* [RP2/32] */, float* scratch /* wave-private [32][RP2+1] */,
                        void* dst_row /* gradient row of this lane's token or null */, int R,
                        bool f32, bool raw, int l32, int hf, float* dslope = nullptr, float pos = 0.f) {
@@ -265,6 +282,9 @@ FB_DEV void store_dphi(const f32x16* acc_phi /* [RP2/32] */, float* scratch /* w
             const float* s = scratch + l32 * (RP2 + 1);
             if (raw) {
                 ((float*)dst_row)[r] = s[r];
+            } else if (DL) {
+                ((float*)dst_row)[r] = QSIDE ? (s[3 * r + 2] + s[3 * r + 1] + s[3 * r])       // b1, b2, b3
+                                             : (s[3 * r] + s[3 * r + 1] + s[3 * r + 2]);      // a1, a2, a3
             } else if (f32) {
                 // distinct limbs on the other side: query side [a1,a1,a2,a1,a2,a3] -> slots 0,2,5
                 // multiply dphi_k; key side [b1,b2,b1,b3,b2,b1] -> slots 0,1,3 multiply dphi_q
@@ -294,20 +314,19 @@ struct OperandRows {
 struct MainArgs {
     OperandRows aq;       // B*H*N rows
     OperandRows ak;       // B*H*M rows
-    const float2* vec;    // [B*H*N]  (lse * log2 e, D): written by the dq kernel, read by the dkv kernel
-    float2* vec_w;        // the same rows, for the dq kernel
-    float exp_mul;        // S exp_mul - lse2 is the exponent of P to base two: log2 e, times the scale where the q columns carry none
-    float dkv_mul;        // factor of d[K | phi_k] (the scale, where the q columns carry none)
+    float* vec;           // per head N values of -lse log2 e, then N of -D: written by the dq kernel, read by the dkv kernel
+    float exp_mul;        // S exp_mul - lse2 is the exponent of P to base two (not used by FOLD): log2 e, times the scale where the q columns carry none
+    float dkv_mul;        // factor of d[K | phi_k] (the scale, where the q columns carry none; 1 / log2 e for FOLD)
 };
 
 // DENSE (RP = 0 only): the bias is a dense [N][M] matrix instead of factors.  Every wave also
 // copies the 32 x 32 bias tile of (its lane rows) x (the streamed block) into the slot, two
 // direct loads per block; the S chain starts from those values; the dq kernel writes
 // dS = dBias from its packed operand registers.
-template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE>
+template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG>
 FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem, const int bh, const int tile) {
     static_assert(!DENSE || RP == 0, "dense bias and factors are exclusive");
-    using K = Cfg<C, RP>;
+    using K = Cfg<C, RP, LIMB, CG>;
     using T1 = typename K::T1;
     using T2 = typename K::T2;
     constexpr int kBiasTile = 32 * 32 * 2;     // one wave's tile: 32 rows of 64 bytes
@@ -338,18 +357,18 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     const bf16_t* t1p = S1.phi + sbase_rows * S1.phi_pitch;
     const float emul = a.exp_mul;
     const bf16_t* t2g = (const bf16_t*)(DKV ? p.dout : p.v) + sbase_rows * C;
-    const float2* vecg = a.vec + (size_t)bh * p.N;                                  // per query row
+    float* vecg = a.vec + (size_t)bh * 2 * p.N;                                     // per query row
 
     // ---- lane-side operands, loop invariant ----
     bf16x8 l1reg[K::KS], l2reg[K::CS];
 #pragma unroll
     for (int ks = 0; ks < K::KS; ks++)
-        l1reg[ks] = as_bf16x8(*(const u32x4*)(ks * 16 < C ? l1m + (size_t)rc * L1.main_pitch + ks * 16 + 8 * hf
-                                                          : l1p + (size_t)rc * L1.phi_pitch + (ks * 16 - C) + 8 * hf));
+        l1reg[ks] = as_bf16x8(*(const u32x4*)(ks * 16 < CG ? l1m + (size_t)rc * L1.main_pitch + ks * 16 + 8 * hf
+                                                           : l1p + (size_t)rc * L1.phi_pitch + (ks * 16 - CG) + 8 * hf));
 #pragma unroll
     for (int cs = 0; cs < K::CS; cs++)
         l2reg[cs] = as_bf16x8(*(const u32x4*)(l2g + (size_t)rc * C + cs * 16 + 8 * hf));
-    float my_lse2 = 0.f, my_d = 0.f;    // dq kernel: this lane's row (formed below, behind the first block loads)
+    float my_nl = 0.f, my_nd = 0.f;     // dq kernel: -lse2 and -D of this lane's row (formed below, behind the first block loads)
 
     f32x16 acc1[K::MB];                 // dAk^T or dAq^T
     f32x16 acc2[DKV ? K::MBC : 1];      // dV^T
@@ -377,7 +396,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     // slots repeat load ND-1 (same source, same destination, same bytes as the wave that owns it).
     // wave-uniform per load: running source pointer of the block being issued, bytes per block,
     // LDS offset inside a slot, row-offset limit for the sequence's last (partial) block;
-    // per lane: byte offset of its source row (a chunk of two rows for the vec rows) and of its
+    // per lane: byte offset of its source row (a chunk of four values for the vec rows) and of its
     // 16 bytes inside the row
     unsigned dma_rowoff[NDW], dma_col[NDW], dma_taillim[NDW];
     const unsigned char* dma_ptr[NDW];
@@ -408,11 +427,12 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             dma_col[j] = (unsigned)chunk * 16u;
             dma_dst[j] = kOffT2 + dst;
         } else {
-            // vec: 32 rows x 8 bytes = 16 chunks of two rows; the other lanes repeat chunk 15
-            row = min(lane, 15);
+            // vec: eight chunks of four -lse2, eight of four -D; the other lanes repeat the last chunk.  A chunk that
+            // holds the head's last row may end in up to three values of whatever follows (inside the workspace).
+            row = min(lane, 15) & 7;
             dma_src_j = (const unsigned char*)vecg;
-            dma_bstride[j] = BT * 8; dma_pitch_j = 16; dma_lshift_j = 1;
-            dma_col[j] = 0u;
+            dma_bstride[j] = BT * 4; dma_pitch_j = 16; dma_lshift_j = 2;
+            dma_col[j] = lane >= 8 ? (unsigned)p.N * 4u : 0u;
             dma_dst[j] = kOffVec;
         }
         dma_dst[j] = __builtin_amdgcn_readfirstlane(dma_dst[j]);     // wave-uniform by construction: keep it scalar
@@ -587,7 +607,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     // operand n of a block whose slot offset is folded into rb (row reads) / tb (transpose reads);
     // callers keep a rolling window opr[n % (LA + 1)]
     auto read_op = [&](const RowBase& rb, const TrBase& tb, int n) __attribute__((always_inline)) {
-        if (n < K::KS) return row_read(rb, 0, T1::NP64, n);
+        if (n < K::KS) return row_read(rb, 0, T1::NP64, n < CG / 16 ? n : n + (C - CG) / 16);
         if (n < NA) return row_read(rb, kOffT2, T2::NP64, n - K::KS);
         if (LAZY_DS) {
             // the P-side output (dV) first: its operand is complete when the first half ends, while dS
@@ -599,24 +619,14 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         return tr_read(tb, kOffT2, T2::NP64, (n - NA - NO1) >> 1, (n - NA - NO1) & 1);
     };
 
-    // Head dimension 16 on the 32-channel operand rows: channels 16..31 are zero on both sides, so the
-    // second k-step of the S chain and of the dP chain contribute nothing (the operand is still read,
-    // which keeps the rolling window's positions).
-    const bool narrow = C == 32 && p.Cg == 16;          // wave-uniform
-    auto dead_step = [&](int n) __attribute__((always_inline)) {
-        return C == 32 && narrow && (n == 1 || n == K::KS + 1);
-    };
-
+    using Yes = std::true_type;
+    using No = std::false_type;
     // P and dS of one accumulator element r (streamed row sb0 + 8*(r/4) + 4*hf + (r%4), lane row ri)
-    auto elem = [&](int r, const f32x16& s, const f32x16& dp, float lvx, float dvx, bool need_mask, int sb0,
+    // SADD, DADD: nl and nd are still to be added (else the tiles started from them)
+    auto elem = [&](int r, const f32x16& s, const f32x16& dp, float nl, float nd, auto sadd, auto dadd,
                     bf16x8 (&pb)[2], bf16x8 (&dsb)[2]) __attribute__((always_inline)) {
-        float pr = fast_exp2(fmaf(s[r], emul, -lvx));
-        float ds = pr * (dp[r] - dvx);
-        if (need_mask) {
-            const int srow = sb0 + 8 * (r / 4) + 4 * hf + (r % 4);
-            const bool dead = srow >= NS || (CAUSAL && (DKV ? (srow < ri) : (srow > ri)));
-            if (dead) { pr = 0.f; ds = 0.f; }   // also discards the filler rows past N
-        }
+        const float pr = fast_exp2(sadd.value ? fmaf(s[r], emul, nl) : s[r]);
+        const float ds = pr * (dadd.value ? dp[r] + nd : dp[r]);
         if (DKV) pb[r / 8][r % 8] = (bf16_t)pr;
         dsb[r / 8][r % 8] = (bf16_t)ds;
     };
@@ -644,7 +654,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         // behind an inner link of a chain would read it too early (seen as a wrong dK at C = 128,
         // R = 9 fp32 factors; those instantiations keep the compiler's forms).
         constexpr bool SV = !DENSE && C + RP <= 144;
-        static_assert(!SV || C != 32, "a chain's last link carries its wait states: it must not be a dead step");
         // one link of the S (n < KS) or dP chain of a block into the VGPR tiles st / dt
         auto chain_link = [&](int n, f32x16& st, f32x16& dt, bf16x8 o) __attribute__((always_inline)) {
             // the last link of each chain
@@ -659,7 +668,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                 else mfma32_vdst(dt, o, l2reg[n - K::KS]);
             }
         };
-        static_assert(K::KS >= 2 && NA - K::KS >= 2, "a first and a last link per chain");
+        static_assert(!SV || (K::KS >= 2 && NA - K::KS >= 2), "a first and a last link per chain");
         issue_block(0, 0); issue_bias(0, 0);
         issue_block(1, 1); issue_bias(1, 1);
         issue_block(2, 2); issue_bias(2, 2);
@@ -676,7 +685,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
             for (int n = 0; n < NA; n++) {
                 const bf16x8 o = read_op(r0, t0, n);
-                if (dead_step(n)) continue;
                 if (SV) {
                     chain_link(n, sA, dA, o);
                 } else {
@@ -688,17 +696,15 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         RowBase rb1 = mk_row(kSlotBytes);     // rows of block i+1
 #pragma unroll
         for (int n = 0; n < LA; n++) opr[n] = read_op(rb1, TrBase{}, n);
-        // (lse2, D) of the 16 streamed rows this lane's accumulator registers belong to, one block ahead
-        float vq[4][4], vd[4][4];
-        const int vlane = kOffVec + 32 * hf;
+        // -lse2 and -D of the 16 streamed rows this lane's accumulator registers belong to, one block ahead
+        f32x4 vq[4], vd[4];
+        const int vlane = kOffVec + 16 * hf;
         auto read_vec = [&](int off) __attribute__((always_inline)) {
             const unsigned char* vp = smem + (vlane + off);
 #pragma unroll
             for (int g = 0; g < 4; g++) {
-                const float4 x0 = *(const float4*)(vp + 64 * g);
-                const float4 x1 = *(const float4*)(vp + 64 * g + 16);
-                vq[g][0] = x0.x; vd[g][0] = x0.y; vq[g][1] = x0.z; vd[g][1] = x0.w;
-                vq[g][2] = x1.x; vd[g][2] = x1.y; vq[g][3] = x1.z; vd[g][3] = x1.w;
+                vq[g] = *(const f32x4*)(vp + 32 * g);
+                vd[g] = *(const f32x4*)(vp + 32 * g + 128);
             }
         };
         read_vec(0);
@@ -721,21 +727,19 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
             for (int n = 0; n < NA; n++) {
                 opr[(n + LA) % (LA + 1)] = read_op(rb1, tb0, n + LA);   // past NA: output operands of block i
-                if (!dead_step(n)) {
-                    if (SV) {
-                        chain_link(n, sn, dn, opr[n % (LA + 1)]);
-                    } else {
-                        if (n < K::KS) sn = mfma32(opr[n % (LA + 1)], l1reg[n], n == 0 ? sinit : sn);
-                        else dn = mfma32(opr[n % (LA + 1)], l2reg[n - K::KS], n == K::KS ? zero : dn);
-                    }
+                if (SV) {
+                    chain_link(n, sn, dn, opr[n % (LA + 1)]);
+                } else {
+                    if (n < K::KS) sn = mfma32(opr[n % (LA + 1)], l1reg[n], n == 0 ? sinit : sn);
+                    else dn = mfma32(opr[n % (LA + 1)], l2reg[n - K::KS], n == K::KS ? zero : dn);
                 }
 #pragma unroll
                 for (int e = (n * 16) / NA; e < ((n + 1) * 16) / NA; e++) {
                     if (LAZY_DS) {
-                        prf[e] = fast_exp2(fmaf(sc[e], emul, -vq[e >> 2][e & 3]));
+                        prf[e] = fast_exp2(fmaf(sc[e], emul, vq[e >> 2][e & 3]));
                         pb[e / 8][e % 8] = (bf16_t)prf[e];
                     } else {
-                        elem(e, sc, dc, vq[e >> 2][e & 3], vd[e >> 2][e & 3], false, sb0, pb, dsb);
+                        elem(e, sc, dc, vq[e >> 2][e & 3], vd[e >> 2][e & 3], Yes{}, Yes{}, pb, dsb);
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -777,7 +781,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                     // dS of block i under the dV MFMAs, 16 / NO2 elements per MFMA
 #pragma unroll
                     for (int e = (m * 16) / NO2; e < ((m + 1) * 16) / NO2; e++)
-                        dsb[e / 8][e % 8] = (bf16_t)(prf[e] * (dc[e] - vd[e >> 2][e & 3]));
+                        dsb[e / 8][e % 8] = (bf16_t)(prf[e] * (dc[e] + vd[e >> 2][e & 3]));
                     __builtin_amdgcn_sched_barrier(0);
                 } else {
                     acc1[(m - NO2) >> 1] = mfma32(opr[n % (LA + 1)], dsb[(m - NO2) & 1], acc1[(m - NO2) >> 1]);
@@ -815,20 +819,23 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         // launched behind it (no separate pass over out and dO).  Placed here so that the row loads
         // are in flight together with the first blocks.
         if (!DKV) {
-            const bf16_t* og = (const bf16_t*)p.out + (lbase + rc) * p.Cg;
+            const bf16_t* og = (const bf16_t*)p.out + (lbase + rc) * CG;
             float dsum = 0.f;
 #pragma unroll
             for (int cs = 0; cs < K::CS; cs++) {
-                if (cs * 16 < p.Cg) {      // (head dimension 16: the widened dO rows hold zeros there, out has no such channels)
+                {
                     const bf16x8 o8 = as_bf16x8(*(const u32x4*)(og + cs * 16 + 8 * hf));
 #pragma unroll
                     for (int e = 0; e < 8; e++) dsum = fmaf((float)o8[e], (float)l2reg[cs][e], dsum);
                 }
             }
             dsum += __shfl_xor(dsum, 32);
-            my_d = dsum;
-            my_lse2 = p.lse[lbase + rc] * kLog2e;
-            if (hf == 0 && ri < NL) a.vec_w[lbase + ri] = make_float2(my_lse2, my_d);
+            my_nd = -dsum;
+            my_nl = -(p.lse[lbase + rc] * kLog2e);
+            if (hf == 0 && ri < NL) {
+                vecg[ri] = my_nl;
+                vecg[NL + ri] = my_nd;
+            }
         }
         wait_vmcnt<0>();
         __syncthreads();
@@ -838,6 +845,29 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
         for (int n = 0; n < LA; n++) opr[n] = read_op(rb0, TrBase{}, n);
 
+        // Start values of the tiles.  dkv: dP from -D (and S from -lse2, FOLD), read straight into the accumulators in
+        // the second half of the block before.  dq at C = 32: the same from this lane's pair; the wider ones have no
+        // registers for it.  A started dP saves its subtraction, FOLD the multiply-add, of about 100 vector
+        // instructions a block where the vector ALU is the bound.
+        constexpr bool SINIT = K::FOLD, DINIT = DKV || C == 32;
+        f32x16 s, dp;
+        auto init_tiles = [&](int off) __attribute__((always_inline)) {
+            const unsigned char* vp = smem + (off + kOffVec + 16 * hf);
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                f32x4 a4 = {0.f, 0.f, 0.f, 0.f}, b4 = {0.f, 0.f, 0.f, 0.f};
+                if (DKV) {
+                    if (SINIT) a4 = *(const f32x4*)(vp + 32 * g);
+                    b4 = *(const f32x4*)(vp + 32 * g + 128);
+                } else {
+                    if (SINIT) a4 = f32x4{my_nl, my_nl, my_nl, my_nl};
+                    if (DINIT) b4 = f32x4{my_nd, my_nd, my_nd, my_nd};
+                }
+#pragma unroll
+                for (int x = 0; x < 4; x++) { s[4 * g + x] = a4[x]; dp[4 * g + x] = b4[x]; }
+            }
+        };
+        init_tiles(0);
         for (int i = 0; i < nIt; i++) {
             const int slot = i & (NSLOT - 1);
             const TrBase tb0 = mk_tr(slot * kSlotBytes);
@@ -845,33 +875,22 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             const int sb0 = blk_of(i) * BT;      // first streamed row of the block
 
             // ---------------- first half: S and dP chains ----------------
-            f32x16 s, dp;
-#pragma unroll
-            for (int r = 0; r < 16; r++) { s[r] = 0.f; dp[r] = 0.f; }
             if (DENSE) bias_init(s, slot * kSlotBytes);
 #pragma unroll
             for (int n = 0; n < NA; n++) {
                 opr[(n + LA) % (LA + 1)] = read_op(rb0, tb0, n + LA);   // n + LA < NOPS: the output operands follow
-                if (dead_step(n)) continue;
                 if (n < K::KS) s = mfma32(opr[n % (LA + 1)], l1reg[n], s);
                 else dp = mfma32(opr[n % (LA + 1)], l2reg[n - K::KS], dp);
             }
             // ---------------- P and dS in accumulator layout ----------------
             bf16x8 pb[2], dsb[2];
-            if (DKV) {
-                const unsigned char* vp = smem + (slot * kSlotBytes + kOffVec + 32 * hf);
+            using SAdd = std::integral_constant<bool, !SINIT>;
+            using DAdd = std::integral_constant<bool, !DINIT>;
+            f32x4 nl4 = {my_nl, my_nl, my_nl, my_nl};
 #pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    const float4 x0 = *(const float4*)(vp + 64 * g);
-                    const float4 x1 = *(const float4*)(vp + 64 * g + 16);
-                    elem(4 * g + 0, s, dp, x0.x, x0.y, false, sb0, pb, dsb);
-                    elem(4 * g + 1, s, dp, x0.z, x0.w, false, sb0, pb, dsb);
-                    elem(4 * g + 2, s, dp, x1.x, x1.y, false, sb0, pb, dsb);
-                    elem(4 * g + 3, s, dp, x1.z, x1.w, false, sb0, pb, dsb);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; r++) elem(r, s, dp, my_lse2, my_d, false, sb0, pb, dsb);
+            for (int r = 0; r < 16; r++) {
+                if (DKV && !SINIT && r % 4 == 0) nl4 = *(const f32x4*)(smem + (slot * kSlotBytes + kOffVec + 16 * hf + 8 * r));
+                elem(r, s, dp, nl4[r % 4], my_nd, SAdd{}, DAdd{}, pb, dsb);
             }
             if ((sb0 + BT > NS) || (CAUSAL && (DKV ? sb0 < rw0 + 31 : sb0 + BT - 1 > rw0))) {
                 // rare (diagonal blocks, sequence end): zero the dead elements behind a real branch
@@ -920,6 +939,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             }
 #pragma unroll
             for (int n = 0; n < LA; n++) opr[n] = nxt[n];
+            init_tiles(((i + 1) & (NSLOT - 1)) * kSlotBytes);
             rb0 = rbn;
         }
         if (DENSE && !DKV && CAUSAL && ri < NL) {
@@ -943,7 +963,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             for (int r = 0; r < 16; r++) acc1[mb][r] *= a.dkv_mul;
     }
     const bool rok = ri < NL;
-    const int Cg = p.Cg;      // channels of the caller's gradient rows (< C: the rest is not stored)
+    constexpr int Cg = CG;    // channels of the caller's gradient rows (< C: the rest is not stored)
     const size_t base = (size_t)bh * NL * Cg;
     const bool g32 = p.grad_f32 != 0;      // wave-uniform
     if (rok) {
@@ -991,20 +1011,20 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     if (RP > 0) {
         const bool f32 = p.phi_f32 != 0;
         const size_t esz = (f32 || g32) ? 4 : 2;
-        float* scratch = (float*)smem + wave * 32 * (K::RP2 + 1);
+        float* scratch = (float*)smem + wave * 32 * (K::MBP * 32 + 1);
         unsigned char* dst = nullptr;
         unsigned char* const dphi = (unsigned char*)(DKV ? p.dphi_k : p.dphi_q);     // NULL: factor gradients not wanted
         if (rok && dphi != nullptr) dst = dphi + ((size_t)bh * NL + ri) * R * esz;
         // the key-side limb order applies to the key's own gradient and vice versa
         float* dsl = nullptr;
         if (!DKV && rok && p.slopes != nullptr && p.dslope != nullptr) dsl = p.dslope + (size_t)bh * NL + ri;
-        store_dphi<K::RP2, !DKV>(&acc1[K::MBC], scratch, dst, R, f32, g32, l32, hf, dsl, (float)ri);
+        store_dphi<K::MBP * 32, !DKV, K::DL>(&acc1[K::MBC], scratch, dst, R, f32, g32, l32, hf, dsl, (float)ri);
     }
 }
 
 // Work units: one 128-row tile per workgroup, or when causal the tile pair (n-1-u, u), whose
 // streamed ranges add up to the same length for every u (no tail of heavy tiles).
-template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE = false>
+template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG>
 __global__ __launch_bounds__(kThreads, (DKV ? Cfg<C, RP>::PIPE : (DENSE || C + RP > 160)) ? 1 : 2) void bwd_main_kernel(BwdParams p, MainArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);
@@ -1015,28 +1035,28 @@ __global__ __launch_bounds__(kThreads, (DKV ? Cfg<C, RP>::PIPE : (DENSE || C + R
     if (CAUSAL) {
         const int other = p.n_tiles - 1 - u;
         // heavier tile first: high query tiles for dq, low key tiles for dkv
-        bwd_tile<C, RP, CAUSAL, DKV, DENSE>(p, a, smem, bh, DKV ? u : other);
+        bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG>(p, a, smem, bh, DKV ? u : other);
         if (u != other) {
             __syncthreads();   // the epilogue's LDS scratch is reused as ring memory
-            bwd_tile<C, RP, CAUSAL, DKV, DENSE>(p, a, smem, bh, DKV ? other : u);
+            bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG>(p, a, smem, bh, DKV ? other : u);
         }
     } else {
-        bwd_tile<C, RP, CAUSAL, DKV, DENSE>(p, a, smem, bh, u);
+        bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG>(p, a, smem, bh, u);
     }
 }
 
 // Pre-pass and the two main kernels.  DENSE: the bias is a dense matrix streamed tile by tile
 // (RP = 0) and the dq kernel also writes dBias.
-template <int C, int RP, bool CAUSAL, bool DENSE = false>
+template <int C, int RP, bool CAUSAL, bool DENSE, bool LIMB, int CG>
 int launch(const BwdParams& pin, hipStream_t stream) {
-    using K = Cfg<C, RP>;
+    using K = Cfg<C, RP, LIMB, CG>;
     constexpr size_t slot = K::T1::BYTES + K::T2::BYTES + (DENSE ? (size_t)kWaves * 32 * 32 * 2 : 0);
     constexpr size_t ring_dq = (size_t)NSLOT * slot;
     constexpr size_t ring_dkv = (size_t)K::NSLOT_DKV * (slot + K::kVecBytes);
     constexpr size_t lds_dq = ring_dq > K::kEpiLds ? ring_dq : K::kEpiLds;
     constexpr size_t lds_dkv = ring_dkv > K::kEpiLds ? ring_dkv : K::kEpiLds;
-    auto kdq = bwd_main_kernel<C, RP, CAUSAL, false, DENSE>;
-    auto kdkv = bwd_main_kernel<C, RP, CAUSAL, true, DENSE>;
+    auto kdq = bwd_main_kernel<C, RP, CAUSAL, false, DENSE, LIMB, CG>;
+    auto kdkv = bwd_main_kernel<C, RP, CAUSAL, true, DENSE, LIMB, CG>;
     static FbLdsOnce once_dq, once_dkv;
     if (!fb_raise_lds_limit((const void*)kdq, lds_dq, once_dq) || !fb_raise_lds_limit((const void*)kdkv, lds_dkv, once_dkv))
         return 1;
@@ -1052,70 +1072,55 @@ int launch(const BwdParams& pin, hipStream_t stream) {
     // that is a power of two (head dimension 64 at the default scale with bf16 factors, and the
     // multiplicative form, whose prepared rows carry their scale already).  Never with a dense bias, which
     // enters the chain unscaled.
+    if (pin.Cg != CG || (LIMB && !pin.phi_f32) || (K::DL && pin.R > 10)) return -1;
     constexpr bool kCanSplit = C % 64 == 0;
     int mant_exp = 0;
     const bool pow2 = std::frexp(pin.scale, &mant_exp) == 0.5f;
-    const bool split_k = kCanSplit && pin.Cg == C;
+    const bool split_k = kCanSplit;
     const bool split_q = split_k && !DENSE && (pow2 || RP == 0 || pin.phi_f32 != 0 || pin.slopes != nullptr);
-    // workspace: vec [rows] float2 | Aq [rows][W or RP2] bf16 | Ak [rowsk][W or RP2] bf16  (each a multiple of 16 bytes)
+    // workspace: vec [rows][2] float | Aq [rows][W or RP2] bf16 | Ak [rowsk][W or RP2] bf16  (each a multiple of 16 bytes)
     unsigned char* ws = (unsigned char*)pin.workspace;
     MainArgs a;
-    a.vec = (const float2*)ws;
-    a.vec_w = (float2*)ws;
+    a.vec = (float*)ws;
     bf16_t* aq = (bf16_t*)(ws + (((size_t)rows * 8 + 15) & ~(size_t)15));
     bf16_t* ak = aq + (size_t)rows * (split_q ? K::RP2 : K::W);
     a.aq = split_q ? OperandRows{(const bf16_t*)pin.q, C, aq, K::RP2} : OperandRows{aq, K::W, aq + C, K::W};
     a.ak = split_k ? OperandRows{(const bf16_t*)pin.k, C, ak, K::RP2} : OperandRows{ak, K::W, ak + C, K::W};
     a.exp_mul = split_q ? kLog2e * pin.scale : kLog2e;
-    a.dkv_mul = split_q ? pin.scale : 1.f;
-    const float qmul = split_q ? 1.f / pin.scale : 1.f;
+    a.dkv_mul = split_q ? pin.scale : (K::FOLD ? kLn2 : 1.f);
+    const float qmul = split_q ? 1.f / pin.scale : (K::FOLD ? kLog2e : 1.f);
+    const float qscale = K::FOLD ? pin.scale * kLog2e : pin.scale;      // the forward's product
 
     BwdParams p = pin;
-    bool narrow = false;
-    if constexpr (C == 32) {
-        if (pin.Cg == 16) {
-            // widened copies of v and dO behind the operand rows; out and dO keep their 16-channel rows
-            // for the row sums
-            narrow = true;
-            constexpr int RPB = kPrepRows<C, RP, false>;
-            const unsigned nb_q = (unsigned)((rows + RPB - 1) / RPB);
-            const unsigned nb_k = (unsigned)((rowsk + RPB - 1) / RPB);
-            bf16_t* vpad = ak + (size_t)rowsk * K::W;
-            bf16_t* dpad = vpad + (size_t)rowsk * 32;
-            hipLaunchKernelGGL(bwd_pad16_kernel, dim3((unsigned)((rowsk * 4 + 255) / 256)), dim3(256), 0, stream,
-                               (const bf16_t*)pin.v, vpad, rowsk);
-            hipLaunchKernelGGL(bwd_pad16_kernel, dim3((unsigned)((rows * 4 + 255) / 256)), dim3(256), 0, stream,
-                               (const bf16_t*)pin.dout, dpad, rows);
-            hipLaunchKernelGGL((bwd_pre_kernel<C, RP>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, 1.f);
-            if (hipGetLastError() != hipSuccess) return 1;
-            p.v = vpad;
-            p.dout = dpad;
-        }
+    auto blocks = [](long long r, int rows_per_block) { return (unsigned)((r + rows_per_block - 1) / rows_per_block); };
+    if constexpr (CG < C) {
+        // widened copies of v and dO behind the operand rows; out and dO keep their 16-channel rows for the row sums
+        bf16_t* vpad = ak + (size_t)rowsk * K::W;
+        bf16_t* dpad = vpad + (size_t)rowsk * 32;
+        hipLaunchKernelGGL(bwd_pad16_kernel, dim3((unsigned)((rowsk * 4 + 255) / 256)), dim3(256), 0, stream,
+                           (const bf16_t*)pin.v, vpad, rowsk);
+        hipLaunchKernelGGL(bwd_pad16_kernel, dim3((unsigned)((rows * 4 + 255) / 256)), dim3(256), 0, stream,
+                           (const bf16_t*)pin.dout, dpad, rows);
+        p.v = vpad;
+        p.dout = dpad;
     }
-    if (!narrow) {
-        if (pin.Cg != C) return -1;
-        auto blocks = [](long long r, int rows_per_block) { return (unsigned)((r + rows_per_block - 1) / rows_per_block); };
-        if constexpr (kCanSplit && RP > 0) {
-            constexpr int RS = kPrepRows<C, RP, true>, RW = kPrepRows<C, RP, false>;
-            if (split_q) {
-                const unsigned nb_q = blocks(rows, RS), nb_k = blocks(rowsk, RS);
-                if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, true, true>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul);
-            } else if (split_k) {
-                const unsigned nb_q = blocks(rows, RW), nb_k = blocks(rowsk, RS);
-                if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, false, true>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, 1.f);
-            } else {
-                const unsigned nb_q = blocks(rows, RW), nb_k = blocks(rowsk, RW);
-                if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, 1.f);
-            }
+    if constexpr (kCanSplit && RP > 0) {
+        constexpr int RS = kPrepRows<C, RP, true>, RW = kPrepRows<C, RP, false>;
+        if (split_q) {
+            const unsigned nb_q = blocks(rows, RS), nb_k = blocks(rowsk, RS);
+            if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, K::DL, true, true>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul, qscale);
         } else {
-            // no factor columns to write for a split side (RP = 0): its workgroups are simply not launched
-            constexpr int RW = kPrepRows<C, RP, false>;
-            const unsigned nb_q = split_q ? 0u : blocks(rows, RW);
-            const unsigned nb_k = split_k ? 0u : blocks(rowsk, RW);
-            if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, 1.f);
+            const unsigned nb_q = blocks(rows, RW), nb_k = blocks(rowsk, RS);
+            if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, K::DL, false, true>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul, qscale);
         }
-        if (hipGetLastError() != hipSuccess) return 1;
+    } else {
+        // no factor columns to write for a split side (RP = 0): its workgroups are simply not launched
+        constexpr int RW = kPrepRows<C, RP, false>;
+        const unsigned nb_q = split_q ? 0u : blocks(rows, RW);
+        const unsigned nb_k = split_k ? 0u : blocks(rowsk, RW);
+        if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, K::DL>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul, qscale);
     }
+    if (hipGetLastError() != hipSuccess) return 1;
 
     auto set_tiles = [](BwdParams& p, int lane_rows) {
         p.n_tiles = (lane_rows + 127) / 128;
@@ -1132,28 +1137,38 @@ int launch(const BwdParams& pin, hipStream_t stream) {
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
-template <int C, int RP>
+template <int C, int CG, int RP, bool LIMB = false>
 int dispatch_causal(const BwdParams& p, hipStream_t stream) {
-    return p.causal ? launch<C, RP, true>(p, stream) : launch<C, RP, false>(p, stream);
+    return p.causal ? launch<C, RP, true, false, LIMB, CG>(p, stream) : launch<C, RP, false, false, LIMB, CG>(p, stream);
 }
 
-template <int C>
+template <int C, int CG>
 int dispatch_rp(const BwdParams& p, int rp, hipStream_t stream) {
+    if (p.phi_f32 && rp > 32) return rp <= 64 ? dispatch_causal<C, CG, 64, true>(p, stream) : -1;     // DL
+    if constexpr (C == 32 && CG == C) {      // FOLD
+        if (p.phi_f32 && rp == 16) return dispatch_causal<C, CG, 16, true>(p, stream);
+        if (p.phi_f32 && rp == 32) return dispatch_causal<C, CG, 32, true>(p, stream);
+    }
     switch (rp) {
-        case 0: return dispatch_causal<C, 0>(p, stream);
-        case 16: return dispatch_causal<C, 16>(p, stream);
-        case 32: return dispatch_causal<C, 32>(p, stream);
-        case 48: return dispatch_causal<C, 48>(p, stream);
-        case 64: return dispatch_causal<C, 64>(p, stream);
+        case 0: return dispatch_causal<C, CG, 0>(p, stream);
+        case 16: return dispatch_causal<C, CG, 16>(p, stream);
+        case 32: return dispatch_causal<C, CG, 32>(p, stream);
+        case 48: return dispatch_causal<C, CG, 48>(p, stream);
+        case 64: return dispatch_causal<C, CG, 64>(p, stream);
         default: break;
     }
     // wider rows: the C (R - 1) extra channels of the multiplicative form (bf16 columns)
     if constexpr (C <= 64) {
         if (p.phi_f32) return -1;
-        if (rp == 96) return dispatch_causal<C, 96>(p, stream);
-        if (rp == 128) return dispatch_causal<C, 128>(p, stream);
+        if (rp == 96) return dispatch_causal<C, CG, 96>(p, stream);
+        if (rp == 128) return dispatch_causal<C, CG, 128>(p, stream);
     }
     return -1;
+}
+
+template <int C, int CG>
+int dispatch_dense(const BwdParams& p, hipStream_t stream) {
+    return p.causal ? launch<C, 0, true, true, false, CG>(p, stream) : launch<C, 0, false, true, false, CG>(p, stream);
 }
 
 }  // namespace
@@ -1167,20 +1182,20 @@ size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R) 
 
 int fb_launch_bwd_dense_bf16(const BwdParams& p, int C, hipStream_t stream) {
     switch (C) {
-        case 16: return p.causal ? launch<32, 0, true, true>(p, stream) : launch<32, 0, false, true>(p, stream);   // p.Cg = 16
-        case 32: return p.causal ? launch<32, 0, true, true>(p, stream) : launch<32, 0, false, true>(p, stream);
-        case 64: return p.causal ? launch<64, 0, true, true>(p, stream) : launch<64, 0, false, true>(p, stream);
-        case 128: return p.causal ? launch<128, 0, true, true>(p, stream) : launch<128, 0, false, true>(p, stream);
+        case 16: return dispatch_dense<32, 16>(p, stream);
+        case 32: return dispatch_dense<32, 32>(p, stream);
+        case 64: return dispatch_dense<64, 64>(p, stream);
+        case 128: return dispatch_dense<128, 128>(p, stream);
         default: return -1;
     }
 }
 
 int fb_launch_bwd_bf16(const BwdParams& p, int C, int rp, hipStream_t stream) {
     switch (C) {
-        case 16: return dispatch_rp<32>(p, rp, stream);      // p.Cg = 16
-        case 32: return dispatch_rp<32>(p, rp, stream);
-        case 64: return dispatch_rp<64>(p, rp, stream);
-        case 128: return dispatch_rp<128>(p, rp, stream);
+        case 16: return dispatch_rp<32, 16>(p, rp, stream);
+        case 32: return dispatch_rp<32, 32>(p, rp, stream);
+        case 64: return dispatch_rp<64, 64>(p, rp, stream);
+        case 128: return dispatch_rp<128, 128>(p, rp, stream);
         default: return -1;
     }
 }

@@ -264,4 +264,44 @@ FB_DEV bf16x8 phi_chunk_switch(const void* row, int c8, int R, bool f32, float m
     }
 }
 
+// Columns [8*C8, 8*C8+8) of the two-part limb layout of up to ten fp32 ranks in 64 columns: column j < 32 holds
+// limb slot j % 3 of rank j / 3 from the pairs (a1,b3) (a2,b2) (a3,b1), column 32 + j from (a1,b1) (a1,b2) (a2,b1).
+// The same six products as the layout above; the first part holds every limb of either side once.
+template <bool QSIDE, int C8>
+FB_DEV bf16x8 phi_chunk_dl(const float* row, int R, float mul) {
+    constexpr int half = C8 / 4, j0 = (C8 & 3) * 8, r0 = j0 / 3;
+    bf16_t limb[4][3];
+#pragma unroll
+    for (int d = 0; d < 4; d++) {
+        const float x = (r0 + d < R && r0 + d <= (j0 + 7) / 3) ? row[r0 + d] * mul : 0.f;
+        const bf16_t l1 = (bf16_t)x;
+        const float e1 = x - (float)l1;
+        const bf16_t l2 = (bf16_t)e1;
+        limb[d][0] = l1;
+        limb[d][1] = l2;
+        limb[d][2] = (bf16_t)(e1 - (float)l2);
+    }
+    bf16x8 out;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+        const int j = j0 + e, slot = j % 3;
+        const int n = half == 0 ? (QSIDE ? slot : 2 - slot) : (QSIDE ? slot >> 1 : slot & 1);
+        out[e] = limb[j / 3 - r0][n];
+    }
+    return out;
+}
+template <bool QSIDE>
+FB_DEV bf16x8 phi_chunk_dl_switch(const float* row, int c8, int R, float mul) {
+    switch (c8) {
+        case 0: return phi_chunk_dl<QSIDE, 0>(row, R, mul);
+        case 1: return phi_chunk_dl<QSIDE, 1>(row, R, mul);
+        case 2: return phi_chunk_dl<QSIDE, 2>(row, R, mul);
+        case 3: return phi_chunk_dl<QSIDE, 3>(row, R, mul);
+        case 4: return phi_chunk_dl<QSIDE, 4>(row, R, mul);
+        case 5: return phi_chunk_dl<QSIDE, 5>(row, R, mul);
+        case 6: return phi_chunk_dl<QSIDE, 6>(row, R, mul);
+        default: return phi_chunk_dl<QSIDE, 7>(row, R, mul);
+    }
+}
+
 #endif

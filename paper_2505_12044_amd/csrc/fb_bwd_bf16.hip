@@ -9,20 +9,19 @@
 // gradient is ever written.  No atomics; results are deterministic.
 //
 // Kernels:
-//   pre   : writes the concatenated operands Aq = [q*scale | phi_q | 0], Ak = [k | phi_k | 0]
-//           (bf16, width W = C + 32 or C + 64 when R > 0; fp32 factors as three bf16 limbs, six product
-//           columns per rank as in the forward) into the workspace -- or, for C = 64, 128, only their
-//           factor columns, the channel columns being read from k (and from q, where the scores are
-//           formed from q itself) in place
+//   pre   : writes the factor columns of the operands Aq = [q*scale | phi_q | 0], Ak = [k | phi_k | 0]
+//           into the workspace (bf16, 32 to 128 columns; fp32 factors as three bf16 limbs, six product columns
+//           per rank as in the forward), once per head where the factors are shared over the batch; the
+//           channel columns are read from k, and from q or its scaled copy, in place
 //   main<DKV = false> : a lane owns a query; streams 32-key blocks;   accumulates dAq^T; runs first and
-//                       leaves (lse * log2 e, D) per query row for the other
+//                       leaves -lse * log2 e and -D per query row, and q*scale where it is a rounding, for the other
 //   main<DKV = true>  : a lane owns a key;   streams 32-query blocks; accumulates dV^T, dAk^T
 // Both main kernels recompute S and dP (7 contractions instead of 5, but no atomic dQ).  They
 // use the transposed orientation of the forward: the lane-side operands stay in registers,
 // score-shaped accumulators feed the next MFMA as its B operand without leaving registers,
 // and the transposed A operands come from the LDS transpose read.
 //
-// Streaming.  Because the operand rows exist in memory, a streamed block is a pure
+// Streaming.  Because the operand columns exist in memory, a streamed block is a pure
 // copy, done with direct-to-LDS loads (global_load_lds_dwordx4 from inline assembly, see
 // fb_fwd_bf16_dma.h for why) into a ring of four block slots; nothing passes through
 // registers.  One barrier per iteration, in the middle:
@@ -122,8 +121,10 @@ struct Cfg {
     static constexpr int MBP = DL ? 1 : RP2 / 32;      // 32-column blocks of the factor gradients
     static constexpr int MB = C / 32 + MBP;            // 32-column blocks of dAq / dAk
     static constexpr int MBC = C / 32;
-    using T1 = Tile<W>;
+    using TC = Tile<C>;                                // channel panels of a streamed operand tile; T2: the dP operand
+    using TP = Tile<RP2>;                              // factor panels, behind them
     using T2 = Tile<C>;
+    static constexpr int T1_BYTES = TC::BYTES + TP::BYTES, T1_NDMA = TC::NDMA + TP::NDMA;
     static constexpr int kVecBytes = 1024;             // -lse2 of 32 rows, then their -D, in the first 256 bytes
     // Form of the dkv kernel.  Up to 128 operand columns its accumulators leave room for two waves per SIMD (three
     // at C = 32), which fill each other's gaps as they do in the dq kernel; above, one wave per SIMD overlaps
@@ -139,118 +140,105 @@ struct Cfg {
 // ------------------------------------------------------------------------------------------
 // prep / vec
 // ------------------------------------------------------------------------------------------
-// One side per launch: QSIDE writes Aq = [q*scale | phi_q | 0] for the B*H*N query rows,
-// otherwise Ak = [k | phi_k | 0] for the B*H*M key rows.
-// A workgroup covers kPrepRows<C, RP> whole rows (one thread per 16-byte piece; the few threads past
-// the last whole row idle), so a thread's row and piece come from its index by a division by a
-// constant, and the head and position of the row from one block-uniform division plus a wrap.
-//
-// SPLIT: the main kernels read the C channel columns straight from the caller's q or k rows, and
-// only the factor columns are written, as rows of RP2 columns (key side: a plain saving, the k
-// columns were a copy; query side: the scale moves out of the q columns, see fmul).
-template <int C, int RP, bool SPLIT>
-constexpr int kPrepRows = 256 / ((SPLIT ? Cfg<C, RP>::RP2 : Cfg<C, RP>::W) / 8);
+// The factor columns of the operand rows, RP2 to a row: limbs or copies of phi (or generated ALiBi factors).  The
+// channel columns are the caller's q and k, read in place (or, where the scale has to be rounded into q, the scaled
+// rows that the dq kernel leaves; head dimension 16: the widened copies below).  Factors shared over the batch, or
+// generated from slopes, are written once per head and not once per batch element (B 384, H 4, N 384, C 32, R 16:
+// whole rows per batch element 42 us, this 4 us and the scaled q rows inside the dq kernel).
+// A workgroup covers kPrepRows whole rows (one thread per 16-byte piece; the few threads past the last whole row
+// idle), so a thread's row and piece come from its index by a division by a constant, and the head and position of
+// the row from one block-uniform division plus a wrap.
+template <int RP2>
+constexpr int kPrepRows = 256 / (RP2 > 0 ? RP2 / 8 : 1);
 
 // fmul: factor of the factor columns (1, or 1/scale on the query side of a launch whose q columns
-// carry no scale: q k^T scale + phi_q phi_k^T = scale (q k^T + (phi_q / scale) phi_k^T); applied to fp32
-// factors before the limb split, as the forward does, and to bf16 factors only as a power of two).
-// qscale: factor of the q columns.
-template <int C, int RP, bool QSIDE, bool SPLIT, bool DL>
-FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const unsigned block, const float fmul,
-                           const float qscale) {
-    using K = Cfg<C, RP>;
-    static_assert(!SPLIT || (RP > 0 && C % 64 == 0), "split rows: whole 64-column panels of channels, and factor columns to write");
-    constexpr int CPR = (SPLIT ? K::RP2 : K::W) / 8;
-    constexpr int RPB = kPrepRows<C, RP, SPLIT>;
-    constexpr int DW = SPLIT ? K::RP2 : K::W;                 // columns of a destination row
-    constexpr int C0 = SPLIT ? C / 8 : 0;                     // first piece of a destination row
+// carry no scale: q k^T scale + phi_q phi_k^T = scale (q k^T + (phi_q / scale) phi_k^T), or log2 e, see FOLD;
+// applied to fp32 factors before the limb split, as the forward does, and to bf16 factors only as a power of two).
+template <int RP2, bool QSIDE, bool DL>
+FB_DEV void bwd_prep_block(const BwdParams& p, bf16_t* __restrict__ dst, const unsigned block, const long long rows,
+                           const float fmul) {
+    constexpr int CPR = RP2 / 8;
+    constexpr int RPB = kPrepRows<RP2>;
     const unsigned len = (unsigned)(QSIDE ? p.N : p.M);
     const unsigned dr = threadIdx.x / CPR;
-    const int c = (int)(threadIdx.x - dr * CPR) + C0;
+    const int pc = (int)(threadIdx.x - dr * CPR);
     const long long row0 = (long long)block * RPB;            // block-uniform
-    const long long row = row0 + dr;                          // (b*H + h)*len + i
-    const long long rows = (long long)p.B * p.H * len;
+    const long long row = row0 + dr;                          // (b*H + h)*len + i; shared factors: h*len + i
     if (dr >= (unsigned)RPB || row >= rows) return;
     bf16x8 a;
-    if (c < C / 8) {
-        bf16x8 x;
-        if (c * 8 < p.Cg) {
-            x = as_bf16x8(*(const u32x4*)((const bf16_t*)(QSIDE ? p.q : p.k) + row * p.Cg + c * 8));
-        } else {      // channels the caller's rows do not have
-#pragma unroll
-            for (int e = 0; e < 8; e++) x[e] = (bf16_t)0.f;
-        }
-        if (QSIDE) {
-#pragma unroll
-            for (int e = 0; e < 8; e++) a[e] = (bf16_t)((float)x[e] * qscale);
-        } else {
-            a = x;
-        }
+    const bool f32 = p.phi_f32 != 0;
+    const size_t esz = f32 ? 4 : 2;
+    // rows < 2^31: the block's first row splits into head and position once, the thread's row wraps
+    const unsigned bh0 = (unsigned)((unsigned long long)row0 / len);
+    unsigned bb = bh0 / (unsigned)p.H;
+    unsigned h = bh0 - bb * (unsigned)p.H;
+    unsigned i = (unsigned)((unsigned long long)row0 - (unsigned long long)bh0 * len) + dr;
+    while (i >= len) {
+        i -= len;
+        if (++h == (unsigned)p.H) { h = 0; ++bb; }
+    }
+    if (p.slopes != nullptr) {
+        // ALiBi factors of Example 3.4 from the head's slope and the row's position (App. D)
+        const float m = p.slopes[h];
+        float pair[2];
+        pair[0] = QSIDE ? -m * (float)i : 1.f;
+        pair[1] = QSIDE ? m : (float)i;
+        a = phi_chunk_switch<QSIDE>(pair, pc, 2, true, fmul);
     } else {
-        const bool f32 = p.phi_f32 != 0;
-        const size_t esz = f32 ? 4 : 2;
-        // rows < 2^31: the block's first row splits into head and position once, the thread's row wraps
-        const unsigned bh0 = (unsigned)((unsigned long long)row0 / len);
-        unsigned bb = bh0 / (unsigned)p.H;
-        unsigned h = bh0 - bb * (unsigned)p.H;
-        unsigned i = (unsigned)((unsigned long long)row0 - (unsigned long long)bh0 * len) + dr;
-        while (i >= len) {
-            i -= len;
-            if (++h == (unsigned)p.H) { h = 0; ++bb; }
-        }
-        const int pc = c - C / 8;
-        if (p.slopes != nullptr) {
-            // ALiBi factors of Example 3.4 from the head's slope and the row's position (App. D)
-            const float m = p.slopes[h];
-            float pair[2];
-            pair[0] = QSIDE ? -m * (float)i : 1.f;
-            pair[1] = QSIDE ? m : (float)i;
-            a = phi_chunk_switch<QSIDE>(pair, pc, 2, true, fmul);
+        const size_t off = ((size_t)bb * (QSIDE ? p.phi_bstride : p.phik_bstride) + ((size_t)h * len + i) * p.R) * esz;
+        const unsigned char* src = (const unsigned char*)(QSIDE ? p.phi_q : p.phi_k) + off;
+        if (!f32 && (p.R & 7) == 0) {
+            // bf16 factors in whole 16-byte pieces: a copy (rows and the batch stride are then multiples of 16 bytes)
+            u32x4 raw = u32x4{0u, 0u, 0u, 0u};
+            if (pc * 8 < p.R) raw = *(const u32x4*)(src + pc * 16);
+            a = as_bf16x8(raw);
+        } else if (DL) {
+            a = phi_chunk_dl_switch<QSIDE>((const float*)src, pc, p.R, fmul);
         } else {
-            const size_t off = ((size_t)bb * (QSIDE ? p.phi_bstride : p.phik_bstride) + ((size_t)h * len + i) * p.R) * esz;
-            const unsigned char* src = (const unsigned char*)(QSIDE ? p.phi_q : p.phi_k) + off;
-            if (!f32 && (p.R & 7) == 0) {
-                // bf16 factors in whole 16-byte pieces: a copy (rows and the batch stride are then multiples of 16 bytes)
-                u32x4 raw = u32x4{0u, 0u, 0u, 0u};
-                if (pc * 8 < p.R) raw = *(const u32x4*)(src + pc * 16);
-                a = as_bf16x8(raw);
-            } else if (DL) {
-                a = phi_chunk_dl_switch<QSIDE>((const float*)src, pc, p.R, fmul);
-            } else {
-                a = phi_chunk_switch<QSIDE>(src, pc, p.R, f32, fmul);
-            }
-            if (!f32 && fmul != 1.f) {      // a power of two: exact
+            a = phi_chunk_switch<QSIDE>(src, pc, p.R, f32, fmul);
+        }
+        if (!f32 && fmul != 1.f) {      // a power of two: exact
 #pragma unroll
-                for (int e = 0; e < 8; e++) a[e] = (bf16_t)((float)a[e] * fmul);
-            }
+            for (int e = 0; e < 8; e++) a[e] = (bf16_t)((float)a[e] * fmul);
         }
     }
-    *(u32x4*)(dst + row * DW + (c - C0) * 8) = as_uint4(a);
+    *(u32x4*)(dst + row * RP2 + pc * 8) = as_uint4(a);
 }
 
-// The whole pre-pass in one launch: the first nb_q workgroups write the query-side rows, the rest the
-// key-side rows.  SQ, SK: that side is written in the split form (factor columns only).
-template <int C, int RP, bool DL, bool SQ = false, bool SK = false>
+// Both sides in one launch: the first nb_q workgroups write the query-side rows, the rest the key-side rows.
+template <int RP2, bool DL>
 __global__ __launch_bounds__(256) void bwd_pre_kernel(BwdParams p, bf16_t* __restrict__ aq, bf16_t* __restrict__ ak,
-                                                      unsigned nb_q, float qmul, float qscale) {
+                                                      unsigned nb_q, long long rows_q, long long rows_k, float qmul) {
     const unsigned blk = blockIdx.x;
     if (blk < nb_q) {
-        bwd_prep_block<C, RP, true, SQ, DL>(p, aq, blk, qmul, qscale);
+        bwd_prep_block<RP2, true, DL>(p, aq, blk, rows_q, qmul);
     } else {
-        bwd_prep_block<C, RP, false, SK, DL>(p, ak, blk - nb_q, 1.f, 1.f);
+        bwd_prep_block<RP2, false, DL>(p, ak, blk - nb_q, rows_k, 1.f);
     }
 }
 
-// Head dimension 16: rows of 16 channels widened to 32 with zeros (the main kernels stream
-// v and dO tiles of 32 channels).  One thread per 16-byte piece of the destination.
-__global__ __launch_bounds__(256) void bwd_pad16_kernel(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst,
-                                                        long long rows) {
+// Head dimension 16: rows of 16 channels widened to 32 with zeros (the main kernels stream tiles of 32 channels).
+// One thread per 16-byte piece of the destination; blockIdx.y: q (times qscale), dO, k, v.
+struct Widen16 {
+    bf16_t *q, *dout, *k, *v;
+};
+__global__ __launch_bounds__(256) void bwd_widen16_kernel(BwdParams p, Widen16 w, long long rows_q, long long rows_k,
+                                                          float qscale) {
+    const unsigned side = blockIdx.y;
+    const bf16_t* src = (const bf16_t*)(side == 0 ? p.q : side == 1 ? p.dout : side == 2 ? p.k : p.v);
+    bf16_t* dst = side == 0 ? w.q : side == 1 ? w.dout : side == 2 ? w.k : w.v;
     const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
     const long long row = gid >> 2;
     const int c = (int)(gid & 3);
-    if (row >= rows) return;
+    if (row >= (side < 2 ? rows_q : rows_k)) return;
     u32x4 x = u32x4{0u, 0u, 0u, 0u};
     if (c < 2) x = *(const u32x4*)(src + row * 16 + c * 8);
+    if (side == 0) {
+        bf16x8 a = as_bf16x8(x);
+#pragma unroll
+        for (int e = 0; e < 8; e++) a[e] = (bf16_t)((float)a[e] * qscale);
+        x = as_uint4(a);
+    }
     *(u32x4*)(dst + row * 32 + c * 8) = x;
 }
 
@@ -304,18 +292,20 @@ FB_DEV void store_dphi(const f32x16* acc_phi /* [RP2/32] */, float* scratch /* w
 //   T1 tile: rows of the streamed operand of S (Aq when DKV, else Ak), width W
 //   T2 tile: rows of the streamed operand of dP (dO when DKV, else V), width C
 // ------------------------------------------------------------------------------------------
-// Operand rows [channels | factor columns] of one side.  Whole rows in the workspace: main = the rows,
-// phi = main + C, both pitches W.  Split: main = the caller's q or k rows (pitch C), phi = rows of the
-// RP2 factor columns in the workspace.
+// Operand rows [channels | factor columns] of one side: rows of C channels (the caller's q or k, or copies in the
+// workspace) and rows of the RP2 factor columns, one set per batch element or one for all (shared).
 struct OperandRows {
-    const bf16_t* main; int main_pitch;
-    const bf16_t* phi;  int phi_pitch;
+    const bf16_t* main;
+    const bf16_t* phi;
+    int shared;
 };
 struct MainArgs {
     OperandRows aq;       // B*H*N rows
     OperandRows ak;       // B*H*M rows
     float* vec;           // per head N values of -lse log2 e, then N of -D: written by the dq kernel, read by the dkv kernel
     float exp_mul;        // S exp_mul - lse2 is the exponent of P to base two (not used by FOLD): log2 e, times the scale where the q columns carry none
+    bf16_t* q_out;        // not NULL: the dq kernel forms its operand rows as bf16(q q_mul) and leaves them here (= aq.main)
+    float q_mul;
     float dkv_mul;        // factor of d[K | phi_k] (the scale, where the q columns carry none; 1 / log2 e for FOLD)
 };
 
@@ -327,13 +317,14 @@ template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG>
 FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem, const int bh, const int tile) {
     static_assert(!DENSE || RP == 0, "dense bias and factors are exclusive");
     using K = Cfg<C, RP, LIMB, CG>;
-    using T1 = typename K::T1;
+    using TC = typename K::TC;
+    using TP = typename K::TP;
     using T2 = typename K::T2;
     constexpr int kBiasTile = 32 * 32 * 2;     // one wave's tile: 32 rows of 64 bytes
-    constexpr int kOffT2 = T1::BYTES, kOffVec = T1::BYTES + T2::BYTES;
+    constexpr int kOffT2 = K::T1_BYTES, kOffVec = K::T1_BYTES + T2::BYTES;
     constexpr int kOffBias = kOffVec + (DKV ? K::kVecBytes : 0);
     constexpr int kSlotBytes = kOffBias + (DENSE ? kWaves * kBiasTile : 0);
-    constexpr int ND = T1::NDMA + T2::NDMA + (DKV ? 1 : 0);       // direct loads per block
+    constexpr int ND = K::T1_NDMA + T2::NDMA + (DKV ? 1 : 0);       // direct loads per block
     constexpr int NDW = (ND + kWaves - 1) / kWaves;               // ... per wave, at most
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
@@ -350,11 +341,13 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     const size_t lbase = (size_t)bh * NL, sbase_rows = (size_t)bh * NS;
     const OperandRows& L1 = DKV ? a.ak : a.aq;                                      // lane-side operand of S
     const OperandRows& S1 = DKV ? a.aq : a.ak;                                      // streamed operand of S
-    const bf16_t* l1m = L1.main + lbase * L1.main_pitch;
-    const bf16_t* l1p = L1.phi + lbase * L1.phi_pitch;
+    const int b_ = bh / p.H, h_ = bh - b_ * p.H;
+    const bool q_scaled_here = !DKV && a.q_out != nullptr;                          // wave-uniform
+    const bf16_t* l1m = (q_scaled_here ? (const bf16_t*)p.q : L1.main) + lbase * C;
+    const bf16_t* l1p = L1.phi + (size_t)(L1.shared ? h_ : bh) * NL * K::RP2;
     const bf16_t* l2g = (const bf16_t*)(DKV ? p.v : p.dout) + lbase * C;            // lane-side operand of dP
-    const bf16_t* t1m = S1.main + sbase_rows * S1.main_pitch;
-    const bf16_t* t1p = S1.phi + sbase_rows * S1.phi_pitch;
+    const bf16_t* t1m = S1.main + sbase_rows * C;
+    const bf16_t* t1p = S1.phi + (size_t)(S1.shared ? h_ : bh) * NS * K::RP2;
     const float emul = a.exp_mul;
     const bf16_t* t2g = (const bf16_t*)(DKV ? p.dout : p.v) + sbase_rows * C;
     float* vecg = a.vec + (size_t)bh * 2 * p.N;                                     // per query row
@@ -363,8 +356,17 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     bf16x8 l1reg[K::KS], l2reg[K::CS];
 #pragma unroll
     for (int ks = 0; ks < K::KS; ks++)
-        l1reg[ks] = as_bf16x8(*(const u32x4*)(ks * 16 < CG ? l1m + (size_t)rc * L1.main_pitch + ks * 16 + 8 * hf
-                                                           : l1p + (size_t)rc * L1.phi_pitch + (ks * 16 - CG) + 8 * hf));
+        l1reg[ks] = as_bf16x8(*(const u32x4*)(ks * 16 < CG ? l1m + (size_t)rc * C + ks * 16 + 8 * hf
+                                                           : l1p + (size_t)rc * K::RP2 + (ks * 16 - CG) + 8 * hf));
+    if (CG == C && q_scaled_here) {
+        bf16_t* qo = a.q_out + (lbase + rc) * C + 8 * hf;
+#pragma unroll
+        for (int ks = 0; ks < C / 16; ks++) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) l1reg[ks][e] = (bf16_t)((float)l1reg[ks][e] * a.q_mul);
+            if (ri < NL) *(u32x4*)(qo + ks * 16) = as_uint4(l1reg[ks]);
+        }
+    }
 #pragma unroll
     for (int cs = 0; cs < K::CS; cs++)
         l2reg[cs] = as_bf16x8(*(const u32x4*)(l2g + (size_t)rc * C + cs * 16 + 8 * hf));
@@ -409,19 +411,17 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         const unsigned char* dma_src_j;
         int dma_pitch_j, dma_lshift_j;
         int row = 0, chunk = 0, dst = 0;
-        if (d < T1::NDMA) {
-            T1::dma_map(d, lane, row, chunk, dst);
-            // a panel of 64 (or the last 32) columns comes from one array: the channel rows, or the factor
-            // rows when it starts at or behind column C (split rows have C % 64 == 0, so no panel mixes)
-            const int panel = d < T1::NP64 * 4 ? (d >> 2) : T1::NP64;
-            const bool fpart = panel * 64 >= C;
-            const int pitch_el = fpart ? S1.phi_pitch : S1.main_pitch;
+        if (d < K::T1_NDMA) {
+            const bool fpart = d >= TC::NDMA;      // a load takes channel or factor columns, never both
+            if (fpart) TP::dma_map(d - TC::NDMA, lane, row, chunk, dst);
+            else TC::dma_map(d, lane, row, chunk, dst);
+            const int pitch_el = fpart ? K::RP2 : C;
             dma_src_j = (const unsigned char*)(fpart ? t1p : t1m);
             dma_bstride[j] = BT * pitch_el * 2; dma_pitch_j = pitch_el * 2; dma_lshift_j = 0;
-            dma_col[j] = (unsigned)(fpart ? chunk - C / 8 : chunk) * 16u;
-            dma_dst[j] = dst;
-        } else if (d < T1::NDMA + T2::NDMA) {
-            T2::dma_map(d - T1::NDMA, lane, row, chunk, dst);
+            dma_col[j] = (unsigned)chunk * 16u;
+            dma_dst[j] = fpart ? TC::BYTES + dst : dst;
+        } else if (d < K::T1_NDMA + T2::NDMA) {
+            T2::dma_map(d - K::T1_NDMA, lane, row, chunk, dst);
             dma_src_j = (const unsigned char*)t2g;
             dma_bstride[j] = BT * C * 2; dma_pitch_j = C * 2; dma_lshift_j = 0;
             dma_col[j] = (unsigned)chunk * 16u;
@@ -457,7 +457,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     };
     // ---- dense bias tile of this wave: rows = queries, columns = keys, 64-byte rows; lane l of
     // load i covers tile row 16*i + l/4; chunk position l%4 holds 8-key chunk (l%4) ^ ((row>>2)&3)
-    const int b_ = bh / p.H, h_ = bh - b_ * p.H;
     const unsigned char* bias_src = nullptr;   // wave-uniform base of this wave's tiles
     size_t bias_bstep = 0;                     // bytes per streamed block
     int bias_var[2], bias_pitch = 0, bias_lshift = 0;
@@ -547,8 +546,8 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     }
     // The same offsets with a slot's byte offset added, built once per block instead of once per
     // read (the slot is a run-time value, the rest of a read's address is an immediate).
-    constexpr bool ANY64 = T1::NP64 > 0 || T2::NP64 > 0;
-    constexpr bool ANY32 = T1::HAS32 || T2::HAS32;
+    constexpr bool ANY64 = TC::NP64 > 0 || TP::NP64 > 0;
+    constexpr bool ANY32 = TC::HAS32 || TP::HAS32;
     struct RowBase { int b64[4]; int b32[2]; };
     struct TrBase { int t64[2][2]; int t32[2]; };
     auto mk_row = [&](int off) __attribute__((always_inline)) {
@@ -604,18 +603,22 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         return join_tr(lds_read_tr16((const bf16_t*)(smem + tb.t32[0] + imm)),
                        lds_read_tr16((const bf16_t*)(smem + tb.t32[1] + imm)));
     };
+    auto tr_read1 = [&](const TrBase& tb, int mb, int kk) __attribute__((always_inline)) {
+        return mb < C / 32 ? tr_read(tb, 0, TC::NP64, mb, kk) : tr_read(tb, TC::BYTES, TP::NP64, mb - C / 32, kk);
+    };
     // operand n of a block whose slot offset is folded into rb (row reads) / tb (transpose reads);
     // callers keep a rolling window opr[n % (LA + 1)]
     auto read_op = [&](const RowBase& rb, const TrBase& tb, int n) __attribute__((always_inline)) {
-        if (n < K::KS) return row_read(rb, 0, T1::NP64, n < CG / 16 ? n : n + (C - CG) / 16);
+        if (n < CG / 16) return row_read(rb, 0, TC::NP64, n);
+        if (n < K::KS) return row_read(rb, TC::BYTES, TP::NP64, n - CG / 16);
         if (n < NA) return row_read(rb, kOffT2, T2::NP64, n - K::KS);
         if (LAZY_DS) {
             // the P-side output (dV) first: its operand is complete when the first half ends, while dS
             // is still being formed under these MFMAs
             if (n < NA + NO2) return tr_read(tb, kOffT2, T2::NP64, (n - NA) >> 1, (n - NA) & 1);
-            return tr_read(tb, 0, T1::NP64, (n - NA - NO2) >> 1, (n - NA - NO2) & 1);
+            return tr_read1(tb, (n - NA - NO2) >> 1, (n - NA - NO2) & 1);
         }
-        if (n < NA + NO1) return tr_read(tb, 0, T1::NP64, (n - NA) >> 1, (n - NA) & 1);
+        if (n < NA + NO1) return tr_read1(tb, (n - NA) >> 1, (n - NA) & 1);
         return tr_read(tb, kOffT2, T2::NP64, (n - NA - NO1) >> 1, (n - NA - NO1) & 1);
     };
 
@@ -1050,7 +1053,7 @@ __global__ __launch_bounds__(kThreads, (DKV ? Cfg<C, RP>::PIPE : (DENSE || C + R
 template <int C, int RP, bool CAUSAL, bool DENSE, bool LIMB, int CG>
 int launch(const BwdParams& pin, hipStream_t stream) {
     using K = Cfg<C, RP, LIMB, CG>;
-    constexpr size_t slot = K::T1::BYTES + K::T2::BYTES + (DENSE ? (size_t)kWaves * 32 * 32 * 2 : 0);
+    constexpr size_t slot = K::T1_BYTES + K::T2::BYTES + (DENSE ? (size_t)kWaves * 32 * 32 * 2 : 0);
     constexpr size_t ring_dq = (size_t)NSLOT * slot;
     constexpr size_t ring_dkv = (size_t)K::NSLOT_DKV * (slot + K::kVecBytes);
     constexpr size_t lds_dq = ring_dq > K::kEpiLds ? ring_dq : K::kEpiLds;
@@ -1063,62 +1066,60 @@ int launch(const BwdParams& pin, hipStream_t stream) {
 
     const long long rows = (long long)pin.B * pin.H * pin.N;      // query rows
     const long long rowsk = (long long)pin.B * pin.H * pin.M;     // key rows
-    // Split rows (C a multiple of 64, caller's rows of C channels): the k columns of the key-side rows were
-    // a copy, so the kernels read k itself.  On the query side the q columns carry the scale; it can move
-    // onto the factor columns (as 1/scale) and into the exponent and the dK epilogue, so that q is read in
-    // place too -- where the forward formed its scores that way as well (lse and D belong to the forward's
-    // scores, and the recomputed ones must be those): no factors, fp32 factors (scaled before the limb
-    // split) and ALiBi factors made in the kernels; and wherever bf16(q scale) = q scale, i.e. for a scale
-    // that is a power of two (head dimension 64 at the default scale with bf16 factors, and the
-    // multiplicative form, whose prepared rows carry their scale already).  Never with a dense bias, which
-    // enters the chain unscaled.
     if (pin.Cg != CG || (LIMB && !pin.phi_f32) || (K::DL && pin.R > 10)) return -1;
-    constexpr bool kCanSplit = C % 64 == 0;
+    // k is read in place.  On the query side the q columns carry the scale; it can move onto the factor columns (as
+    // 1/scale) and into the exponent and the dK epilogue, so that q is read in place too -- where the forward formed
+    // its scores that way as well (lse and D belong to the forward's scores, and the recomputed ones must be those):
+    // C = 64 and 128 with no factors, fp32 factors (scaled before the limb split) and ALiBi factors made in the
+    // kernels; and wherever bf16(q scale) = q scale, i.e. for a scale that is a power of two (head dimension 64 at the
+    // default scale with bf16 factors, and the multiplicative form, whose prepared rows carry their scale already).
+    // Never with a dense bias, which enters the chain unscaled.  Elsewhere the dq kernel, which holds every q row
+    // once, leaves the scaled rows for the dkv kernel.
     int mant_exp = 0;
     const bool pow2 = std::frexp(pin.scale, &mant_exp) == 0.5f;
-    const bool split_k = kCanSplit;
-    const bool split_q = split_k && !DENSE && (pow2 || RP == 0 || pin.phi_f32 != 0 || pin.slopes != nullptr);
-    // workspace: vec [rows][2] float | Aq [rows][W or RP2] bf16 | Ak [rowsk][W or RP2] bf16  (each a multiple of 16 bytes)
+    const bool raw_q = C % 64 == 0 && !DENSE && (pow2 || RP == 0 || pin.phi_f32 != 0 || pin.slopes != nullptr);
+    const float qscale = K::FOLD ? pin.scale * kLog2e : pin.scale;      // the forward's product
+    const float qmul = raw_q ? 1.f / pin.scale : (K::FOLD ? kLog2e : 1.f);
+    // workspace: vec [rows][2] float | Aq: scaled rows of C channels, factor rows | Ak: (head dimension 16: widened
+    // rows), factor rows | head dimension 16: widened v, dO  (each a multiple of 16 bytes)
     unsigned char* ws = (unsigned char*)pin.workspace;
     MainArgs a;
     a.vec = (float*)ws;
-    bf16_t* aq = (bf16_t*)(ws + (((size_t)rows * 8 + 15) & ~(size_t)15));
-    bf16_t* ak = aq + (size_t)rows * (split_q ? K::RP2 : K::W);
-    a.aq = split_q ? OperandRows{(const bf16_t*)pin.q, C, aq, K::RP2} : OperandRows{aq, K::W, aq + C, K::W};
-    a.ak = split_k ? OperandRows{(const bf16_t*)pin.k, C, ak, K::RP2} : OperandRows{ak, K::W, ak + C, K::W};
-    a.exp_mul = split_q ? kLog2e * pin.scale : kLog2e;
-    a.dkv_mul = split_q ? pin.scale : (K::FOLD ? kLn2 : 1.f);
-    const float qmul = split_q ? 1.f / pin.scale : (K::FOLD ? kLog2e : 1.f);
-    const float qscale = K::FOLD ? pin.scale * kLog2e : pin.scale;      // the forward's product
+    bf16_t* next = (bf16_t*)(ws + (((size_t)rows * 8 + 15) & ~(size_t)15));
+    auto take = [&](long long n_rows, int width) {
+        bf16_t* r = next;
+        next += (size_t)n_rows * width;
+        return r;
+    };
+    const int shared_q = pin.slopes != nullptr || pin.phi_bstride == 0, shared_k = pin.slopes != nullptr || pin.phik_bstride == 0;
+    const long long prows_q = RP == 0 ? 0 : shared_q ? (long long)pin.H * pin.N : rows;
+    const long long prows_k = RP == 0 ? 0 : shared_k ? (long long)pin.H * pin.M : rowsk;
+    bf16_t* aqm = raw_q ? nullptr : take(rows, C);
+    bf16_t* aqp = take(prows_q, K::RP2);
+    bf16_t* akm = CG < C ? take(rowsk, C) : nullptr;
+    bf16_t* akp = take(prows_k, K::RP2);
+    a.aq = OperandRows{raw_q ? (const bf16_t*)pin.q : aqm, aqp, shared_q};
+    a.ak = OperandRows{CG < C ? akm : (const bf16_t*)pin.k, akp, shared_k};
+    a.q_out = raw_q || CG < C ? nullptr : aqm;
+    a.q_mul = qscale;
+    a.exp_mul = raw_q ? kLog2e * pin.scale : kLog2e;
+    a.dkv_mul = raw_q ? pin.scale : (K::FOLD ? kLn2 : 1.f);
 
     BwdParams p = pin;
-    auto blocks = [](long long r, int rows_per_block) { return (unsigned)((r + rows_per_block - 1) / rows_per_block); };
     if constexpr (CG < C) {
-        // widened copies of v and dO behind the operand rows; out and dO keep their 16-channel rows for the row sums
-        bf16_t* vpad = ak + (size_t)rowsk * K::W;
-        bf16_t* dpad = vpad + (size_t)rowsk * 32;
-        hipLaunchKernelGGL(bwd_pad16_kernel, dim3((unsigned)((rowsk * 4 + 255) / 256)), dim3(256), 0, stream,
-                           (const bf16_t*)pin.v, vpad, rowsk);
-        hipLaunchKernelGGL(bwd_pad16_kernel, dim3((unsigned)((rows * 4 + 255) / 256)), dim3(256), 0, stream,
-                           (const bf16_t*)pin.dout, dpad, rows);
-        p.v = vpad;
-        p.dout = dpad;
+        // out and dO keep their 16-channel rows for the row sums
+        const Widen16 w{aqm, take(rows, C), akm, take(rowsk, C)};
+        const long long most = rows > rowsk ? rows : rowsk;
+        hipLaunchKernelGGL(bwd_widen16_kernel, dim3((unsigned)((most * 4 + 255) / 256), 4), dim3(256), 0, stream, pin, w,
+                           rows, rowsk, qscale);
+        p.v = w.v;
+        p.dout = w.dout;
     }
-    if constexpr (kCanSplit && RP > 0) {
-        constexpr int RS = kPrepRows<C, RP, true>, RW = kPrepRows<C, RP, false>;
-        if (split_q) {
-            const unsigned nb_q = blocks(rows, RS), nb_k = blocks(rowsk, RS);
-            if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, K::DL, true, true>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul, qscale);
-        } else {
-            const unsigned nb_q = blocks(rows, RW), nb_k = blocks(rowsk, RS);
-            if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, K::DL, false, true>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul, qscale);
-        }
-    } else {
-        // no factor columns to write for a split side (RP = 0): its workgroups are simply not launched
-        constexpr int RW = kPrepRows<C, RP, false>;
-        const unsigned nb_q = split_q ? 0u : blocks(rows, RW);
-        const unsigned nb_k = split_k ? 0u : blocks(rowsk, RW);
-        if (nb_q + nb_k) hipLaunchKernelGGL((bwd_pre_kernel<C, RP, K::DL>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aq, ak, nb_q, qmul, qscale);
+    if constexpr (RP > 0) {
+        constexpr int RPB = kPrepRows<K::RP2>;
+        const unsigned nb_q = (unsigned)((prows_q + RPB - 1) / RPB), nb_k = (unsigned)((prows_k + RPB - 1) / RPB);
+        hipLaunchKernelGGL((bwd_pre_kernel<K::RP2, K::DL>), dim3(nb_q + nb_k), dim3(256), 0, stream, pin, aqp, akp, nb_q,
+                           prows_q, prows_k, qmul);
     }
     if (hipGetLastError() != hipSuccess) return 1;
 

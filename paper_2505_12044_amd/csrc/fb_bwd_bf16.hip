@@ -907,28 +907,35 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                     }
                 }
             }
-            // ---------------- dBias = dS, straight from the packed operand registers ----------------
-            int nstores = 0;
-            if (DENSE && !DKV) {
-                const int Mk = p.M;
-                if (ri < NL) {
-                    bf16_t* drow = dbg + (size_t)ri * Mk + sb0 + 4 * hf;
-#pragma unroll
-                    for (int g = 0; g < 4; g++) {
-                        if (sb0 + 8 * g + 4 * hf < Mk) {
-                            const u32x4 w = as_uint4(dsb[g >> 1]);
-                            *(u32x2*)(drow + 8 * g) = (g & 1) ? u32x2{w.z, w.w} : u32x2{w.x, w.y};
-                        }
-                    }
-                }
-                // the wait below may count the stores only when every one of them is certain to issue
-                if (rw0 + 31 < NL && sb0 + BT <= Mk) nstores = 4;
-            }
             // ---------------- block i+1 has landed; everyone has left block i-1 ----------------
-            wait_prev_loads(nstores);
+            // (behind them lie the loads of block i+2 and, with a dense bias, the dBias stores of the two blocks before
+            // this one: whole blocks, so all of them have issued where the wave's rows are all inside)
+            wait_prev_loads(DENSE && !DKV && rw0 + 31 < NL ? 4 : 0);
             __syncthreads();
             issue_block(i + 3, (i + 3) & (NSLOT - 1));
             issue_bias(i + 3, (i + 3) & (NSLOT - 1));
+
+            // ---------------- dBias = dS ----------------
+            // The packed operand registers of a lane hold keys 8g + 4 hf + 0..3 of its row: one exchange across the halves
+            // per register pair makes whole 16-byte pieces, group 2 gp + hf in half hf.  Issued behind the loads, so a
+            // store has two blocks' time before anything waits for it (B 8, H 12, N 1024, C 64: 110 -> 103 us).
+            if (DENSE && !DKV) {
+                const int Mk = p.M;
+                u32x4 piece[2];
+#pragma unroll
+                for (int gp = 0; gp < 2; gp++) {
+                    const u32x4 w = as_uint4(dsb[gp]);
+                    const auto r0 = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
+                    const auto r1 = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
+                    piece[gp] = u32x4{(unsigned)r0[0], (unsigned)r1[0], (unsigned)r0[1], (unsigned)r1[1]};
+                }
+                if (ri < NL) {
+                    bf16_t* drow = dbg + (size_t)ri * Mk + sb0 + 8 * hf;
+#pragma unroll
+                    for (int gp = 0; gp < 2; gp++)
+                        if (sb0 + 16 * gp + 8 * hf < Mk) *(u32x4*)(drow + 16 * gp) = piece[gp];
+                }
+            }
 
             // ---------------- second half: output chains ----------------
             bf16x8 nxt[LA];      // first operands of block i+1 (the window restarts at 0 with every block)
@@ -948,10 +955,10 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         if (DENSE && !DKV && CAUSAL && ri < NL) {
             // key blocks above the diagonal are never visited: their dBias is zero
             for (int blk = b_end; blk < nblk_all; blk++) {
-                bf16_t* drow = dbg + (size_t)ri * p.M + blk * BT + 4 * hf;
+                bf16_t* drow = dbg + (size_t)ri * p.M + blk * BT + 8 * hf;
 #pragma unroll
-                for (int g = 0; g < 4; g++)
-                    if (blk * BT + 8 * g + 4 * hf < p.M) *(u32x2*)(drow + 8 * g) = u32x2{0u, 0u};
+                for (int gp = 0; gp < 2; gp++)
+                    if (blk * BT + 16 * gp + 8 * hf < p.M) *(u32x4*)(drow + 16 * gp) = u32x4{0u, 0u, 0u, 0u};
             }
         }
     }

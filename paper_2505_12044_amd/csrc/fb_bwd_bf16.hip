@@ -584,8 +584,9 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     constexpr bool LAZY_DS = PIPE && NO2 >= 8;
     constexpr int NOPS = NA + NO1 + NO2;
     // LDS operand reads run LA MFMAs ahead of their use; the first half never reads past its own block
-    // (measured: look-ahead 2..4 for dq and 5..12 for dkv all run within 1 %)
-    constexpr int LA_WANT = PIPE ? 6 : 3;
+    // (PIPE: 5..12 run within 1 %.  Plain, three against five ahead, kernel times: B 1, H 8, N 32186, C 16, R 9 dkv
+    // 3179 -> 3071 us; B 4, H 16, N 4096, C 64, 64 columns dq 673 -> 658 us; C = 128 dq -1 %; N <= 1024 equal)
+    constexpr int LA_WANT = PIPE ? 6 : 5;
     constexpr int LA_CAP = (NO1 + NO2) < NA ? (NO1 + NO2) : NA;
     constexpr int LA = LA_CAP < LA_WANT ? LA_CAP : LA_WANT;
     bf16x8 opr[LA + 1];

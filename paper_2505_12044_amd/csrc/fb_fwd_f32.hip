@@ -154,9 +154,11 @@ __global__ __launch_bounds__((Cfg<C, RP>::kTwo ? 512 : 256), (Cfg<C, RP>::kTwo ?
                 if (key >= M || (p.causal && key > qi)) s[r] = -INFINITY;
             }
         }
-        const float mnew = fmaxf(fmaxf(m, half_max(max16(s))), -1e30f);      // a row with no visible key yet keeps p = 0
+        // The maximum itself, however low it is; a row with no visible key yet (maximum -inf) keeps p = 0
+        const float mnew = fmaxf(m, half_max(max16(s)));
+        const float msub = mnew == -INFINITY ? 0.f : mnew;
         if (__any(mnew > m)) {
-            const float alpha = fast_exp2((m - mnew) * kLog2e);
+            const float alpha = fast_exp2((m - msub) * kLog2e);
             l *= alpha;
 #pragma unroll
             for (int cb = 0; cb < K::NCB; cb++)
@@ -167,7 +169,7 @@ __global__ __launch_bounds__((Cfg<C, RP>::kTwo ? 512 : 256), (Cfg<C, RP>::kTwo ?
         float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int r = 0; r < 16; r++) {
-            s[r] = fast_exp2((s[r] - m) * kLog2e);
+            s[r] = fast_exp2((s[r] - msub) * kLog2e);
             ps[r & 3] += s[r];
         }
         l += (ps[0] + ps[1]) + (ps[2] + ps[3]);
@@ -222,11 +224,12 @@ __global__ __launch_bounds__((Cfg<C, RP>::kTwo ? 512 : 256), (Cfg<C, RP>::kTwo ?
         if (q0 + row >= N) break;
         float mm = -INFINITY;
         for (int w = 0; w < KW; w++) mm = fmaxf(mm, tile0[w * K::kSlot + 32 * K::OP + row]);
+        const float msub = mm == -INFINITY ? 0.f : mm;
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
         float lt = 0.f;
         for (int w = 0; w < KW; w++) {
             const float* t = tile0 + w * K::kSlot;
-            const float a = fast_exp2((t[32 * K::OP + row] - mm) * kLog2e);
+            const float a = fast_exp2((t[32 * K::OP + row] - msub) * kLog2e);
             lt = fmaf(a, t[32 * K::OP + 32 + row], lt);
             acc += a * *(const f32x4*)(t + row * K::OP + c);
         }

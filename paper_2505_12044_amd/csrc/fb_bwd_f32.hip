@@ -48,7 +48,7 @@ struct Cfg {
 
 // KEYSIDE = false: lanes are queries, keys are streamed; outputs dq, dphi_q, D (and dBias when DENSE).
 // KEYSIDE = true:  lanes are keys, queries are streamed; outputs dk, dv, dphi_k.
-// DENSE: the bias is a materialised [N, M] matrix per head, the start value of the score chain (the
+// DENSE: the bias is a materialised [N, M] matrix per head, added to the scores (the
 // training-side baseline of Sec. 4.3); dBias = dS is written by the query-side launch, zero where masked.
 template <int C, int RP, bool KEYSIDE, bool DENSE = false>
 __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bwd_f32_kernel(BwdParams p, float* __restrict__ Dws, int kw_log2) {
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
         f32x16 s, dp;
 #pragma unroll
         for (int r = 0; r < 16; r++) {
-            s[r] = DENSE ? bv[r % (DENSE ? 16 : 1)] : 0.f;
+            s[r] = 0.f;
             dp[r] = 0.f;
         }
 #pragma unroll
@@ -234,6 +234,10 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
                 if (n < K::NCH) s = mfma32f(a[e], ar[n][e], s);
                 else dp = mfma32f(a[e], er[n - K::NCH][e], dp);
             }
+        }
+        if (DENSE) {      // behind the products, as the forward adds it
+#pragma unroll
+            for (int r = 0; r < 16; r++) s[r] += bv[r % (DENSE ? 16 : 1)];
         }
 #pragma unroll
         for (int n = 0; n < K::NPF; n++) rc[n] = load_row(nxt, n);

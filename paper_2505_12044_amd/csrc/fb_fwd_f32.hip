@@ -132,13 +132,17 @@ __global__ __launch_bounds__((Cfg<C, RP>::kTwo ? 512 : 256), (Cfg<C, RP>::kTwo ?
         __builtin_amdgcn_sched_barrier(0);      // requests stay ahead of the chain they land under
         f32x16 s;
 #pragma unroll
-        for (int r = 0; r < 16; r++) s[r] = DENSE ? bv[r % (DENSE ? 16 : 1)] : 0.f;
+        for (int r = 0; r < 16; r++) s[r] = 0.f;
 #pragma unroll
         for (int i = 0; i < K::NCH; i++) {
             const f32x4 a = kc[i % K::NPF];
             if (i + K::NPF < K::NCH) kc[i % K::NPF] = load_k(blk, i + K::NPF);
 #pragma unroll
             for (int e = 0; e < 4; e++) s = mfma32f(a[e], qr[i][e], s);
+        }
+        if (DENSE) {      // one rounding at the bias's size; a chain started from the bias would round each partial sum there
+#pragma unroll
+            for (int r = 0; r < 16; r++) s[r] += bv[r % (DENSE ? 16 : 1)];
         }
 #pragma unroll
         for (int i = 0; i < K::NPF; i++) kc[i] = load_k(nxt, i);

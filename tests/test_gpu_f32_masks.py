@@ -86,3 +86,33 @@ def test_factor_products_below_the_smallest_score(B, H, N, M):
         # the last column of dphi_q is a sum that cancels against 1e16
         _close("dphi_q", got[3][:, :R - 1], dpq[:, :R - 1])
         _close("dphi_k", got[4], dpk)
+
+
+@pytest.mark.parametrize("offset", [30.0, 300.0, 3000.0])
+@pytest.mark.parametrize("C,causal", [(16, True), (64, False), (128, False)])
+def test_dense_bias_with_a_common_offset(C, causal, offset):
+    """Softmax does not see a row's common offset; the scores do, by one rounding: the products are summed at their own
+    size and the bias is added once.  With u half a last place at the scores' size, a score is off by u (and 1e-6 of
+    products), lse by u more, so P = exp(S - lse) and dBias = P (dP - D) by 2 u relative, and D, a sum over the row of
+    P, by u; 5 u covers both and the products."""
+    rng = np.random.default_rng(int(offset) + C)
+    f32 = lambda *s: rng.standard_normal(s).astype(np.float32)
+    N = 230
+    q, k, v, dout = 2 * f32(1, 1, N, C), f32(1, 1, N, C), f32(1, 1, N, C), f32(1, 1, N, C)
+    bias = f32(1, 1, N, N) + np.float32(offset)
+    d = [_t(q), _t(k), _t(v), _t(bias)]
+    out, lse = api.fb_dense_bias_attn_fwd(*d, causal=causal)
+    grads = api.fb_dense_bias_attn_bwd(*d, out, lse, _t(dout), causal=causal)
+    torch.cuda.synchronize()
+    ro, rl = O.attention_with_bias(q[0, 0], k[0, 0], v[0, 0], bias[0, 0], causal=causal)
+    u = float(np.spacing(np.float32(rl.max()))) / 2 + 1e-6
+    elo = np.abs(host(lse[0, 0]) - rl).max()
+    eo = np.abs(host(out[0, 0]) - ro).max()
+    print(f"offset {offset} C {C}: u {u:.2e} lse {elo:.2e} out {eo:.2e}", flush=True)
+    assert elo <= 2 * u
+    assert eo <= u * np.abs(v).max()
+    ref = O.attention_with_bias_grads(q[0, 0], k[0, 0], v[0, 0], bias[0, 0], dout[0, 0], causal=causal)
+    for name, g, r in zip(("dq", "dk", "dv", "dbias"), grads, ref):
+        e = np.abs(host(g[0, 0]) - r).max()
+        print(f"  {name} {e:.2e} of {np.abs(r).max():.2e}: {e / np.abs(r).max() / u:.2f} u", flush=True)
+        assert e <= 5 * u * np.abs(r).max(), name

@@ -117,7 +117,7 @@ struct Cfg {
     // way here, the exponent of P needs no multiply-add (the score chain starts at -lse log2 e), and the scores round
     // as the forward's did (gradients against 64 bits, N 3001, R 9: 3.3e-3 -> 3.0e-3).  Not at head dimension 16,
     // whose q scale is exact at the default scale: log2 e would round it (dk 2.5e-3 -> 3.6e-3).
-    static constexpr bool FOLD = LIMB && C == 32 && CG == C;
+    static constexpr bool FOLD = LIMB && score_log2e(CG, true);
     static constexpr int MBP = DL ? 1 : RP2 / 32;      // 32-column blocks of the factor gradients
     static constexpr int MB = C / 32 + MBP;            // 32-column blocks of dAq / dAk
     static constexpr int MBC = C / 32;
@@ -1085,7 +1085,8 @@ int launch(const BwdParams& pin, hipStream_t stream) {
     // once, leaves the scaled rows for the dkv kernel.
     int mant_exp = 0;
     const bool pow2 = std::frexp(pin.scale, &mant_exp) == 0.5f;
-    const bool raw_q = C % 64 == 0 && !DENSE && (pow2 || RP == 0 || pin.phi_f32 != 0 || pin.slopes != nullptr);
+    const bool f32_factors = pin.phi_f32 != 0 || pin.slopes != nullptr;
+    const bool raw_q = !DENSE && (score_raw_q(CG, RP > 0 && !f32_factors) || (C % 64 == 0 && pow2));
     const float qscale = K::FOLD ? pin.scale * kLog2e : pin.scale;      // the forward's product
     const float qmul = raw_q ? 1.f / pin.scale : (K::FOLD ? kLog2e : 1.f);
     // workspace: vec [rows][2] float | Aq: scaled rows of C channels, factor rows | Ak: (head dimension 16: widened
@@ -1154,7 +1155,7 @@ int dispatch_causal(const BwdParams& p, hipStream_t stream) {
 template <int C, int CG>
 int dispatch_rp(const BwdParams& p, int rp, hipStream_t stream) {
     if (p.phi_f32 && rp > 32) return rp <= 64 ? dispatch_causal<C, CG, 64, true>(p, stream) : -1;     // DL
-    if constexpr (C == 32 && CG == C) {      // FOLD
+    if constexpr (score_log2e(CG, true)) {      // FOLD
         if (p.phi_f32 && rp == 16) return dispatch_causal<C, CG, 16, true>(p, stream);
         if (p.phi_f32 && rp == 32) return dispatch_causal<C, CG, 32, true>(p, stream);
     }

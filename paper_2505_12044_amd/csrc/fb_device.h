@@ -92,6 +92,14 @@ FB_DEV bf16x8 join_tr(s16x4 lo, s16x4 hi) {
     return __builtin_bit_cast(bf16x8, v);
 }
 
+// How the scores are formed.  lse and the output belong to the forward's scores and the backward recomputes exactly
+// those, so every kernel that rounds the query operand takes the rule from here (c: channels in the caller's rows):
+//   32 channels, fp32 factors (or generated ones): bf16(q scale log2 e), log2 e on the factors as well;
+//   64 and 128 channels, no bf16 factors: q itself, the scale in the exponent and 1/scale on the factors;
+//   else bf16(q scale).
+constexpr bool score_log2e(int c, bool f32_factors) { return c == 32 && f32_factors; }
+constexpr bool score_raw_q(int c, bool bf16_factors) { return c % 64 == 0 && !bf16_factors; }
+
 FB_DEV float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // acc + a.x + a.y for a packed bf16 pair (v_dot2c_f32_bf16 against {1, 1}): the softmax row sum

@@ -161,9 +161,11 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_dma_kernel(FwdParams p) 
 
     // ---- query operand [q*scale | phi_q | 0] (rows past N read row N-1 and are never stored); as in the
     // four-wave kernel, with no factors or fp32 factors at C = 64, 128 it is [q | phi_q / scale | 0] and the
-    // scale sits in the exponent's multiply-add
-    constexpr bool RAWQ = !DENSE && C % 64 == 0 && (PM == 0 || PM == 3);
-    const float emul = RAWQ ? p.scale * kLog2e : kLog2e;
+    // scale sits in the exponent's multiply-add, and with fp32 factors at C = 32 all of it carries log2 e
+    constexpr bool RAWQ = !DENSE && score_raw_q(C, PM == 1 || PM == 2), FOLD = !DENSE && score_log2e(C, PM == 3);
+    const float qscale = FOLD ? p.scale * kLog2e : p.scale;
+    const float fmul = FOLD ? kLog2e : (RAWQ ? p.inv_scale : 1.f);
+    const float emul = RAWQ ? p.scale * kLog2e : (FOLD ? 1.f : kLog2e);
     bf16x8 qreg[K::KS];
     {
         const int qc = min(qi, N - 1);
@@ -173,10 +175,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_dma_kernel(FwdParams p) 
             if (ks < K::KSC) {
                 const bf16x8 x = as_bf16x8(*(const u32x4*)(qg + (size_t)qc * C + ks * 16 + 8 * hf));
 #pragma unroll
-                for (int e = 0; e < 8; e++) val[e] = RAWQ ? x[e] : (bf16_t)((float)x[e] * p.scale);
+                for (int e = 0; e < 8; e++) val[e] = RAWQ ? x[e] : (bf16_t)((float)x[e] * qscale);
             } else {
                 const int c8 = (ks - K::KSC) * 2 + hf;
-                val = phi_chunk_gather<true>(pqg + (size_t)qc * R * phi_esz, c8, R, phi_f32, RAWQ ? p.inv_scale : 1.f);
+                val = phi_chunk_gather<true>(pqg + (size_t)qc * R * phi_esz, c8, R, phi_f32, fmul);
             }
             qreg[ks] = val;
         }

@@ -72,9 +72,9 @@ __global__ __launch_bounds__(kFewThreads, 2) void fwd_few_kernel(FwdParams p, in
     const PT* pqg = (const PT*)p.phi_q + (size_t)b * p.phi_bstride + (size_t)h * N * R;
     const PT* pkg = (const PT*)p.phi_k + (size_t)b * p.phik_bstride + (size_t)h * M * R;
 
-    // The backward recomputes the scores of this pass: q itself where its operand rows hold q, else bf16(q scale),
-    // as in fwd_tile.
-    constexpr bool RAWQ = C % 64 == 0 && PF32;
+    // The rounding of the query that the backward repeats
+    constexpr bool RAWQ = score_raw_q(C, !PF32), LOG2E = score_log2e(C, PF32 && RT != 0);
+    const float qscale = LOG2E ? p.scale * kLog2e : p.scale;
     u32x4 q[NQ];
     const PT* pq[NQ];                    // wave-uniform rows; queries past N repeat the last one and are not stored
 #pragma unroll
@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kFewThreads, 2) void fwd_few_kernel(FwdParams p, in
         if (!RAWQ) {
             bf16x8 x = as_bf16x8(q[n]);
 #pragma unroll
-            for (int e = 0; e < 8; e++) x[e] = (bf16_t)((float)x[e] * p.scale);
+            for (int e = 0; e < 8; e++) x[e] = (bf16_t)((float)x[e] * qscale);
             q[n] = as_uint4(x);
         }
         pq[n] = pqg + (size_t)qi * R;
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(kFewThreads, 2) void fwd_few_kernel(FwdParams p, in
 #pragma unroll
         for (int e = 0; e < 8; e++) o[n][e] = 0.f;
     }
-    const float emul = RAWQ ? p.scale * kLog2e : kLog2e;
+    const float emul = RAWQ ? p.scale * kLog2e : (LOG2E ? 1.f : kLog2e);
 
     const int u_begin = split * units_per_split;
     const int u_end = min(u_begin + units_per_split, (M + K::UNIT - 1) / K::UNIT);

@@ -129,13 +129,13 @@ FB_DEV void fwd_tile(const FwdParams& p, unsigned char* smem, const int bh, cons
     // issued twice against the same K operand registers - was measured and lost: the extra MFMA per
     // block costs more than the sixteen multiply-adds it saves, 0.0695 against 0.0668 ms on the
     // Pairformer shape.)
-    constexpr bool FOLD = !DENSE && (PM == 3 || PM == 4) && C == 32;
+    constexpr bool FOLD = !DENSE && score_log2e(C, PM == 3 || PM == 4);
     // RAWQ (head dimensions 64 and 128; no factors, fp32 factors or factors made in the kernel): the
     // query operand is q itself, not bf16(q scale).  q k^T scale + phi_q phi_k^T = scale (q k^T +
     // (phi_q / scale) phi_k^T): the factor columns carry 1/scale (applied in fp32, before the limb
     // split) and the scale goes into the exponent's multiply-add.  One rounding less on the scores,
     // and the backward, which recomputes exactly these scores, can read q in place as well.
-    constexpr bool RAWQ = !DENSE && !FOLD && C % 64 == 0 && CG == C && (PM == 0 || PM == 3 || PM == 4);
+    constexpr bool RAWQ = !DENSE && CG == C && score_raw_q(C, PM == 1 || PM == 2);
     const float qmul = FOLD ? kLog2e : (RAWQ ? p.inv_scale : 1.f);       // factor of the query-side factor columns
     const float emul = RAWQ ? p.scale * kLog2e : kLog2e;                 // scores to exponents of two
     const float slope = PM == 4 ? p.slopes[h] * qmul : 0.f;

@@ -97,10 +97,13 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_pp_kernel(FwdParams p) {
 
     // ---- query operand [q*scale | phi_q | 0] (rows past N read row N-1 and are never stored); as in the
     // four-wave kernel, with no factors or fp32 factors at C = 64, 128 it is [q | phi_q / scale | 0] and the
-    // scale sits in the exponent's multiply-add, so that every forward variant forms the scores the
-    // backward recomputes
-    const bool rawq = !DENSE && C % 64 == 0 && (PM == 0 || phi_f32);      // wave-uniform
-    const float emul = rawq ? p.scale * kLog2e : kLog2e;
+    // scale sits in the exponent's multiply-add, and with fp32 factors at C = 32 all of it carries log2 e: every
+    // forward variant forms the scores the backward recomputes
+    const bool rawq = !DENSE && score_raw_q(C, PM != 0 && !phi_f32);      // wave-uniform
+    const bool fold = !DENSE && score_log2e(C, phi_f32);
+    const float qscale = fold ? p.scale * kLog2e : p.scale;
+    const float fmul = fold ? kLog2e : (rawq ? p.inv_scale : 1.f);
+    const float emul = rawq ? p.scale * kLog2e : (fold ? 1.f : kLog2e);
     bf16x8 qreg[K::KS];
     {
         const int qc = min(qi, N - 1);
@@ -110,10 +113,10 @@ __global__ __launch_bounds__(kThreads, 2) void fwd_bf16_pp_kernel(FwdParams p) {
             if (ks < C / 16) {
                 const bf16x8 x = as_bf16x8(*(const u32x4*)(qg + (size_t)qc * C + ks * 16 + 8 * hf));
 #pragma unroll
-                for (int e = 0; e < 8; e++) val[e] = rawq ? x[e] : (bf16_t)((float)x[e] * p.scale);
+                for (int e = 0; e < 8; e++) val[e] = rawq ? x[e] : (bf16_t)((float)x[e] * qscale);
             } else {
                 const int c8 = (ks - C / 16) * 2 + hf;
-                val = phi_chunk_gather<true>(pqg + (size_t)qc * R * phi_esz, c8, R, phi_f32, rawq ? p.inv_scale : 1.f);
+                val = phi_chunk_gather<true>(pqg + (size_t)qc * R * phi_esz, c8, R, phi_f32, fmul);
             }
             qreg[ks] = val;
         }

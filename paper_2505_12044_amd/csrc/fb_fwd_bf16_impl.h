@@ -119,17 +119,17 @@ FB_DEV void fwd_tile(const FwdParams& p, unsigned char* smem, const int bh, cons
     // of the exponential (q * scale * log2 e, phi_q * log2 e) and the score accumulator can start
     // at minus the row's reference maximum: the softmax then needs no multiply-add per score.
     // bf16 factors are copied as they are (a rescaled copy would round them again), so those
-    // modes keep the multiply-add.  The start value takes 16 registers per query block: used on
-    // the 32-channel tiles, where the vector ALU is the bound (-7 % on the C = 16 point-cloud
-    // shape) and the registers are free.  At C = 128 it gains 1-2 % at most, and it rounds
-    // q * scale * log2 e where the backward rounds q * scale: scores that differ by one bf16
-    // rounding between the passes leave the rows of dS summing to ~1e-3 D instead of zero, which
-    // factor gradients of absolute positions (ALiBi) multiply by up to N.  Not used there.
+    // modes keep the multiply-add.  The start value takes 16 registers per query block: used at
+    // 32 channels, where the vector ALU is the bound and the registers are free; the backward forms
+    // its scores the same way.  Not at 16 channels, where q * scale is exact at the default scale and
+    // log2 e would round it (point cloud N 4096, R 9, against 64 bits: out 3.1e-3 -> 2.3e-3, dphi_q
+    // 1.5e-2 -> 1.2e-2 without it; training at N 32186 7375 -> 7412 us).  At C = 128 it gains 1-2 % at
+    // most for registers that kernel does not have.
     // (The same fold for bf16 factors - phi_q * log2 e carried as two bf16 limbs, the factor k-steps
     // issued twice against the same K operand registers - was measured and lost: the extra MFMA per
     // block costs more than the sixteen multiply-adds it saves, 0.0695 against 0.0668 ms on the
     // Pairformer shape.)
-    constexpr bool FOLD = !DENSE && score_log2e(C, PM == 3 || PM == 4);
+    constexpr bool FOLD = !DENSE && score_log2e(CG, PM == 3 || PM == 4);
     // RAWQ (head dimensions 64 and 128; no factors, fp32 factors or factors made in the kernel): the
     // query operand is q itself, not bf16(q scale).  q k^T scale + phi_q phi_k^T = scale (q k^T +
     // (phi_q / scale) phi_k^T): the factor columns carry 1/scale (applied in fp32, before the limb

@@ -37,7 +37,7 @@ def _row_sums(N, M, H, C, R, phi, scale, qb):
     assert (err <= 6 * sigma).all()
 
 
-FACTORS = [(16, 2, "bf16"), (32, 2, "f32"), (32, 9, "f32"), (32, 8, "bf16"),
+FACTORS = [(16, 2, "f32"), (16, 9, "f32"), (16, 2, "bf16"), (32, 2, "f32"), (32, 9, "f32"), (32, 8, "bf16"),
            (64, 2, "f32"), (64, 2, "bf16"), (128, 9, "f32"), (128, 8, "bf16")]
 
 

@@ -124,12 +124,12 @@ def _stream(stream) -> Optional[int]:
 
 
 def _scratch(nbytes: int, device, stream) -> torch.Tensor:
-    """A workspace the wrapper allocates itself.  The kernels run on `stream`; when that is not
-    torch's current stream the caching allocator must be told, or it could hand the block to
+    """A workspace the wrapper allocates itself.  The kernels run on `stream` (a Stream or a raw handle); when
+    that is not torch's current stream the caching allocator must be told, or it could hand the block to
     other work as soon as the tensor is dropped."""
     ws = torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
-    if stream is not None and hasattr(stream, "cuda_stream") and stream != torch.cuda.current_stream():
-        ws.record_stream(stream)
+    if stream is not None and _stream(stream) != _stream(None):
+        ws.record_stream(stream if hasattr(stream, "cuda_stream") else torch.cuda.ExternalStream(int(stream), device=device))
     return ws
 
 

@@ -88,3 +88,18 @@ def test_few_queries_decoder_positions():
     torch.cuda.synchronize()
     ro, rl = O.batched_attention_lowrank(q, k, v, pq, pk)
     assert np.abs(host(out) - ro).max() <= 2e-2 and np.abs(host(lse) - rl).max() <= 2e-3
+
+
+def test_few_queries_scratch_on_a_raw_stream_handle():
+    # the split's workspace is the binding's own: memory that the current stream takes right behind the call must not be it
+    q, k, v, pq, pk = _case(2, 4, 2, 20000, 64, 2, "f32", True, seed=9)
+    d = [dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), dev(pq, "f32"), dev(pk, "f32")]
+    nbytes = api.load_library().fb_lowrank_xattn_fwd_workspace_bytes(2, 4, 2, 20000, 64, 2, api.FB_BF16)
+    assert nbytes > 0
+    out, lse = api.fb_lowrank_xattn_fwd(*d)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    o2, l2 = api.fb_lowrank_xattn_fwd(*d, stream=side.cuda_stream)
+    torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(255)
+    torch.cuda.synchronize()
+    assert torch.equal(out, o2) and torch.equal(lse, l2)

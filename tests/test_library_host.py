@@ -243,3 +243,25 @@ def test_hand_placed_mfma_forms_keep_their_wait_states():
     assert chk.scan_asm(fenced)[1] == []
     seen, found = chk.check()
     assert seen > 0 and found == [], found[:3]
+
+
+def test_scratch_is_recorded_on_the_stream_that_uses_it(monkeypatch):
+    """A workspace the binding allocates is dropped when the call returns: the allocator has to know the stream the kernels
+    run on, also where the caller passes its raw handle."""
+    import torch
+
+    class Stream:
+        def __init__(self, handle, device=None):
+            self.cuda_stream = handle
+    seen = []
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: Stream(7))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 7, raising=False)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", Stream)
+    monkeypatch.setattr(torch.Tensor, "record_stream", lambda t, s: seen.append(s.cuda_stream))
+    for stream in (None, 7, Stream(7)):
+        api._scratch(64, "cpu", stream)
+    assert seen == []
+    for stream in (11, Stream(12), 0):
+        api._scratch(64, "cpu", stream)
+    assert seen == [11, 12, 0]

@@ -87,6 +87,8 @@ const char* fb_status_string(int status);
  *                 kernel takes, the first walks its off-diagonal key blocks upwards from key 0
  *                 and the second downwards, so the workgroups of a head read the same block at
  *                 the same time (fewer L2 misses); 0: both walk downwards from the diagonal.
+ *   "fwd_few"     1: the few-query kernel takes every call it can (at most 8 queries, fewer than keys, R <= 16;
+ *                 fwd_qb 0); 0 (default): those it is the faster kernel for.
  */
 int fb_tune_set(const char* name, int value);
 
@@ -118,7 +120,7 @@ int fb_lowrank_xattn_fwd(const void* q, const void* k, const void* v,
  * fb_lowrank_xattn_fwd with device scratch: where a few queries meet many keys (decode), the keys of a head are
  * split over the GPU and the partial results pass through `workspace` (16-byte aligned, at least as large as the
  * query below says; 0 where nothing is needed).  Without one (NULL, or too small), as in fb_lowrank_xattn_fwd, a
- * head stays in one workgroup.
+ * head stays in one workgroup, of the few-query kernel or of the tile kernel, whichever is expected to be faster.
  */
 size_t fb_lowrank_xattn_fwd_workspace_bytes(int B, int H, int N, int M, int C, int R, fb_dtype dtype);
 

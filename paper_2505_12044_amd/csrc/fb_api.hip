@@ -118,6 +118,11 @@ int fb_tune_set(const char* name, int value) {
         g_causal_up.store(value, std::memory_order_relaxed);
         return FB_OK;
     }
+    if (std::strcmp(name, "fwd_few") == 0) {
+        if (value != 0 && value != 1) return FB_ERR_SHAPE;
+        fb_few_tune(value);
+        return FB_OK;
+    }
     return FB_ERR_UNSUPPORTED;
 }
 
@@ -152,14 +157,15 @@ static int lowrank_fwd_impl(const void* q, const void* k, const void* v,
     p.causal_up = g_causal_up.load(std::memory_order_relaxed);
     p.scale = scale > 0.f ? scale : 1.0f / std::sqrt((float)C);
     p.inv_scale = 1.0f / p.scale;
+    const long long BH = (long long)B * H;
+    // scratch for the splits of the few-query kernel; a workspace too small for them is left alone
+    const bool scratch = N <= 8 && workspace != nullptr && aligned16(workspace) &&
+                         workspace_bytes >= fb_few_workspace_bytes(BH, N, M, C);
     int rc;
     if (dtype == FB_F32) {
         rc = fb_launch_fwd_f32(p, C, false, (hipStream_t)stream);
-    } else if (g_fwd_qb.load(std::memory_order_relaxed) == 0 && fb_few_queries((long long)B * H, N, M, R)) {
-        // a workspace too small for the splits is left alone
-        const bool split = workspace != nullptr && aligned16(workspace) &&
-                           workspace_bytes >= fb_few_workspace_bytes((long long)B * H, N, M, C);
-        rc = fb_launch_fwd_bf16_few(p, C, split ? workspace : nullptr, (hipStream_t)stream);
+    } else if (g_fwd_qb.load(std::memory_order_relaxed) == 0 && fb_few_queries(BH, N, M, C, R, phi_dtype == FB_F32, scratch)) {
+        rc = fb_launch_fwd_bf16_few(p, C, scratch ? workspace : nullptr, (hipStream_t)stream);
     } else {
         int qb = pick_qb(B, H, N, C, rp, false, causal != 0);
         if (N != M && qb != 2) qb = 1;     // only the four-wave kernel takes N != M
@@ -188,8 +194,11 @@ int fb_lowrank_xattn_fwd(const void* q, const void* k, const void* v,
 
 size_t fb_lowrank_xattn_fwd_workspace_bytes(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
     if (B <= 0 || H <= 0 || N <= 0 || M <= 0 || R < 0 || (C != 16 && C != 32 && C != 64 && C != 128)) return 0;
-    if (dtype != FB_BF16 || !fb_few_queries((long long)B * H, N, M, R)) return 0;
-    return fb_few_workspace_bytes((long long)B * H, N, M, C);
+    if (dtype != FB_BF16) return 0;
+    // the factors' type is not known here: whichever takes the split
+    const long long BH = (long long)B * H;
+    if (!fb_few_queries(BH, N, M, C, R, true, true) && !fb_few_queries(BH, N, M, C, R, false, true)) return 0;
+    return fb_few_workspace_bytes(BH, N, M, C);
 }
 
 int fb_lowrank_xattn_fwd_ws(const void* q, const void* k, const void* v,

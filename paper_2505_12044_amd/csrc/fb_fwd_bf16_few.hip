@@ -13,6 +13,7 @@
 // The factor product is a chain of fp32 multiply-adds on the stored factors (no limbs).
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "fb_device.h"
@@ -283,13 +284,13 @@ struct FewPlan { int nq, n_split, units_per_split; };
 constexpr int kFewGroups = 512;
 constexpr int kFewSteps = 2;
 
-FewPlan few_plan(long long BH, int N, int M, int C) {
+FewPlan few_plan(long long BH, int N, int M, int C, bool scratch) {
     FewPlan f;
     f.nq = N == 1 ? 1 : (N == 2 ? 2 : (N <= 4 ? 4 : 8));
     const int unit = kFewWaves * (f.nq <= 2 ? 8 : 4) * (512 / C);       // FewCfg::UNIT
     const int units = (M + unit - 1) / unit;
     long long want = (kFewGroups + BH - 1) / BH;
-    const int most = units < 8 ? 1 : units / kFewSteps;
+    const int most = units < 8 || !scratch ? 1 : units / kFewSteps;
     if (want > most) want = most;
     f.units_per_split = (int)((units + want - 1) / want);
     f.n_split = (units + f.units_per_split - 1) / f.units_per_split;
@@ -335,25 +336,66 @@ int few_queries(const FwdParams& p, const FewPlan& f, void* ws, hipStream_t stre
 
 }  // namespace
 
-// Which calls.  Per key byte this kernel does N (R + 4) units of vector work, the tile kernel the same matrix work
-// for any N <= 32; what the tile kernel lacks is workgroups.  us here / there, M 2048 (R 2 with N <= 4: M 4096):
-//   8 heads      every N <= 8, R <= 16: 18-21 / 27-82
-//   128 heads    N 1 R 2 C 128 43 / 129; N 4 R 16 C 128 40 / 45; N 8 R 2 39 / 45; N 8 R 8 51 / 45
-//   1024 heads   N 1 R 2 177 / 233 and N 4 R 2 C 64 93 / 167 (512 heads); N 4 R 8 C 128 221 / 184; N 8 R 2 260 / 190
-bool fb_few_queries(long long BH, int N, int M, int R) {
+// Which calls: the kernel that takes less time by the two estimates below, in ns, fitted to 5629 calls of 1 to 4096
+// heads, 16 to 16384 keys, N 1, 2, 4, 8, every head dimension and factor form, with scratch and without.  Chosen by them,
+// one call in a hundred is more than 3 % slower than on the tile kernel (worst 1.3x, at 15 us), and the average call is
+// within 0.6 % of the faster kernel.  us on the tile kernel / here in one workgroup a head / here with the split:
+//   8 heads, M 16384, C 128:   N 1 R 2 355 / 198 / 25;   N 8 R 16 bf16 349 / 1115 / 55
+//   8 heads, M 300:            C 16 N 1 R 2 7.1 / 3.7;   C 16 N 8 R 16 bf16 5.9 / 11.5
+//   1024 heads, M 2048, C 128: N 1 R 2 187 / 177;   N 8 R 2 191 / 255
+namespace {
+
+// A workgroup: prologue and merges (a shuffle per group level and query), then its steps, each with the factor chain.
+// Past one round of 320 workgroups the waves that have keys count (the last step of a short sequence leaves some idle).
+double few_ns(long long BH, int M, int C, int R, const FewPlan& f) {
+    static constexpr double kStep[4] = {1150, 1500, 1250, 1950}, kFactor[4] = {130, 160, 100, 150};
+    const int i = f.nq == 1 ? 0 : (f.nq == 2 ? 1 : (f.nq == 4 ? 2 : 3));
+    const int levels = C == 16 ? 5 : (C == 32 ? 4 : (C == 64 ? 3 : 2));
+    const int wave_keys = (f.nq <= 2 ? 8 : 4) * (512 / C);
+    const double fixed = 140.0 * f.nq * levels;
+    const double steps = f.units_per_split * (kStep[i] + kFactor[i] * R);
+    const int units = (M + kFewWaves * wave_keys - 1) / (kFewWaves * wave_keys);
+    const double fill = (double)((M + wave_keys - 1) / wave_keys) / ((double)units * kFewWaves);
+    const double one = fixed + steps, busy = (fixed + steps * fill) * (double)BH * f.n_split / 320.0;
+    return 1800 + (f.n_split > 1 ? 4000 : 0) + (busy > one ? busy : one);
+}
+
+// The tile kernel: a workgroup a head, a prologue and a ring step per 32 keys.  fp32 factors take six columns a rank (one,
+// two or three to four k-steps), and bf16 ranks that are no multiple of eight are gathered one by one.
+double tile_ns(long long BH, int M, int C, int R, bool phi_f32) {
+    const int c = C == 16 ? 0 : (C == 32 ? 1 : (C == 64 ? 2 : 3));
+    static constexpr double kBlock[4] = {290, 380, 500, 640};            // ns per 32 keys, no or whole-chunk factors
+    static constexpr double kMid[4] = {1.25, 1.25, 1.1, 1.7}, kWide[4] = {1.35, 1.35, 1.3, 2.4};      // fp32, R 3..8, 9..10
+    double fixed = c == 3 ? 1000 : 600, step = kBlock[c];
+    if (!phi_f32) {
+        if ((R & 7) != 0) step *= 1.6;
+    } else if (R > 0) {
+        fixed += R <= 2 ? 800 : (R <= 8 ? 1700 : 4200);
+        if (R > 2) step *= R <= 8 ? kMid[c] : kWide[c];
+    }
+    const double rounds = (double)BH / (c == 3 ? 300 : 400);
+    return 2200 + (fixed + (M + 31) / 32 * step) * (rounds > 1 ? rounds : 1);
+}
+
+std::atomic<int> g_few_always{0};
+
+}  // namespace
+
+void fb_few_tune(int always) { g_few_always.store(always, std::memory_order_relaxed); }
+
+bool fb_few_queries(long long BH, int N, int M, int C, int R, bool phi_f32, bool scratch) {
     if (N > 8 || N >= M || R > 16) return false;
-    const int work = N * (R + 4);
-    return work <= (BH <= 64 ? 160 : (BH <= 256 ? 80 : 24));
+    if (g_few_always.load(std::memory_order_relaxed) != 0) return true;
+    return few_ns(BH, M, C, R, few_plan(BH, N, M, C, scratch)) < tile_ns(BH, M, C, R, phi_f32);
 }
 
 size_t fb_few_workspace_bytes(long long BH, int N, int M, int C) {
-    const FewPlan f = few_plan(BH, N, M, C);
+    const FewPlan f = few_plan(BH, N, M, C, true);
     return f.n_split > 1 ? (size_t)BH * f.n_split * N * (C + 2) * sizeof(float) : 0;
 }
 
 int fb_launch_fwd_bf16_few(const FwdParams& p, int C, void* ws, hipStream_t stream) {
-    FewPlan f = few_plan((long long)p.B * p.H, p.N, p.M, C);
-    if (ws == nullptr) { f.units_per_split *= f.n_split; f.n_split = 1; }
+    const FewPlan f = few_plan((long long)p.B * p.H, p.N, p.M, C, ws != nullptr);
     switch (C) {
         case 16: return few_queries<16>(p, f, ws, stream);
         case 32: return few_queries<32>(p, f, ws, stream);

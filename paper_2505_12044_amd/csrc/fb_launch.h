@@ -14,9 +14,11 @@ int fb_launch_fwd_f32(const FwdParams& p, int C, bool dense, hipStream_t stream)
 int fb_launch_fwd_bf16(const FwdParams& p, int C, int rp, bool dense, int qb, hipStream_t stream);
 // ALiBi factors generated in the kernel from p.slopes (p.phi_q / p.phi_k unused); qb = 1 or 2.
 int fb_launch_fwd_bf16_alibi(const FwdParams& p, int C, int qb, hipStream_t stream);
-// Few queries against many keys (no mask).  fb_few_queries: whether that kernel takes the call; ws: device scratch of
-// fb_few_workspace_bytes(B*H, N, M, C) bytes for the partial results of a head's splits, or NULL (no splits).
-bool fb_few_queries(long long BH, int N, int M, int R);
+// Few queries against many keys (no mask).  fb_few_queries: whether that kernel takes the call, with scratch for the
+// splits or without; ws: device scratch of fb_few_workspace_bytes(B*H, N, M, C) bytes for the partial results of a head's
+// splits, or NULL (no splits); fb_few_tune(1): it takes every call it can (tests).
+bool fb_few_queries(long long BH, int N, int M, int C, int R, bool phi_f32, bool scratch);
+void fb_few_tune(int always);
 size_t fb_few_workspace_bytes(long long BH, int N, int M, int C);
 int fb_launch_fwd_bf16_few(const FwdParams& p, int C, void* ws, hipStream_t stream);
 // p.workspace points at fb_bwd_workspace_bytes(B*H*N, B*H*M, C, R) bytes of device scratch.

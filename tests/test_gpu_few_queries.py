@@ -103,3 +103,44 @@ def test_few_queries_scratch_on_a_raw_stream_handle():
     torch.empty(nbytes, dtype=torch.uint8, device="cuda").fill_(255)
     torch.cuda.synchronize()
     assert torch.equal(out, o2) and torch.equal(lse, l2)
+
+
+@pytest.fixture
+def always_few():
+    api.fb_tune_set("fwd_few", 1)
+    yield
+    api.fb_tune_set("fwd_few", 0)
+
+
+# Every size on the few-query kernel, whichever kernel is the faster one: the edges above, and a length that is split over
+# the grid with a ragged last step
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("C,R,phi,M_split", [(128, 2, "f32", 1111), (64, 0, "f32", 2111), (32, 9, "f32", 4200), (32, 16, "bf16", 4200),
+                                             (16, 5, "bf16", 8300), (16, 2, "f32", 8300)])
+def test_few_queries_every_form(always_few, N, C, R, phi, M_split):
+    size = api.load_library().fb_lowrank_xattn_fwd_workspace_bytes
+    assert size(2, 2, N, M_split, C, R, api.FB_BF16) > 0 and size(2, 2, N, 129, C, R, api.FB_BF16) == 0
+    for M in (N + 1, 31, 129, M_split):
+        _check(2, 2, N, M, C, R, phi, shared=N % 2 == 0)
+
+
+# Calls that the tile kernel does faster: many queries and factors without scratch for the splits, short sequences
+@pytest.mark.parametrize("B,H,N,M,C,R,phi,scratch", [(1, 2, 8, 10000, 128, 16, "bf16", False), (1, 8, 8, 5000, 64, 8, "bf16", False),
+                                                     (1, 2, 8, 64, 16, 16, "bf16", True), (2, 4, 4, 300, 32, 8, "bf16", True)])
+def test_calls_that_stay_on_the_tile_kernel(B, H, N, M, C, R, phi, scratch):
+    q, k, v, pq, pk = _case(B, H, N, M, C, R, phi, True, seed=M)
+    d = [dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16"), dev(pq, phi), dev(pk, phi)]
+    ws = torch.empty(1 << 24, dtype=torch.uint8, device="cuda")
+    res = []
+    for qb in (0, 1):
+        out, lse = torch.empty_like(d[0]), torch.empty((B, H, N), device="cuda")
+        api.fb_tune_set("fwd_qb", qb)
+        st = api.load_library().fb_lowrank_xattn_fwd_ws(*(t.data_ptr() for t in d), out.data_ptr(), lse.data_ptr(), B, H, N, M, C, R,
+                                                        api.FB_BF16, api.FB_F32 if phi == "f32" else api.FB_BF16, 1, 0.0,
+                                                        ws.data_ptr() if scratch else None, ws.numel() if scratch else 0,
+                                                        torch.cuda.current_stream().cuda_stream or None)
+        api.fb_tune_set("fwd_qb", 0)
+        assert st == 0
+        res.append((out, lse))
+    torch.cuda.synchronize()
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])

@@ -170,26 +170,35 @@ def fb_lowrank_attn_fwd(q, k, v, phi_q, phi_k, out=None, lse=None, causal=False,
     return out, lse
 
 
+def fb_lowrank_xattn_fwd_workspace_bytes(B, H, N, M, C, R, dtype_code=FB_BF16) -> int:
+    return int(load_library().fb_lowrank_xattn_fwd_workspace_bytes(B, H, N, M, C, R, dtype_code))
+
+
 def fb_lowrank_xattn_fwd(q, k, v, phi_q, phi_k, out=None, lse=None, scale: float = 0.0,
-                         phi_batch_broadcast: Optional[bool] = None, stream=None):
-    """Cross-attention: q [B,H,N,C], k, v [B,H,M,C], phi_q [B or 1,H,N,R], phi_k [B or 1,H,M,R]."""
+                         phi_batch_broadcast: Optional[bool] = None, stream=None, workspace=None):
+    """Cross-attention: q [B,H,N,C], k, v [B,H,M,C], phi_q [B or 1,H,N,R], phi_k [B or 1,H,M,R].
+    A few queries against many keys (decode) use scratch of fb_lowrank_xattn_fwd_workspace_bytes: the caller's
+    workspace, else the binding's own.  A call that is given out and lse but no workspace allocates nothing and does
+    without (the keys of a head are then not split over the GPU)."""
     lib = load_library()
     B, H, N, C = q.shape
     M = k.shape[2]
     R = 0 if phi_q is None else phi_q.shape[-1]
     if phi_batch_broadcast is None:
         phi_batch_broadcast = phi_q is not None and phi_q.shape[0] == 1 and B > 1
+    # only a few queries against many keys ever need scratch
+    if workspace is None and N <= 8 and (out is None or lse is None):
+        need = int(lib.fb_lowrank_xattn_fwd_workspace_bytes(B, H, N, M, C, R, _dtype_code(q)))
+        workspace = _scratch(need, q.device, stream) if need else None
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     phi_code = _dtype_code(phi_q) if phi_q is not None else _dtype_code(q)
-    # only a few queries against many keys ever need scratch
-    need = int(lib.fb_lowrank_xattn_fwd_workspace_bytes(B, H, N, M, C, R, _dtype_code(q))) if N <= 8 else 0
-    workspace = _scratch(need, q.device, stream) if need else None
     st = lib.fb_lowrank_xattn_fwd_ws(_ptr(q), _ptr(k), _ptr(v), _ptr(phi_q), _ptr(phi_k), _ptr(out),
                                      _ptr(lse), B, H, N, M, C, R, _dtype_code(q), phi_code,
-                                     int(bool(phi_batch_broadcast)), float(scale), _ptr(workspace), need,
+                                     int(bool(phi_batch_broadcast)), float(scale), _ptr(workspace), ws_bytes,
                                      _stream(stream))
     _check(st, "fb_lowrank_xattn_fwd")
     return out, lse

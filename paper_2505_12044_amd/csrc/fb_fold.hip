@@ -46,18 +46,20 @@ FB_DEV void store_vec(T* p, const float (&x)[V]) {
 // Training steps with it against torch's sum and conversion per tensor: B 384, H 4, N 384, C 32, R 16 bf16
 // 407 -> 368 us (the two sums took 69 us), dense bias B 8, H 12, N 1024, C 64 341 -> 315 us (71 us), relative
 // positions B 8, H 12, N 1024, R 32 225 -> 216 us.
-// Two tensors (phi_q and phi_k) in one launch: workgroups [0, nb0) belong to the first.
+// Two tensors (phi_q and phi_k) in one launch: workgroups [0, nb0) belong to the first.  block0: workgroups of the
+// launches before this one.
 template <typename T, int V, int G>
 __global__ __launch_bounds__(kFoldThreads) void fold_batch_kernel(const T* __restrict__ src0, T* __restrict__ dst0, long long n0,
                                                                   const T* __restrict__ src1, T* __restrict__ dst1, long long n1,
-                                                                  unsigned nb0, int B) {
+                                                                  long long block0, long long nb0, int B) {
     constexpr int P = kFoldThreads / G;        // pieces per workgroup
-    const bool second = blockIdx.x >= nb0;
+    const long long block = block0 + blockIdx.x;
+    const bool second = block >= nb0;
     const T* const src = second ? src1 : src0;
     T* const dst = second ? dst1 : dst0;
     const long long n = second ? n1 : n0;
     const int piece = threadIdx.x % P, g = threadIdx.x / P;
-    const long long i = ((long long)(blockIdx.x - (second ? nb0 : 0u)) * P + piece) * V;
+    const long long i = ((block - (second ? nb0 : 0)) * P + piece) * V;
     float acc[V];
 #pragma unroll
     for (int e = 0; e < V; e++) acc[e] = 0.f;
@@ -108,11 +110,16 @@ template <typename T, int V, int G>
 int launch_fold(const void* s0, void* d0, long long n0, const void* s1, void* d1, long long n1, int B, hipStream_t stream) {
     constexpr int P = kFoldThreads / G;
     auto blocks = [](long long n) { return (n / V + P - 1) / P; };
-    const long long nb0 = blocks(n0), nb1 = blocks(n1);
-    if (nb0 + nb1 >= (1LL << 31)) return -1;
-    hipLaunchKernelGGL((fold_batch_kernel<T, V, G>), dim3((unsigned)(nb0 + nb1)), dim3(kFoldThreads), 0, stream,
-                       (const T*)s0, (T*)d0, n0, (const T*)s1, (T*)d1, n1, (unsigned)nb0, B);
-    return hipGetLastError() == hipSuccess ? 0 : 1;
+    const long long nb0 = blocks(n0), nb = nb0 + blocks(n1);
+    // a launch takes fewer than 2^32 threads: larger tensors (from 2^28 values of an odd length on) in several, each long
+    // enough that the gap between them does not show
+    constexpr long long kMost = 1LL << 20;
+    for (long long block0 = 0; block0 < nb; block0 += kMost) {
+        hipLaunchKernelGGL((fold_batch_kernel<T, V, G>), dim3((unsigned)(nb - block0 < kMost ? nb - block0 : kMost)),
+                           dim3(kFoldThreads), 0, stream, (const T*)s0, (T*)d0, n0, (const T*)s1, (T*)d1, n1, block0, nb0, B);
+        if (hipGetLastError() != hipSuccess) return 1;
+    }
+    return 0;
 }
 
 template <typename T, int V>

@@ -47,3 +47,14 @@ def test_fold_batch_unaligned_rows():
     got = api.fb_fold_batch(g)
     torch.cuda.synchronize()
     _check(g, got[0])
+
+
+def test_fold_batch_in_several_launches():
+    # 2^32 + 1 values: one by one (the rows are not 16-byte aligned) they are more threads than one launch takes
+    n = (1 << 32) + 1
+    g = torch.ones((2, n), dtype=torch.bfloat16, device="cuda")
+    g[1, ::4097] = 3.0
+    g[0, -1] = 5.0
+    got, = api.fb_fold_batch(g)
+    g[0] += g[1]
+    assert got.shape == (1, n) and torch.equal(got[0], g[0])

@@ -253,8 +253,11 @@ int launch(const FwdParams& pin, hipStream_t stream) {
     const int kw = f32_split((long long)p.B * p.H * tiles, (p.M + BK - 1) / BK, K::kMaxKw);
     int kw_log2 = 0;
     while ((1 << kw_log2) < kw) kw_log2++;
-    const int waves = kw > 4 ? kw : 4;
-    const int qw = waves / kw;
+    // four tiles a workgroup (two, one where waves share them), but no more than a head has: heads of up to 32 queries
+    // are workgroups of one wave, of which a launch takes 2^26
+    const int most = kw > 4 ? 1 : 4 / kw;
+    const int qw = tiles < most ? tiles : most;
+    const int waves = qw * kw;
     const size_t lds = kw > 1 ? (size_t)waves * K::kSlot * 4 : 0;
     if (lds > 0 && !fb_raise_lds_limit((const void*)kern, (size_t)K::kMaxKw * K::kSlot * 4, once)) return 1;
     p.n_units = (tiles + qw - 1) / qw;

@@ -48,3 +48,14 @@ def test_forward_and_backward_beyond_2_31_elements():
     for name, t in (("dk", grads[1]), ("dv", grads[2]), ("dphi_k", grads[4])):
         x = t[B - 1, H - 1].float()
         assert torch.isfinite(x).all() and float(x.abs().max()) > 0, name
+
+
+def test_fp32_forward_over_2_24_heads():
+    # one query and one key a head: out is v, lse the score (1/sqrt(C) = 1/4 is exact); four waves a head would be 2^32 threads
+    BH, C = 1 << 24, 16
+    g = torch.Generator(device="cuda").manual_seed(9003)
+    q, k, v = (torch.randn((BH, 1, 1, C), device="cuda", generator=g) for _ in range(3))
+    out, lse = api.fb_lowrank_attn_fwd(q, k, v, None, None)
+    assert torch.equal(out, v)
+    ref = (q.double() * k.double()).sum(-1) * 0.25
+    assert float((lse.double() - ref).abs().max()) <= 1e-5

@@ -26,7 +26,7 @@
  *     contractions run as bf16 MFMA with fp32 accumulation; fp32 factors are then split
  *     into three bf16 limbs inside the kernel (six product columns per rank), which keeps
  *     ~24 bits of each factor (needed e.g. for ALiBi positions up to N).  With
- *     dtype = FB_F32 everything is fp32 FMA and phi_dtype must be FB_F32.
+ *     dtype = FB_F32 every product and sum is fp32 and phi_dtype must be FB_F32.
  *   - Supported: C in {16, 32, 64, 128}; 0 <= R, with the
  *     padded factor width (R for bf16 factors, 6R for fp32 factors in a bf16 run, rounded up
  *     to 16) at most 64; fp32 forward: R <= 64.  R = 0 (phi pointers may be NULL) is plain
@@ -87,8 +87,6 @@ const char* fb_status_string(int status);
  *                 kernel takes, the first walks its off-diagonal key blocks upwards from key 0
  *                 and the second downwards, so the workgroups of a head read the same block at
  *                 the same time (fewer L2 misses); 0: both walk downwards from the diagonal.
- *   "fwd_few"     1: the few-query kernel takes every call it can (at most 8 queries, fewer than keys, R <= 16;
- *                 fwd_qb 0); 0 (default): those it is the faster kernel for.
  */
 int fb_tune_set(const char* name, int value);
 
@@ -227,7 +225,7 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
  * gradients are the trailing R columns of the same contractions that give dq and dk
  * (Sec. 3.2 "Speed up training"; Sec. 4.1 "Implementation choices").
  * `out` and `lse` are the forward's results.  dtype = FB_BF16, or FB_F32 (all tensors and the
- * factors float, N keys = N queries: the full-precision path, fp32 FMA arithmetic, which uses only
+ * factors float, N keys = N queries: the full-precision path, fp32 products and sums, which uses only
  * the first 4 B H N bytes of the workspace, for D).
  * workspace: device scratch of at least fb_lowrank_attn_bwd_workspace_bytes(...) bytes,
  * 16-byte aligned, owned by the caller; its contents on entry are ignored and it may be

@@ -118,11 +118,6 @@ int fb_tune_set(const char* name, int value) {
         g_causal_up.store(value, std::memory_order_relaxed);
         return FB_OK;
     }
-    if (std::strcmp(name, "fwd_few") == 0) {
-        if (value != 0 && value != 1) return FB_ERR_SHAPE;
-        fb_few_tune(value);
-        return FB_OK;
-    }
     return FB_ERR_UNSUPPORTED;
 }
 

@@ -919,7 +919,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             // ---------------- dBias = dS ----------------
             // The packed operand registers of a lane hold keys 8g + 4 hf + 0..3 of its row: one exchange across the halves
             // per register pair makes whole 16-byte pieces, group 2 gp + hf in half hf.  Issued behind the loads, so a
-            // store has two blocks' time before anything waits for it (B 8, H 12, N 1024, C 64: 110 -> 103 us).
+            // store has two blocks' time before anything waits for it (B 8, H 12, N 1024, C 64: 110 -> 100 us).
             if (DENSE && !DKV) {
                 const int Mk = p.M;
                 u32x4 piece[2];

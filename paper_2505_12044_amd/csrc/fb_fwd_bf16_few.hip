@@ -9,11 +9,11 @@
 //   all 2 U row loads in flight, and needs no exchange but the sum over its lanes of the score (DPP adds);
 //   the groups of a wave, then the waves of a workgroup, are merged once at the end; the splits of a (b, h) leave
 //   (m, l, o) in the workspace and a second kernel merges them (in a fixed order).
-// B 8, H 16, N 1, M 4096, C 128, R 2: 129 -> 43 us, 6.2 TB/s of K and V (a large copy reads and writes at 6.3).
+// B 8, H 16, N 1, M 4096, C 128, R 2, inputs from memory: 127 -> 51 us a call, 5.3 TB/s of K and V (a large reduction
+// reads at 6.1); 43 us where they lie in the Infinity Cache.
 // The factor product is a chain of fp32 multiply-adds on the stored factors (no limbs).
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <type_traits>
 
 #include "fb_device.h"
@@ -277,8 +277,9 @@ __global__ __launch_bounds__(256) void few_merge_kernel(const float* __restrict_
 
 struct FewPlan { int nq, n_split, units_per_split; };
 
-// Splits: enough workgroups to keep the memory system busy (kFewGroups of four waves).  B 8, H 16, M 4096, C 128, R 2, N 1: 43 us with 512, 44 with 1024, 45 with 2048; N 8, M 2048,
-// C 64: 26, 31, 41 (a split's merge and prologue weigh more).
+// Splits: enough workgroups to keep the memory system busy (kFewGroups of four waves).  us with 256, 512, 1024, 2048, inputs
+// from memory, R 2: 128 heads, N 1, M 4096, C 128 48, 50, 51, 53; 16 heads, N 8, M 16384, C 128 53, 49, 61, 84; 128 heads,
+// N 8, M 2048, C 64 29, 26, 32, 32 (a split's merge and prologue weigh more with more queries).
 // A workgroup walks at least kFewSteps steps, and heads of fewer than eight steps are not split: the merge is a
 // second launch (3 us of the GPU, as much of the host), which M = 300 keys (5 us in one workgroup) do not repay.
 constexpr int kFewGroups = 512;
@@ -377,15 +378,10 @@ double tile_ns(long long BH, int M, int C, int R, bool phi_f32) {
     return 2200 + (fixed + (M + 31) / 32 * step) * (rounds > 1 ? rounds : 1);
 }
 
-std::atomic<int> g_few_always{0};
-
 }  // namespace
-
-void fb_few_tune(int always) { g_few_always.store(always, std::memory_order_relaxed); }
 
 bool fb_few_queries(long long BH, int N, int M, int C, int R, bool phi_f32, bool scratch) {
     if (N > 8 || N >= M || R > 16) return false;
-    if (g_few_always.load(std::memory_order_relaxed) != 0) return true;
     return few_ns(BH, M, C, R, few_plan(BH, N, M, C, scratch)) < tile_ns(BH, M, C, R, phi_f32);
 }
 

@@ -14,7 +14,7 @@
 // released their registers and land under the value chain, value rows under the score chain.  No barrier and no
 // staging in the loop.  Bound: the matrix pipe, (C + RP + C) / 2 k-steps of 64 cycles per 32 x 32 block.
 // Measured, against the one-thread-per-query FMA kernel this replaced: B 2, H 8, N 1500, C 64, R 8 2725 -> 102 us
-// (98 TFLOP/s of executed matrix work, 153 reached by a large fp32 matrix product on the same card); B 1, H 2,
+// (98 TFLOP/s of executed matrix work, 143 reached by a large fp32 matrix product on the same card); B 1, H 2,
 // N 256, R 4 (16 tiles, eight waves each) 437 -> 11 us.  Requests pinned ahead of their chains instead of where the
 // compiler sinks them, and buffer addressing (one address register per row block), were 135 -> 102 us of that.
 #include <hip/hip_runtime.h>

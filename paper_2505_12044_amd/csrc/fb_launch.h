@@ -16,15 +16,14 @@ int fb_launch_fwd_bf16(const FwdParams& p, int C, int rp, bool dense, int qb, hi
 int fb_launch_fwd_bf16_alibi(const FwdParams& p, int C, int qb, hipStream_t stream);
 // Few queries against many keys (no mask).  fb_few_queries: whether that kernel takes the call, with scratch for the
 // splits or without; ws: device scratch of fb_few_workspace_bytes(B*H, N, M, C) bytes for the partial results of a head's
-// splits, or NULL (no splits); fb_few_tune(1): it takes every call it can (tests).
+// splits, or NULL (no splits).
 bool fb_few_queries(long long BH, int N, int M, int C, int R, bool phi_f32, bool scratch);
-void fb_few_tune(int always);
 size_t fb_few_workspace_bytes(long long BH, int N, int M, int C);
 int fb_launch_fwd_bf16_few(const FwdParams& p, int C, void* ws, hipStream_t stream);
 // p.workspace points at fb_bwd_workspace_bytes(B*H*N, B*H*M, C, R) bytes of device scratch.
 int fb_launch_bwd_bf16(const BwdParams& p, int C, int rp, hipStream_t stream);
 size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R);
-// fp32 tensors and fp32 factors (N = M): p.workspace holds one float per query row (a prefix of the
+// fp32 tensors and fp32 factors: p.workspace holds one float per query row (a prefix of the
 // size above).
 int fb_launch_bwd_f32(const BwdParams& p, int C, hipStream_t stream);
 int fb_launch_bwd_dense_f32(const BwdParams& p, int C, hipStream_t stream);

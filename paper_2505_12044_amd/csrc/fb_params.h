@@ -16,7 +16,7 @@ struct FwdParams {
     void* out;            // [B,H,N,C]
     float* lse;           // [B,H,N]
     int B, H, N, R;       // N = number of queries
-    int M;                // number of keys (= N except for cross-attention, four-wave bf16 kernel only)
+    int M;                // number of keys (= N except for cross-attention: fp32, four-wave and few-query kernels)
     int causal;
     int phi_f32;          // factors stored as float (else bf16)
     long long phi_bstride;   // elements between batch items of phi_q (0 when shared over batch)

@@ -105,23 +105,13 @@ def test_few_queries_scratch_on_a_raw_stream_handle():
     assert torch.equal(out, o2) and torch.equal(lse, l2)
 
 
-@pytest.fixture
-def always_few():
-    api.fb_tune_set("fwd_few", 1)
-    yield
-    api.fb_tune_set("fwd_few", 0)
-
-
-# Every size on the few-query kernel, whichever kernel is the faster one: the edges above, and a length that is split over
-# the grid with a ragged last step
+# Every channel count and factor form with its keys split over the grid, the last step ragged
 @pytest.mark.parametrize("N", [1, 2, 3, 5, 8])
-@pytest.mark.parametrize("C,R,phi,M_split", [(128, 2, "f32", 1111), (64, 0, "f32", 2111), (32, 9, "f32", 4200), (32, 16, "bf16", 4200),
-                                             (16, 5, "bf16", 8300), (16, 2, "f32", 8300)])
-def test_few_queries_every_form(always_few, N, C, R, phi, M_split):
-    size = api.load_library().fb_lowrank_xattn_fwd_workspace_bytes
-    assert size(2, 2, N, M_split, C, R, api.FB_BF16) > 0 and size(2, 2, N, 129, C, R, api.FB_BF16) == 0
-    for M in (N + 1, 31, 129, M_split):
-        _check(2, 2, N, M, C, R, phi, shared=N % 2 == 0)
+@pytest.mark.parametrize("C,R,phi,M", [(128, 2, "f32", 1111), (64, 0, "f32", 2111), (32, 9, "f32", 4200), (32, 16, "bf16", 4200),
+                                       (16, 5, "bf16", 8300), (16, 2, "f32", 8300)])
+def test_few_queries_split(N, C, R, phi, M):
+    assert api.fb_lowrank_xattn_fwd_workspace_bytes(2, 2, N, M, C, R) > 0
+    _check(2, 2, N, M, C, R, phi, shared=N % 2 == 0)
 
 
 # Calls that the tile kernel does faster: many queries and factors without scratch for the splits, short sequences

@@ -219,12 +219,6 @@ def test_tune_knob(lib):
     assert lib.fb_tune_set(b"fwd_causal_up", 2) == 2
     assert lib.fb_tune_set(b"fwd_causal_up", 1) == 0
     assert lib.fb_tune_set(b"fwd_lds_pad", 0) == 3          # probe knob removed
-    assert lib.fb_tune_set(b"fwd_few", 2) == 2
-    assert lib.fb_tune_set(b"fwd_few", 1) == 0
-    assert lib.fb_lowrank_xattn_fwd_workspace_bytes(1, 1, 8, 1 << 15, 16, 16, api.FB_BF16) > 0
-    assert lib.fb_lowrank_xattn_fwd_workspace_bytes(1, 1, 9, 1 << 15, 16, 16, api.FB_BF16) == 0
-    assert lib.fb_lowrank_xattn_fwd_workspace_bytes(1, 1, 8, 1 << 15, 16, 17, api.FB_BF16) == 0
-    assert lib.fb_tune_set(b"fwd_few", 0) == 0
     assert lib.fb_tune_set(b"nope", 1) == 3
     assert lib.fb_tune_set(None, 1) == 1
 

@@ -189,11 +189,12 @@ int fb_lowrank_xattn_fwd(const void* q, const void* k, const void* v,
 
 size_t fb_lowrank_xattn_fwd_workspace_bytes(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
     if (B <= 0 || H <= 0 || N <= 0 || M <= 0 || R < 0 || (C != 16 && C != 32 && C != 64 && C != 128)) return 0;
-    if (dtype != FB_BF16) return 0;
-    // the factors' type is not known here: whichever takes the split
+    if (dtype != FB_BF16 || N > 8) return 0;
     const long long BH = (long long)B * H;
-    if (!fb_few_queries(BH, N, M, C, R, true, true) && !fb_few_queries(BH, N, M, C, R, false, true)) return 0;
-    return fb_few_workspace_bytes(BH, N, M, C);
+    const size_t need = fb_few_workspace_bytes(BH, N, M, C);
+    // the factors' type is not known here: whichever takes the split
+    if (need > 0 && !fb_few_queries(BH, N, M, C, R, true, true) && !fb_few_queries(BH, N, M, C, R, false, true)) return 0;
+    return need;
 }
 
 int fb_lowrank_xattn_fwd_ws(const void* q, const void* k, const void* v,

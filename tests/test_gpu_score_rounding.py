@@ -29,11 +29,15 @@ def _row_sums(N, M, H, C, R, phi, scale, qb):
     finally:
         api.fb_tune_set("fwd_qb", 0)
     bwd = api.fb_lowrank_attn_bwd if N == M else api.fb_lowrank_xattn_bwd
-    P = host(bwd(*d, out, lse, dev(dout, "bf16"), scale=scale)[2])[0][:, :, :len(rows)]
+    dv = bwd(*d, out, lse, dev(dout, "bf16"), scale=scale)[2]
+    _check_rows(dv, len(rows), f"N {N} M {M} C {C} R {R} {phi} scale {scale} form {qb}")
+
+
+def _check_rows(dv, n, label):
+    P = host(dv)[0][:, :, :n]
     err = np.abs(P.sum(1) - 1.0)
     sigma = 2.0 ** -8 / 3 ** 0.5 * np.sqrt(3 * (P ** 2).sum(1))
-    print(f"N {N} M {M} C {C} R {R} {phi} scale {scale} form {qb}: worst row sum off by {err.max():.2e}, {(err / sigma).max():.1f} sigma",
-          flush=True)
+    print(f"{label}: worst row sum off by {err.max():.2e}, {(err / sigma).max():.1f} sigma", flush=True)
     assert (err <= 6 * sigma).all()
 
 
@@ -52,3 +56,31 @@ def test_rows_of_p_sum_to_one(N, H, scale, C, R, phi):
 @pytest.mark.parametrize("C,R,phi", FACTORS)
 def test_rows_of_p_sum_to_one_after_each_forward(qb, C, R, phi):
     _row_sums(2048, 2048, 2, C, R, phi, 0.0, qb)
+
+
+@pytest.mark.parametrize("C", [16, 32, 64, 128])
+@pytest.mark.parametrize("form", ["alibi", "dense", "cosmul"])
+def test_rows_of_p_sum_to_one_other_entry_points(form, C):
+    N, H = 1000, 2
+    rng = np.random.default_rng(C)
+    mk = lambda *s: rng.standard_normal(s).astype(np.float32)
+    q, k, v = W.round_bf16(mk(1, H, N, C)), W.round_bf16(mk(1, H, N, C) + 1), W.round_bf16(mk(1, H, N, C))
+    rows = rng.permutation(N)[:C]
+    dout = np.zeros((1, H, N, C), np.float32)
+    dout[:, :, rows, np.arange(C)] = 1.0
+    d, do = [dev(x, "bf16") for x in (q, k, v)], dev(dout, "bf16")
+    if form == "alibi":
+        m = dev(np.array([0.01, 0.002], np.float32), "f32")
+        out, lse = api.fb_alibi_attn_fwd(*d, m, causal=True)
+        dv = api.fb_alibi_attn_bwd(*d, m, out, lse, do, causal=True)[2]
+    elif form == "dense":
+        b = dev(W.round_bf16(mk(1, H, N, N)), "bf16")
+        out, lse = api.fb_dense_bias_attn_fwd(*d, b)
+        dv = api.fb_dense_bias_attn_bwd(*d, b, out, lse, do)[2]
+    else:
+        R = 1 if C == 128 else 2
+        f = [dev(mk(1, H, N, R), "f32") for _ in range(2)]
+        out, lse = api.fb_lowrank_mulbias_attn_fwd(*d, *f)
+        dv = api.fb_lowrank_mulbias_attn_bwd(*d, *f, out, lse, do)[2]
+    torch.cuda.synchronize()
+    _check_rows(dv, C, f"{form} C {C}")

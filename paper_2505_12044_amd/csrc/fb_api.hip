@@ -161,6 +161,8 @@ static int lowrank_fwd_impl(const void* q, const void* k, const void* v,
         rc = fb_launch_fwd_f32(p, C, false, (hipStream_t)stream);
     } else if (g_fwd_qb.load(std::memory_order_relaxed) == 0 && fb_few_queries(BH, N, M, C, R, phi_dtype == FB_F32, scratch)) {
         rc = fb_launch_fwd_bf16_few(p, C, scratch ? workspace : nullptr, (hipStream_t)stream);
+    } else if (g_fwd_qb.load(std::memory_order_relaxed) == 0 && fb_short_fwd(p, C, rp)) {
+        rc = fb_launch_fwd_bf16_short(p, C, rp, (hipStream_t)stream);
     } else {
         int qb = pick_qb(B, H, N, C, rp, false, causal != 0);
         if (N != M && qb != 2) qb = 1;     // only the four-wave kernel takes N != M
@@ -429,8 +431,9 @@ static int lowrank_bwd_impl(const void* q, const void* k, const void* v,
     p.phi_bstride = phi_batch_broadcast ? 0 : (long long)H * N * R;
     p.phik_bstride = phi_batch_broadcast ? 0 : (long long)H * M * R;
     p.scale = scale > 0.f ? scale : 1.0f / std::sqrt((float)C);
-    const int rc = dtype == FB_F32 ? fb_launch_bwd_f32(p, C, (hipStream_t)stream)
-                                   : fb_launch_bwd_bf16(p, C, rp, (hipStream_t)stream);
+    const int rc = dtype == FB_F32           ? fb_launch_bwd_f32(p, C, (hipStream_t)stream)
+                   : fb_short_bwd(p, C, rp) ? fb_launch_bwd_bf16_short(p, C, rp, (hipStream_t)stream)
+                                            : fb_launch_bwd_bf16(p, C, rp, (hipStream_t)stream);
     return rc == 0 ? FB_OK : (rc < 0 ? FB_ERR_UNSUPPORTED : FB_ERR_LAUNCH);
 }
 

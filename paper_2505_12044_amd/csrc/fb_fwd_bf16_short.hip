@@ -1,0 +1,364 @@
+// bf16 MFMA forward for short key sequences on the 32-channel tiles (head dimensions 16 and 32), gfx950.
+//
+// At these sizes a query tile of the ring kernel (fb_fwd_bf16_impl.h) walks a dozen 32-key blocks, each with a staging
+// step and a barrier around five matrix instructions: no pipe is busy (B 384, H 4, N 384, C 32, R 16: vector ALU 56 %,
+// matrix pipe 21 %, a third of the wave time spent waiting).  Here a head's [K | phi_k] and V lie in LDS whole, and one
+// workgroup per CU walks the heads: one wave per 32 query rows, no barrier inside a head, and the next head's rows
+// travel global -> registers -> the second LDS buffer while this one is computed.
+//
+// Orientation, softmax and the rounding of the operands are those of the ring kernel: a query is a lane, the scores of
+// a 32-key block sit in its accumulator registers, lazy reference maximum.  A wave takes its last visible block first
+// (the diagonal, or the partial block at the end), which is the only one with masks and gives every row its reference;
+// the other blocks follow two at a time, so the score chain of one overlaps the exponentials of the other.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "fb_device.h"
+#include "fb_launch.h"
+#include "fb_params.h"
+
+namespace {
+
+constexpr int kMaxWaves = 12;          // three waves per SIMD: 168 registers
+constexpr size_t kLdsBytes = 160 * 1024;
+constexpr float kSumLimit = 256.0f;    // see fb_fwd_bf16_impl.h
+
+// LDS image of a head: K rows, V rows (CG channels, unpadded, in 16-byte pieces whose place in a 64-byte row is swizzled
+// so that row reads and transpose reads are conflict-free), factor rows (pitch an odd number of 16-byte pieces).
+template <int CG, int RP>
+struct Cfg {
+    static constexpr int KC = CG / 16, KS = (CG + RP) / 16;            // k-steps of the score contraction: channels, all
+    static constexpr int RB = CG * 2;                                  // bytes of a k (or v) row
+    static constexpr int PP = RP == 0 ? 0 : RP == 16 ? 32 : RP * 2 + 16;
+    static constexpr int PCH = RP / 8;                                 // 16-byte pieces of a factor row
+    static constexpr int kRow = 2 * RB + PP;                           // LDS bytes per key and buffer
+    FB_DEV static int swz(int row) { return CG == 32 ? (row >> 2) & 3 : 0; }
+};
+
+// lane l reads sbase + voff (bytes); its 16 bytes land at LDS byte address lds_addr + 16 * l.  Inline assembly, because
+// behind the builtin the compiler makes every LDS read wait for all of them.
+FB_DEV void dma16(const void* sbase, unsigned voff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
+}
+
+// PM: 0 = no factors, 1 = bf16 factors in whole 16-byte pieces (R % 8 == 0), 2 = bf16 factors of any R, 3 = fp32 factors
+template <int CG, int RP, int PM, bool CAUSAL>
+__global__ __launch_bounds__(kMaxWaves * 64) void fwd_short_kernel(FwdParams p, int units, int upr) {
+    using K = Cfg<CG, RP>;
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr bool F32 = PM == 3;
+    constexpr bool FOLD = score_log2e(CG, F32);
+    const float emul = FOLD ? 1.f : kLog2e;
+    const int N = p.N, M = p.M, R = p.R;
+    const int NT = blockDim.x, nw = NT >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int nkb = (M + 31) >> 5, Mp = nkb * 32;
+    const unsigned buf_bytes = (unsigned)(Mp * K::kRow), voff0 = (unsigned)(Mp * K::RB), poff0 = 2 * voff0;
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+    const size_t esz = F32 ? 4 : 2;
+
+    // ---- a head's k and v rows: direct loads of 64 pieces, dealt to the waves (rows past M repeat row M - 1) ----
+    constexpr int RPD = 1024 / K::RB;        // rows per direct load
+    const unsigned drow = (unsigned)lane / (K::RB / 16);
+    const unsigned dcol = (((unsigned)lane % (K::RB / 16)) ^ (unsigned)K::swz((int)drow)) * 16;   // RPD is a multiple of 16: the swizzle repeats
+    auto issue_kv = [&](int bh, unsigned buf) __attribute__((always_inline)) {
+        const unsigned char* kg = (const unsigned char*)p.k + (size_t)bh * M * K::RB;
+        const unsigned char* vg = (const unsigned char*)p.v + (size_t)bh * M * K::RB;
+        for (int d = wave; d < Mp / RPD; d += nw) {
+            const unsigned off = min((unsigned)(d * RPD) + drow, (unsigned)(M - 1)) * K::RB + dcol;
+            dma16(kg, off, lds0 + buf + d * 1024);
+            dma16(vg, off, lds0 + buf + voff0 + d * 1024);
+        }
+    };
+    // ---- factor rows, piece by piece through registers ----
+    const int n_phi = Mp * K::PCH;
+    auto phi_piece = [&](int bh, int e) __attribute__((always_inline)) {
+        const int b = bh / p.H, h = bh - b * p.H;
+        const unsigned row = min((unsigned)e / (K::PCH > 0 ? K::PCH : 1), (unsigned)(M - 1));
+        const int c8 = (unsigned)e % (K::PCH > 0 ? K::PCH : 1);
+        const unsigned char* src =
+            (const unsigned char*)p.phi_k + ((size_t)b * p.phik_bstride + ((size_t)h * M + row) * R) * esz;
+        if (PM == 1) return c8 * 8 < R ? *(const u32x4*)(src + c8 * 16) : u32x4{0u, 0u, 0u, 0u};
+        return phi_chunk_raw(src, c8, R, F32, true);
+    };
+    auto phi_store = [&](unsigned buf, int e, const u32x4& raw) __attribute__((always_inline)) {
+        const unsigned row = (unsigned)e / (K::PCH > 0 ? K::PCH : 1);
+        const int c8 = (unsigned)e % (K::PCH > 0 ? K::PCH : 1);
+        *(u32x4*)(smem + buf + poff0 + row * K::PP + c8 * 16) = PM == 1 ? raw : as_uint4(phi_chunk_finish<false>(raw, c8, F32));
+    };
+    constexpr int PIT = K::PCH / 2 > 0 ? K::PCH / 2 : 1;      // pieces a thread keeps in flight: all of them where N >= M
+
+    // ---- query rows: raw in registers while they travel ----
+    u32x4 qraw[K::KC];
+    bf16x8 qphi[RP / 16 > 0 ? RP / 16 : 1];
+    auto load_q = [&](int unit, int bh) __attribute__((always_inline)) {
+        const int b = bh / p.H, h = bh - b * p.H;
+        const int qi = min(((unit - bh * upr) * nw + wave) * 32 + l32, N - 1);
+        const bf16_t* q = (const bf16_t*)p.q + ((size_t)bh * N + qi) * CG + 8 * hf;
+#pragma unroll
+        for (int ks = 0; ks < K::KC; ks++) qraw[ks] = *(const u32x4*)(q + ks * 16);
+        if (RP > 0) {
+            const unsigned char* src = (const unsigned char*)p.phi_q + ((size_t)b * p.phi_bstride + ((size_t)h * N + qi) * R) * esz;
+#pragma unroll
+            for (int ks = 0; ks < RP / 16; ks++) {
+                const int c8 = ks * 2 + hf;
+                if (PM == 1) qphi[ks] = as_bf16x8(c8 * 8 < R ? *(const u32x4*)(src + c8 * 16) : u32x4{0u, 0u, 0u, 0u});
+                else qphi[ks] = phi_chunk_gather<true>(src, c8, R, F32, FOLD ? kLog2e : 1.f);
+            }
+        }
+    };
+
+    int unit = blockIdx.x;
+    if (unit >= units) return;
+    int bh = unit / upr;
+    issue_kv(bh, 0);
+    load_q(unit, bh);
+    for (int e = tid; e < n_phi; e += NT) phi_store(0, e, phi_piece(bh, e));
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+    __syncthreads();
+
+    // ---- LDS operand addresses (bytes inside a 32-key tile) ----
+    const int i16 = lane & 15, blk16 = CG == 32 ? l32 >> 4 : 0;
+    unsigned krow[K::KC], vtr[2];
+#pragma unroll
+    for (int ks = 0; ks < K::KC; ks++) krow[ks] = l32 * K::RB + (((2 * ks + hf) ^ K::swz(l32)) << 4);
+    const unsigned prow = l32 * K::PP + hf * 16;
+#pragma unroll
+    for (int hi = 0; hi < 2; hi++) {
+        const int row = 8 * hi + 4 * hf + (i16 >> 2);
+        vtr[hi] = row * K::RB + (((2 * blk16 + ((i16 & 3) >> 1)) ^ K::swz(row)) << 4) + (i16 & 1) * 8;
+    }
+
+    unsigned buf = 0;
+    for (;;) {
+        const unsigned nbuf = buf_bytes - buf;
+        const int qw0 = ((unit - bh * upr) * nw + wave) * 32;       // first query row of this wave
+        const int next = unit + (int)gridDim.x;
+        const bool more = next < units;                             // workgroup-uniform
+        const int nbh = more ? next / upr : bh;
+        const bool fresh = nbh != bh;                               // another head's rows have to be staged
+
+        bf16x8 qreg[K::KS];
+        const float qscale = FOLD ? p.scale * kLog2e : p.scale;
+#pragma unroll
+        for (int ks = 0; ks < K::KS; ks++) {
+            if (ks < K::KC) {
+                const bf16x8 x = as_bf16x8(qraw[ks]);
+#pragma unroll
+                for (int e = 0; e < 8; e++) qreg[ks][e] = (bf16_t)((float)x[e] * qscale);
+            } else {
+                qreg[ks] = qphi[ks - K::KC];
+            }
+        }
+        // everything the next unit reads is requested here and met at the end of this one
+        u32x4 praw[PIT];
+        if (fresh) issue_kv(nbh, nbuf);
+        if (more) load_q(next, nbh);
+        if (RP > 0 && fresh) {
+#pragma unroll
+            for (int it = 0; it < PIT; it++)
+                if (tid + it * NT < n_phi) praw[it] = phi_piece(nbh, tid + it * NT);
+        }
+
+        f32x16 oacc;
+        float mref = -INFINITY, lsum = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r++) oacc[r] = 0.f;
+
+        // NB blocks starting at key block kb; FIRST: the masked block that gives every row its reference
+        auto step = [&](int kb, auto nb_tag, auto first_tag) __attribute__((always_inline)) {
+            constexpr int NB = decltype(nb_tag)::value;
+            constexpr bool FIRST = decltype(first_tag)::value;
+            f32x16 s[NB];
+            bf16x8 va[NB][2];
+            const unsigned char* kt = smem + (buf + kb * 32 * K::RB);
+            const unsigned char* pt = smem + (buf + poff0 + kb * 32 * K::PP);
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+#pragma unroll
+                for (int r = 0; r < 16; r++) s[b][r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < K::KS; ks++) {
+                    const bf16x8 a = as_bf16x8(ks < K::KC ? *(const u32x4*)(kt + krow[ks < K::KC ? ks : 0] + b * 32 * K::RB)
+                                                          : *(const u32x4*)(pt + prow + b * 32 * K::PP + (ks - K::KC) * 32));
+                    s[b] = mfma32(a, qreg[ks], s[b]);
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < NB; b++)
+#pragma unroll
+                for (int kk = 0; kk < 2; kk++)
+                    va[b][kk] = join_tr(lds_read_tr16((const bf16_t*)(kt + voff0 + vtr[0] + (2 * b + kk) * 16 * K::RB)),
+                                        lds_read_tr16((const bf16_t*)(kt + voff0 + vtr[1] + (2 * b + kk) * 16 * K::RB)));
+            bf16x8 pb[NB][2];
+            auto exps = [&](float nm) __attribute__((always_inline)) {
+                float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int b = 0; b < NB; b++)
+#pragma unroll
+                    for (int r = 0; r < 16; r += 2) {
+                        const bf16x2 pr2 = {(bf16_t)fast_exp2(fmaf(s[b][r], emul, nm)), (bf16_t)fast_exp2(fmaf(s[b][r + 1], emul, nm))};
+                        ps[(r >> 1) & 3] = pair_sum(pr2, ps[(r >> 1) & 3]);
+                        pb[b][r / 8][r % 8] = pr2[0];
+                        pb[b][r / 8][r % 8 + 1] = pr2[1];
+                    }
+                return (ps[0] + ps[1]) + (ps[2] + ps[3]);
+            };
+            float psum;
+            if constexpr (FIRST) {
+                const int qi = qw0 + l32;
+                if (CAUSAL || (kb * 32 + 32 > M)) {
+#pragma unroll
+                    for (int r = 0; r < 16; r++) {
+                        const int key = kb * 32 + 8 * (r / 4) + 4 * hf + (r % 4);
+                        if (key >= M || (CAUSAL && key > qi)) s[0][r] = -INFINITY;
+                    }
+                }
+                mref = fmaxf(half_max(max16(s[0])) * emul, -1e30f);
+                psum = exps(-mref);
+            } else {
+                psum = exps(-mref);
+                if (__any(!(psum < kSumLimit))) {
+                    // the scores outgrew the reference: take the true maximum, rescale, redo the exponentials
+                    asm volatile("" ::: "memory");
+                    float mx = max16(s[0]);
+                    if (NB == 2) mx = fmaxf(mx, max16(s[NB - 1]));
+                    mx = half_max(mx) * emul;
+                    if (__any(mx > mref)) {
+                        const float mnew = fmaxf(mref, mx);
+                        const float alpha = fast_exp2(mref - mnew);
+                        mref = mnew;
+                        lsum *= alpha;
+#pragma unroll
+                        for (int r = 0; r < 16; r++) oacc[r] *= alpha;
+                    }
+                    psum = exps(-mref);
+                }
+            }
+            lsum += psum;
+#pragma unroll
+            for (int b = 0; b < NB; b++)
+#pragma unroll
+                for (int kk = 0; kk < 2; kk++) oacc = mfma32(va[b][kk], pb[b][kk], oacc);
+        };
+        using One = std::integral_constant<int, 1>;
+        using Two = std::integral_constant<int, 2>;
+
+        if (qw0 < N) {      // wave-uniform
+            const int last = CAUSAL ? min(qw0 >> 5, nkb - 1) : nkb - 1;
+            step(last, One{}, std::true_type{});
+            int kb = 0;
+            for (; kb + 2 <= last; kb += 2) step(kb, Two{}, std::false_type{});
+            if (kb < last) step(kb, One{}, std::false_type{});
+        }
+        if (fresh) {
+            // the next head's rows have landed before anyone reads them; the stores of the results follow behind the
+            // barrier, so nothing waits for them until the next unit ends
+            if (RP > 0) {
+#pragma unroll
+                for (int it = 0; it < PIT; it++)
+                    if (tid + it * NT < n_phi) phi_store(nbuf, tid + it * NT, praw[it]);
+                for (int e = tid + PIT * NT; e < n_phi; e += NT) phi_store(nbuf, e, phi_piece(nbh, e));
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+            __syncthreads();
+        }
+        // ---- epilogue: o = O / l, lse = m + ln l ----
+        const int qi = qw0 + l32;
+        const float ltot = half_sum(lsum);
+        const float inv = 1.f / ltot;
+        if (qi < N) {
+            bf16_t* og = (bf16_t*)p.out + ((size_t)bh * N + qi) * CG;
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                if (8 * g >= CG) continue;
+                bf16x4 o4;
+#pragma unroll
+                for (int x = 0; x < 4; x++) o4[x] = (bf16_t)(oacc[4 * g + x] * inv);
+                *(u32x2*)(og + 8 * g + 4 * hf) = __builtin_bit_cast(u32x2, o4);
+            }
+            if (hf == 0) p.lse[(size_t)bh * N + qi] = (mref + __log2f(ltot)) * kLn2;
+        }
+        if (!more) break;
+        if (fresh) buf = nbuf;
+        unit = next;
+        bh = nbh;
+    }
+}
+
+template <int CG, int RP, int PM, bool CAUSAL>
+int launch(const FwdParams& pin, int nw, int cus, hipStream_t stream) {
+    using K = Cfg<CG, RP>;
+    auto kern = fwd_short_kernel<CG, RP, PM, CAUSAL>;
+    static FbLdsOnce once;
+    if (!fb_raise_lds_limit((const void*)kern, kLdsBytes, once)) return 1;
+    const int upr = (pin.N + 32 * nw - 1) / (32 * nw);
+    const long long units = (long long)pin.B * pin.H * upr;
+    const size_t lds = (size_t)2 * ((pin.M + 31) / 32 * 32) * K::kRow;
+    // workgroups that stay resident: by LDS and by the twelve waves that the registers allow
+    const long long per_cu = kMaxWaves / nw < (int)(kLdsBytes / lds) ? kMaxWaves / nw : (long long)(kLdsBytes / lds);
+    const long long most = (long long)cus * (per_cu < 1 ? 1 : per_cu);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(units < most ? units : most)), dim3(64 * nw), lds, stream, pin, (int)units, upr);
+    return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+template <int CG, int RP, int PM>
+int dispatch_causal(const FwdParams& p, int nw, int cus, hipStream_t stream) {
+    return p.causal ? launch<CG, RP, PM, true>(p, nw, cus, stream) : launch<CG, RP, PM, false>(p, nw, cus, stream);
+}
+template <int CG, int RP>
+int dispatch_pm(const FwdParams& p, int nw, int cus, hipStream_t stream) {
+    if (p.phi_f32) return p.causal ? launch<CG, RP, 3, true>(p, nw, cus, stream) : -1;
+    if (p.R % 8 == 0) return dispatch_causal<CG, RP, 1>(p, nw, cus, stream);
+    return dispatch_causal<CG, RP, 2>(p, nw, cus, stream);
+}
+template <int CG>
+int dispatch_rp(const FwdParams& p, int rp, int nw, int cus, hipStream_t stream) {
+    switch (rp) {
+        case 0: return dispatch_causal<CG, 0, 0>(p, nw, cus, stream);
+        case 16: return dispatch_pm<CG, 16>(p, nw, cus, stream);
+        case 32: return dispatch_pm<CG, 32>(p, nw, cus, stream);
+        default: return -1;
+    }
+}
+
+}  // namespace
+
+// Self-attention whose keys fit LDS twice.  Kernel times against the ring kernel's (start / this, us), full attention,
+// bf16 factors unless said:
+//   up to 128 keys it is the faster one throughout (C 32, R 16: 1.1-1.2, N 64 with 1024 heads 7.7 / 5.5; C 16 1.05-1.1);
+//   up to 256 keys at C 32 (R 16: 0.98 at 64 heads to 1.25 at 256; R 4 1.0-1.27), beyond from 128 heads on, as one
+//   workgroup takes a whole head (N 384: 64 heads 8.4 / 10.8, 256 heads 16.0 / 12.8, 1024 heads 45.6 / 43.6);
+//   factor blocks of 32 columns at C 32 spill a few registers: beyond 128 keys only where the heads fill one round of
+//   workgroups (256 heads 1.1-1.2, 1024 heads 0.90-0.94);
+//   no factors, or C 16 with R 8 (N 256: 0.9-1.1): not beyond 128 keys; C 16 with other factors as C 32.
+//   fp32 factors are split once a head, but only by one workgroup: 0.7-0.95, never.
+// Causal the ring kernel's 128-row tiles do up to twice the work: 1.2-2.3 throughout (C 32, N 256: 256 heads 14.7 / 7.6,
+// 1024 heads 27.7 / 24.4), but for 32 factor columns at many heads (0.95-0.98) and fp32 factors (N 384: 44.1 / 31.5,
+// N 256: 256 heads 18.6 / 12.9, 400 heads 21.4 / 21.7).
+bool fb_short_fwd(const FwdParams& p, int C, int rp) {
+    if (C > 32 || rp > 32 || p.N != p.M || p.slopes != nullptr) return false;
+    const long long BH = (long long)p.B * p.H;
+    const int nkb = (p.M + 31) / 32;
+    if (nkb > kMaxWaves || BH >= (1LL << 30)) return false;
+    const size_t row = C == 16 ? (rp == 0 ? Cfg<16, 0>::kRow : rp == 16 ? Cfg<16, 16>::kRow : Cfg<16, 32>::kRow)
+                               : (rp == 0 ? Cfg<32, 0>::kRow : rp == 16 ? Cfg<32, 16>::kRow : Cfg<32, 32>::kRow);
+    if ((size_t)2 * nkb * 32 * row > kLdsBytes) return false;
+    if (rp > 0 && p.phi_f32) return p.causal && (nkb > 8 || (nkb > 4 && BH <= 256));
+    const bool wide = C == 32 && rp == 32;
+    if (p.causal) return !wide || nkb <= 4 || nkb > 8 || BH <= 512;
+    if (nkb <= 4) return true;
+    if (rp == 0 || (C == 16 && rp == 16 && p.R % 8 == 0)) return false;
+    if (wide) return BH >= 160 && BH <= 256;
+    return nkb <= 8 || BH >= 128;
+}
+
+int fb_launch_fwd_bf16_short(const FwdParams& p, int C, int rp, hipStream_t stream) {
+    const int cus = fb_cu_count(), nw = (p.N + 31) / 32;
+    if (cus <= 0) return 1;
+    return C == 16 ? dispatch_rp<16>(p, rp, nw, cus, stream) : dispatch_rp<32>(p, rp, nw, cus, stream);
+}

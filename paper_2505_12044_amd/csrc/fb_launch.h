@@ -20,8 +20,15 @@ int fb_launch_fwd_bf16_alibi(const FwdParams& p, int C, int qb, hipStream_t stre
 bool fb_few_queries(long long BH, int N, int M, int C, int R, bool phi_f32, bool scratch);
 size_t fb_few_workspace_bytes(long long BH, int N, int M, int C);
 int fb_launch_fwd_bf16_few(const FwdParams& p, int C, void* ws, hipStream_t stream);
+// Short sequences on the 32-channel tiles (N = M): a head's keys and values in LDS whole.  fb_short_fwd: whether that
+// kernel takes the call.
+bool fb_short_fwd(const FwdParams& p, int C, int rp);
+int fb_launch_fwd_bf16_short(const FwdParams& p, int C, int rp, hipStream_t stream);
 // p.workspace points at fb_bwd_workspace_bytes(B*H*N, B*H*M, C, R) bytes of device scratch.
 int fb_launch_bwd_bf16(const BwdParams& p, int C, int rp, hipStream_t stream);
+// Short key sequences on the 32-channel tiles: one kernel, no workspace.  fb_short_bwd: whether it takes the call.
+bool fb_short_bwd(const BwdParams& p, int C, int rp);
+int fb_launch_bwd_bf16_short(const BwdParams& p, int C, int rp, hipStream_t stream);
 size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R);
 // fp32 tensors and fp32 factors: p.workspace holds one float per query row (a prefix of the
 // size above).
@@ -59,6 +66,18 @@ inline bool fb_raise_lds_limit(const void* kern, size_t bytes, FbLdsOnce& once) 
     if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) return false;
     if (tracked) once.done[dev].store(true, std::memory_order_release);
     return true;
+}
+
+// Compute units of the current device (0 on failure), asked once per device.
+inline int fb_cu_count() {
+    static std::atomic<int> known[kFbMaxDevices] = {};
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    const bool tracked = dev >= 0 && dev < kFbMaxDevices;
+    if (tracked && (n = known[dev].load(std::memory_order_relaxed)) > 0) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (tracked) known[dev].store(n, std::memory_order_relaxed);
+    return n;
 }
 
 #endif

@@ -1,0 +1,95 @@
+"""The kernels for heads whose keys fit one workgroup (head dimensions 16 and 32, up to 384 keys): one to twelve 32-key
+tiles, odd and even numbers of query blocks, partial last tiles, fewer queries than keys, factor widths of one and two
+16-column groups with every remainder the kernels take, several heads to a workgroup, and the lengths just outside.
+Against the float64 oracle at the bounds of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fb_oracle as O
+from paper_2505_12044_amd import api, workloads as W
+from tests._gpu_util import check_fwd, check_grad, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(B, H, N, M, C, R, phi, causal, shared, heads, offset=0.0):
+    rng = np.random.default_rng(N * 7919 + M * 31 + C + R)
+    rd = lambda *s: W.round_bf16(rng.standard_normal(s).astype(np.float32))
+    q, k, v, dout = rd(B, H, N, C), rd(B, H, M, C), rd(B, H, M, C), rd(B, H, N, C)
+    Bp, sc = 1 if shared else B, max(R, 1) ** -0.25
+    pq = (sc * rng.standard_normal((Bp, H, N, R))).astype(np.float32)
+    pk = (sc * rng.standard_normal((Bp, H, M, R))).astype(np.float32)
+    if offset:      # the bias grows along the keys, so the reference maximum of the first block is outgrown
+        pq[..., 0], pk[..., 0] = 1.0, np.linspace(0.0, offset, M, dtype=np.float32)
+    if phi == "bf16":
+        pq, pk = W.round_bf16(pq), W.round_bf16(pk)
+    d = [dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16")] + ([dev(pq, phi), dev(pk, phi)] if R else [None, None])
+    if N == M:
+        out, lse = api.fb_lowrank_attn_fwd(*d, causal=causal)
+        grads = api.fb_lowrank_attn_bwd(*d, out, lse, dev(dout, "bf16"), causal=causal)
+    else:
+        out, lse = api.fb_lowrank_xattn_fwd(*d)
+        grads = api.fb_lowrank_xattn_bwd(*d, out, lse, dev(dout, "bf16"))
+    torch.cuda.synchronize()
+    label = f"short B{B} H{H} N{N} M{M} C{C} R{R} {phi} causal={causal} shared={shared}"
+    for b, h in heads:
+        fq, fk = pq[0 if shared else b, h], pk[0 if shared else b, h]
+        ro, rl = O.attention_lowrank(q[b, h], k[b, h], v[b, h], fq, fk, causal=causal)
+        check_fwd(f"{label} ({b},{h})", "out", host(out[b, h]), ro)
+        check_fwd(f"{label} ({b},{h})", "lse", host(lse[b, h]), rl)
+        ref = O.attention_lowrank_grads(q[b, h], k[b, h], v[b, h], fq, fk, dout[b, h], causal=causal)
+        for name, g, r in zip(("dq", "dk", "dv", "dphi_q", "dphi_k"), grads, ref):
+            if g is not None:
+                other = pk if name == "dphi_q" else pq
+                gain = max(1.0, float(np.abs(other).max())) if name.startswith("dphi") else 1.0
+                # a few keys or queries sum many rows: bound by the size of the result as in the other sweeps
+                check_grad(f"{label} ({b},{h})", name, host(g[b, h]), r, data_scaled=True, gain=gain)
+
+
+@pytest.mark.parametrize("N", [1, 31, 32, 33, 64, 65, 97, 128, 129, 161, 192, 225, 321, 353, 383, 384, 385])
+@pytest.mark.parametrize("C,R", [(16, 8), (16, 28), (32, 4), (32, 16), (32, 24)])
+@pytest.mark.parametrize("causal", [False, True])
+def test_lengths(N, C, R, causal):
+    _run(2, 3, N, N, C, R, "bf16", causal, N % 2 == 0, [(0, 0), (1, 2)])
+
+
+@pytest.mark.parametrize("N,M", [(1, 384), (33, 383), (32, 65), (64, 70), (100, 320), (200, 230)])
+@pytest.mark.parametrize("C,R", [(16, 12), (32, 16), (32, 32)])
+def test_fewer_queries_than_keys(N, M, C, R):
+    _run(3, 2, N, M, C, R, "bf16", False, True, [(0, 1), (2, 0)])
+
+
+@pytest.mark.parametrize("C,R,phi", [(16, 0, "bf16"), (32, 0, "bf16"), (16, 3, "f32"), (32, 5, "f32"), (32, 10, "bf16"), (16, 18, "bf16")])
+@pytest.mark.parametrize("N", [40, 180, 290, 384])
+@pytest.mark.parametrize("causal", [False, True])
+def test_other_factors(C, R, phi, N, causal):
+    _run(1, 2, N, N, C, R, phi, causal, True, [(0, 1)])
+
+
+# several heads to a workgroup: 256 CUs hold 256 workgroups of seven to twelve waves, 512 of six
+@pytest.mark.parametrize("B,H,N", [(130, 4, 300), (300, 2, 384), (60, 20, 40), (75, 8, 225)])
+@pytest.mark.parametrize("C,R,causal,shared", [(32, 16, False, True), (16, 16, True, False)])
+def test_many_heads(B, H, N, C, R, causal, shared):
+    _run(B, H, N, N, C, R, "bf16", causal, shared, [(0, 0), (B // 2, H - 1), (B - 1, H - 1), (B - 1, 0)])
+
+
+@pytest.mark.parametrize("C", [16, 32])
+@pytest.mark.parametrize("N", [96, 300])
+def test_outgrown_reference(C, N):
+    """The bias rises by 30 along the keys: the rescaling path of every later block."""
+    _run(64, 4, N, N, C, 8, "bf16", False, True, [(0, 0), (63, 3)], offset=30.0)
+
+
+def test_same_result_on_every_run():
+    torch.manual_seed(5)
+    t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    q, k, v, do, pq, pk = t(90, 4, 333, 32), t(90, 4, 333, 32), t(90, 4, 333, 32), t(90, 4, 333, 32), t(1, 4, 333, 16), t(1, 4, 333, 16)
+    first = None
+    for _ in range(4):
+        out, lse = api.fb_lowrank_attn_fwd(q, k, v, pq, pk)
+        got = (out, lse) + tuple(api.fb_lowrank_attn_bwd(q, k, v, pq, pk, out, lse, do))
+        torch.cuda.synchronize()
+        if first is None:
+            first = got
+        assert all(torch.equal(a, b) for a, b in zip(first, got))

@@ -225,9 +225,11 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
  * gradients are the trailing R columns of the same contractions that give dq and dk
  * (Sec. 3.2 "Speed up training"; Sec. 4.1 "Implementation choices").
  * `out` and `lse` are the forward's results.  dtype = FB_BF16, or FB_F32 (all tensors and the
- * factors float, N keys = N queries: the full-precision path, fp32 products and sums, which uses only
- * the first 4 B H N bytes of the workspace, for D).
- * workspace: device scratch of at least fb_lowrank_attn_bwd_workspace_bytes(...) bytes,
+ * factors float, N keys = N queries: the full-precision path, fp32 products and sums, which uses
+ * 4 B H N bytes of the workspace for D and, where the rest of it (up to 1 GiB) takes dS of some or all
+ * heads, leaves dS there between its two sides).
+ * workspace: device scratch of at least fb_lowrank_attn_bwd_workspace_bytes(...) bytes (FB_F32: the
+ * size with room for dS; what the formula below gives is accepted and computes S and dP once more instead),
  * 16-byte aligned, owned by the caller; its contents on entry are ignored and it may be
  * reused as soon as the call's work on `stream` has finished.  It receives, per (b, h, i):
  * (lse * log2 e, D_i = sum_c dout * out) and the concatenated bf16 operand rows
@@ -253,7 +255,7 @@ int fb_lowrank_attn_bwd(const void* q, const void* k, const void* v,
  * (bit-identical) results; the scratch that fb_lowrank_attn_bwd takes from the caller lives in
  * a static device array of FB_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held
  * from library load until the process ends.  The call allocates and frees nothing.
- *   Limit: fb_lowrank_attn_bwd_workspace_bytes(B, H, N, C, R, dtype) <= FB_STATIC_SCRATCH_BYTES
+ *   Limit: fb_lowrank_attn_bwd_workspace_bytes(B, H, N, C, R, FB_BF16) <= FB_STATIC_SCRATCH_BYTES
  *   (e.g. B H N <= 86480 rows at C = 128 with factors); larger problems return
  *   FB_ERR_TOO_LARGE and launch nothing.
  *   Every call on a GPU uses that GPU's one array: calls that overlap on the same GPU (two

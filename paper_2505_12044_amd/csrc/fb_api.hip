@@ -397,6 +397,15 @@ static size_t bwd_ws_impl(int B, int H, int N, int M, int C, int R) {
     return fb_bwd_workspace_bytes((long long)B * H * N, (long long)B * H * M, C, R);
 }
 
+// What the size queries return: the least a call needs (bwd_ws_impl, what the calls check), for fp32 with the room that
+// saves the query side its recomputation.
+static size_t bwd_ws_query(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
+    const size_t least = bwd_ws_impl(B, H, N, M, C, R);
+    if (dtype != FB_F32 || least == 0) return least;
+    const size_t f32 = fb_bwd_f32_workspace_bytes((long long)B * H, N, M, C);
+    return f32 > least ? f32 : least;
+}
+
 static int lowrank_bwd_impl(const void* q, const void* k, const void* v,
                             const void* phi_q, const void* phi_k,
                             const void* out, const float* lse, const void* dout,
@@ -426,6 +435,7 @@ static int lowrank_bwd_impl(const void* q, const void* k, const void* v,
     p.out = out; p.lse = lse; p.dout = dout;
     p.dq = dq; p.dk = dk; p.dv = dv; p.dphi_q = dphi_q; p.dphi_k = dphi_k;
     p.workspace = workspace;
+    p.workspace_bytes = workspace_bytes;
     p.B = B; p.H = H; p.N = N; p.M = M; p.R = R; p.Cg = C; p.causal = causal != 0;
     p.phi_f32 = phi_dtype == FB_F32;
     p.phi_bstride = phi_batch_broadcast ? 0 : (long long)H * N * R;
@@ -512,13 +522,11 @@ int fb_dense_bias_attn_bwd(const void* q, const void* k, const void* v, const vo
 }
 
 size_t fb_lowrank_attn_bwd_workspace_bytes(int B, int H, int N, int C, int R, fb_dtype dtype) {
-    (void)dtype;
-    return bwd_ws_impl(B, H, N, N, C, R);
+    return bwd_ws_query(B, H, N, N, C, R, dtype);
 }
 
 size_t fb_lowrank_xattn_bwd_workspace_bytes(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
-    (void)dtype;
-    return bwd_ws_impl(B, H, N, M, C, R);
+    return bwd_ws_query(B, H, N, M, C, R, dtype);
 }
 
 int fb_lowrank_attn_bwd(const void* q, const void* k, const void* v,

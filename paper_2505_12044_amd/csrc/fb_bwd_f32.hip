@@ -34,6 +34,33 @@ constexpr int kThreads = 256;
 constexpr int BT = 32;       // streamed rows per block
 constexpr int OPITCH = 36;   // row pitch of an output tile in LDS (floats)
 
+// dS of one head, whole tiles.
+size_t ds_head_bytes(int N, int M) { return (size_t)((N + 31) & ~31) * ((M + 31) & ~31) * 4; }
+size_t d_bytes(long long rows) { return ((size_t)rows * 4 + 255) & ~(size_t)255; }
+// At most this much dS at a time.  (256 MB, what the last-level cache holds, cuts B 16, H 4, N 1500, C 64 into three
+// launches whose tiles fill the chip badly: 1514 us; in one 1084, recomputed 1329.)
+constexpr size_t kMaxStored = (size_t)1 << 30;
+// Heads whose dS the workspace takes at a time, 0 where the query side recomputes it.  Stored against recomputed,
+// kernel times (us): C 32, R 8 64 heads of N 1024 333 / 290; C 64 16 heads of N 1500 372 / 301; C 128 790 / 553; from
+// the smallest calls on (C 64, 2 heads of 256 34 / 29), where one launch more costs the host what it saves: left to
+// recompute below about 60 us.  Not at 16 channels: a block's recomputation takes 1300 cycles of the matrix pipe, its
+// 8 KB to memory and back more.
+int stored_heads(const BwdParams& p, int C, float*& dS) {
+    const size_t off = d_bytes((long long)p.B * p.H * p.N), per = ds_head_bytes(p.N, p.M);
+    const long long heads = (long long)p.B * p.H;
+    size_t avail = p.workspace_bytes > off ? p.workspace_bytes - off : 0;
+    if (avail > kMaxStored) avail = kMaxStored;
+    const long long fit = (long long)(avail / per);
+    if (fit <= 0) return 0;
+    const long long parts = (heads + fit - 1) / fit, chunk = (heads + parts - 1) / parts;
+    // several launches have to be worth filling the chip (four waves to a 32-row tile)
+    const int nq = (p.N + 31) / 32, nk = (p.M + 31) / 32;
+    if ((double)heads * nq * nk * C < 262144.0) return 0;
+    if (parts > 1 && chunk * (nq < nk ? nq : nk) < 512) return 0;
+    dS = (float*)((unsigned char*)p.workspace + off);
+    return (int)chunk;
+}
+
 template <int C, int RP, bool KEYSIDE>
 struct Cfg {
     static constexpr int W = C + RP;
@@ -50,14 +77,17 @@ struct Cfg {
 // KEYSIDE = true:  lanes are keys, queries are streamed; outputs dk, dv, dphi_k.
 // DENSE: the bias is a materialised [N, M] matrix per head, added to the scores (the
 // training-side baseline of Sec. 4.3); dBias = dS is written by the query-side launch, zero where masked.
-template <int C, int RP, bool KEYSIDE, bool DENSE = false>
-__global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bwd_f32_kernel(BwdParams p, float* __restrict__ Dws, int kw_log2) {
+// dS: the heads head0.. of this launch, dS transposed, [keys][queries] padded to whole tiles (STORE: written; the query
+// side's second contraction is then a launch of its own, bwd_f32_dq_kernel).
+template <int C, int RP, bool KEYSIDE, bool DENSE = false, bool STORE = false>
+__global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bwd_f32_kernel(BwdParams p, float* __restrict__ Dws, int kw_log2, float* __restrict__ dS, int head0) {
+    static_assert(!STORE || (KEYSIDE && !DENSE), "the key side stores dS");
     using K = Cfg<C, RP, KEYSIDE>;
     __shared__ __align__(16) float otile[kThreads / 64][32 * OPITCH];
     const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);      // contiguous runs of units per XCD
     if (L >= p.total_tiles) return;
-    const int bh = L / p.n_tiles;                          // p.n_tiles: workgroups per (b, h)
-    const int u0 = L - bh * p.n_tiles;
+    const int bhl = L / p.n_tiles;                         // p.n_tiles: workgroups per (b, h)
+    const int u0 = L - bhl * p.n_tiles, bh = head0 + bhl;
     const int u = (p.causal && !KEYSIDE) ? p.n_tiles - 1 - u0 : u0;      // causal: long tiles first
     const int b = bh / p.H, h = bh - b * p.H;
     const int N = p.N, M = p.M, R = p.R;                   // N queries, M keys
@@ -257,6 +287,12 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
             }
         }
         load_vec(nxt);
+        if (STORE) {
+            const size_t pitch = (size_t)nall * BT, rows = (size_t)((NL + 31) & ~31);
+            float* drow = dS + ((size_t)bhl * rows + row) * pitch + blk * BT + 4 * hf;
+#pragma unroll
+            for (int g = 0; g < 4; g++) *(f32x4*)(drow + 8 * g) = f32x4{dp[4 * g], dp[4 * g + 1], dp[4 * g + 2], dp[4 * g + 3]};
+        }
         if (DENSE && !KEYSIDE && row < NL) {
             float* drow = dbg + (size_t)row * M;
 #pragma unroll
@@ -328,25 +364,179 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
     }
 }
 
-template <int C, int RP, bool KEYSIDE, bool DENSE>
-int launch_side(const BwdParams& pin, hipStream_t stream) {
-    BwdParams p = pin;
-    const int rows = KEYSIDE ? p.M : p.N, other = KEYSIDE ? p.N : p.M;
+// D_i = sum_c dout_ic out_ic of `rows` rows: C / 4 threads a row.  Bound by its reads.
+template <int C>
+__global__ __launch_bounds__(256) void bwd_f32_d_kernel(const float* __restrict__ out, const float* __restrict__ dout, float* __restrict__ D, long long rows) {
+    constexpr int T = C / 4;
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x, row = i / T;
+    if (row >= rows) return;                 // whole rows leave together (256 is a multiple of T)
+    const f32x4 a = *(const f32x4*)(out + i * 4), b = *(const f32x4*)(dout + i * 4);
+    float s = fmaf(a[0], b[0], fmaf(a[1], b[1], fmaf(a[2], b[2], a[3] * b[3])));
+#pragma unroll
+    for (int m = 1; m < T; m <<= 1) s += __shfl_xor(s, m);
+    if (i % T == 0) D[row] = s;
+}
+
+// d[q | phi_q] = dS [k | phi_k] from the dS that the key side stored: lanes are queries, both operands of a k-step are 4
+// bytes a lane and 128 in a row, one block ahead.  Bound by the matrix pipe (48 instructions of 64 cycles a 32 x 32
+// block at C 64, R 8) with the read of dS, 4 KB a block, behind it.
+template <int C, int RP>
+__global__ __launch_bounds__(kThreads, 2) void bwd_f32_dq_kernel(BwdParams p, const float* __restrict__ dS, int head0, int kw_log2) {
+    using K = Cfg<C, RP, false>;
+    __shared__ __align__(16) float otile[kThreads / 64][32 * OPITCH];
+    const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);
+    if (L >= p.total_tiles) return;
+    const int bhl = L / p.n_tiles;
+    const int u0 = L - bhl * p.n_tiles, bh = head0 + bhl;
+    const int u = p.causal ? p.n_tiles - 1 - u0 : u0;      // causal: long tiles first
+    const int b = bh / p.H, h = bh - b * p.H;
+    const int N = p.N, M = p.M, R = p.R;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int l32 = lane & 31, hf = lane >> 5;
+    const int KW = 1 << kw_log2;
+    const int part = wave & (KW - 1);
+    const int tile = u * ((kThreads / 64) >> kw_log2) + (wave >> kw_log2);
+    const int row0 = tile * 32;
+    const int nkb = (M + BT - 1) / BT, pitch = (N + 31) & ~31;
+
+    const f32_buf kb = make_buf((const float*)p.k + (size_t)bh * M * C, (size_t)M * C * 4);
+    const f32_buf pb = RP > 0 ? make_buf((const float*)p.phi_k + (size_t)b * p.phik_bstride + (size_t)h * M * R, (size_t)M * R * 4) : kb;
+    const f32_buf sb = make_buf(dS + (size_t)bhl * nkb * BT * pitch, (size_t)nkb * BT * pitch * 4);
+
+    f32x16 acc[K::TA];
+#pragma unroll
+    for (int t = 0; t < K::TA; t++)
+#pragma unroll
+        for (int r = 0; r < 16; r++) acc[t][r] = 0.f;
+    int b1 = p.causal ? min(nkb, tile + 1) : nkb;
+    if (row0 >= N) b1 = 0;
+
+    auto load_ds = [&](int blk, float (&x)[16]) __attribute__((always_inline)) {
+        const unsigned off = ((unsigned)(blk * BT + 4 * hf) * (unsigned)pitch + (unsigned)(row0 + l32)) * 4u;
+#pragma unroll
+        for (int r = 0; r < 16; r++) x[r] = buf_f32(sb, off + (8 * (r / 4) + r % 4) * ((unsigned)pitch * 4u));
+    };
+    // column tile t of block blk of [k | phi_k]; rows past M read zero, columns past C + R some real element
+    auto load_cols = [&](int blk, int t, float (&x)[16]) __attribute__((always_inline)) {
+        const unsigned r0 = (unsigned)(blk * BT + 4 * hf);
+        const int c0 = t * 32;
+        if (c0 < C) {
+            const unsigned off = r0 * (C * 4u) + 4u * (c0 + l32);
+#pragma unroll
+            for (int r = 0; r < 16; r++) x[r] = buf_f32(kb, off + (8 * (r / 4) + r % 4) * (C * 4u));
+        } else {
+            unsigned off = (r0 * (unsigned)R + (unsigned)min(c0 + l32 - C, R - 1)) * 4u;
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                x[r] = buf_f32(pb, off);
+                off += (r & 3) == 3 ? 20u * (unsigned)R : 4u * (unsigned)R;
+            }
+        }
+    };
+    float ds[2][16], cc[2][16];
+    if (part < b1) {
+        load_ds(part, ds[0]);
+        load_cols(part, 0, cc[0]);
+    }
+    // two blocks at a time: the register sets change roles without copies
+    auto block = [&](int blk, float (&cur)[16], float (&nxt)[16], int c0) __attribute__((always_inline)) {
+        const int next = min(blk + KW, b1 - 1);
+        load_ds(next, nxt);
+#pragma unroll
+        for (int t = 0; t < K::TA; t++) {
+            load_cols(t + 1 < K::TA ? blk : next, t + 1 < K::TA ? t + 1 : 0, cc[(c0 + t + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[t] = mfma32f(cc[(c0 + t) & 1][r], cur[r], acc[t]);
+        }
+    };
+    int blk = part;
+    for (; blk + KW < b1; blk += 2 * KW) {
+        block(blk, ds[0], ds[1], 0);
+        block(blk + KW, ds[1], ds[0], K::TA & 1);
+    }
+    if (blk < b1) block(blk, ds[0], ds[1], 0);
+
+    // ---- epilogue: tile by tile through LDS, where the KW partial sums meet ----
+    float* dxg = (float*)p.dq + (size_t)bh * N * C;
+    float* dphig = (float*)p.dphi_q;
+    if (dphig) dphig += (size_t)bh * N * R;
+#pragma unroll
+    for (int t = 0; t < K::TA; t++) {
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < 4; g++)
+            *(f32x4*)(&otile[wave][l32 * OPITCH + 8 * g + 4 * hf]) = f32x4{acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+        __syncthreads();
+        for (int e = part * 64 + lane; e < 32 * 8; e += KW * 64) {
+            const int rr = e >> 3, c = t * 32 + (e & 7) * 4;
+            if (row0 + rr >= N) break;
+            f32x4 w = {0.f, 0.f, 0.f, 0.f};
+            for (int x = 0; x < KW; x++) w += *(const f32x4*)(&otile[wave - part + x][rr * OPITCH + (e & 7) * 4]);
+            const size_t orow = (size_t)(row0 + rr);
+            if (c < C) {
+                w *= p.scale;
+                *(f32x4*)(dxg + orow * C + c) = w;
+            } else if (dphig) {
+#pragma unroll
+                for (int x = 0; x < 4; x++)
+                    if (c + x - C < R) dphig[orow * R + (c + x - C)] = w[x];
+            }
+        }
+    }
+}
+
+// Tiles of one launch over `heads` heads, `rows` rows a head: p's counters, the split of a tile over waves.
+int set_tiles(BwdParams& p, long long heads, int rows, int other) {
     const int tiles = (rows + 31) / 32;
-    const int kw = f32_split((long long)p.B * p.H * tiles, (other + BT - 1) / BT, 4);
+    const int kw = f32_split(heads * tiles, (other + BT - 1) / BT, 4);
     int kw_log2 = 0;
     while ((1 << kw_log2) < kw) kw_log2++;
     const int qw = (kThreads / 64) / kw;
     p.n_tiles = (tiles + qw - 1) / qw;
-    p.total_tiles = p.B * p.H * p.n_tiles;
+    p.total_tiles = (int)heads * p.n_tiles;
     p.tiles_per_xcd = (p.total_tiles + 7) / 8;
+    return kw_log2;
+}
+
+template <int C, int RP, bool KEYSIDE, bool DENSE>
+int launch_side(const BwdParams& pin, hipStream_t stream) {
+    BwdParams p = pin;
+    const int kw_log2 = set_tiles(p, (long long)p.B * p.H, KEYSIDE ? p.M : p.N, KEYSIDE ? p.N : p.M);
     hipLaunchKernelGGL((bwd_f32_kernel<C, RP, KEYSIDE, DENSE>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
-                       (float*)p.workspace, kw_log2);
+                       (float*)p.workspace, kw_log2, (float*)nullptr, 0);
     return hipGetLastError() == hipSuccess ? 0 : 1;
+}
+
+// Key side first, leaving dS for the query side, `chunk` heads at a time.
+template <int C, int RP>
+int launch_stored(const BwdParams& pin, float* dS, int chunk, hipStream_t stream) {
+    const long long rows = (long long)pin.B * pin.H * pin.N;
+    hipLaunchKernelGGL((bwd_f32_d_kernel<C>), dim3((unsigned)((rows * (C / 4) + 255) / 256)), dim3(256), 0, stream, (const float*)pin.out,
+                       (const float*)pin.dout, (float*)pin.workspace, rows);
+    if (hipGetLastError() != hipSuccess) return 1;
+    const int heads = pin.B * pin.H;
+    for (int h0 = 0; h0 < heads; h0 += chunk) {
+        const int n = heads - h0 < chunk ? heads - h0 : chunk;
+        BwdParams p = pin;
+        int kw_log2 = set_tiles(p, n, p.M, p.N);
+        hipLaunchKernelGGL((bwd_f32_kernel<C, RP, true, false, true>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
+                           (float*)p.workspace, kw_log2, dS, h0);
+        kw_log2 = set_tiles(p, n, p.N, p.M);
+        hipLaunchKernelGGL((bwd_f32_dq_kernel<C, RP>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p, (const float*)dS, h0, kw_log2);
+        if (hipGetLastError() != hipSuccess) return 1;
+    }
+    return 0;
 }
 
 template <int C, int RP, bool DENSE = false>
 int launch(const BwdParams& p, hipStream_t stream) {
+    if constexpr (C >= 32 && !DENSE) {
+        float* dS;
+        const int chunk = stored_heads(p, C, dS);
+        if (chunk > 0) return launch_stored<C, RP>(p, dS, chunk, stream);
+    }
     const int rc = launch_side<C, RP, false, DENSE>(p, stream);      // also leaves D for the key side
     return rc != 0 ? rc : launch_side<C, RP, true, DENSE>(p, stream);
 }
@@ -362,8 +552,16 @@ int dispatch_c(const BwdParams& p, hipStream_t stream) {
 
 }  // namespace
 
+// Workspace with which the query side takes dS from the key side instead of recomputing it.
+size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C) {
+    const size_t per = ds_head_bytes(N, M);
+    if (C < 32 || per > kMaxStored) return 0;
+    const size_t fit = kMaxStored / per;
+    return d_bytes(heads * N) + ((size_t)heads < fit ? (size_t)heads : fit) * per;
+}
+
 // fp32 tensors and fp32 factors (N queries, M keys; causal needs N = M); p.workspace: at least
-// 4 B H N bytes (the D row sums).
+// 4 B H N bytes (the D row sums); with fb_bwd_f32_workspace_bytes of them the query side is one contraction.
 // Returns 0 on success, 1 on launch failure, -1 when no instantiation fits.
 int fb_launch_bwd_f32(const BwdParams& p, int C, hipStream_t stream) {
     if (p.R > 64 || (p.causal && p.N != p.M)) return -1;

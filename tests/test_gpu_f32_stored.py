@@ -1,0 +1,75 @@
+"""The fp32 backward that stores dS between its two sides: partial tiles on both sides, causal, separate key lengths,
+factor widths with every kind of last column tile, one launch over all heads and several over parts of them, and the
+workspace just too small for it (the recomputing form).  Against the float64 oracle at the fp32 bounds, and the two
+forms against each other."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fb_oracle as O
+from paper_2505_12044_amd import api
+from tests._gpu_util import host, report
+
+pytestmark = pytest.mark.gpu
+
+NAMES = ("dq", "dk", "dv", "dphi_q", "dphi_k")
+
+
+def _up(n):
+    return (n + 31) // 32 * 32
+
+
+def _run(B, H, N, M, C, R, causal, shared, heads, ws_heads=None):
+    rng = np.random.default_rng(7 * N + 3 * M + C + R)
+    f32 = lambda *s: rng.standard_normal(s).astype(np.float32)
+    q, dout, k, v = f32(B, H, N, C), f32(B, H, N, C), f32(B, H, M, C), f32(B, H, M, C)
+    Bp = 1 if shared else B
+    pq = (0.5 * f32(Bp, H, N, R)) if R else None
+    pk = (0.5 * f32(Bp, H, M, R)) if R else None
+    t = lambda x: None if x is None else torch.from_numpy(x).cuda()
+    d = [t(q), t(k), t(v), t(pq), t(pk)]
+    kw = {}
+    if ws_heads is not None:      # room for dS of ws_heads heads behind D, and the least the call takes
+        least = api.fb_lowrank_attn_bwd_workspace_bytes(B, H, N, C, R)
+        room = (B * H * N * 4 + 255) // 256 * 256 + ws_heads * _up(N) * _up(M) * 4
+        kw["workspace"] = torch.empty(max(least, room), dtype=torch.uint8, device="cuda")
+    if N == M:
+        out, lse = api.fb_lowrank_attn_fwd(*d, causal=causal)
+        grads = api.fb_lowrank_attn_bwd(*d, out, lse, t(dout), causal=causal, **kw)
+    else:
+        out, lse = api.fb_lowrank_xattn_fwd(*d)
+        grads = api.fb_lowrank_xattn_bwd(*d, out, lse, t(dout), **kw)
+    torch.cuda.synchronize()
+    for b, h in heads:
+        fq = pq[min(b, Bp - 1), h] if R else np.zeros((N, 0))
+        fk = pk[min(b, Bp - 1), h] if R else np.zeros((M, 0))
+        label = f"f32 stored B{B} H{H} N{N} M{M} C{C} R{R} causal={causal} room={ws_heads} (b,h)=({b},{h})"
+        print(label, flush=True)
+        ref = O.attention_lowrank_grads(q[b, h], k[b, h], v[b, h], fq, fk, dout[b, h], causal=causal)
+        for name, g, r in zip(NAMES, grads, ref):
+            if g is None:
+                continue
+            e, _, big = report(label, name, host(g[b, h]), r)
+            assert e <= 1e-4 * max(1.0, big), (label, name, e, big)
+    return grads
+
+
+@pytest.mark.parametrize("N,M,causal", [(601, 601, False), (601, 601, True), (640, 640, True), (523, 801, False), (1000, 385, False)])
+@pytest.mark.parametrize("C,R", [(32, 0), (32, 5), (32, 33), (64, 8), (64, 64), (128, 3)])
+def test_stored_ds(N, M, causal, C, R):
+    _run(4, 8, N, M, C, R, causal, N % 2 == 0, [(0, 0), (3, 7)])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("C,R", [(32, 8), (64, 3)])
+def test_parts_and_recomputed(causal, C, R):
+    """60 heads of 601 rows: dS of all, of 35 (two launches of 30) and of none."""
+    got = [_run(15, 4, 601, 601, C, R, causal, True, [(0, 0), (7, 2), (14, 3)], ws_heads=n) for n in (60, 35, 0)]
+    # a launch's split of a tile over waves follows from its tile count, so the sums' order differs: a few ulp of fp32
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            assert float((x - y).norm() / y.norm()) < 1e-5
+
+
+def test_an_oversized_workspace_is_fine():
+    _run(2, 8, 700, 700, 64, 4, False, True, [(1, 7)], ws_heads=40)

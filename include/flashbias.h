@@ -226,16 +226,17 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
  * (Sec. 3.2 "Speed up training"; Sec. 4.1 "Implementation choices").
  * `out` and `lse` are the forward's results.  dtype = FB_BF16, or FB_F32 (all tensors and the
  * factors float, N keys = N queries: the full-precision path, fp32 products and sums, which uses
- * 4 B H N bytes of the workspace for D and, where the rest of it (up to 1 GiB) takes dS of some or all
- * heads, leaves dS there between its two sides).
- * workspace: device scratch of at least fb_lowrank_attn_bwd_workspace_bytes(...) bytes (FB_F32: the
- * size with room for dS; what the formula below gives is accepted and computes S and dP once more instead),
+ * 4 B H N bytes of the workspace for D).
+ * workspace: device scratch of at least fb_lowrank_attn_bwd_workspace_bytes(...) bytes,
  * 16-byte aligned, owned by the caller; its contents on entry are ignored and it may be
  * reused as soon as the call's work on `stream` has finished.  It receives, per (b, h, i):
  * (lse * log2 e, D_i = sum_c dout * out) and the concatenated bf16 operand rows
  * [q*scale | phi_q | 0] and [k | phi_k | 0] that the two main kernels stream
  * (8 + 4 * (C + 64) bytes per row when R > 0, 8 + 4 * C otherwise; C = 16 counts as 32 and
- * adds 32-channel copies of v and dout, 128 more bytes per row).
+ * adds 32-channel copies of v and dout, 128 more bytes per row).  For FB_F32 at C >= 32 and FB_BF16 at C = 128 the
+ * query adds up to 1 GiB, in which the key side leaves dS (4 or 2 bytes a pair) of some or all heads for the query side;
+ * a workspace with less of that, down to the formula's size, is accepted, and dS is computed twice instead (FB_BF16: with
+ * the same result to the bit).
  * Results are deterministic (no floating-point atomics).
  */
 size_t fb_lowrank_attn_bwd_workspace_bytes(int B, int H, int N, int C, int R, fb_dtype dtype);
@@ -251,11 +252,12 @@ int fb_lowrank_attn_bwd(const void* q, const void* k, const void* v,
 /*
  * Allocation-free variant of fb_lowrank_attn_bwd, for callers that cannot allocate device
  * memory or carry a workspace: code under HIP graph capture, tight serving / training loops,
- * harnesses that forbid hipMalloc.  Same arguments without the workspace, same kernels, same
- * (bit-identical) results; the scratch that fb_lowrank_attn_bwd takes from the caller lives in
- * a static device array of FB_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held
- * from library load until the process ends.  The call allocates and frees nothing.
- *   Limit: fb_lowrank_attn_bwd_workspace_bytes(B, H, N, C, R, FB_BF16) <= FB_STATIC_SCRATCH_BYTES
+ * harnesses that forbid hipMalloc.  Same arguments without the workspace, same kernels and
+ * (bit-identical) results as with a workspace of FB_STATIC_SCRATCH_BYTES; the scratch that
+ * fb_lowrank_attn_bwd takes from the caller lives in a static device array of that size inside
+ * the library, one copy per GPU, held from library load until the process ends.  The call
+ * allocates and frees nothing.
+ *   Limit: the workspace formula above (without the room for dS) <= FB_STATIC_SCRATCH_BYTES
  *   (e.g. B H N <= 86480 rows at C = 128 with factors); larger problems return
  *   FB_ERR_TOO_LARGE and launch nothing.
  *   Every call on a GPU uses that GPU's one array: calls that overlap on the same GPU (two

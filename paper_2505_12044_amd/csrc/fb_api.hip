@@ -321,12 +321,16 @@ int fb_lowrank_mulbias_attn_fwd(const void* q, const void* k, const void* v,
     return rc == 0 ? FB_OK : (rc < 0 ? FB_ERR_UNSUPPORTED : FB_ERR_LAUNCH);
 }
 
+// q', k' (C R bf16 channels each), their gradients (float) and the additive backward's own scratch: what the call checks
+static size_t mulbias_bwd_least(int B, int H, int N, int C, int R) {
+    const long long rows = (long long)B * H * N;
+    return (size_t)2 * rows * C * R * (2 + 4) + fb_bwd_workspace_bytes(rows, rows, C, C * (R - 1));
+}
+
 size_t fb_lowrank_mulbias_attn_bwd_workspace_bytes(int B, int H, int N, int C, int R, fb_dtype dtype) {
     (void)dtype;
     if (B <= 0 || H <= 0 || N <= 0 || C <= 0 || R <= 0) return 0;
-    const long long rows = (long long)B * H * N;
-    // q', k' (C R bf16 channels each), their gradients (float) and the additive backward's own scratch
-    return (size_t)2 * rows * C * R * (2 + 4) + fb_bwd_workspace_bytes(rows, rows, C, C * (R - 1));
+    return mulbias_bwd_least(B, H, N, C, R) + fb_bwd_stored_bytes((long long)B * H, N, N, C);
 }
 
 int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
@@ -349,7 +353,7 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
     for (const void* ptr : ptrs) if (!aligned16(ptr)) return FB_ERR_ALIGN;
     const void* p4[] = {phi_q, phi_k, dphi_q, dphi_k};
     for (const void* ptr : p4) if ((reinterpret_cast<uintptr_t>(ptr) & 3u) != 0) return FB_ERR_ALIGN;
-    if (!workspace || workspace_bytes < fb_lowrank_mulbias_attn_bwd_workspace_bytes(B, H, N, C, R, dtype))
+    if (!workspace || workspace_bytes < mulbias_bwd_least(B, H, N, C, R))
         return FB_ERR_WORKSPACE;
     if (!aligned16(workspace)) return FB_ERR_ALIGN;
 
@@ -377,6 +381,7 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
     p.out = out; p.lse = lse; p.dout = dout;
     p.dq = dqh; p.dk = dkh; p.dv = dv; p.dphi_q = rest ? dqr : nullptr; p.dphi_k = rest ? dkr : nullptr;
     p.workspace = inner;
+    p.workspace_bytes = workspace_bytes - (size_t)((unsigned char*)inner - ws);
     p.B = B; p.H = H; p.N = N; p.M = N; p.R = rest; p.Cg = C; p.causal = causal != 0;
     p.phi_f32 = 0;
     p.grad_f32 = 1;
@@ -397,12 +402,14 @@ static size_t bwd_ws_impl(int B, int H, int N, int M, int C, int R) {
     return fb_bwd_workspace_bytes((long long)B * H * N, (long long)B * H * M, C, R);
 }
 
-// What the size queries return: the least a call needs (bwd_ws_impl, what the calls check), for fp32 with the room that
-// saves the query side its recomputation.
+// What the size queries return: the least a call needs (bwd_ws_impl, what the calls check) with the room that lets one
+// side of the backward take dS from the other.
 static size_t bwd_ws_query(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
     const size_t least = bwd_ws_impl(B, H, N, M, C, R);
-    if (dtype != FB_F32 || least == 0) return least;
-    const size_t f32 = fb_bwd_f32_workspace_bytes((long long)B * H, N, M, C);
+    if (least == 0) return 0;
+    const long long BH = (long long)B * H;
+    if (dtype != FB_F32) return least + fb_bwd_stored_bytes(BH, N, M, C);
+    const size_t f32 = fb_bwd_f32_workspace_bytes(BH, N, M, C);
     return f32 > least ? f32 : least;
 }
 
@@ -448,8 +455,7 @@ static int lowrank_bwd_impl(const void* q, const void* k, const void* v,
 }
 
 size_t fb_alibi_attn_bwd_workspace_bytes(int B, int H, int N, int C, fb_dtype dtype) {
-    (void)dtype;
-    return bwd_ws_impl(B, H, N, N, C, 2);
+    return bwd_ws_query(B, H, N, N, C, 2, dtype);
 }
 
 int fb_alibi_attn_bwd(const void* q, const void* k, const void* v, const float* slopes,
@@ -474,6 +480,7 @@ int fb_alibi_attn_bwd(const void* q, const void* k, const void* v, const float* 
     p.dq = dq; p.dk = dk; p.dv = dv; p.dphi_q = nullptr; p.dphi_k = nullptr;
     p.dslope = dslope_rows;
     p.workspace = workspace;
+    p.workspace_bytes = workspace_bytes;
     p.B = B; p.H = H; p.N = N; p.M = N; p.R = 2; p.Cg = C; p.causal = causal != 0;
     p.phi_f32 = 1;
     p.phi_bstride = 0;

@@ -9,6 +9,7 @@
 // gradient is ever written.  No atomics; results are deterministic.
 //
 // Kernels:
+//   rows  : where dS is stored (below): -lse * log2 e, -D and the scaled q rows, ahead of the other two
 //   pre   : writes the factor columns of the operands Aq = [q*scale | phi_q | 0], Ak = [k | phi_k | 0]
 //           into the workspace (bf16, 32 to 128 columns; fp32 factors as three bf16 limbs, six product columns
 //           per rank as in the forward), once per head where the factors are shared over the batch; the
@@ -16,7 +17,8 @@
 //   main<DKV = false> : a lane owns a query; streams 32-key blocks;   accumulates dAq^T; runs first and
 //                       leaves -lse * log2 e and -D per query row, and q*scale where it is a rounding, for the other
 //   main<DKV = true>  : a lane owns a key;   streams 32-query blocks; accumulates dV^T, dAk^T
-// Both main kernels recompute S and dP (7 contractions instead of 5, but no atomic dQ).  They
+// Both main kernels recompute S and dP (7 contractions instead of 5, but no atomic dQ), except at C = 128 where the
+// workspace has room: there dkv runs first and leaves dS, and dq is its output contraction alone.  They
 // use the transposed orientation of the forward: the lane-side operands stay in registers,
 // score-shaped accumulators feed the next MFMA as its B operand without leaving registers,
 // and the transposed A operands come from the LDS transpose read.
@@ -75,6 +77,11 @@ FB_DEV void wait_vmcnt_n(int n) {   // n is wave-uniform; larger values wait for
 // lane l reads sbase + voff (bytes); its 16 bytes land at LDS byte address lds_addr + 16 * l
 FB_DEV void dma16(const void* sbase, unsigned voff, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
+}
+// the same for bytes that are read once: they leave the caches to the operand tiles
+FB_DEV void dma16nt(const void* sbase, unsigned voff, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                  :: "v"(voff), "s"(sbase), "s"(lds_addr) : "memory", "m0");
 }
 
@@ -242,6 +249,46 @@ __global__ __launch_bounds__(256) void bwd_widen16_kernel(BwdParams p, Widen16 w
     *(u32x4*)(dst + row * 32 + c * 8) = x;
 }
 
+// Stored dS: what the dq kernel's prologue leaves where it runs first, -lse log2 e and -D of every query row and, where
+// the scale has to be rounded into q, the scaled rows.  Two threads a row, each summing as a lane of that prologue does:
+// the two forms of the backward agree to the bit.  Bound by its reads.
+template <int C>
+__global__ __launch_bounds__(256) void bwd_rows_kernel(BwdParams p, float* __restrict__ vec, bf16_t* __restrict__ q_out, float q_mul, long long rows) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x, row = i >> 1;
+    const int hf = (int)(i & 1);
+    if (row >= rows) return;                 // both threads of a row leave together
+    const size_t off = (size_t)row * C + 8 * hf;
+    u32x4 o[C / 16], d[C / 16];
+#pragma unroll
+    for (int cs = 0; cs < C / 16; cs++) {
+        o[cs] = *(const u32x4*)((const bf16_t*)p.out + off + cs * 16);
+        d[cs] = *(const u32x4*)((const bf16_t*)p.dout + off + cs * 16);
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int cs = 0; cs < C / 16; cs++) {
+        const bf16x8 o8 = as_bf16x8(o[cs]), d8 = as_bf16x8(d[cs]);
+#pragma unroll
+        for (int e = 0; e < 8; e++) sum = fmaf((float)o8[e], (float)d8[e], sum);
+    }
+    sum += __shfl_xor(sum, 1);
+    if (q_out != nullptr) {
+#pragma unroll
+        for (int cs = 0; cs < C / 16; cs++) {
+            bf16x8 q = as_bf16x8(*(const u32x4*)((const bf16_t*)p.q + off + cs * 16));
+#pragma unroll
+            for (int e = 0; e < 8; e++) q[e] = (bf16_t)((float)q[e] * q_mul);
+            *(u32x4*)(q_out + off + cs * 16) = as_uint4(q);
+        }
+    }
+    if (hf == 0) {
+        const unsigned head = (unsigned)((unsigned long long)row / (unsigned)p.N), pos = (unsigned)(row - (long long)head * p.N);
+        float* v = vec + (size_t)head * 2 * p.N + pos;
+        v[0] = -(p.lse[row] * kLog2e);
+        v[p.N] = -sum;
+    }
+}
+
 // Write one wave's factor-gradient columns to LDS scratch and reduce limb columns.
 // acc[mb] holds columns mb*32 + 8*g + 4*hf + x (register 4*g + x) for row l32.
 // raw: the R columns are written as float without any limb summing (gradients of bf16 columns
@@ -307,25 +354,42 @@ struct MainArgs {
     bf16_t* q_out;        // not NULL: the dq kernel forms its operand rows as bf16(q q_mul) and leaves them here (= aq.main)
     float q_mul;
     float dkv_mul;        // factor of d[K | phi_k] (the scale, where the q columns carry none; 1 / log2 e for FOLD)
+    bf16_t* ds;           // stored dS of the heads head0.. in 32 x 32 tiles (see store_ds)
+    unsigned ds_pitch;    // queries and keys of a head, padded to whole tiles of the two kernels
+    unsigned ds_rows;
+    int head0;
 };
+
+// What a main kernel does about dS.  RECOMPUTE: each forms S, P, dP and dS itself.  STORE (dkv) leaves dS in the
+// workspace, LOAD (dq) takes it from there and is left with its output contraction alone.
+enum { RECOMPUTE = 0, STORE = 1, LOAD = 2 };
+
+constexpr int kWavesLd = 4;       // of the dq kernel that takes dS from the workspace
+template <int C, int RP, bool LIMB, int CG>
+constexpr int kSlotBytesLd = Cfg<C, RP, LIMB, CG>::T1_BYTES + kWavesLd * 32 * 32 * 2;
+template <int C, int RP, bool LIMB, int CG>
+constexpr int kSlotsLd = 80 * 1024 / kSlotBytesLd<C, RP, LIMB, CG>;      // two workgroups a CU
 
 // DENSE (RP = 0 only): the bias is a dense [N][M] matrix instead of factors.  Every wave also
 // copies the 32 x 32 bias tile of (its lane rows) x (the streamed block) into the slot, two
 // direct loads per block; the S chain starts from those values; the dq kernel writes
 // dS = dBias from its packed operand registers.
-template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG>
+template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG, int MODE>
 FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem, const int bh, const int tile) {
     static_assert(!DENSE || RP == 0, "dense bias and factors are exclusive");
+    constexpr bool ST = MODE == STORE, LD = MODE == LOAD;
+    constexpr int WV = LD ? kWavesLd : kWaves, kRows = WV * 32;      // waves and lane-side rows of the workgroup
+    static_assert((!ST || DKV) && (!LD || !DKV) && (MODE == RECOMPUTE || (!DENSE && CG == C)), "stored dS");
     using K = Cfg<C, RP, LIMB, CG>;
     using TC = typename K::TC;
     using TP = typename K::TP;
     using T2 = typename K::T2;
     constexpr int kBiasTile = 32 * 32 * 2;     // one wave's tile: 32 rows of 64 bytes
-    constexpr int kOffT2 = K::T1_BYTES, kOffVec = K::T1_BYTES + T2::BYTES;
-    constexpr int kOffBias = kOffVec + (DKV ? K::kVecBytes : 0);
-    constexpr int kSlotBytes = kOffBias + (DENSE ? kWaves * kBiasTile : 0);
-    constexpr int ND = K::T1_NDMA + T2::NDMA + (DKV ? 1 : 0);       // direct loads per block
-    constexpr int NDW = (ND + kWaves - 1) / kWaves;               // ... per wave, at most
+    constexpr int kOffT2 = K::T1_BYTES, kOffVec = K::T1_BYTES + (LD ? 0 : T2::BYTES);
+    constexpr int kOffBias = kOffVec + (DKV ? K::kVecBytes : 0);      // this wave's 32 x 32 tile of the dense bias, or of dS (LD)
+    constexpr int kSlotBytes = kOffBias + (DENSE || LD ? WV * kBiasTile : 0);
+    constexpr int ND = K::T1_NDMA + (LD ? 0 : T2::NDMA) + (DKV ? 1 : 0);       // direct loads per block
+    constexpr int NDW = (ND + WV - 1) / WV;               // ... per wave, at most
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
     // NL rows on the lane side (keys when DKV, else queries), NS rows on the streamed side
@@ -333,7 +397,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
-    const int r0 = tile * 128;            // first lane-side row of the workgroup
+    const int r0 = tile * kRows;          // first lane-side row of the workgroup
     const int rw0 = r0 + wave * 32;       // ... of this wave
     const int ri = rw0 + l32;             // this lane's row
     const int rc = min(ri, NL - 1);       // rows past the end compute on the last row and are not stored
@@ -342,7 +406,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     const OperandRows& L1 = DKV ? a.ak : a.aq;                                      // lane-side operand of S
     const OperandRows& S1 = DKV ? a.aq : a.ak;                                      // streamed operand of S
     const int b_ = bh / p.H, h_ = bh - b_ * p.H;
-    const bool q_scaled_here = !DKV && a.q_out != nullptr;                          // wave-uniform
+    const bool q_scaled_here = !DKV && !LD && a.q_out != nullptr;                          // wave-uniform
     const bf16_t* l1m = (q_scaled_here ? (const bf16_t*)p.q : L1.main) + lbase * C;
     const bf16_t* l1p = L1.phi + (size_t)(L1.shared ? h_ : bh) * NL * K::RP2;
     const bf16_t* l2g = (const bf16_t*)(DKV ? p.v : p.dout) + lbase * C;            // lane-side operand of dP
@@ -355,7 +419,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     // ---- lane-side operands, loop invariant ----
     bf16x8 l1reg[K::KS], l2reg[K::CS];
 #pragma unroll
-    for (int ks = 0; ks < K::KS; ks++)
+    for (int ks = 0; ks < (LD ? 0 : K::KS); ks++)
         l1reg[ks] = as_bf16x8(*(const u32x4*)(ks * 16 < CG ? l1m + (size_t)rc * C + ks * 16 + 8 * hf
                                                            : l1p + (size_t)rc * K::RP2 + (ks * 16 - CG) + 8 * hf));
     if (CG == C && q_scaled_here) {
@@ -368,7 +432,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         }
     }
 #pragma unroll
-    for (int cs = 0; cs < K::CS; cs++)
+    for (int cs = 0; cs < (LD ? 0 : K::CS); cs++)
         l2reg[cs] = as_bf16x8(*(const u32x4*)(l2g + (size_t)rc * C + cs * 16 + 8 * hf));
     float my_nl = 0.f, my_nd = 0.f;     // dq kernel: -lse2 and -D of this lane's row (formed below, behind the first block loads)
 
@@ -387,7 +451,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     int b_begin = 0, b_end = nblk_all;
     if (CAUSAL) {
         if (DKV) b_begin = r0 / BT;                            // queries before the first key see nothing
-        else b_end = min(nblk_all, (min(NS, r0 + 128) + BT - 1) / BT);
+        else b_end = min(nblk_all, (min(NS, r0 + kRows) + BT - 1) / BT);
     }
     const int nIt = b_end - b_begin;
     auto blk_of = [&](int i) __attribute__((always_inline)) { return min(b_begin + i, nblk_all - 1); };
@@ -407,7 +471,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     int dma_blk = blk_of(0);                                 // block the running pointers stand at
 #pragma unroll
     for (int j = 0; j < NDW; j++) {
-        const int d = min(wave + kWaves * j, ND - 1);
+        const int d = min(wave + WV * j, ND - 1);
         const unsigned char* dma_src_j;
         int dma_pitch_j, dma_lshift_j;
         int row = 0, chunk = 0, dst = 0;
@@ -486,20 +550,33 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         bias_lshift = DKV ? 0 : 3;
         bias_bstep = DKV ? (size_t)BT * Mk * 2 : (size_t)BT * 2;
     }
+    if (LD) {
+        // tile (streamed block, this wave's queries), see store_ds; rows of the LDS tile = keys
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const int trow = 16 * i + (lane >> 2), c = (lane & 3) ^ ((trow >> 2) & 3);
+            bias_var[i] = 0;
+            bias_fix[i] = (unsigned)((c >> 1) * 1024 + trow * 32 + (c & 1) * 16);
+        }
+        bias_src = (const unsigned char*)(a.ds + (size_t)(bh - a.head0) * a.ds_rows * a.ds_pitch + (size_t)rw0 * 32);
+        bias_bstep = (size_t)BT * a.ds_pitch * 2;
+    }
     auto issue_bias = [&](int i, int slot) __attribute__((always_inline)) {
-        if (!DENSE) return;
+        if (!DENSE && !LD) return;
         const int blk = blk_of(i);
         const int left = NS - blk * BT - 1;
         const unsigned dst = lds0 + slot * kSlotBytes + kOffBias + wave * kBiasTile;
 #pragma unroll
         for (int x = 0; x < 2; x++) {
-            const unsigned voff = (unsigned)(min(bias_var[x], left >> bias_lshift) * bias_pitch) + bias_fix[x];
-            dma16(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
+            const unsigned voff = (unsigned)((LD ? bias_var[x] : min(bias_var[x], left >> bias_lshift)) * bias_pitch) + bias_fix[x];
+            if (LD) dma16nt(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
+            else dma16(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
         }
     };
     // all but the newest block's loads (plus `stores` global stores issued since) may remain
     auto wait_prev_loads = [&](int stores) __attribute__((always_inline)) {
-        constexpr int NLD = NDW + (DENSE ? 2 : 0);
+        // (ST: behind them also the two stores of each of the last two blocks, which every wave issues)
+        constexpr int NLD = NDW + (DENSE || LD ? 2 : 0) + (ST ? 4 : 0);
         if (stores == 0) wait_vmcnt<NLD>();
         else wait_vmcnt_n(NLD + stores);
     };
@@ -621,6 +698,26 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         }
         if (n < NA + NO1) return tr_read1(tb, (n - NA) >> 1, (n - NA) & 1);
         return tr_read(tb, kOffT2, T2::NP64, (n - NA - NO1) >> 1, (n - NA - NO1) & 1);
+    };
+
+    // Stored dS: 32 x 32 tiles of 2 KB, [key tile][query tile], so that a wave's store and load of one is contiguous (rows
+    // of a whole matrix, 64 bytes a wave and block at a stride of N: B 2, H 8, N 16384 training 14.8 ms).  In a tile, piece
+    // (gp, key, hf) of 16 bytes holds the queries 16 gp + 8 hf + 0..7 of a key: a lane's packed registers after one
+    // exchange across the halves per register pair.  Keys past the last are zero.
+    bf16_t* const ds_row = ST ? a.ds + (size_t)(bh - a.head0) * a.ds_rows * a.ds_pitch + (size_t)(rw0 >> 5) * 32 * a.ds_pitch + l32 * 16 + 8 * hf : nullptr;
+    auto store_ds = [&](const bf16x8 (&dsb)[2], int sb0) __attribute__((always_inline)) {
+        if (!ST) return;
+#pragma unroll
+        for (int gp = 0; gp < 2; gp++) {
+            u32x4 w = as_uint4(dsb[gp]);
+            const auto r0 = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
+            const auto r1 = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
+            w = u32x4{(unsigned)r0[0], (unsigned)r1[0], (unsigned)r0[1], (unsigned)r1[1]};
+            if (rw0 + 31 >= NL && ri >= NL) w = u32x4{0u, 0u, 0u, 0u};
+            // read once, by the next launch: past the caches, which the streamed operands need (B 2, H 8, N 16384 training
+            // 9256 -> 8984 us, B 4, H 16, N 4096 causal 1374 -> 1302 us with the loads marked alike)
+            __builtin_nontemporal_store(w, (u32x4*)(ds_row + (size_t)sb0 * 32 + 512 * gp));
+        }
     };
 
     using Yes = std::true_type;
@@ -791,6 +888,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                     acc1[(m - NO2) >> 1] = mfma32(opr[n % (LA + 1)], dsb[(m - NO2) & 1], acc1[(m - NO2) >> 1]);
                 }
             }
+            store_ds(dsb, sb0);
 #pragma unroll
             for (int n = 0; n < LA; n++) opr[n] = nxt[n];
             read_vec(sl1 * kSlotBytes);
@@ -810,6 +908,55 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             body(i, sA, dA, sB, dB);
             sA = sB;
             dA = dB;
+        }
+    } else if constexpr (LD) {
+        // dS comes from the workspace, 2 KB a wave and block beside the shared operand tile.  Bound by that read, 4.2 TB/s
+        // where the dS of a launch is far larger than the last-level cache (C = 128, R 8: 10 matrix instructions a block
+        // where the recomputing form has 27; B 2, H 8, N 16384 3110 -> 2040 us).  Eight waves with a ring of 160 KB: 315 us
+        // a launch of 2 heads against 254, half the workgroups.
+        constexpr int NS_ = kSlotsLd<C, RP, LIMB, CG>;
+#pragma unroll
+        for (int j = 0; j < NS_ - 1; j++) { issue_block(j, j); issue_bias(j, j); }
+        wait_vmcnt<0>();
+        __syncthreads();
+        auto read_d = [&](int slot_off, int kk) __attribute__((always_inline)) {
+            const unsigned char* t = smem + (slot_off + kOffBias + wave * kBiasTile + kk * 1024);
+            return join_tr(lds_read_tr16((const bf16_t*)(t + tr32[0])), lds_read_tr16((const bf16_t*)(t + tr32[1])));
+        };
+        constexpr int LB = NO1 < 4 ? NO1 : 4;       // operands read ahead
+        bf16x8 opd[LB + 1], dcur[2];
+        {
+            const TrBase t0 = mk_tr(0);
+#pragma unroll
+            for (int n = 0; n < LB; n++) opd[n] = tr_read1(t0, n >> 1, n & 1);
+#pragma unroll
+            for (int kk = 0; kk < 2; kk++) dcur[kk] = read_d(0, kk);
+        }
+        // causal: the dkv launch visits whole 128-row tiles; the blocks of a wave past its own are not there
+        const int b_own = CAUSAL ? min(b_end, (rw0 / 128 + 1) * 4) : b_end;
+        int sl = 0;
+        for (int i = 0; i < nIt; i++) {
+            const int sln = sl + 1 == NS_ ? 0 : sl + 1, slp = sl == 0 ? NS_ - 1 : sl - 1;
+            const int off = sl * kSlotBytes, offn = sln * kSlotBytes;
+            const TrBase tb0 = mk_tr(off), tbn = mk_tr(offn);
+            wait_vmcnt<(NDW + 2) * (NS_ - 3)>();       // block i + 1 has landed; everyone has left block i - 1
+            __syncthreads();
+            issue_block(i + NS_ - 1, slp);
+            issue_bias(i + NS_ - 1, slp);
+            bf16x8 nxt[LB], dn[2];
+            const bool own = !CAUSAL || i < b_own;      // wave-uniform
+#pragma unroll
+            for (int n = 0; n < NO1; n++) {
+                if (n + LB < NO1) opd[(n + LB) % (LB + 1)] = tr_read1(tb0, (n + LB) >> 1, (n + LB) & 1);
+                else nxt[n + LB - NO1] = tr_read1(tbn, (n + LB - NO1) >> 1, (n + LB - NO1) & 1);
+                if (n >= NO1 - 2) dn[n - (NO1 - 2)] = read_d(offn, n - (NO1 - 2));
+                if (own) acc1[n >> 1] = mfma32(opd[n % (LB + 1)], dcur[n & 1], acc1[n >> 1]);
+            }
+#pragma unroll
+            for (int n = 0; n < LB; n++) opd[n] = nxt[n];
+#pragma unroll
+            for (int kk = 0; kk < 2; kk++) dcur[kk] = dn[kk];
+            sl = sln;
         }
     } else {
         // Two or three waves per SIMD: another workgroup's wave fills the gaps.  Iteration i:
@@ -915,6 +1062,8 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             __syncthreads();
             issue_block(i + 3, (i + 3) & (NSLOT - 1));
             issue_bias(i + 3, (i + 3) & (NSLOT - 1));
+
+            store_ds(dsb, sb0);
 
             // ---------------- dBias = dS ----------------
             // The packed operand registers of a lane hold keys 8g + 4 hf + 0..3 of its row: one exchange across the halves
@@ -1035,25 +1184,62 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 
 // Work units: one 128-row tile per workgroup, or when causal the tile pair (n-1-u, u), whose
 // streamed ranges add up to the same length for every u (no tail of heavy tiles).
-template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG>
-__global__ __launch_bounds__(kThreads, (DKV ? Cfg<C, RP>::PIPE : (DENSE || C + RP > 160)) ? 1 : 2) void bwd_main_kernel(BwdParams p, MainArgs a) {
+template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG, int MODE = RECOMPUTE>
+__global__ __launch_bounds__(MODE == LOAD ? kWavesLd * 64 : kThreads, (DKV ? Cfg<C, RP>::PIPE : (MODE == RECOMPUTE && (DENSE || C + RP > 160))) ? 1 : 2) void bwd_main_kernel(BwdParams p, MainArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);
     if (L >= p.total_tiles) return;
     const int n_units = CAUSAL ? (p.n_tiles + 1) / 2 : p.n_tiles;   // p.n_tiles: 128-row tiles of the lane side
-    const int bh = L / n_units;
-    const int u = L - bh * n_units;
+    const int bhl = L / n_units, bh = a.head0 + bhl;
+    const int u = L - bhl * n_units;
     if (CAUSAL) {
         const int other = p.n_tiles - 1 - u;
         // heavier tile first: high query tiles for dq, low key tiles for dkv
-        bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG>(p, a, smem, bh, DKV ? u : other);
+        bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG, MODE>(p, a, smem, bh, DKV ? u : other);
         if (u != other) {
             __syncthreads();   // the epilogue's LDS scratch is reused as ring memory
-            bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG>(p, a, smem, bh, DKV ? other : u);
+            bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG, MODE>(p, a, smem, bh, DKV ? other : u);
         }
     } else {
-        bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG>(p, a, smem, bh, u);
+        bwd_tile<C, RP, CAUSAL, DKV, DENSE, LIMB, CG, MODE>(p, a, smem, bh, u);
     }
+}
+
+// Instantiations with a stored dS: where the dq kernel's recomputation takes clearly longer than 4 KB a 32 x 32 block to
+// memory and back.  Training, start / stored (us), C = 128: B 2, H 8, N 16384 9590 / 8984; B 4, H 16, N 4096 causal 1377 /
+// 1302; B 4, H 8, N 4096 1296 / 1194; B 1, H 2, N 8192 606 / 510; B 8, H 8, N 2048 696 / 661.  C = 64: B 8, H 12, N 1024,
+// R 32 204 / 209; B 8, H 8, N 2048, R 16 413 / 418; two columns of 64 (multiplicative) 2060 / 2065: left.
+template <int C, int RP, bool DENSE, int CG>
+constexpr bool kStored = C == 128 && !DENSE;
+// What is saved grows with the pairs, what the extra launch and the pass over the query rows cost with the call and the rows
+// (start / stored, us, C = 128, R 8): 512 heads of N 256 181 / 188, 128 of 512 159 / 164, 32 of 1024 158 / 161 (8.4 M by this
+// measure); 64 of 1024 202 / 196 (16.8 M), 256 of 1000 770 / 752, 8 of 2048 172 / 151 (21 M), 2 of 4096 313 / 266, causal 15
+// of 3000 288 / 261.
+bool stored_pays(long long heads, int N, int M, bool causal) {
+    return (double)heads * N * ((causal ? 0.5 : 1.0) * M - 768.0) >= (double)(1 << 24);
+}
+constexpr size_t kMaxStored = (size_t)1 << 30;      // at a time
+size_t ds_head_bytes(int N, int M) { return (size_t)((N + 127) / 128 * 128) * ((M + 127) / 128 * 128) * 2; }
+// Heads per launch whose dS fits `room` bytes, 0: recompute.
+int stored_heads(int heads, int N, int M, bool causal, bool one_wave, size_t room) {
+    const size_t per = ds_head_bytes(N, M);
+    if (room > kMaxStored) room = kMaxStored;
+    const long long fit = (long long)(room / per);
+    if (fit <= 0) return 0;
+    if (!stored_pays(heads, N, M, causal)) return 0;
+    if (fit >= heads) return heads;
+    // the dkv launches' rounds of workgroups (one or two a CU): per head, against those of one launch over all heads
+    const int tiles = (M + 127) / 128;
+    const long long units = causal ? (tiles + 1) / 2 : tiles, slots = one_wave ? 256 : 512;
+    auto rounds = [&](long long h) { return (double)((h * units + slots - 1) / slots); };
+    long long best = 0;
+    double cost = 1.1 * rounds(heads);
+    for (long long c = fit; c >= 1 && c * 4 >= fit; c--) {
+        const long long whole = heads / c, rest = heads - whole * c;
+        const double t = whole * rounds(c) + (rest > 0 ? rounds(rest) : 0.0);
+        if (t < cost) { best = c; cost = t; }
+    }
+    return (int)best;
 }
 
 // Pre-pass and the two main kernels.  DENSE: the bias is a dense matrix streamed tile by tile
@@ -1132,17 +1318,50 @@ int launch(const BwdParams& pin, hipStream_t stream) {
     }
     if (hipGetLastError() != hipSuccess) return 1;
 
-    auto set_tiles = [](BwdParams& p, int lane_rows) {
-        p.n_tiles = (lane_rows + 127) / 128;
+    const int all_heads = p.B * p.H;
+    auto set_tiles = [](BwdParams& p, int lane_rows, int heads, int tile_rows = 128) {
+        p.n_tiles = (lane_rows + tile_rows - 1) / tile_rows;
         const int n_units = CAUSAL ? (p.n_tiles + 1) / 2 : p.n_tiles;
-        p.total_tiles = p.B * p.H * n_units;
+        p.total_tiles = heads * n_units;
         p.tiles_per_xcd = (p.total_tiles + 7) / 8;
     };
+    a.ds = nullptr;
+    a.ds_pitch = a.ds_rows = 0;
+    a.head0 = 0;
+    if constexpr (kStored<C, RP, DENSE, CG>) {
+        // dkv first, chunk by chunk of heads, leaving dS for dq
+        const size_t least = (fb_bwd_workspace_bytes(rows, rowsk, CG, pin.R) + 255) & ~(size_t)255;
+        const size_t room = pin.workspace_bytes > least ? pin.workspace_bytes - least : 0;
+        const int chunk = stored_heads(all_heads, pin.N, pin.M, CAUSAL, K::PIPE, room);
+        if (chunk > 0) {
+            constexpr size_t lds_load = (size_t)kSlotsLd<C, RP, LIMB, CG> * kSlotBytesLd<C, RP, LIMB, CG>;
+            static_assert(kSlotsLd<C, RP, LIMB, CG> >= 4 && lds_load >= K::kEpiLds, "ring and epilogue");
+            auto kst = bwd_main_kernel<C, RP, CAUSAL, true, DENSE, LIMB, CG, STORE>;
+            auto kld = bwd_main_kernel<C, RP, CAUSAL, false, DENSE, LIMB, CG, LOAD>;
+            static FbLdsOnce once_st, once_ld;
+            if (!fb_raise_lds_limit((const void*)kst, lds_dkv, once_st) || !fb_raise_lds_limit((const void*)kld, lds_load, once_ld)) return 1;
+            a.ds = (bf16_t*)(ws + least);
+            a.ds_pitch = (unsigned)((p.N + 127) / 128 * 128);
+            a.ds_rows = (unsigned)((p.M + 127) / 128 * 128);
+            hipLaunchKernelGGL((bwd_rows_kernel<C>), dim3((unsigned)((rows * 2 + 255) / 256)), dim3(256), 0, stream, pin, a.vec, a.q_out,
+                               a.q_mul, rows);
+            a.q_out = nullptr;
+            for (a.head0 = 0; a.head0 < all_heads; a.head0 += chunk) {
+                const int n = all_heads - a.head0 < chunk ? all_heads - a.head0 : chunk;
+                set_tiles(p, p.M, n);
+                hipLaunchKernelGGL(kst, dim3(8 * p.tiles_per_xcd), dim3(kThreads), lds_dkv, stream, p, a);
+                set_tiles(p, p.N, n, kWavesLd * 32);
+                hipLaunchKernelGGL(kld, dim3(8 * p.tiles_per_xcd), dim3(kWavesLd * 64), lds_load, stream, p, a);
+                if (hipGetLastError() != hipSuccess) return 1;
+            }
+            return 0;
+        }
+    }
     // dq first: it also leaves (lse log2 e, D) of every query row for the dkv kernel
-    set_tiles(p, p.N);
+    set_tiles(p, p.N, all_heads);
     hipLaunchKernelGGL(kdq, dim3(8 * p.tiles_per_xcd), dim3(kThreads), lds_dq, stream, p, a);
     if (hipGetLastError() != hipSuccess) return 1;
-    set_tiles(p, p.M);
+    set_tiles(p, p.M, all_heads);
     hipLaunchKernelGGL(kdkv, dim3(8 * p.tiles_per_xcd), dim3(kThreads), lds_dkv, stream, p, a);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
@@ -1188,6 +1407,13 @@ size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R) 
     // Head dimension 16 runs on 32-channel operand rows and adds widened copies of v and dO.
     const int w = (C == 16 ? 32 : C) + (R > 64 ? 128 : (R > 0 ? 64 : 0)) + (C == 16 ? 32 : 0);
     return (((size_t)rows_q * 8 + 15) & ~(size_t)15) + (size_t)(rows_q + rows_k) * w * 2;
+}
+
+size_t fb_bwd_stored_bytes(long long heads, int N, int M, int C) {
+    const size_t per = ds_head_bytes(N, M);
+    if (C != 128 || per > kMaxStored || !stored_pays(heads, N, M, false)) return 0;
+    const size_t fit = kMaxStored / per;
+    return 256 + ((size_t)heads < fit ? (size_t)heads : fit) * per;
 }
 
 int fb_launch_bwd_dense_bf16(const BwdParams& p, int C, hipStream_t stream) {

@@ -43,7 +43,7 @@ struct BwdParams {
     void* dbias;          // [B,H,N,M]
     long long bias_bstride;  // elements between batch items of bias (0 when shared)
     void* workspace;      // device scratch: -lse2 and -D of every query row, and the operand columns that are not read in place
-    size_t workspace_bytes;  // its size (fp32: what it holds beyond D takes dS)
+    size_t workspace_bytes;  // its size (what it holds beyond the rest takes dS)
     int B, H, N, R;       // N = number of queries
     int M;                // number of keys (= N except for cross-attention)
     int Cg;               // channels per head in caller memory (16 runs on the C = 32 kernels), else C

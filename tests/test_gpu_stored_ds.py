@@ -1,0 +1,91 @@
+"""The bf16 backward at 128 channels that stores dS between its two main kernels: every factor form, causal, separate key
+lengths, partial tiles, trained slopes, one launch over all heads and several over parts of them.  It agrees to the bit
+with the recomputing form (the workspace without room for dS), and with the float64 oracle at the bounds of the other tests."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fb_oracle as O
+from paper_2505_12044_amd import api, workloads as W
+from tests._gpu_util import check_grad, dev, host
+
+pytestmark = pytest.mark.gpu
+C = 128
+
+
+def _inputs(B, H, N, M, R, phi, shared):
+    rng = np.random.default_rng(N * 13 + M + R)
+    rd = lambda *s: W.round_bf16(rng.standard_normal(s).astype(np.float32))
+    q, k, v, dout = rd(B, H, N, C), rd(B, H, M, C), rd(B, H, M, C), rd(B, H, N, C)
+    Bp, sc = 1 if shared else B, max(R, 1) ** -0.25
+    pq = (sc * rng.standard_normal((Bp, H, N, R))).astype(np.float32)
+    pk = (sc * rng.standard_normal((Bp, H, M, R))).astype(np.float32)
+    if phi == "bf16":
+        pq, pk = W.round_bf16(pq), W.round_bf16(pk)
+    return q, k, v, dout, pq, pk
+
+
+def _least(B, H, N, M, R):      # the workspace formula of the header
+    return (B * H * N * 8 + 15) // 16 * 16 + B * H * (N + M) * (C + (64 if R else 0)) * 2
+
+
+@pytest.mark.parametrize("N,M,causal", [(1647, 0, False), (2207, 0, True), (2176, 0, True), (700, 1600, False), (3300, 1105, False)])
+@pytest.mark.parametrize("R,phi", [(0, "bf16"), (8, "bf16"), (20, "bf16"), (64, "bf16"), (3, "f32"), (10, "f32")])
+def test_stored_and_recomputed(N, M, causal, R, phi):
+    B, H, L = (4 if causal or N < 1000 else 2), 8, M or N
+    shared = R % 3 != 0
+    q, k, v, dout, pq, pk = _inputs(B, H, N, L, R, phi, shared)
+    d = [dev(q, "bf16"), dev(k, "bf16"), dev(v, "bf16")] + ([dev(pq, phi), dev(pk, phi)] if R else [None, None])
+    got = []
+    assert api.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, L, C, R) > _least(B, H, N, L, R)
+    for room in (True, False):
+        kw = {} if room else {"workspace": torch.empty(_least(B, H, N, L, R), dtype=torch.uint8, device="cuda")}
+        if M:
+            out, lse = api.fb_lowrank_xattn_fwd(*d)
+            got.append(api.fb_lowrank_xattn_bwd(*d, out, lse, dev(dout, "bf16"), **kw))
+        else:
+            out, lse = api.fb_lowrank_attn_fwd(*d, causal=causal)
+            got.append(api.fb_lowrank_attn_bwd(*d, out, lse, dev(dout, "bf16"), causal=causal, **kw))
+    torch.cuda.synchronize()
+    for x, y in zip(*got):
+        assert (x is None and y is None) or torch.equal(x, y)
+    b, h = B - 1, H - 1
+    fq, fk = pq[0 if shared else b, h], pk[0 if shared else b, h]
+    ref = O.attention_lowrank_grads(q[b, h], k[b, h], v[b, h], fq, fk, dout[b, h], causal=causal)
+    for name, g, r in zip(("dq", "dk", "dv", "dphi_q", "dphi_k"), got[0], ref):
+        if g is not None:
+            other = pk if name == "dphi_q" else pq
+            gain = max(1.0, float(np.abs(other).max())) if name.startswith("dphi") else 1.0
+            check_grad(f"stored N{N} M{L} R{R} {phi} causal={causal}", name, host(g[b, h]), r, gain=gain)
+
+
+@pytest.mark.parametrize("N,B,H,heads", [(1024, 8, 8, 32), (1100, 8, 8, 32)])
+def test_parts_of_the_heads(N, B, H, heads):
+    """Room for the dS of half the heads: two launches of each kernel, the same gradients."""
+    torch.manual_seed(3)
+    t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    q, k, v, do, pq, pk = t(B, H, N, C), t(B, H, N, C), t(B, H, N, C), t(B, H, N, C), t(1, H, N, 8), t(1, H, N, 8)
+    out, lse = api.fb_lowrank_attn_fwd(q, k, v, pq, pk)
+    one = ((N + 127) // 128 * 128) ** 2 * 2
+    got = []
+    for room in (B * H * one, heads * one, 0):
+        ws = torch.empty(_least(B, H, N, N, 8) + (room + 256 if room else 0), dtype=torch.uint8, device="cuda")
+        got.append(api.fb_lowrank_attn_bwd(q, k, v, pq, pk, out, lse, do, workspace=ws))
+    torch.cuda.synchronize()
+    for other in got[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(got[0], other))
+
+
+def test_slope_gradient():
+    torch.manual_seed(4)
+    B, H, N = 4, 8, 2200
+    t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    q, k, v, do = t(B, H, N, C), t(B, H, N, C), t(B, H, N, C), t(B, H, N, C)
+    slopes = torch.tensor(W.alibi_slopes_f32(H), device="cuda")
+    out, lse = api.fb_alibi_attn_fwd(q, k, v, slopes, causal=True)
+    got = []
+    for ws in (None, torch.empty(_least(B, H, N, N, 2), dtype=torch.uint8, device="cuda")):
+        rows = torch.empty(B, H, N, device="cuda")
+        got.append((rows,) + tuple(api.fb_alibi_attn_bwd(q, k, v, slopes, out, lse, do, causal=True, workspace=ws, dslope_rows=rows)))
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(*got))

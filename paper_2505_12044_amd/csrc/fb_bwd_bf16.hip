@@ -353,6 +353,7 @@ struct MainArgs {
     float exp_mul;        // S exp_mul - lse2 is the exponent of P to base two (not used by FOLD): log2 e, times the scale where the q columns carry none
     bf16_t* q_out;        // not NULL: the dq kernel forms its operand rows as bf16(q q_mul) and leaves them here (= aq.main)
     float q_mul;
+    float k_mul;          // dkv kernel, dense bias: its key rows carry the scale (else 1)
     float dkv_mul;        // factor of d[K | phi_k] (the scale, where the q columns carry none; 1 / log2 e for FOLD)
     bf16_t* ds;           // stored dS of the heads head0.. in 32 x 32 tiles (see store_ds)
     unsigned ds_pitch;    // queries and keys of a head, padded to whole tiles of the two kernels
@@ -361,7 +362,8 @@ struct MainArgs {
 };
 
 // What a main kernel does about dS.  RECOMPUTE: each forms S, P, dP and dS itself.  STORE (dkv) leaves dS in the
-// workspace, LOAD (dq) takes it from there and is left with its output contraction alone.
+// workspace, or in dBias where the bias is a dense matrix, LOAD (dq) takes it from there and is left with its output
+// contraction alone.
 enum { RECOMPUTE = 0, STORE = 1, LOAD = 2 };
 
 constexpr int kWavesLd = 4;       // of the dq kernel that takes dS from the workspace
@@ -372,14 +374,14 @@ constexpr int kSlotsLd = 80 * 1024 / kSlotBytesLd<C, RP, LIMB, CG>;      // two 
 
 // DENSE (RP = 0 only): the bias is a dense [N][M] matrix instead of factors.  Every wave also
 // copies the 32 x 32 bias tile of (its lane rows) x (the streamed block) into the slot, two
-// direct loads per block; the S chain starts from those values; the dq kernel writes
+// direct loads per block; the S chain starts from those values; the dq kernel (STORE: the dkv kernel, turned in LDS) writes
 // dS = dBias from its packed operand registers.
 template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG, int MODE>
 FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem, const int bh, const int tile) {
     static_assert(!DENSE || RP == 0, "dense bias and factors are exclusive");
     constexpr bool ST = MODE == STORE, LD = MODE == LOAD;
     constexpr int WV = LD ? kWavesLd : kWaves, kRows = WV * 32;      // waves and lane-side rows of the workgroup
-    static_assert((!ST || DKV) && (!LD || !DKV) && (MODE == RECOMPUTE || (!DENSE && CG == C)), "stored dS");
+    static_assert((!ST || DKV) && (!LD || !DKV) && (MODE == RECOMPUTE || CG == C), "stored dS");
     using K = Cfg<C, RP, LIMB, CG>;
     using TC = typename K::TC;
     using TP = typename K::TP;
@@ -430,6 +432,12 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             for (int e = 0; e < 8; e++) l1reg[ks][e] = (bf16_t)((float)l1reg[ks][e] * a.q_mul);
             if (ri < NL) *(u32x4*)(qo + ks * 16) = as_uint4(l1reg[ks]);
         }
+    }
+    if (DENSE && ST && a.k_mul != 1.f) {      // wave-uniform
+#pragma unroll
+        for (int ks = 0; ks < C / 16; ks++)
+#pragma unroll
+            for (int e = 0; e < 8; e++) l1reg[ks][e] = (bf16_t)((float)l1reg[ks][e] * a.k_mul);
     }
 #pragma unroll
     for (int cs = 0; cs < (LD ? 0 : K::CS); cs++)
@@ -526,7 +534,8 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     int bias_var[2], bias_pitch = 0, bias_lshift = 0;
     unsigned bias_fix[2];
     if (DENSE) {
-        const bf16_t* bg = (const bf16_t*)p.bias + (size_t)b_ * p.bias_bstride + (size_t)h_ * p.N * p.M;
+        const bf16_t* bg = LD ? (const bf16_t*)p.dbias + (size_t)bh * p.N * p.M
+                              : (const bf16_t*)p.bias + (size_t)b_ * p.bias_bstride + (size_t)h_ * p.N * p.M;
         const int Mk = p.M;
 #pragma unroll
         for (int i = 0; i < 2; i++) {
@@ -550,7 +559,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         bias_lshift = DKV ? 0 : 3;
         bias_bstep = DKV ? (size_t)BT * Mk * 2 : (size_t)BT * 2;
     }
-    if (LD) {
+    if (LD && !DENSE) {
         // tile (streamed block, this wave's queries), see store_ds; rows of the LDS tile = keys
 #pragma unroll
         for (int i = 0; i < 2; i++) {
@@ -568,15 +577,15 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         const unsigned dst = lds0 + slot * kSlotBytes + kOffBias + wave * kBiasTile;
 #pragma unroll
         for (int x = 0; x < 2; x++) {
-            const unsigned voff = (unsigned)((LD ? bias_var[x] : min(bias_var[x], left >> bias_lshift)) * bias_pitch) + bias_fix[x];
-            if (LD) dma16nt(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
+            const unsigned voff = (unsigned)((LD && !DENSE ? bias_var[x] : min(bias_var[x], left >> bias_lshift)) * bias_pitch) + bias_fix[x];
+            if (LD && !DENSE) dma16nt(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
             else dma16(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
         }
     };
     // all but the newest block's loads (plus `stores` global stores issued since) may remain
     auto wait_prev_loads = [&](int stores) __attribute__((always_inline)) {
         // (ST: behind them also the two stores of each of the last two blocks, which every wave issues)
-        constexpr int NLD = NDW + (DENSE || LD ? 2 : 0) + (ST ? 4 : 0);
+        constexpr int NLD = NDW + (DENSE || LD ? 2 : 0) + (ST && !DENSE ? 4 : 0);
         if (stores == 0) wait_vmcnt<NLD>();
         else wait_vmcnt_n(NLD + stores);
     };
@@ -704,9 +713,9 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
     // of a whole matrix, 64 bytes a wave and block at a stride of N: B 2, H 8, N 16384 training 14.8 ms).  In a tile, piece
     // (gp, key, hf) of 16 bytes holds the queries 16 gp + 8 hf + 0..7 of a key: a lane's packed registers after one
     // exchange across the halves per register pair.  Keys past the last are zero.
-    bf16_t* const ds_row = ST ? a.ds + (size_t)(bh - a.head0) * a.ds_rows * a.ds_pitch + (size_t)(rw0 >> 5) * 32 * a.ds_pitch + l32 * 16 + 8 * hf : nullptr;
+    bf16_t* const ds_row = ST && !DENSE ? a.ds + (size_t)(bh - a.head0) * a.ds_rows * a.ds_pitch + (size_t)(rw0 >> 5) * 32 * a.ds_pitch + l32 * 16 + 8 * hf : nullptr;
     auto store_ds = [&](const bf16x8 (&dsb)[2], int sb0) __attribute__((always_inline)) {
-        if (!ST) return;
+        if (!ST || DENSE) return;
 #pragma unroll
         for (int gp = 0; gp < 2; gp++) {
             u32x4 w = as_uint4(dsb[gp]);
@@ -719,6 +728,44 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             __builtin_nontemporal_store(w, (u32x4*)(ds_row + (size_t)sb0 * 32 + 512 * gp));
         }
     };
+
+    // dBias = dS, by the dq kernel (dsb: keys 8g + 4 hf + 0..3 of this lane's query) or, ST, by the dkv kernel, whose lanes
+    // hold queries of a key: its 32 x 32 tile is turned in LDS, in the bias tile of the block, which this wave alone reads
+    // and has read.  One exchange across the halves per register pair makes whole 16-byte pieces, group 2 gp + hf in half hf.
+    bf16_t* const dbg = DENSE ? (bf16_t*)p.dbias + (size_t)bh * p.N * p.M : nullptr;
+    auto store_dbias = [&](const bf16x8 (&dsb)[2], int sb0, int slot_off) __attribute__((always_inline)) {
+        if (!DENSE || (DKV && !ST)) return;
+        u32x4 w[2] = {as_uint4(dsb[0]), as_uint4(dsb[1])};
+        if (DKV) {
+            unsigned char* tp = smem + (slot_off + kOffBias + wave * kBiasTile);
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const u32x4 v = w[g >> 1];
+                *(u32x2*)(tp + l32 * 64 + ((g ^ ((l32 >> 2) & 3)) << 4) + hf * 8) = (g & 1) ? u32x2{v.z, v.w} : u32x2{v.x, v.y};
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int gp = 0; gp < 2; gp++)
+                w[gp] = as_uint4(join_tr(lds_read_tr16((const bf16_t*)(tp + boff[2 * gp])), lds_read_tr16((const bf16_t*)(tp + boff[2 * gp + 1]))));
+            asm volatile("" ::: "memory");
+        }
+        u32x4 piece[2];
+#pragma unroll
+        for (int gp = 0; gp < 2; gp++) {
+            const auto r0 = __builtin_amdgcn_permlane32_swap(w[gp].x, w[gp].z, false, false);
+            const auto r1 = __builtin_amdgcn_permlane32_swap(w[gp].y, w[gp].w, false, false);
+            piece[gp] = u32x4{(unsigned)r0[0], (unsigned)r1[0], (unsigned)r0[1], (unsigned)r1[1]};
+        }
+        const int row = DKV ? sb0 + l32 : ri, col = (DKV ? rw0 : sb0) + 8 * hf;
+        if (row < p.N) {
+            bf16_t* drow = dbg + (size_t)row * p.M + col;
+#pragma unroll
+            for (int gp = 0; gp < 2; gp++)
+                if (col + 16 * gp < p.M) *(u32x4*)(drow + 16 * gp) = piece[gp];
+        }
+    };
+    // what wait_prev_loads has to allow for it (whole blocks, so all stores have issued where the wave's rows are all inside)
+    const int dbias_stores = DENSE && (!DKV || ST) && rw0 + 31 < NL ? 4 : 0;
 
     using Yes = std::true_type;
     using No = std::false_type;
@@ -864,7 +911,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                 }
             }
             // block i+2 has landed; everyone has left block i-1
-            wait_prev_loads(0);
+            wait_prev_loads(dbias_stores);
             __syncthreads();
             issue_block(i + 4, sl4);
             issue_bias(i + 4, sl4);
@@ -889,6 +936,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
                 }
             }
             store_ds(dsb, sb0);
+            store_dbias(dsb, sb0, sl * kSlotBytes);
 #pragma unroll
             for (int n = 0; n < LA; n++) opr[n] = nxt[n];
             read_vec(sl1 * kSlotBytes);
@@ -913,13 +961,25 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         // dS comes from the workspace, 2 KB a wave and block beside the shared operand tile.  Bound by that read, 4.2 TB/s
         // where the dS of a launch is far larger than the last-level cache (C = 128, R 8: 10 matrix instructions a block
         // where the recomputing form has 27; B 2, H 8, N 16384 3110 -> 2040 us).  Eight waves with a ring of 160 KB: 315 us
-        // a launch of 2 heads against 254, half the workgroups.
+        // a launch of 2 heads against 254, half the workgroups.  From dBias (B 8, H 12, N 1024, C 64, 200 MB): 45 us, where
+        // the recomputing form takes 103; the dkv kernel that writes it 100 instead of 82.
         constexpr int NS_ = kSlotsLd<C, RP, LIMB, CG>;
 #pragma unroll
         for (int j = 0; j < NS_ - 1; j++) { issue_block(j, j); issue_bias(j, j); }
         wait_vmcnt<0>();
         __syncthreads();
-        auto read_d = [&](int slot_off, int kk) __attribute__((always_inline)) {
+        auto read_d = [&](int slot_off, int kk, int blk) __attribute__((always_inline)) {
+            if (DENSE) {
+                const unsigned char* t = smem + (slot_off + kOffBias + wave * kBiasTile);
+                const u32x2 lo = *(const u32x2*)(t + boff[2 * kk]), hi = *(const u32x2*)(t + boff[2 * kk + 1]);
+                u32x4 w = {lo.x, lo.y, hi.x, hi.y};
+                const int left = NS - blk * BT - 16 * kk;      // keys past the last, in whole eights
+                if (left < 16) {
+                    if (left <= 8) w.z = w.w = 0u;
+                    if (left <= 0) w.x = w.y = 0u;
+                }
+                return as_bf16x8(w);
+            }
             const unsigned char* t = smem + (slot_off + kOffBias + wave * kBiasTile + kk * 1024);
             return join_tr(lds_read_tr16((const bf16_t*)(t + tr32[0])), lds_read_tr16((const bf16_t*)(t + tr32[1])));
         };
@@ -930,7 +990,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
             for (int n = 0; n < LB; n++) opd[n] = tr_read1(t0, n >> 1, n & 1);
 #pragma unroll
-            for (int kk = 0; kk < 2; kk++) dcur[kk] = read_d(0, kk);
+            for (int kk = 0; kk < 2; kk++) dcur[kk] = read_d(0, kk, blk_of(0));
         }
         // causal: the dkv launch visits whole 128-row tiles; the blocks of a wave past its own are not there
         const int b_own = CAUSAL ? min(b_end, (rw0 / 128 + 1) * 4) : b_end;
@@ -949,7 +1009,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             for (int n = 0; n < NO1; n++) {
                 if (n + LB < NO1) opd[(n + LB) % (LB + 1)] = tr_read1(tb0, (n + LB) >> 1, (n + LB) & 1);
                 else nxt[n + LB - NO1] = tr_read1(tbn, (n + LB - NO1) >> 1, (n + LB - NO1) & 1);
-                if (n >= NO1 - 2) dn[n - (NO1 - 2)] = read_d(offn, n - (NO1 - 2));
+                if (n >= NO1 - 2) dn[n - (NO1 - 2)] = read_d(offn, n - (NO1 - 2), blk_of(i + 1));
                 if (own) acc1[n >> 1] = mfma32(opd[n % (LB + 1)], dcur[n & 1], acc1[n >> 1]);
             }
 #pragma unroll
@@ -991,8 +1051,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         wait_vmcnt<0>();
         __syncthreads();
         RowBase rb0 = mk_row(0);
-        bf16_t* dbg = nullptr;      // dBias rows of this (b, h)
-        if (DENSE && !DKV) dbg = (bf16_t*)p.dbias + (size_t)bh * p.N * p.M;
 #pragma unroll
         for (int n = 0; n < LA; n++) opr[n] = read_op(rb0, TrBase{}, n);
 
@@ -1057,35 +1115,17 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             }
             // ---------------- block i+1 has landed; everyone has left block i-1 ----------------
             // (behind them lie the loads of block i+2 and, with a dense bias, the dBias stores of the two blocks before
-            // this one: whole blocks, so all of them have issued where the wave's rows are all inside)
-            wait_prev_loads(DENSE && !DKV && rw0 + 31 < NL ? 4 : 0);
+            // this one)
+            wait_prev_loads(dbias_stores);
             __syncthreads();
             issue_block(i + 3, (i + 3) & (NSLOT - 1));
             issue_bias(i + 3, (i + 3) & (NSLOT - 1));
 
             store_ds(dsb, sb0);
 
-            // ---------------- dBias = dS ----------------
-            // The packed operand registers of a lane hold keys 8g + 4 hf + 0..3 of its row: one exchange across the halves
-            // per register pair makes whole 16-byte pieces, group 2 gp + hf in half hf.  Issued behind the loads, so a
-            // store has two blocks' time before anything waits for it (B 8, H 12, N 1024, C 64: 110 -> 100 us).
-            if (DENSE && !DKV) {
-                const int Mk = p.M;
-                u32x4 piece[2];
-#pragma unroll
-                for (int gp = 0; gp < 2; gp++) {
-                    const u32x4 w = as_uint4(dsb[gp]);
-                    const auto r0 = __builtin_amdgcn_permlane32_swap(w.x, w.z, false, false);
-                    const auto r1 = __builtin_amdgcn_permlane32_swap(w.y, w.w, false, false);
-                    piece[gp] = u32x4{(unsigned)r0[0], (unsigned)r1[0], (unsigned)r0[1], (unsigned)r1[1]};
-                }
-                if (ri < NL) {
-                    bf16_t* drow = dbg + (size_t)ri * Mk + sb0 + 8 * hf;
-#pragma unroll
-                    for (int gp = 0; gp < 2; gp++)
-                        if (sb0 + 16 * gp + 8 * hf < Mk) *(u32x4*)(drow + 16 * gp) = piece[gp];
-                }
-            }
+            // ---------------- dBias = dS, issued behind the loads: a store has two blocks' time before anything waits for
+            // it (dq, B 8, H 12, N 1024, C 64: 110 -> 100 us) ----------------
+            store_dbias(dsb, sb0, slot * kSlotBytes);
 
             // ---------------- second half: output chains ----------------
             bf16x8 nxt[LA];      // first operands of block i+1 (the window restarts at 0 with every block)
@@ -1102,14 +1142,14 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             init_tiles(((i + 1) & (NSLOT - 1)) * kSlotBytes);
             rb0 = rbn;
         }
-        if (DENSE && !DKV && CAUSAL && ri < NL) {
-            // key blocks above the diagonal are never visited: their dBias is zero
-            for (int blk = b_end; blk < nblk_all; blk++) {
-                bf16_t* drow = dbg + (size_t)ri * p.M + blk * BT + 8 * hf;
+    }
+    if (DENSE && !DKV && CAUSAL && ri < NL) {
+        // key blocks above the diagonal are never visited: their dBias is zero
+        for (int blk = b_end; blk < nblk_all; blk++) {
+            bf16_t* drow = dbg + (size_t)ri * p.M + blk * BT + 8 * hf;
 #pragma unroll
-                for (int gp = 0; gp < 2; gp++)
-                    if (blk * BT + 16 * gp + 8 * hf < p.M) *(u32x4*)(drow + 16 * gp) = u32x4{0u, 0u, 0u, 0u};
-            }
+            for (int gp = 0; gp < 2; gp++)
+                if (blk * BT + 16 * gp + 8 * hf < p.M) *(u32x4*)(drow + 16 * gp) = u32x4{0u, 0u, 0u, 0u};
         }
     }
     wait_vmcnt<0>();     // no direct load may outlive this tile's use of the ring
@@ -1210,13 +1250,22 @@ __global__ __launch_bounds__(MODE == LOAD ? kWavesLd * 64 : kThreads, (DKV ? Cfg
 // 1302; B 4, H 8, N 4096 1296 / 1194; B 1, H 2, N 8192 606 / 510; B 8, H 8, N 2048 696 / 661.  C = 64: B 8, H 12, N 1024,
 // R 32 204 / 209; B 8, H 8, N 2048, R 16 413 / 418; two columns of 64 (multiplicative) 2060 / 2065: left.
 template <int C, int RP, bool DENSE, int CG>
-constexpr bool kStored = C == 128 && !DENSE;
+constexpr bool kStored = DENSE ? CG == C : C == 128;
 // What is saved grows with the pairs, what the extra launch and the pass over the query rows cost with the call and the rows
 // (start / stored, us, C = 128, R 8): 512 heads of N 256 181 / 188, 128 of 512 159 / 164, 32 of 1024 158 / 161 (8.4 M by this
 // measure); 64 of 1024 202 / 196 (16.8 M), 256 of 1000 770 / 752, 8 of 2048 172 / 151 (21 M), 2 of 4096 313 / 266, causal 15
 // of 3000 288 / 261.
 bool stored_pays(long long heads, int N, int M, bool causal) {
     return (double)heads * N * ((causal ? 0.5 : 1.0) * M - 768.0) >= (double)(1 << 24);
+}
+// With a dense bias dBias is that dS: the dkv kernel writes it, the dq kernel reads it (start / now, us: B 8, H 12, N 1024, C 64
+// 272 / 242, causal N 1000 243 / 242; C 128: B 2, H 8, N 2048 296 / 267, causal 318 / 279; C 32: B 8, H 16, N 1024 306 / 286;
+// B 1, H 2, N 2048, C 64 161 / 134).  Not in calls that the launches bound, which one more costs 3 us of 140: B 4, H 8,
+// N 512, C 64 140 / 143, B 64, H 16, N 128, C 64 146 / 149, B 16, H 16, N 512, C 32 142 / 145,
+// B 1, H 2, N 1024, C 64 122 / 125.
+bool dense_stored_pays(long long heads, int N, int M, int C) {
+    const double pairs = (double)heads * N * M;
+    return (N >= 1024 && M >= 1024 && pairs >= (double)(1 << 23)) || pairs * (C == 32 ? 16 : C) >= (double)(1u << 31);
 }
 constexpr size_t kMaxStored = (size_t)1 << 30;      // at a time
 size_t ds_head_bytes(int N, int M) { return (size_t)((N + 127) / 128 * 128) * ((M + 127) / 128 * 128) * 2; }
@@ -1297,6 +1346,7 @@ int launch(const BwdParams& pin, hipStream_t stream) {
     a.ak = OperandRows{CG < C ? akm : (const bf16_t*)pin.k, akp, shared_k};
     a.q_out = raw_q || CG < C ? nullptr : aqm;
     a.q_mul = qscale;
+    a.k_mul = 1.f;
     a.exp_mul = raw_q ? kLog2e * pin.scale : kLog2e;
     a.dkv_mul = raw_q ? pin.scale : (K::FOLD ? kLn2 : 1.f);
 
@@ -1332,7 +1382,7 @@ int launch(const BwdParams& pin, hipStream_t stream) {
         // dkv first, chunk by chunk of heads, leaving dS for dq
         const size_t least = (fb_bwd_workspace_bytes(rows, rowsk, CG, pin.R) + 255) & ~(size_t)255;
         const size_t room = pin.workspace_bytes > least ? pin.workspace_bytes - least : 0;
-        const int chunk = stored_heads(all_heads, pin.N, pin.M, CAUSAL, K::PIPE, room);
+        const int chunk = DENSE ? (dense_stored_pays(all_heads, pin.N, pin.M, C) ? all_heads : 0) : stored_heads(all_heads, pin.N, pin.M, CAUSAL, K::PIPE, room);
         if (chunk > 0) {
             constexpr size_t lds_load = (size_t)kSlotsLd<C, RP, LIMB, CG> * kSlotBytesLd<C, RP, LIMB, CG>;
             static_assert(kSlotsLd<C, RP, LIMB, CG> >= 4 && lds_load >= K::kEpiLds, "ring and epilogue");
@@ -1343,6 +1393,11 @@ int launch(const BwdParams& pin, hipStream_t stream) {
             a.ds = (bf16_t*)(ws + least);
             a.ds_pitch = (unsigned)((p.N + 127) / 128 * 128);
             a.ds_rows = (unsigned)((p.M + 127) / 128 * 128);
+            if (DENSE && pow2 && !K::FOLD) {      // bf16(k scale) = k scale: the key rows take it, once a wave, and q is read in place
+                a.aq.main = (const bf16_t*)pin.q;
+                a.q_out = nullptr;
+                a.k_mul = a.dkv_mul = pin.scale;
+            }
             hipLaunchKernelGGL((bwd_rows_kernel<C>), dim3((unsigned)((rows * 2 + 255) / 256)), dim3(256), 0, stream, pin, a.vec, a.q_out,
                                a.q_mul, rows);
             a.q_out = nullptr;

@@ -1230,7 +1230,7 @@ __global__ __launch_bounds__(MODE == LOAD ? kWavesLd * 64 : kThreads, (DKV ? Cfg
     const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);
     if (L >= p.total_tiles) return;
     const int n_units = CAUSAL ? (p.n_tiles + 1) / 2 : p.n_tiles;   // p.n_tiles: 128-row tiles of the lane side
-    const int bhl = L / n_units, bh = a.head0 + bhl;
+    const int bhl = L / n_units, bh = MODE == RECOMPUTE || DENSE ? bhl : a.head0 + bhl;
     const int u = L - bhl * n_units;
     if (CAUSAL) {
         const int other = p.n_tiles - 1 - u;

@@ -7,9 +7,10 @@
 // travel global -> registers -> the second LDS buffer while this one is computed.
 //
 // Orientation, softmax and the rounding of the operands are those of the ring kernel: a query is a lane, the scores of
-// a 32-key block sit in its accumulator registers, lazy reference maximum.  A wave takes its last visible block first
-// (the diagonal, or the partial block at the end), which is the only one with masks and gives every row its reference;
-// the other blocks follow two at a time, so the score chain of one overlaps the exponentials of the other.
+// a 32-key block sit in its accumulator registers, lazy reference maximum.  A wave takes its rows' first block alone,
+// for the reference: key 0's, as the ring kernel does, so P is rounded to bf16 at the same scale and the sums follow in
+// the same order (the same bits; full attention), or the diagonal one when causal.  The other blocks follow two at a
+// time, so the score chain of one overlaps the exponentials of the other.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -45,7 +46,7 @@ FB_DEV void dma16(const void* sbase, unsigned voff, unsigned lds_addr) {
 
 // PM: 0 = no factors, 1 = bf16 factors in whole 16-byte pieces (R % 8 == 0), 2 = bf16 factors of any R, 3 = fp32 factors
 template <int CG, int RP, int PM, bool CAUSAL>
-__global__ __launch_bounds__(kMaxWaves * 64) void fwd_short_kernel(FwdParams p, int units, int upr) {
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_short_kernel(FwdParams p, int units, int upr) {
     using K = Cfg<CG, RP>;
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool F32 = PM == 3;
@@ -169,10 +170,12 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fwd_short_kernel(FwdParams p, 
 #pragma unroll
         for (int r = 0; r < 16; r++) oacc[r] = 0.f;
 
-        // NB blocks starting at key block kb; FIRST: the masked block that gives every row its reference
-        auto step = [&](int kb, auto nb_tag, auto first_tag) __attribute__((always_inline)) {
+        // NB blocks starting at key block kb; FIRST: the one that gives every row its reference; MASK: it may be partial or
+        // the diagonal one
+        auto step = [&](int kb, auto nb_tag, auto first_tag, auto mask_tag) __attribute__((always_inline)) {
             constexpr int NB = decltype(nb_tag)::value;
-            constexpr bool FIRST = decltype(first_tag)::value;
+            constexpr bool FIRST = decltype(first_tag)::value, MASK = decltype(mask_tag)::value;
+            static_assert(NB == 1 || !(FIRST || MASK), "two blocks: plain ones");
             f32x16 s[NB];
             bf16x8 va[NB][2];
             const unsigned char* kt = smem + (buf + kb * 32 * K::RB);
@@ -195,65 +198,83 @@ __global__ __launch_bounds__(kMaxWaves * 64) void fwd_short_kernel(FwdParams p, 
                     va[b][kk] = join_tr(lds_read_tr16((const bf16_t*)(kt + voff0 + vtr[0] + (2 * b + kk) * 16 * K::RB)),
                                         lds_read_tr16((const bf16_t*)(kt + voff0 + vtr[1] + (2 * b + kk) * 16 * K::RB)));
             bf16x8 pb[NB][2];
-            auto exps = [&](float nm) __attribute__((always_inline)) {
+            // P = exp2(S log2e - mref), packed, and this lane's row sum of block b
+            auto exps = [&](int b, float nm) __attribute__((always_inline)) {
                 float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int b = 0; b < NB; b++)
-#pragma unroll
-                    for (int r = 0; r < 16; r += 2) {
-                        const bf16x2 pr2 = {(bf16_t)fast_exp2(fmaf(s[b][r], emul, nm)), (bf16_t)fast_exp2(fmaf(s[b][r + 1], emul, nm))};
-                        ps[(r >> 1) & 3] = pair_sum(pr2, ps[(r >> 1) & 3]);
-                        pb[b][r / 8][r % 8] = pr2[0];
-                        pb[b][r / 8][r % 8 + 1] = pr2[1];
-                    }
+                for (int r = 0; r < 16; r += 2) {
+                    const bf16x2 pr2 = {(bf16_t)fast_exp2(fmaf(s[b][r], emul, nm)), (bf16_t)fast_exp2(fmaf(s[b][r + 1], emul, nm))};
+                    ps[(r >> 1) & 3] = pair_sum(pr2, ps[(r >> 1) & 3]);
+                    pb[b][r / 8][r % 8] = pr2[0];
+                    pb[b][r / 8][r % 8 + 1] = pr2[1];
+                }
                 return (ps[0] + ps[1]) + (ps[2] + ps[3]);
             };
-            float psum;
-            if constexpr (FIRST) {
+            if (MASK && (CAUSAL || kb * 32 + 32 > M)) {
                 const int qi = qw0 + l32;
-                if (CAUSAL || (kb * 32 + 32 > M)) {
 #pragma unroll
-                    for (int r = 0; r < 16; r++) {
-                        const int key = kb * 32 + 8 * (r / 4) + 4 * hf + (r % 4);
-                        if (key >= M || (CAUSAL && key > qi)) s[0][r] = -INFINITY;
-                    }
+                for (int r = 0; r < 16; r++) {
+                    const int key = kb * 32 + 8 * (r / 4) + 4 * hf + (r % 4);
+                    if (key >= M || (CAUSAL && key > qi)) s[0][r] = -INFINITY;
                 }
-                mref = fmaxf(half_max(max16(s[0])) * emul, -1e30f);
-                psum = exps(-mref);
-            } else {
-                psum = exps(-mref);
-                if (__any(!(psum < kSumLimit))) {
-                    // the scores outgrew the reference: take the true maximum, rescale, redo the exponentials
-                    asm volatile("" ::: "memory");
-                    float mx = max16(s[0]);
-                    if (NB == 2) mx = fmaxf(mx, max16(s[NB - 1]));
-                    mx = half_max(mx) * emul;
+            }
+            if constexpr (FIRST) mref = fmaxf(half_max(max16(s[0])) * emul, -1e30f);
+            float psum[NB], all = 0.f;
+#pragma unroll
+            for (int b = 0; b < NB; b++) {
+                psum[b] = exps(b, -mref);
+                all += psum[b];
+            }
+            if (!FIRST && __any(!(all < kSumLimit))) {
+                // rare: the scores may have outgrown the reference.  Block by block, as the ring kernel does: where a
+                // block's own sum says so, take its true maximum, rescale, redo the exponentials
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int b = 0; b < NB; b++) {
+                    if (!__any(!(psum[b] < kSumLimit))) continue;
+                    const float mx = half_max(max16(s[b])) * emul;
                     if (__any(mx > mref)) {
                         const float mnew = fmaxf(mref, mx);
                         const float alpha = fast_exp2(mref - mnew);
                         mref = mnew;
+                        if (b == 1) {      // the block before belongs to what is rescaled
+                            lsum += psum[0];
+                            psum[0] = 0.f;
+#pragma unroll
+                            for (int kk = 0; kk < 2; kk++) {
+                                oacc = mfma32(va[0][kk], pb[0][kk], oacc);
+                                pb[0][kk] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
+                            }
+                        }
                         lsum *= alpha;
 #pragma unroll
                         for (int r = 0; r < 16; r++) oacc[r] *= alpha;
+#pragma unroll
+                        for (int x = b + 1; x < NB; x++) psum[x] = exps(x, -mref);
                     }
-                    psum = exps(-mref);
+                    psum[b] = exps(b, -mref);
                 }
             }
-            lsum += psum;
 #pragma unroll
-            for (int b = 0; b < NB; b++)
+            for (int b = 0; b < NB; b++) {
+                lsum += psum[b];
 #pragma unroll
                 for (int kk = 0; kk < 2; kk++) oacc = mfma32(va[b][kk], pb[b][kk], oacc);
+            }
         };
         using One = std::integral_constant<int, 1>;
         using Two = std::integral_constant<int, 2>;
 
         if (qw0 < N) {      // wave-uniform
-            const int last = CAUSAL ? min(qw0 >> 5, nkb - 1) : nkb - 1;
-            step(last, One{}, std::true_type{});
-            int kb = 0;
-            for (; kb + 2 <= last; kb += 2) step(kb, Two{}, std::false_type{});
-            if (kb < last) step(kb, One{}, std::false_type{});
+            using Yes = std::true_type;
+            using No = std::false_type;
+            using Tail = std::integral_constant<bool, !CAUSAL>;
+            const int diag = min(qw0 >> 5, nkb - 1);
+            const int whole = CAUSAL ? diag : M >> 5, end = CAUSAL ? diag : nkb;      // blocks without masks, all blocks but the first taken
+            step(CAUSAL ? diag : 0, One{}, Yes{}, Yes{});
+            int kb = CAUSAL ? 0 : 1;
+            for (; kb + 2 <= whole; kb += 2) step(kb, Two{}, No{}, No{});
+            for (; kb < end; kb++) step(kb, One{}, No{}, Tail{});
         }
         if (fresh) {
             // the next head's rows have landed before anyone reads them; the stores of the results follow behind the

@@ -81,6 +81,31 @@ def test_outgrown_reference(C, N):
     _run(64, 4, N, N, C, 8, "bf16", False, True, [(0, 0), (63, 3)], offset=30.0)
 
 
+@pytest.mark.parametrize("N", [20, 32, 64, 95, 224, 300, 384])
+@pytest.mark.parametrize("C,R,offset", [(16, 0, 0), (16, 12, 0), (32, 4, 0), (32, 16, 0), (32, 32, 0), (16, 12, 30), (32, 16, 30)])
+def test_rounds_as_the_ring_kernel_does(N, C, R, offset):
+    """Full attention: the reference maximum comes from the same block and the sums follow in the same order as in the
+    kernel that longer heads take, so the output is the same to the bit (offset: also where the bias along the keys
+    outgrows the reference); a rescaled row sum may be contracted differently."""
+    torch.manual_seed(N + C + R)
+    t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    B, H = 70, 4
+    q, k, v, pq, pk = t(B, H, N, C), t(B, H, N, C), t(B, H, N, C), t(1, H, N, R), t(1, H, N, R)
+    if offset:
+        pq[..., 0], pk[..., 0] = 1.0, torch.linspace(0.0, offset, N, device="cuda").to(torch.bfloat16)
+    if R == 0:
+        pq = pk = None
+    got = api.fb_lowrank_attn_fwd(q, k, v, pq, pk)
+    try:
+        api.fb_tune_set("fwd_qb", 1)
+        ref = api.fb_lowrank_attn_fwd(q, k, v, pq, pk)
+    finally:
+        api.fb_tune_set("fwd_qb", 0)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], ref[0])
+    assert float((got[1] - ref[1]).abs().max()) <= 2 ** -21 * max(1.0, float(ref[1].abs().max()))
+
+
 def test_same_result_on_every_run():
     torch.manual_seed(5)
     t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)

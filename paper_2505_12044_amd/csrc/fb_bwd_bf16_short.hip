@@ -151,15 +151,19 @@ __global__ __launch_bounds__(kMaxWaves * 64) void bwd_short_kernel(BwdParams p, 
         } else if (o_role) {
             const int row = piece / (CG / 8), chunk = piece % (CG / 8);
             *(u32x4*)(t + K::T1 + tile_off<32>(row, chunk)) = r0;
+            // D in the order of the two-kernel form: one chain over the even pieces of a row, one over the odd ones, added
             const bf16x8 d8 = as_bf16x8(r0), o8 = as_bf16x8(r1);
             float dsum = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; e++) dsum = fmaf((float)o8[e], (float)d8[e], dsum);
+            for (int c = 0; c < CG / 16; c++) {
+                if (c > 0) dsum = __shfl_xor(dsum, 2);
+#pragma unroll
+                for (int e = 0; e < 8; e++) dsum = fmaf((float)o8[e], (float)d8[e], dsum);
+            }
             dsum += __shfl_xor(dsum, 1);
-            if (CG == 32) dsum += __shfl_xor(dsum, 2);
-            if (chunk == 0) {
+            if (chunk == CG / 8 - 2) {
                 float* v = (float*)(t + K::T1 + K::T2);
-                v[row] = -rl;
+                v[row] = -(rl * kLog2e);
                 v[32 + row] = -dsum;
             }
         } else if (RP > 0) {
@@ -267,8 +271,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) void bwd_short_kernel(BwdParams p, 
             if (live) {
                 const int t1 = ring + (2 * par + j) * K::kSlot, t2 = t1 + K::T1;
                 const int ra = t1 + row1, rb = t2 + row2, ta = t1 + tr1, tb = t2 + tr2;
-                // The S chain starts from -lse and the dP chain from -D of the block's rows.  Operands are read LA matrix
-                // instructions ahead: S, dP, dV, d[K | phi_k] in this order.
+                // S is formed as the forward forms it and P = exp2(S log2e - lse log2e), so P sums to one as far as the
+                // forward's did; the dP chain starts from -D of the block's rows.  Operands are read LA matrix instructions
+                // ahead: S, dP, dV, d[K | phi_k] in this order.
                 constexpr int NA = K::KS + K::KC, NOPS = NA + 2 + 2 * K::MB, LA = 3;
                 bf16x8 opr[LA + 1];
                 auto read_op = [&](int n) __attribute__((always_inline)) {
@@ -281,11 +286,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) void bwd_short_kernel(BwdParams p, 
                 f32x16 s, dp;
                 const unsigned char* vp = smem + (t2 + K::T2 + 16 * hf);
 #pragma unroll
-                for (int g = 0; g < 4; g++) {
-                    const f32x4 nl = *(const f32x4*)(vp + 32 * g);
-#pragma unroll
-                    for (int x = 0; x < 4; x++) s[4 * g + x] = nl[x];
-                }
+                for (int r = 0; r < 16; r++) s[r] = 0.f;
 #pragma unroll
                 for (int n = 0; n < LA; n++) opr[n] = read_op(n);
 #pragma unroll
@@ -303,9 +304,11 @@ __global__ __launch_bounds__(kMaxWaves * 64) void bwd_short_kernel(BwdParams p, 
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 bf16x8 pb[2];
+                f32x4 nl;
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
-                    const float pr = fast_exp2(s[r] * emul);
+                    if (r % 4 == 0) nl = *(const f32x4*)(vp + 8 * r);
+                    const float pr = fast_exp2(fmaf(s[r], emul, nl[r % 4]));
                     pb[r / 8][r % 8] = (bf16_t)pr;
                     dsb[r / 8][r % 8] = (bf16_t)(pr * dp[r]);
                 }

@@ -52,6 +52,13 @@ def test_rows_of_p_sum_to_one(N, H, scale, C, R, phi):
     _row_sums(N, 4096, H, C, R, phi, scale, 0)
 
 
+@pytest.mark.parametrize("N,H", [(96, 8), (180, 8), (384, 208)])      # heads that one workgroup takes whole
+@pytest.mark.parametrize("C,R,phi", [(16, 8, "bf16"), (16, 20, "bf16"), (32, 8, "bf16"), (32, 24, "bf16")])
+@pytest.mark.parametrize("scale", [0.0, 0.3])
+def test_rows_of_p_sum_to_one_in_short_heads(N, H, C, R, phi, scale):
+    _row_sums(N, N, H, C, R, phi, scale, 0)
+
+
 @pytest.mark.parametrize("qb", [1, 2, 8, 16])               # every forward kernel, as many queries as keys
 @pytest.mark.parametrize("C,R,phi", FACTORS)
 def test_rows_of_p_sum_to_one_after_each_forward(qb, C, R, phi):

@@ -106,6 +106,31 @@ def test_rounds_as_the_ring_kernel_does(N, C, R, offset):
     assert float((got[1] - ref[1]).abs().max()) <= 2 ** -21 * max(1.0, float(ref[1].abs().max()))
 
 
+@pytest.mark.parametrize("M", [20, 64, 95, 160, 300, 384])
+@pytest.mark.parametrize("C,R", [(16, 8), (16, 28), (32, 4), (32, 16), (32, 32)])
+@pytest.mark.parametrize("level", [0.0, 2.0 ** 14])
+def test_recomputes_the_scores_of_the_two_kernel_backward(M, C, R, level):
+    """More query blocks than key blocks take the two kernels of longer heads.  Rows with a zero upstream gradient add
+    nothing to the key side, so its gradients have to be those of the call without them, to the bit: the same scores, P,
+    dP and dS.  level: a common part of all scores of a row (-lse is then of that size too)."""
+    torch.manual_seed(M + C + R)
+    t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    B, H, N, more = 50, 4, M, (M + 31) // 32 * 32 + 32
+    q, k, v, do, pq, pk = t(B, H, more, C), t(B, H, M, C), t(B, H, M, C), t(B, H, more, C), t(1, H, more, R), t(1, H, M, R)
+    do[:, :, N:] = 0.0
+    if level:
+        pq[..., 0], pk[..., 0] = level, 1.0
+    out, lse = api.fb_lowrank_xattn_fwd(q, k, v, pq, pk)
+    ref = api.fb_lowrank_xattn_bwd(q, k, v, pq, pk, out, lse, do)
+    cut = lambda x: x[:, :, :N].contiguous()
+    got = api.fb_lowrank_attn_bwd(cut(q), k, v, cut(pq), pk, cut(out), cut(lse), cut(do))
+    torch.cuda.synchronize()
+    for name, x, y in zip(("dk", "dv", "dphi_k"), (got[1], got[2], got[4]), (ref[1], ref[2], ref[4])):
+        assert torch.isfinite(x.float()).all() and torch.equal(x, y), name
+    for name, x, y in zip(("dq", "dphi_q"), (got[0], got[3]), (cut(ref[0]), cut(ref[3]))):      # the same dS, summed in another order
+        assert float((x.float() - y.float()).norm() / y.float().norm()) <= 1e-3, name
+
+
 def test_same_result_on_every_run():
     torch.manual_seed(5)
     t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)

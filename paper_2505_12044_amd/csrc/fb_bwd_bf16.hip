@@ -1268,7 +1268,8 @@ bool dense_stored_pays(long long heads, int N, int M, int C) {
     return (N >= 1024 && M >= 1024 && pairs >= (double)(1 << 23)) || pairs * (C == 32 ? 16 : C) >= (double)(1u << 31);
 }
 constexpr size_t kMaxStored = (size_t)1 << 30;      // at a time
-size_t ds_head_bytes(int N, int M) { return (size_t)((N + 127) / 128 * 128) * ((M + 127) / 128 * 128) * 2; }
+// dS of one head, whole tiles (any int: the size queries come before the limits are checked; at most 2^63).
+size_t ds_head_bytes(int N, int M) { return ((size_t)N + 127) / 128 * 128 * (((size_t)M + 127) / 128 * 128) * 2; }
 // Heads per launch whose dS fits `room` bytes, 0: recompute.
 int stored_heads(int heads, int N, int M, bool causal, bool one_wave, size_t room) {
     const size_t per = ds_head_bytes(N, M);

@@ -34,8 +34,11 @@ constexpr int kThreads = 256;
 constexpr int BT = 32;       // streamed rows per block
 constexpr int OPITCH = 36;   // row pitch of an output tile in LDS (floats)
 
-// dS of one head, whole tiles.
-size_t ds_head_bytes(int N, int M) { return (size_t)((N + 31) & ~31) * ((M + 31) & ~31) * 4; }
+// dS of one head, whole tiles (any int: the size queries come before the limits are checked).
+size_t ds_head_bytes(int N, int M) {
+    const size_t pairs = (((size_t)N + 31) & ~(size_t)31) * (((size_t)M + 31) & ~(size_t)31);      // at most 2^62
+    return pairs > (SIZE_MAX >> 2) ? SIZE_MAX : pairs * 4;
+}
 size_t d_bytes(long long rows) { return ((size_t)rows * 4 + 255) & ~(size_t)255; }
 // At most this much dS at a time.  (256 MB, what the last-level cache holds, cuts B 16, H 4, N 1500, C 64 into three
 // launches whose tiles fill the chip badly: 1514 us; in one 1084, recomputed 1329.)

@@ -182,6 +182,19 @@ def test_size_limits_follow_the_indexing(lib):
     assert a(64, 64, 64, 64, 64, 64, 1, 1, (1 << 24) + 1, 16, 1, api.FB_BF16, 0.0, None) == 3   # fp32 positions
 
 
+@pytest.mark.parametrize("C", [32, 64, 128])
+@pytest.mark.parametrize("dtype", [api.FB_F32, api.FB_BF16])
+def test_backward_size_queries_take_any_length(lib, C, dtype):
+    """The queries run ahead of the limits: padding a length next to the largest int must not wrap (it did, to a head of
+    zero bytes that the query then divided by).  Such heads have no room for dS, so the plain formula is the answer."""
+    for N in (2 ** 31 - 32, 2 ** 31 - 31, 2 ** 31 - 1):
+        for M in (N, 64):
+            need = N * 8 + 15 & ~15
+            need += (N + M) * (C + 64) * 2
+            assert lib.fb_lowrank_xattn_bwd_workspace_bytes(1, 1, N, M, C, 8, dtype) == need
+        assert lib.fb_lowrank_attn_bwd_workspace_bytes(1, 1, N, C, 8, dtype) == (N * 8 + 15 & ~15) + 2 * N * (C + 64) * 2
+
+
 def test_noalloc_backward_host_checks(lib):
     """The allocation-free backward rejects bad shapes and problems beyond its static scratch on
     the host, before any device call."""

@@ -234,12 +234,20 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
  * [q*scale | phi_q | 0] and [k | phi_k | 0] that the two main kernels stream
  * (8 + 4 * (C + 64) bytes per row when R > 0, 8 + 4 * C otherwise; C = 16 counts as 32 and
  * adds 32-channel copies of v and dout, 128 more bytes per row).  For FB_F32 at C >= 32 and FB_BF16 at C = 128 the
- * query adds up to 1 GiB, in which the key side leaves dS (4 or 2 bytes a pair) of some or all heads for the query side;
+ * query adds up to 1 GiB, in which the key side leaves dS (4 or 2 bytes a pair) of some or all heads for the query side,
+ * wherever the call will use it (with or without the causal mask, which the query does not know);
  * a workspace with less of that, down to the formula's size, is accepted, and dS is computed twice instead (FB_BF16: with
- * the same result to the bit).
+ * the same result to the bit).  fb_attn_bwd_call_workspace_bytes gives either size for one mask.
  * Results are deterministic (no floating-point atomics).
  */
 size_t fb_lowrank_attn_bwd_workspace_bytes(int B, int H, int N, int C, int R, fb_dtype dtype);
+
+/*
+ * What one low-rank backward (self- or cross-attention; ALiBi with R = 2) takes: causal 0 or 1, the size of the query for
+ * a call with this mask alone, nothing in it that the call would not use; causal < 0, the formula's size, the least that is
+ * accepted, for a caller short of memory.  The multiplicative backward adds the same room for dS to its own least.
+ */
+size_t fb_attn_bwd_call_workspace_bytes(int B, int H, int N, int M, int C, int R, int causal, fb_dtype dtype);
 
 int fb_lowrank_attn_bwd(const void* q, const void* k, const void* v,
                         const void* phi_q, const void* phi_k,

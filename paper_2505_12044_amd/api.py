@@ -28,6 +28,7 @@ EXPORTS = (
     "fb_lowrank_mulbias_attn_bwd_workspace_bytes", "fb_lowrank_mulbias_attn_bwd",
     "fb_alibi_attn_bwd_workspace_bytes", "fb_alibi_attn_bwd", "fb_lowrank_attn_bwd_noalloc",
     "fb_fold_batch", "fb_lowrank_xattn_fwd_workspace_bytes", "fb_lowrank_xattn_fwd_ws",
+    "fb_attn_bwd_call_workspace_bytes",
 )
 
 FB_STATIC_SCRATCH_BYTES = 64 << 20     # include/flashbias.h
@@ -73,6 +74,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.fb_dense_bias_attn_bwd_workspace_bytes.argtypes = [ci] * 4 + [ci]
     lib.fb_dense_bias_attn_bwd.restype = ci
     lib.fb_dense_bias_attn_bwd.argtypes = [vp] * 11 + [ci] * 5 + [ci, ci, cf, vp, sz, vp]
+    lib.fb_attn_bwd_call_workspace_bytes.restype = sz
+    lib.fb_attn_bwd_call_workspace_bytes.argtypes = [ci] * 7 + [ci]
     lib.fb_lowrank_xattn_bwd_workspace_bytes.restype = sz
     lib.fb_lowrank_xattn_bwd_workspace_bytes.argtypes = [ci] * 6 + [ci]
     lib.fb_lowrank_xattn_bwd.restype = ci
@@ -216,8 +219,8 @@ def fb_alibi_attn_bwd(q, k, v, slopes, out, lse, dout, causal=False, scale: floa
     B, H, N, C = q.shape
     if slopes.dtype != torch.float32 or slopes.numel() != H:
         raise FlashBiasError("slopes must be a float32 tensor with one entry per head")
-    need = fb_alibi_attn_bwd_workspace_bytes(B, H, N, C)
     if workspace is None:
+        need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, 2, int(bool(causal)), _dtype_code(q))
         workspace = _scratch(need, q.device, stream)
     if grads is None:
         grads = (torch.empty_like(q), torch.empty_like(k), torch.empty_like(v))
@@ -272,8 +275,11 @@ def fb_lowrank_mulbias_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, causal=Fa
     R = phi_q.shape[-1]
     if phi_batch_broadcast is None:
         phi_batch_broadcast = phi_q.shape[0] == 1 and B > 1
-    need = fb_lowrank_mulbias_attn_bwd_workspace_bytes(B, H, N, C, R)
     if workspace is None:
+        need = fb_lowrank_mulbias_attn_bwd_workspace_bytes(B, H, N, C, R)
+        if C == 128:      # the query holds the room for dS of either mask
+            full, masked = (lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, 0, m, FB_BF16) for m in (0, 1))
+            need += (masked if causal else full) - max(full, masked)
         workspace = _scratch(need, q.device, stream)
     if grads is None:
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
@@ -344,8 +350,8 @@ def fb_lowrank_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, causal=False, sca
     if phi_batch_broadcast is None:
         phi_batch_broadcast = phi_q is not None and phi_q.shape[0] == 1 and B > 1
     phi_code = _dtype_code(phi_q) if phi_q is not None else _dtype_code(q)
-    need = fb_lowrank_attn_bwd_workspace_bytes(B, H, N, C, R, _dtype_code(q))
     if workspace is None:
+        need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, R, int(bool(causal)), _dtype_code(q))
         workspace = _scratch(need, q.device, stream)
     if grads is None:
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
@@ -397,8 +403,8 @@ def fb_lowrank_xattn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, scale: float = 0
     if phi_batch_broadcast is None:
         phi_batch_broadcast = phi_q is not None and phi_q.shape[0] == 1 and B > 1
     phi_code = _dtype_code(phi_q) if phi_q is not None else _dtype_code(q)
-    need = int(lib.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, M, C, R, _dtype_code(q)))
     if workspace is None:
+        need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, 0, _dtype_code(q))
         workspace = _scratch(need, q.device, stream)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     dpq = dpk = None

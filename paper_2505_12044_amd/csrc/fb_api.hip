@@ -321,6 +321,13 @@ int fb_lowrank_mulbias_attn_fwd(const void* q, const void* k, const void* v,
     return rc == 0 ? FB_OK : (rc < 0 ? FB_ERR_UNSUPPORTED : FB_ERR_LAUNCH);
 }
 
+// Room for dS that some mask of the call takes (N = M: full or causal), bf16.
+static size_t stored_room(int B, int H, int N, int M, int C) {
+    const size_t full = fb_bwd_stored_bytes((long long)B * H, N, M, C, false);
+    const size_t causal = N == M ? fb_bwd_stored_bytes((long long)B * H, N, M, C, true) : 0;
+    return full > causal ? full : causal;
+}
+
 // q', k' (C R bf16 channels each), their gradients (float) and the additive backward's own scratch: what the call checks
 static size_t mulbias_bwd_least(int B, int H, int N, int C, int R) {
     const long long rows = (long long)B * H * N;
@@ -330,7 +337,7 @@ static size_t mulbias_bwd_least(int B, int H, int N, int C, int R) {
 size_t fb_lowrank_mulbias_attn_bwd_workspace_bytes(int B, int H, int N, int C, int R, fb_dtype dtype) {
     (void)dtype;
     if (B <= 0 || H <= 0 || N <= 0 || C <= 0 || R <= 0) return 0;
-    return mulbias_bwd_least(B, H, N, C, R) + fb_bwd_stored_bytes((long long)B * H, N, N, C);
+    return mulbias_bwd_least(B, H, N, C, R) + stored_room(B, H, N, N, C);
 }
 
 int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
@@ -403,14 +410,19 @@ static size_t bwd_ws_impl(int B, int H, int N, int M, int C, int R) {
 }
 
 // What the size queries return: the least a call needs (bwd_ws_impl, what the calls check) with the room that lets one
-// side of the backward take dS from the other.
+// side of the backward take dS from the other, wherever the launch will do that for one of the masks.
 static size_t bwd_ws_query(int B, int H, int N, int M, int C, int R, fb_dtype dtype) {
     const size_t least = bwd_ws_impl(B, H, N, M, C, R);
     if (least == 0) return 0;
-    const long long BH = (long long)B * H;
-    if (dtype != FB_F32) return least + fb_bwd_stored_bytes(BH, N, M, C);
-    const size_t f32 = fb_bwd_f32_workspace_bytes(BH, N, M, C);
+    if (dtype != FB_F32) return least + stored_room(B, H, N, M, C);
+    const size_t f32 = fb_bwd_f32_workspace_bytes((long long)B * H, N, M, C);
     return f32 > least ? f32 : least;
+}
+
+size_t fb_attn_bwd_call_workspace_bytes(int B, int H, int N, int M, int C, int R, int causal, fb_dtype dtype) {
+    if (causal < 0 || dtype == FB_F32) return causal < 0 ? bwd_ws_impl(B, H, N, M, C, R) : bwd_ws_query(B, H, N, M, C, R, dtype);
+    const size_t least = bwd_ws_impl(B, H, N, M, C, R);
+    return least == 0 ? 0 : least + fb_bwd_stored_bytes((long long)B * H, N, M, C, causal != 0);
 }
 
 static int lowrank_bwd_impl(const void* q, const void* k, const void* v,

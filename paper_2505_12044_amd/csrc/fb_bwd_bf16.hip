@@ -1271,16 +1271,16 @@ constexpr size_t kMaxStored = (size_t)1 << 30;      // at a time
 // dS of one head, whole tiles (any int: the size queries come before the limits are checked; at most 2^63).
 size_t ds_head_bytes(int N, int M) { return ((size_t)N + 127) / 128 * 128 * (((size_t)M + 127) / 128 * 128) * 2; }
 // Heads per launch whose dS fits `room` bytes, 0: recompute.
-int stored_heads(int heads, int N, int M, bool causal, bool one_wave, size_t room) {
+int stored_heads(long long heads, int N, int M, bool causal, size_t room) {
     const size_t per = ds_head_bytes(N, M);
     if (room > kMaxStored) room = kMaxStored;
     const long long fit = (long long)(room / per);
     if (fit <= 0) return 0;
     if (!stored_pays(heads, N, M, causal)) return 0;
-    if (fit >= heads) return heads;
-    // the dkv launches' rounds of workgroups (one or two a CU): per head, against those of one launch over all heads
+    if (fit >= heads) return (int)heads;
+    // the dkv launches' rounds of workgroups (one a CU): per head, against those of one launch over all heads
     const int tiles = (M + 127) / 128;
-    const long long units = causal ? (tiles + 1) / 2 : tiles, slots = one_wave ? 256 : 512;
+    const long long units = causal ? (tiles + 1) / 2 : tiles, slots = 256;
     auto rounds = [&](long long h) { return (double)((h * units + slots - 1) / slots); };
     long long best = 0;
     double cost = 1.1 * rounds(heads);
@@ -1383,7 +1383,7 @@ int launch(const BwdParams& pin, hipStream_t stream) {
         // dkv first, chunk by chunk of heads, leaving dS for dq
         const size_t least = (fb_bwd_workspace_bytes(rows, rowsk, CG, pin.R) + 255) & ~(size_t)255;
         const size_t room = pin.workspace_bytes > least ? pin.workspace_bytes - least : 0;
-        const int chunk = DENSE ? (dense_stored_pays(all_heads, pin.N, pin.M, C) ? all_heads : 0) : stored_heads(all_heads, pin.N, pin.M, CAUSAL, K::PIPE, room);
+        const int chunk = DENSE ? (dense_stored_pays(all_heads, pin.N, pin.M, C) ? all_heads : 0) : stored_heads(all_heads, pin.N, pin.M, CAUSAL, room);
         if (chunk > 0) {
             constexpr size_t lds_load = (size_t)kSlotsLd<C, RP, LIMB, CG> * kSlotBytesLd<C, RP, LIMB, CG>;
             static_assert(kSlotsLd<C, RP, LIMB, CG> >= 4 && lds_load >= K::kEpiLds, "ring and epilogue");
@@ -1465,11 +1465,9 @@ size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R) 
     return (((size_t)rows_q * 8 + 15) & ~(size_t)15) + (size_t)(rows_q + rows_k) * w * 2;
 }
 
-size_t fb_bwd_stored_bytes(long long heads, int N, int M, int C) {
-    const size_t per = ds_head_bytes(N, M);
-    if (C != 128 || per > kMaxStored || !stored_pays(heads, N, M, false)) return 0;
-    const size_t fit = kMaxStored / per;
-    return 256 + ((size_t)heads < fit ? (size_t)heads : fit) * per;
+size_t fb_bwd_stored_bytes(long long heads, int N, int M, int C, bool causal) {
+    const int chunk = C != 128 ? 0 : stored_heads(heads, N, M, causal, kMaxStored);
+    return chunk > 0 ? 256 + (size_t)chunk * ds_head_bytes(N, M) : 0;
 }
 
 int fb_launch_bwd_dense_bf16(const BwdParams& p, int C, hipStream_t stream) {

@@ -48,19 +48,15 @@ constexpr size_t kMaxStored = (size_t)1 << 30;
 // the smallest calls on (C 64, 2 heads of 256 34 / 29), where one launch more costs the host what it saves: left to
 // recompute below about 60 us.  Not at 16 channels: a block's recomputation takes 1300 cycles of the matrix pipe, its
 // 8 KB to memory and back more.
-int stored_heads(const BwdParams& p, int C, float*& dS) {
-    const size_t off = d_bytes((long long)p.B * p.H * p.N), per = ds_head_bytes(p.N, p.M);
-    const long long heads = (long long)p.B * p.H;
-    size_t avail = p.workspace_bytes > off ? p.workspace_bytes - off : 0;
+int stored_heads(long long heads, int N, int M, int C, size_t avail) {
     if (avail > kMaxStored) avail = kMaxStored;
-    const long long fit = (long long)(avail / per);
+    const long long fit = (long long)(avail / ds_head_bytes(N, M));
     if (fit <= 0) return 0;
     const long long parts = (heads + fit - 1) / fit, chunk = (heads + parts - 1) / parts;
     // several launches have to be worth filling the chip (four waves to a 32-row tile)
-    const int nq = (p.N + 31) / 32, nk = (p.M + 31) / 32;
+    const long long nq = ((long long)N + 31) / 32, nk = ((long long)M + 31) / 32;
     if ((double)heads * nq * nk * C < 262144.0) return 0;
     if (parts > 1 && chunk * (nq < nk ? nq : nk) < 512) return 0;
-    dS = (float*)((unsigned char*)p.workspace + off);
     return (int)chunk;
 }
 
@@ -536,9 +532,9 @@ int launch_stored(const BwdParams& pin, float* dS, int chunk, hipStream_t stream
 template <int C, int RP, bool DENSE = false>
 int launch(const BwdParams& p, hipStream_t stream) {
     if constexpr (C >= 32 && !DENSE) {
-        float* dS;
-        const int chunk = stored_heads(p, C, dS);
-        if (chunk > 0) return launch_stored<C, RP>(p, dS, chunk, stream);
+        const size_t off = d_bytes((long long)p.B * p.H * p.N);
+        const int chunk = stored_heads((long long)p.B * p.H, p.N, p.M, C, p.workspace_bytes > off ? p.workspace_bytes - off : 0);
+        if (chunk > 0) return launch_stored<C, RP>(p, (float*)((unsigned char*)p.workspace + off), chunk, stream);
     }
     const int rc = launch_side<C, RP, false, DENSE>(p, stream);      // also leaves D for the key side
     return rc != 0 ? rc : launch_side<C, RP, true, DENSE>(p, stream);
@@ -555,16 +551,15 @@ int dispatch_c(const BwdParams& p, hipStream_t stream) {
 
 }  // namespace
 
-// Workspace with which the query side takes dS from the key side instead of recomputing it.
+// Workspace with which the query side takes dS from the key side, by the rule and in the parts of the launch; 0 where it
+// recomputes dS in any case.
 size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C) {
-    const size_t per = ds_head_bytes(N, M);
-    if (C < 32 || per > kMaxStored) return 0;
-    const size_t fit = kMaxStored / per;
-    return d_bytes(heads * N) + ((size_t)heads < fit ? (size_t)heads : fit) * per;
+    const int chunk = C < 32 ? 0 : stored_heads(heads, N, M, C, kMaxStored);
+    return chunk > 0 ? d_bytes(heads * N) + (size_t)chunk * ds_head_bytes(N, M) : 0;
 }
 
 // fp32 tensors and fp32 factors (N queries, M keys; causal needs N = M); p.workspace: at least
-// 4 B H N bytes (the D row sums); with fb_bwd_f32_workspace_bytes of them the query side is one contraction.
+// 4 B H N bytes (the D row sums), and room for dS as far as p.workspace_bytes says.
 // Returns 0 on success, 1 on launch failure, -1 when no instantiation fits.
 int fb_launch_bwd_f32(const BwdParams& p, int C, hipStream_t stream) {
     if (p.R > 64 || (p.causal && p.N != p.M)) return -1;

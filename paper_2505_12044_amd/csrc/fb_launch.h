@@ -31,8 +31,8 @@ bool fb_short_bwd(const BwdParams& p, int C, int rp);
 int fb_launch_bwd_bf16_short(const BwdParams& p, int C, int rp, hipStream_t stream);
 size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R);
 // Room behind that size (from the next multiple of 256 bytes on) with which the dq kernel takes dS from the dkv kernel,
-// 0: no use for it.  p.workspace_bytes says what there is.
-size_t fb_bwd_stored_bytes(long long heads, int N, int M, int C);
+// 0: no use for it.  The launch decides by the same rule from p.workspace_bytes.
+size_t fb_bwd_stored_bytes(long long heads, int N, int M, int C, bool causal);
 // fp32 tensors and fp32 factors: p.workspace holds one float per query row (a prefix of the size above) and, where
 // p.workspace_bytes allows it (fb_bwd_f32_workspace_bytes; 0: no use for more), dS of some or all heads behind them.
 size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C);

@@ -195,6 +195,75 @@ def test_backward_size_queries_take_any_length(lib, C, dtype):
         assert lib.fb_lowrank_attn_bwd_workspace_bytes(1, 1, N, C, 8, dtype) == (N * 8 + 15 & ~15) + 2 * N * (C + 64) * 2
 
 
+def _least(B, H, N, M, C, R):
+    return (B * H * N * 8 + 15 & ~15) + B * H * (N + M) * (C + (64 if R else 0)) * 2
+
+
+def _stored_heads_bf16(heads, N, M, causal):
+    """The launch's rule, every chunk of heads tried: what the pairs save against the extra launch, then rounds of 256
+    workgroups of the key side against one launch over all heads."""
+    up = lambda n: -(-n // 128) * 128
+    per = up(N) * up(M) * 2
+    fit = (1 << 30) // per
+    if fit == 0 or heads * N * ((0.5 if causal else 1.0) * M - 768.0) < 1 << 24:
+        return 0, per
+    if fit >= heads:
+        return heads, per
+    tiles = up(M) // 128
+    units = (tiles + 1) // 2 if causal else tiles
+    rounds = lambda h: -(-h * units // 256)
+    best, cost = 0, 1.1 * rounds(heads)
+    for c in range(fit, 0, -1):
+        if c * 4 < fit:
+            break
+        t = heads // c * rounds(c) + rounds(heads % c)
+        if t < cost:
+            best, cost = c, t
+    return best, per
+
+
+def _stored_heads_f32(heads, N, M, C):
+    up = lambda n: -(-n // 32) * 32
+    per, nq, nk = up(N) * up(M) * 4, -(-N // 32), -(-M // 32)
+    fit = (1 << 30) // per
+    if fit == 0 or heads * nq * nk * C < 262144:
+        return 0, per
+    parts = -(-heads // fit)
+    chunk = -(-heads // parts)
+    return (0 if parts > 1 and chunk * min(nq, nk) < 512 else chunk), per
+
+
+SIZES = [(1, 1, 100), (4, 16, 256), (16, 16, 1000), (4, 16, 1024), (64, 4, 1024), (8, 8, 1100), (64, 4, 1536), (4, 16, 1500), (16, 60, 1100), (1, 16, 2048),
+         (4, 16, 4096), (3, 5, 3000), (2, 8, 8192), (1, 16, 8800), (2, 8, 10000), (1, 16, 12000), (1, 2, 16000), (2, 8, 16384),
+         (1, 1, 23168), (1, 1, 23169), (2, 8, 30000), (1 << 16, 4, 8), (1 << 18, 1, 1)]
+
+
+@pytest.mark.parametrize("B,H,N", SIZES)
+def test_backward_asks_for_no_room_it_does_not_use(lib, B, H, N):
+    """Beyond the formula the size of a call is what the launch's rule for its mask stores, to the byte (bf16: up to the
+    next multiple of 256 behind the formula), and the query, which does not know the mask, the larger of the two."""
+    call = lib.fb_attn_bwd_call_workspace_bytes
+    for M in (N, N // 2 + 1):
+        for R in (0, 8):
+            least = _least(B, H, N, M, 128, R)
+            assert call(B, H, N, M, 128, R, -1, api.FB_BF16) == least
+            sizes = []
+            for causal in (0, 1):
+                chunk, per = _stored_heads_bf16(B * H, N, M, causal)
+                sizes.append(least + (256 + chunk * per if chunk else 0))
+                assert call(B, H, N, M, 128, R, causal, api.FB_BF16) == sizes[-1], (M, R, causal)
+            assert lib.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, M, 128, R, api.FB_BF16) == (max(sizes) if M == N else sizes[0])
+            for C in (32, 64, 128):
+                chunk, per = _stored_heads_f32(B * H, N, M, C)
+                need = max(_least(B, H, N, M, C, R), (B * H * N * 4 + 255 & ~255) + chunk * per if chunk else 0)
+                assert call(B, H, N, M, C, R, 0, api.FB_F32) == call(B, H, N, M, C, R, 1, api.FB_F32) == need
+                assert lib.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, M, C, R, api.FB_F32) == need
+    assert call(B, H, N, N, 64, 8, 0, api.FB_BF16) == _least(B, H, N, N, 64, 8)
+    assert lib.fb_alibi_attn_bwd_workspace_bytes(B, H, N, 128, api.FB_BF16) == lib.fb_lowrank_attn_bwd_workspace_bytes(B, H, N, 128, 2, api.FB_BF16)
+    room = lib.fb_lowrank_attn_bwd_workspace_bytes(B, H, N, 128, 0, api.FB_BF16) - _least(B, H, N, N, 128, 0)
+    assert lib.fb_lowrank_mulbias_attn_bwd_workspace_bytes(B, H, N, 128, 1, api.FB_BF16) == 2 * B * H * N * 128 * 6 + _least(B, H, N, N, 128, 0) + room
+
+
 def test_noalloc_backward_host_checks(lib):
     """The allocation-free backward rejects bad shapes and problems beyond its static scratch on
     the host, before any device call."""

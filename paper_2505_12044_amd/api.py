@@ -9,7 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
-from typing import Optional, Tuple
+from typing import Callable, Optional, Tuple
 
 import torch
 
@@ -126,14 +126,26 @@ def _stream(stream) -> Optional[int]:
     return h or None
 
 
-def _scratch(nbytes: int, device, stream) -> torch.Tensor:
-    """A workspace the wrapper allocates itself.  The kernels run on `stream` (a Stream or a raw handle); when
+def _scratch(nbytes: int, device, stream, least: Optional[Callable[[], int]] = None) -> torch.Tensor:
+    """A workspace the wrapper allocates itself, of `least()` bytes (what the call accepts at a pinch) where there is no
+    memory for `nbytes`.  The kernels run on `stream` (a Stream or a raw handle); when
     that is not torch's current stream the caching allocator must be told, or it could hand the block to
     other work as soon as the tensor is dropped."""
-    ws = torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
+    try:
+        ws = torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        if least is None or least() >= nbytes:
+            raise
+        ws = torch.empty(max(int(least()), 16), dtype=torch.uint8, device=device)
     if stream is not None and _stream(stream) != _stream(None):
         ws.record_stream(stream if hasattr(stream, "cuda_stream") else torch.cuda.ExternalStream(int(stream), device=device))
     return ws
+
+
+def _bwd_scratch(lib, B, H, N, M, C, R, causal, dtype_code, device, stream) -> torch.Tensor:
+    """Workspace of one low-rank backward: with the room for dS that it uses (up to 1 GiB), without where memory is short."""
+    size = lambda mask: lib.fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, mask, dtype_code)
+    return _scratch(size(int(bool(causal))), device, stream, lambda: size(-1))
 
 
 def _check(status: int, what: str) -> None:
@@ -220,8 +232,7 @@ def fb_alibi_attn_bwd(q, k, v, slopes, out, lse, dout, causal=False, scale: floa
     if slopes.dtype != torch.float32 or slopes.numel() != H:
         raise FlashBiasError("slopes must be a float32 tensor with one entry per head")
     if workspace is None:
-        need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, 2, int(bool(causal)), _dtype_code(q))
-        workspace = _scratch(need, q.device, stream)
+        workspace = _bwd_scratch(lib, B, H, N, N, C, 2, causal, _dtype_code(q), q.device, stream)
     if grads is None:
         grads = (torch.empty_like(q), torch.empty_like(k), torch.empty_like(v))
     dq, dk, dv = grads
@@ -276,11 +287,12 @@ def fb_lowrank_mulbias_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, causal=Fa
     if phi_batch_broadcast is None:
         phi_batch_broadcast = phi_q.shape[0] == 1 and B > 1
     if workspace is None:
-        need = fb_lowrank_mulbias_attn_bwd_workspace_bytes(B, H, N, C, R)
+        need = least = fb_lowrank_mulbias_attn_bwd_workspace_bytes(B, H, N, C, R)
         if C == 128:      # the query holds the room for dS of either mask
-            full, masked = (lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, 0, m, FB_BF16) for m in (0, 1))
-            need += (masked if causal else full) - max(full, masked)
-        workspace = _scratch(need, q.device, stream)
+            full, masked, plain = (lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, 0, m, FB_BF16) for m in (0, 1, -1))
+            least -= max(full, masked) - plain
+            need = least + (masked if causal else full) - plain
+        workspace = _scratch(need, q.device, stream, lambda: least)
     if grads is None:
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         dpq = torch.empty((B, H, N, R), dtype=phi_q.dtype, device=q.device)
@@ -343,7 +355,9 @@ def fb_lowrank_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, causal=False, sca
                         phi_batch_broadcast: Optional[bool] = None, workspace=None, grads=None,
                         stream=None):
     """dq, dk, dv, dphi_q, dphi_k for an upstream gradient dout.  dphi_* are [B,H,N,R]
-    (per batch element) in the factors' dtype; None when R = 0."""
+    (per batch element) in the factors' dtype; None when R = 0.  Without a workspace of the caller's the binding
+    allocates one for the call: linear in B H N, and up to 1 GiB more for dS (bf16 at C = 128, fp32 from C = 32 on)
+    where the call uses it and the memory is there; any workspace from the linear size on is taken."""
     lib = load_library()
     B, H, N, C = q.shape
     R = 0 if phi_q is None else phi_q.shape[-1]
@@ -351,8 +365,7 @@ def fb_lowrank_attn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, causal=False, sca
         phi_batch_broadcast = phi_q is not None and phi_q.shape[0] == 1 and B > 1
     phi_code = _dtype_code(phi_q) if phi_q is not None else _dtype_code(q)
     if workspace is None:
-        need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, N, C, R, int(bool(causal)), _dtype_code(q))
-        workspace = _scratch(need, q.device, stream)
+        workspace = _bwd_scratch(lib, B, H, N, N, C, R, causal, _dtype_code(q), q.device, stream)
     if grads is None:
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         dpq = dpk = None
@@ -404,8 +417,7 @@ def fb_lowrank_xattn_bwd(q, k, v, phi_q, phi_k, out, lse, dout, scale: float = 0
         phi_batch_broadcast = phi_q is not None and phi_q.shape[0] == 1 and B > 1
     phi_code = _dtype_code(phi_q) if phi_q is not None else _dtype_code(q)
     if workspace is None:
-        need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, 0, _dtype_code(q))
-        workspace = _scratch(need, q.device, stream)
+        workspace = _bwd_scratch(lib, B, H, N, M, C, R, False, _dtype_code(q), q.device, stream)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     dpq = dpk = None
     if R:

@@ -89,3 +89,25 @@ def test_slope_gradient():
         got.append((rows,) + tuple(api.fb_alibi_attn_bwd(q, k, v, slopes, out, lse, do, causal=True, workspace=ws, dslope_rows=rows)))
     torch.cuda.synchronize()
     assert all(torch.equal(x, y) for x, y in zip(*got))
+
+
+def test_runs_where_there_is_no_memory_for_ds():
+    """A process that may take no more than the least workspace: the same gradients, without dS in memory."""
+    torch.manual_seed(6)
+    B, H, N = 2, 8, 2200
+    t = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    q, k, v, do, pq, pk = t(B, H, N, C), t(B, H, N, C), t(B, H, N, C), t(B, H, N, C), t(1, H, N, 8), t(1, H, N, 8)
+    out, lse = api.fb_lowrank_attn_fwd(q, k, v, pq, pk)
+    ref = api.fb_lowrank_attn_bwd(q, k, v, pq, pk, out, lse, do)
+    grads = tuple(torch.empty_like(x) for x in ref)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    try:
+        torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + _least(B, H, N, N, 8) + (48 << 20)) / total)
+        got = api.fb_lowrank_attn_bwd(q, k, v, pq, pk, out, lse, do, grads=grads)
+        torch.cuda.synchronize()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    for x, y in zip(got, ref):
+        assert torch.equal(x, y)

@@ -327,6 +327,27 @@ def test_hand_placed_mfma_forms_keep_their_wait_states():
     assert seen > 0 and found == [], found[:3]
 
 
+def test_scratch_falls_back_to_the_least_size(monkeypatch):
+    """A backward that fits without the room for dS runs without it; any other shortage is reported as before."""
+    import torch
+    real, limit = torch.empty, 100 << 20
+
+    def empty(n, **kw):
+        if n > limit:
+            raise torch.OutOfMemoryError(f"{n} bytes")
+        return real(n, **kw)
+    monkeypatch.setattr(torch, "empty", empty)
+    lib = api.load_library()
+    shape = (1, 4, 4096, 4096, 128, 8)
+    need, least = (lib.fb_attn_bwd_call_workspace_bytes(*shape, m, api.FB_BF16) for m in (0, -1))
+    assert least < limit < need
+    assert api._bwd_scratch(lib, *shape, False, api.FB_BF16, "cpu", None).numel() == least
+    for nbytes, small in ((limit + 1, None), (limit + 1, limit + 1), (limit + 2, limit + 1)):
+        with pytest.raises(torch.OutOfMemoryError):
+            api._scratch(nbytes, "cpu", None, small and (lambda: small))
+    assert api._scratch(limit, "cpu", None, lambda: 64).numel() == limit
+
+
 def test_scratch_is_recorded_on_the_stream_that_uses_it(monkeypatch):
     """A workspace the binding allocates is dropped when the call returns: the allocator has to know the stream the kernels
     run on, also where the caller passes its raw handle."""

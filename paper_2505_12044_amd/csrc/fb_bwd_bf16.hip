@@ -1284,7 +1284,9 @@ int stored_heads(long long heads, int N, int M, bool causal, size_t room) {
     auto rounds = [&](long long h) { return (double)((h * units + slots - 1) / slots); };
     long long best = 0;
     double cost = 1.1 * rounds(heads);
-    for (long long c = fit; c >= 1 && c * 4 >= fit; c--) {
+    // (of the chunks that take equally many rounds the largest is never the worse one: the next smaller one tried is the
+    // largest of one round less, a few steps where the head counts of short heads are thousands)
+    for (long long c = fit; c >= 1 && c * 4 >= fit; c = ((long long)rounds(c) - 1) * slots / units) {
         const long long whole = heads / c, rest = heads - whole * c;
         const double t = whole * rounds(c) + (rest > 0 ? rounds(rest) : 0.0);
         if (t < cost) { best = c; cost = t; }

@@ -234,7 +234,7 @@ def _stored_heads_f32(heads, N, M, C):
 
 
 SIZES = [(1, 1, 100), (4, 16, 256), (16, 16, 1000), (4, 16, 1024), (64, 4, 1024), (8, 8, 1100), (64, 4, 1536), (4, 16, 1500), (16, 60, 1100), (1, 16, 2048),
-         (4, 16, 4096), (3, 5, 3000), (2, 8, 8192), (1, 16, 8800), (2, 8, 10000), (1, 16, 12000), (1, 2, 16000), (2, 8, 16384),
+         (4, 16, 4096), (3, 5, 3000), (40, 40, 800), (100, 50, 900), (33, 33, 1900), (2, 8, 8192), (1, 16, 8800), (2, 8, 10000), (1, 16, 12000), (1, 2, 16000), (2, 8, 16384),
          (1, 1, 23168), (1, 1, 23169), (2, 8, 30000), (1 << 16, 4, 8), (1 << 18, 1, 1)]
 
 

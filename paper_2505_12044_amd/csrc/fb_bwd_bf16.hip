@@ -1270,7 +1270,7 @@ bool dense_stored_pays(long long heads, int N, int M, int C) {
 constexpr size_t kMaxStored = (size_t)1 << 30;      // at a time
 // dS of one head, whole tiles (any int: the size queries come before the limits are checked; at most 2^63).
 size_t ds_head_bytes(int N, int M) { return ((size_t)N + 127) / 128 * 128 * (((size_t)M + 127) / 128 * 128) * 2; }
-// Heads per launch whose dS fits `room` bytes, 0: recompute.
+// Heads per launch whose dS fits `room` bytes, 0: recompute.  (256 CUs where there is no device to ask, as in a size query on another host.)
 int stored_heads(long long heads, int N, int M, bool causal, size_t room) {
     const size_t per = ds_head_bytes(N, M);
     if (room > kMaxStored) room = kMaxStored;
@@ -1280,7 +1280,8 @@ int stored_heads(long long heads, int N, int M, bool causal, size_t room) {
     if (fit >= heads) return (int)heads;
     // the dkv launches' rounds of workgroups (one a CU): per head, against those of one launch over all heads
     const int tiles = (M + 127) / 128;
-    const long long units = causal ? (tiles + 1) / 2 : tiles, slots = 256;
+    const int cus = fb_cu_count();
+    const long long units = causal ? (tiles + 1) / 2 : tiles, slots = cus > 0 ? cus : 256;
     auto rounds = [&](long long h) { return (double)((h * units + slots - 1) / slots); };
     long long best = 0;
     double cost = 1.1 * rounds(heads);

@@ -440,6 +440,7 @@ int dispatch_rp(const BwdParams& p, int rp, int cus, hipStream_t stream) {
 //   to be enough of them.  C 16 (two 16-column groups, no dead rows): N 384 with 1024 heads 126 / 81, 256 heads
 //   48.6 / 24.5, 64 heads 24.7 / 21.9.  Causal 1.3-2.4 throughout.
 //   Without factors there is no pre-pass to save and less to recompute: 0.86-1.2 full, causal 1.02-1.5 from 161 keys on.
+//   (16 heads a 32-key tile, 8 at 16 channels, at 256 CUs.)
 //   Fewer queries than keys 1.25-3 (N 32, M 384); more queries than keys stream through one workgroup: 0.3-1.2, left.
 bool fb_short_bwd(const BwdParams& p, int C, int rp) {
     if (C > 32 || rp > 32 || p.grad_f32 || p.slopes != nullptr) return false;
@@ -449,7 +450,7 @@ bool fb_short_bwd(const BwdParams& p, int C, int rp) {
     if (BH >= (1LL << 30)) return false;
     if (rp == 0) return p.causal && nkb > 5;
     if (p.phi_f32 || p.R % 4 != 0) return false;
-    return p.causal || nkb <= 6 || nqb <= 4 || BH >= (C == 16 ? 8 : 16) * nkb;
+    return p.causal || nkb <= 6 || nqb <= 4 || BH * 256 >= (long long)(C == 16 ? 8 : 16) * nkb * fb_cu_count();
 }
 
 int fb_launch_bwd_bf16_short(const BwdParams& p, int C, int rp, hipStream_t stream) {

@@ -361,6 +361,7 @@ int dispatch_rp(const FwdParams& p, int rp, int nw, int cus, hipStream_t stream)
 // Causal the ring kernel's 128-row tiles do up to twice the work: 1.2-2.3 throughout (C 32, N 256: 256 heads 14.7 / 7.6,
 // 1024 heads 27.7 / 24.4), but for 32 factor columns at many heads (0.95-0.98) and fp32 factors (N 384: 44.1 / 31.5,
 // N 256: 256 heads 18.6 / 12.9, 400 heads 21.4 / 21.7).
+// Head counts are lines in rounds of workgroups, measured at 256 CUs: one and two rounds, five eighths and half of one.
 bool fb_short_fwd(const FwdParams& p, int C, int rp) {
     if (C > 32 || rp > 32 || p.N != p.M || p.slopes != nullptr) return false;
     const long long BH = (long long)p.B * p.H;
@@ -369,13 +370,14 @@ bool fb_short_fwd(const FwdParams& p, int C, int rp) {
     const size_t row = C == 16 ? (rp == 0 ? Cfg<16, 0>::kRow : rp == 16 ? Cfg<16, 16>::kRow : Cfg<16, 32>::kRow)
                                : (rp == 0 ? Cfg<32, 0>::kRow : rp == 16 ? Cfg<32, 16>::kRow : Cfg<32, 32>::kRow);
     if ((size_t)2 * nkb * 32 * row > kLdsBytes) return false;
-    if (rp > 0 && p.phi_f32) return p.causal && (nkb > 8 || (nkb > 4 && BH <= 256));
+    const int cus = fb_cu_count();
+    if (rp > 0 && p.phi_f32) return p.causal && (nkb > 8 || (nkb > 4 && BH <= cus));
     const bool wide = C == 32 && rp == 32;
-    if (p.causal) return !wide || nkb <= 4 || nkb > 8 || BH <= 512;
+    if (p.causal) return !wide || nkb <= 4 || nkb > 8 || BH <= 2LL * cus;
     if (nkb <= 4) return true;
     if (rp == 0 || (C == 16 && rp == 16 && p.R % 8 == 0)) return false;
-    if (wide) return BH >= 160 && BH <= 256;
-    return nkb <= 8 || BH >= 128;
+    if (wide) return BH * 8 >= 5LL * cus && BH <= cus;
+    return nkb <= 8 || BH * 2 >= cus;
 }
 
 int fb_launch_fwd_bf16_short(const FwdParams& p, int C, int rp, hipStream_t stream) {

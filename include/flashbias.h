@@ -236,8 +236,8 @@ int fb_lowrank_mulbias_attn_bwd(const void* q, const void* k, const void* v,
  * adds 32-channel copies of v and dout, 128 more bytes per row).  For FB_F32 at C >= 32 and FB_BF16 at C = 128 the
  * query adds up to 1 GiB, in which the key side leaves dS (4 or 2 bytes a pair) of some or all heads for the query side,
  * wherever the call will use it (with or without the causal mask, which the query does not know);
- * a workspace with less of that, down to the formula's size, is accepted, and dS is computed twice instead (FB_BF16: with
- * the same result to the bit).  fb_attn_bwd_call_workspace_bytes gives either size for one mask.
+ * a workspace with less of that, down to the formula's size, is accepted, and dS is computed twice instead, with
+ * the same result to the bit.  fb_attn_bwd_call_workspace_bytes gives either size for one mask.
  * Results are deterministic (no floating-point atomics).
  */
 size_t fb_lowrank_attn_bwd_workspace_bytes(int B, int H, int N, int C, int R, fb_dtype dtype);
@@ -260,10 +260,10 @@ int fb_lowrank_attn_bwd(const void* q, const void* k, const void* v,
 /*
  * Allocation-free variant of fb_lowrank_attn_bwd, for callers that cannot allocate device
  * memory or carry a workspace: code under HIP graph capture, tight serving / training loops,
- * harnesses that forbid hipMalloc.  Same arguments without the workspace, same kernels and
- * (bit-identical) results as with a workspace of FB_STATIC_SCRATCH_BYTES; the scratch that
- * fb_lowrank_attn_bwd takes from the caller lives in a static device array of that size inside
- * the library, one copy per GPU, held from library load until the process ends.  The call
+ * harnesses that forbid hipMalloc.  Same arguments without the workspace, same
+ * (bit-identical) results; the scratch that fb_lowrank_attn_bwd takes from the caller lives in
+ * a static device array of FB_STATIC_SCRATCH_BYTES inside the library, one copy per GPU, held
+ * from library load until the process ends (dS is stored as far as it has the room).  The call
  * allocates and frees nothing.
  *   Limit: the workspace formula above (without the room for dS) <= FB_STATIC_SCRATCH_BYTES
  *   (e.g. B H N <= 86480 rows at C = 128 with factors); larger problems return

@@ -24,6 +24,8 @@
 // sums meet in LDS at the end.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "fb_f32_tiles.h"
 #include "fb_launch.h"
 #include "fb_params.h"
@@ -46,7 +48,9 @@ constexpr size_t kMaxStored = (size_t)1 << 30;
 // Heads whose dS the workspace takes at a time, 0 where the query side recomputes it.  Stored against recomputed,
 // kernel times (us): C 32, R 8 64 heads of N 1024 333 / 290; C 64 16 heads of N 1500 372 / 301; C 128 790 / 553; from
 // the smallest calls on (C 64, 2 heads of 256 34 / 29), where one launch more costs the host what it saves: left to
-// recompute below about 60 us.  Not at 16 channels: a block's recomputation takes 1300 cycles of the matrix pipe, its
+// recompute below about 60 us.  Neither the mask nor short heads move the line (backward calls, before / now): causal C 32,
+// 64 heads of 1024 323 / 263; C 64, 262144 heads of one row 13455 / 10948, 4096 of 65 causal 628 / 525, 4096 of 4 x 512
+// 1549 / 1218.  Not at 16 channels: a block's recomputation takes 1300 cycles of the matrix pipe, its
 // 8 KB to memory and back more.
 int stored_heads(long long heads, int N, int M, int C, size_t avail) {
     if (avail > kMaxStored) avail = kMaxStored;
@@ -78,9 +82,11 @@ struct Cfg {
 // training-side baseline of Sec. 4.3); dBias = dS is written by the query-side launch, zero where masked.
 // dS: the heads head0.. of this launch, dS transposed, [keys][queries] padded to whole tiles (STORE: written; the query
 // side's second contraction is then a launch of its own, bwd_f32_dq_kernel).
-template <int C, int RP, bool KEYSIDE, bool DENSE = false, bool STORE = false>
+// QSCALE (key side): the scale is multiplied into the streamed q rows, as the forward and the query side do, so that both
+// sides hold the same scores to the bit; without it the lane's k row carries it (a power of two: the same bits).
+template <int C, int RP, bool KEYSIDE, bool DENSE = false, bool STORE = false, bool QSCALE = false>
 __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bwd_f32_kernel(BwdParams p, float* __restrict__ Dws, int kw_log2, float* __restrict__ dS, int head0) {
-    static_assert(!STORE || (KEYSIDE && !DENSE), "the key side stores dS");
+    static_assert(!(STORE || QSCALE) || (KEYSIDE && !DENSE), "the key side stores dS");
     using K = Cfg<C, RP, KEYSIDE>;
     __shared__ __align__(16) float otile[kThreads / 64][32 * OPITCH];
     const int L = (blockIdx.x & 7) * p.tiles_per_xcd + (blockIdx.x >> 3);      // contiguous runs of units per XCD
@@ -130,12 +136,12 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
         dbg = (float*)p.dbias + (size_t)bh * N * M;
     }
 
-    // ---- lane-side operands: the scale sits on the lane side's x columns ----
+    // ---- lane-side operands: the scale sits on the lane side's x columns (QSCALE: on the streamed side's) ----
     f32x4 ar[K::NCH], er[K::NC2];
 #pragma unroll
     for (int i = 0; i < K::NCH; i++) {
         ar[i] = own_chunk<C>(xrow, prow, R, i, hf);
-        if (8 * i < C) ar[i] *= p.scale;
+        if (8 * i < C && !QSCALE) ar[i] *= p.scale;
     }
 #pragma unroll
     for (int i = 0; i < K::NC2; i++) er[i] = *(const f32x4*)(erow + 8 * i + 4 * hf);
@@ -256,7 +262,8 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
         }
 #pragma unroll
         for (int n = 0; n < K::NALL; n++) {
-            const f32x4 a = rc[n % K::NPF];
+            f32x4 a = rc[n % K::NPF];
+            if (QSCALE && 8 * n < C) a *= p.scale;
             if (n + K::NPF < K::NALL) rc[n % K::NPF] = load_row(blk, n + K::NPF);
 #pragma unroll
             for (int e = 0; e < 4; e++) {
@@ -363,17 +370,23 @@ __global__ __launch_bounds__(kThreads, (Cfg<C, RP, KEYSIDE>::kMinWaves)) void bw
     }
 }
 
-// D_i = sum_c dout_ic out_ic of `rows` rows: C / 4 threads a row.  Bound by its reads.
+// D_i = sum_c dout_ic out_ic of `rows` rows: two threads a row, each summing as a lane of the query side does where that
+// runs first, so the two forms agree to the bit.  Bound by its reads.
 template <int C>
 __global__ __launch_bounds__(256) void bwd_f32_d_kernel(const float* __restrict__ out, const float* __restrict__ dout, float* __restrict__ D, long long rows) {
-    constexpr int T = C / 4;
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x, row = i / T;
-    if (row >= rows) return;                 // whole rows leave together (256 is a multiple of T)
-    const f32x4 a = *(const f32x4*)(out + i * 4), b = *(const f32x4*)(dout + i * 4);
-    float s = fmaf(a[0], b[0], fmaf(a[1], b[1], fmaf(a[2], b[2], a[3] * b[3])));
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x, row = i >> 1;
+    const int hf = (int)(i & 1);
+    if (row >= rows) return;                 // both threads of a row leave together
+    const size_t off = (size_t)row * C + 4 * hf;
+    float s = 0.f;
 #pragma unroll
-    for (int m = 1; m < T; m <<= 1) s += __shfl_xor(s, m);
-    if (i % T == 0) D[row] = s;
+    for (int n = 0; n < C / 8; n++) {
+        const f32x4 a = *(const f32x4*)(dout + off + 8 * n), b = *(const f32x4*)(out + off + 8 * n);
+#pragma unroll
+        for (int e = 0; e < 4; e++) s = fmaf(a[e], b[e], s);
+    }
+    s += __shfl_xor(s, 1);
+    if (hf == 0) D[row] = s;
 }
 
 // d[q | phi_q] = dS [k | phi_k] from the dS that the key side stored: lanes are queries, both operands of a k-step are 4
@@ -486,43 +499,53 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_f32_dq_kernel(BwdParams p, co
     }
 }
 
+// Heads a launch of this call is laid out for: those that the room a size query asks for takes at a time.  The split of a
+// tile over waves, which orders the sums, follows from them and not from the heads that the given workspace leaves to one
+// launch, so the gradients do not depend on the workspace.
+template <int C, bool DENSE>
+long long planned_heads(const BwdParams& p) {
+    const long long heads = (long long)p.B * p.H;
+    const int chunk = C < 32 || DENSE ? 0 : stored_heads(heads, p.N, p.M, C, kMaxStored);
+    return chunk > 0 ? chunk : heads;
+}
+
 // Tiles of one launch over `heads` heads, `rows` rows a head: p's counters, the split of a tile over waves.
-int set_tiles(BwdParams& p, long long heads, int rows, int other) {
+int set_tiles(BwdParams& p, int heads, long long planned, int rows, int other) {
     const int tiles = (rows + 31) / 32;
-    const int kw = f32_split(heads * tiles, (other + BT - 1) / BT, 4);
+    const int kw = f32_split(planned * tiles, (other + BT - 1) / BT, 4);
     int kw_log2 = 0;
     while ((1 << kw_log2) < kw) kw_log2++;
     const int qw = (kThreads / 64) / kw;
     p.n_tiles = (tiles + qw - 1) / qw;
-    p.total_tiles = (int)heads * p.n_tiles;
+    p.total_tiles = heads * p.n_tiles;
     p.tiles_per_xcd = (p.total_tiles + 7) / 8;
     return kw_log2;
 }
 
-template <int C, int RP, bool KEYSIDE, bool DENSE>
+template <int C, int RP, bool KEYSIDE, bool DENSE, bool QSCALE = false>
 int launch_side(const BwdParams& pin, hipStream_t stream) {
     BwdParams p = pin;
-    const int kw_log2 = set_tiles(p, (long long)p.B * p.H, KEYSIDE ? p.M : p.N, KEYSIDE ? p.N : p.M);
-    hipLaunchKernelGGL((bwd_f32_kernel<C, RP, KEYSIDE, DENSE>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
+    const int kw_log2 = set_tiles(p, p.B * p.H, planned_heads<C, DENSE>(p), KEYSIDE ? p.M : p.N, KEYSIDE ? p.N : p.M);
+    hipLaunchKernelGGL((bwd_f32_kernel<C, RP, KEYSIDE, DENSE, false, QSCALE>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
                        (float*)p.workspace, kw_log2, (float*)nullptr, 0);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
 // Key side first, leaving dS for the query side, `chunk` heads at a time.
-template <int C, int RP>
+template <int C, int RP, bool QSCALE>
 int launch_stored(const BwdParams& pin, float* dS, int chunk, hipStream_t stream) {
-    const long long rows = (long long)pin.B * pin.H * pin.N;
-    hipLaunchKernelGGL((bwd_f32_d_kernel<C>), dim3((unsigned)((rows * (C / 4) + 255) / 256)), dim3(256), 0, stream, (const float*)pin.out,
+    const long long rows = (long long)pin.B * pin.H * pin.N, planned = planned_heads<C, false>(pin);
+    hipLaunchKernelGGL((bwd_f32_d_kernel<C>), dim3((unsigned)((rows * 2 + 255) / 256)), dim3(256), 0, stream, (const float*)pin.out,
                        (const float*)pin.dout, (float*)pin.workspace, rows);
     if (hipGetLastError() != hipSuccess) return 1;
     const int heads = pin.B * pin.H;
     for (int h0 = 0; h0 < heads; h0 += chunk) {
         const int n = heads - h0 < chunk ? heads - h0 : chunk;
         BwdParams p = pin;
-        int kw_log2 = set_tiles(p, n, p.M, p.N);
-        hipLaunchKernelGGL((bwd_f32_kernel<C, RP, true, false, true>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
+        int kw_log2 = set_tiles(p, n, planned, p.M, p.N);
+        hipLaunchKernelGGL((bwd_f32_kernel<C, RP, true, false, true, QSCALE>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p,
                            (float*)p.workspace, kw_log2, dS, h0);
-        kw_log2 = set_tiles(p, n, p.N, p.M);
+        kw_log2 = set_tiles(p, n, planned, p.N, p.M);
         hipLaunchKernelGGL((bwd_f32_dq_kernel<C, RP>), dim3(8 * p.tiles_per_xcd), dim3(kThreads), 0, stream, p, (const float*)dS, h0, kw_log2);
         if (hipGetLastError() != hipSuccess) return 1;
     }
@@ -532,9 +555,16 @@ int launch_stored(const BwdParams& pin, float* dS, int chunk, hipStream_t stream
 template <int C, int RP, bool DENSE = false>
 int launch(const BwdParams& p, hipStream_t stream) {
     if constexpr (C >= 32 && !DENSE) {
+        int exponent = 0;
+        const bool pow2 = std::frexp(p.scale, &exponent) == 0.5f;
         const size_t off = d_bytes((long long)p.B * p.H * p.N);
         const int chunk = stored_heads((long long)p.B * p.H, p.N, p.M, C, p.workspace_bytes > off ? p.workspace_bytes - off : 0);
-        if (chunk > 0) return launch_stored<C, RP>(p, (float*)((unsigned char*)p.workspace + off), chunk, stream);
+        float* const dS = (float*)((unsigned char*)p.workspace + off);
+        if (chunk > 0) return pow2 ? launch_stored<C, RP, false>(p, dS, chunk, stream) : launch_stored<C, RP, true>(p, dS, chunk, stream);
+        if (!pow2) {
+            const int rc = launch_side<C, RP, false, DENSE>(p, stream);
+            return rc != 0 ? rc : launch_side<C, RP, true, DENSE, true>(p, stream);
+        }
     }
     const int rc = launch_side<C, RP, false, DENSE>(p, stream);      // also leaves D for the key side
     return rc != 0 ? rc : launch_side<C, RP, true, DENSE>(p, stream);

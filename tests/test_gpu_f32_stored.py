@@ -73,3 +73,38 @@ def test_parts_and_recomputed(causal, C, R):
 
 def test_an_oversized_workspace_is_fine():
     _run(2, 8, 700, 700, 64, 4, False, True, [(1, 7)], ws_heads=40)
+
+
+@pytest.mark.parametrize("N,M,causal", [(601, 601, False), (601, 601, True), (640, 577, False), (330, 900, False)])
+@pytest.mark.parametrize("C,R,scale", [(32, 8, 0.0), (64, 3, 0.0), (64, 8, 0.3), (128, 16, 0.0), (128, 0, 0.25)])
+def test_same_bits_with_any_workspace(N, M, causal, C, R, scale):
+    """60 heads: dS of all of them, of 35 (two launches of 30) and of none, and on the static scratch (which takes a few
+    heads at a time, or none): the scores, D and the order of the sums are the same, so are the gradients."""
+    torch.manual_seed(N + C)
+    B, H = 15, 4
+    t = lambda *s: torch.randn(*s, device="cuda")
+    q, k, v, do = t(B, H, N, C), t(B, H, M, C), t(B, H, M, C), t(B, H, N, C)
+    pq, pk = (t(1, H, N, R), t(1, H, M, R)) if R else (None, None)
+    kw = {"scale": scale}
+    if N == M:
+        kw["causal"] = causal
+        fwd, bwd = api.fb_lowrank_attn_fwd, api.fb_lowrank_attn_bwd
+    else:
+        fwd, bwd = api.fb_lowrank_xattn_fwd, api.fb_lowrank_xattn_bwd
+    out, lse = fwd(q, k, v, pq, pk, **kw)
+    least = api.load_library().fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, -1, api.FB_F32)
+    d = (B * H * N * 4 + 255) // 256 * 256
+    got = [bwd(q, k, v, pq, pk, out, lse, do, **kw)]
+    for heads in (60, 35, 0):
+        room = d + heads * _up(N) * _up(M) * 4
+        # (none: the sizes are such that the least workspace leaves no room for it)
+        ws = torch.empty(max(least, room), dtype=torch.uint8, device="cuda")
+        got.append(bwd(q, k, v, pq, pk, out, lse, do, workspace=ws, **kw))
+    if N == M:
+        grads = tuple(None if x is None else torch.empty_like(x) for x in got[0])
+        got.append(api.fb_lowrank_attn_bwd_noalloc(q, k, v, pq, pk, out, lse, do, grads, **kw))
+    torch.cuda.synchronize()
+    for n, other in enumerate(got[1:]):
+        for name, x, y in zip(NAMES, got[0], other):
+            if x is not None:
+                assert torch.equal(x, y), (name, n, float((x - y).abs().max()))

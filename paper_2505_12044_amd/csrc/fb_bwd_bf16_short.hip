@@ -434,23 +434,47 @@ int dispatch_rp(const BwdParams& p, int rp, int cus, hipStream_t stream) {
 
 }  // namespace
 
-// Kernel times against the pair of kernels of fb_bwd_bf16.hip (those / this, us; pre-pass included), full attention:
-//   C 32, R 16: N 64 1.8 (256 heads 12.2 / 6.7), N 128 1.5, N 192 1.1-1.4; N 384 with 1024 heads 136 / 115, 256 heads
-//   43.1 / 34.2, 128 heads 29.6 / 30.3, 64 heads 22.5 / 28.1: one workgroup takes a whole head, so longer heads have
-//   to be enough of them.  C 16 (two 16-column groups, no dead rows): N 384 with 1024 heads 126 / 81, 256 heads
-//   48.6 / 24.5, 64 heads 24.7 / 21.9.  Causal 1.3-2.4 throughout.
-//   Without factors there is no pre-pass to save and less to recompute: 0.86-1.2 full, causal 1.02-1.5 from 161 keys on.
-//   (16 heads a 32-key tile, 8 at 16 channels, at 256 CUs.)
-//   Fewer queries than keys 1.25-3 (N 32, M 384); more queries than keys stream through one workgroup: 0.3-1.2, left.
+// Kernel times against the pair of kernels of fb_bwd_bf16.hip (those / this, pre-pass included), 16 to 4096 heads of every
+// length in steps of 32, 256 CUs, bf16 factors.  One workgroup takes a whole head, so longer heads have to be enough of them
+// (16 a 32-key tile, 8 at 16 channels), and beyond one head a CU the last round has to be full.
+//   C 32, 16 factor columns, full: up to 64 keys 1.06-1.8 (beyond twelve rounds 0.93); 65 to 128 keys 1.3-1.46 in one round, 0.78-1.02 beyond (half of the
+//   six waves only stage rows); up to 192 keys 1.05-1.3 in one round, 1.0-1.18 in full rounds, 0.88-0.97 in others; 224 and
+//   256 keys the same, but no more than 0.92-1.0 from the fourth and fifth round on; beyond 256 keys 1.02-1.25 in full rounds,
+//   0.85-0.98 in others.  Causal: 1.0-1.7, but for 65 to 128 and 224 keys (0.86-1.0 in three rounds and from five on) and 160
+//   and 192 keys in many rounds that are not full (0.95).
+//   32 columns: 1.05-1.9 up to 192 keys (65 to 128 in many rounds 0.91-0.95), beyond 1.0-1.4 in rounds that are full enough;
+//   causal 1.0-2.0.
+//   C 16 (two 16-column groups, no dead rows): 1.07-2.4, but for 65 to 96 keys in many rounds (0.87-0.98).
+//   Without factors there is no pre-pass to save and less to recompute: full 0.86-1.2, never; causal from 161 keys on 1.3-1.44
+//   in one round, 1.0-1.2 in two, 0.84-1.0 beyond at C 32 up to 256 keys; C 16 and longer heads 1.0-2.
+//   Fewer queries than keys 1.0-2.7, once no more than three quarters as many in any number of rounds; more queries than keys
+//   stream through one workgroup: 0.3-1.2, never.
+static bool rounds_pay(int C, int rp, int nkb, bool causal, const FbHeadRounds r) {
+    if (r.rounds == 1) return true;
+    if (nkb == 3 && (C == 16 || rp == 32)) return r.rounds <= (causal ? 10 : 6);
+    if (C == 16) return true;
+    if (rp == 0) return nkb <= 8 ? r.rounds == 2 && (nkb != 7 || r.fill >= 0.75) : r.rounds > 2 || r.fill >= 0.8;
+    if (rp == 32) return causal || (nkb <= 6 ? nkb != 4 || r.rounds <= 10 : r.fill >= (r.rounds <= 4 ? 0.8 : 0.9));
+    if (nkb <= 2) return r.rounds <= 12;
+    if (causal) {
+        if (nkb == 3 || nkb == 4 || nkb == 7) return r.rounds == 2 || r.rounds == 4;
+        return (nkb != 5 && nkb != 6) || r.rounds < 6 || r.fill >= 0.9;
+    }
+    if (nkb <= 4) return false;
+    return r.rounds <= (nkb == 7 ? 3 : nkb == 8 ? 4 : r.rounds) && r.fill >= 1.0 - 0.33 / (double)r.rounds;
+}
+
 bool fb_short_bwd(const BwdParams& p, int C, int rp) {
     if (C > 32 || rp > 32 || p.grad_f32 || p.slopes != nullptr) return false;
     const int nkb = (p.M + 31) / 32, nqb = (p.N + 31) / 32;
     if (nkb > kMaxWaves || nqb > nkb) return false;
     const long long BH = (long long)p.B * p.H;
     if (BH >= (1LL << 30)) return false;
-    if (rp == 0) return p.causal && nkb > 5;
-    if (p.phi_f32 || p.R % 4 != 0) return false;
-    return p.causal || nkb <= 6 || nqb <= 4 || BH * 256 >= (long long)(C == 16 ? 8 : 16) * nkb * fb_cu_count();
+    if (rp == 0 ? !p.causal || nkb <= 5 : p.phi_f32 || p.R % 4 != 0) return false;
+    const int cus = fb_cu_count();
+    if (cus <= 0) return false;
+    if (!p.causal && nkb > 6 && nqb > 4 && BH * 256 < (long long)(C == 16 ? 8 : 16) * nkb * cus) return false;
+    return nqb * 4 <= nkb * 3 || rounds_pay(C, rp, nkb, p.causal, fb_head_rounds(BH, cus));
 }
 
 int fb_launch_bwd_bf16_short(const BwdParams& p, int C, int rp, hipStream_t stream) {

@@ -349,19 +349,20 @@ int dispatch_rp(const FwdParams& p, int rp, int nw, int cus, hipStream_t stream)
 
 }  // namespace
 
-// Self-attention whose keys fit LDS twice.  Kernel times against the ring kernel's (start / this, us), full attention,
-// bf16 factors unless said:
-//   up to 128 keys it is the faster one throughout (C 32, R 16: 1.1-1.2, N 64 with 1024 heads 7.7 / 5.5; C 16 1.05-1.1);
-//   up to 256 keys at C 32 (R 16: 0.98 at 64 heads to 1.25 at 256; R 4 1.0-1.27), beyond from 128 heads on, as one
-//   workgroup takes a whole head (N 384: 64 heads 8.4 / 10.8, 256 heads 16.0 / 12.8, 1024 heads 45.6 / 43.6);
-//   factor blocks of 32 columns at C 32 spill a few registers: beyond 128 keys only where the heads fill one round of
-//   workgroups (256 heads 1.1-1.2, 1024 heads 0.90-0.94);
-//   no factors, or C 16 with R 8 (N 256: 0.9-1.1): not beyond 128 keys; C 16 with other factors as C 32.
+// Self-attention whose keys fit LDS twice.  Kernel times against the ring kernel's (ring / this), 16 to 4096 heads of every
+// length in steps of 32, 256 CUs.  Heads are dealt one at a time to a workgroup that stays, so what counts beyond one head a
+// CU is how full the last round is; the ring kernel's tiles have rounds of their own, three times finer.
+// Full attention, bf16 factors:
+//   up to 128 keys it is the faster one throughout (C 32, R 16 1.0-1.7; C 16 1.0-2.1; no factors 1.0);
+//   C 32 beyond: below five eighths of the CUs 0.94-1.0; one round 1.13-1.24 (up to 192 keys 1.20); two rounds 0.85-0.96
+//   where the second is nearly empty (280 heads), 1.04-1.10 where it is full; then up to 192 keys 0.97-1.12, up to 256 keys
+//   1.0-1.05 in a full third round and 0.91-0.98 after it, beyond 256 keys 1.0-1.13 in full rounds and 0.85-0.97 in others;
+//   C 16: the same shape of line, some 5 % (up to 256 keys) and 15 % (beyond) higher;
+//   32 factor columns at C 32: only where the heads fill one round (1.10-1.35; the last round's spills 0.90-0.94);
+//   no factors, or C 16 with R 8: 0.95-1.02, not beyond 128 keys (at 128 in many rounds 0.93-0.96).
 //   fp32 factors are split once a head, but only by one workgroup: 0.7-0.95, never.
-// Causal the ring kernel's 128-row tiles do up to twice the work: 1.2-2.3 throughout (C 32, N 256: 256 heads 14.7 / 7.6,
-// 1024 heads 27.7 / 24.4), but for 32 factor columns at many heads (0.95-0.98) and fp32 factors (N 384: 44.1 / 31.5,
-// N 256: 256 heads 18.6 / 12.9, 400 heads 21.4 / 21.7).
-// Head counts are lines in rounds of workgroups, measured at 256 CUs: one and two rounds, five eighths and half of one.
+// Causal the ring kernel's 128-row tiles do up to twice the work: 1.04-1.9 throughout, but for 32 factor columns at many
+// heads (0.95-0.98) and fp32 factors (N 256: 256 heads 18.6 / 12.9 us, 400 heads 21.4 / 21.7).
 bool fb_short_fwd(const FwdParams& p, int C, int rp) {
     if (C > 32 || rp > 32 || p.N != p.M || p.slopes != nullptr) return false;
     const long long BH = (long long)p.B * p.H;
@@ -371,13 +372,21 @@ bool fb_short_fwd(const FwdParams& p, int C, int rp) {
                                : (rp == 0 ? Cfg<32, 0>::kRow : rp == 16 ? Cfg<32, 16>::kRow : Cfg<32, 32>::kRow);
     if ((size_t)2 * nkb * 32 * row > kLdsBytes) return false;
     const int cus = fb_cu_count();
+    if (cus <= 0) return false;
     if (rp > 0 && p.phi_f32) return p.causal && (nkb > 8 || (nkb > 4 && BH <= cus));
     const bool wide = C == 32 && rp == 32;
     if (p.causal) return !wide || nkb <= 4 || nkb > 8 || BH <= 2LL * cus;
-    if (nkb <= 4) return true;
-    if (rp == 0 || (C == 16 && rp == 16 && p.R % 8 == 0)) return false;
+    const FbHeadRounds r = fb_head_rounds(BH, cus);
+    const bool light = rp == 0 || (C == 16 && rp == 16 && p.R % 8 == 0);
+    if (nkb <= 4) return nkb <= 3 || !light || r.rounds <= 8;
+    if (light) return false;
     if (wide) return BH * 8 >= 5LL * cus && BH <= cus;
-    return nkb <= 8 || BH * 2 >= cus;
+    if (C == 32 ? BH * 8 < 5LL * cus : nkb > 8 && BH * 2 < cus) return false;
+    if (r.rounds == 1) return true;
+    if (C == 16) return r.fill >= (nkb > 8 ? 0.72 : r.rounds <= 3 ? 0.8 : 0.92);
+    if (nkb <= 6) return r.rounds > 2 || r.fill >= 0.8;
+    if (nkb <= 8) return r.rounds <= 3 && r.fill >= 0.85;
+    return r.fill >= (r.rounds == 2 ? 0.75 : 0.97);
 }
 
 int fb_launch_fwd_bf16_short(const FwdParams& p, int C, int rp, hipStream_t stream) {

@@ -72,6 +72,16 @@ inline bool fb_raise_lds_limit(const void* kern, size_t bytes, FbLdsOnce& once) 
     return true;
 }
 
+// Heads dealt to one workgroup a CU, head after head: how many the busiest CU gets, and how much of that all of them get.
+struct FbHeadRounds {
+    long long rounds;
+    double fill;
+};
+inline FbHeadRounds fb_head_rounds(long long heads, int cus) {
+    const long long rounds = (heads + cus - 1) / cus;
+    return {rounds, (double)heads / ((double)rounds * cus)};
+}
+
 // Compute units of the current device (0 on failure), asked once per device.
 inline int fb_cu_count() {
     static std::atomic<int> known[kFbMaxDevices] = {};

@@ -380,6 +380,7 @@ template <int C, int RP, bool CAUSAL, bool DKV, bool DENSE, bool LIMB, int CG, i
 FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem, const int bh, const int tile) {
     static_assert(!DENSE || RP == 0, "dense bias and factors are exclusive");
     constexpr bool ST = MODE == STORE, LD = MODE == LOAD;
+    static_assert(!ST || DENSE || (DKV && Cfg<C, RP, LIMB, CG>::PIPE), "dS is stored by the PIPE form alone");
     constexpr int WV = LD ? kWavesLd : kWaves, kRows = WV * 32;      // waves and lane-side rows of the workgroup
     static_assert((!ST || DKV) && (!LD || !DKV) && (MODE == RECOMPUTE || CG == C), "stored dS");
     using K = Cfg<C, RP, LIMB, CG>;
@@ -564,7 +565,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
         for (int i = 0; i < 2; i++) {
             const int trow = 16 * i + (lane >> 2), c = (lane & 3) ^ ((trow >> 2) & 3);
-            bias_var[i] = 0;
             bias_fix[i] = (unsigned)((c >> 1) * 1024 + trow * 32 + (c & 1) * 16);
         }
         bias_src = (const unsigned char*)(a.ds + (size_t)(bh - a.head0) * a.ds_rows * a.ds_pitch + (size_t)rw0 * 32);
@@ -577,9 +577,8 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
         const unsigned dst = lds0 + slot * kSlotBytes + kOffBias + wave * kBiasTile;
 #pragma unroll
         for (int x = 0; x < 2; x++) {
-            const unsigned voff = (unsigned)((LD && !DENSE ? bias_var[x] : min(bias_var[x], left >> bias_lshift)) * bias_pitch) + bias_fix[x];
-            if (LD && !DENSE) dma16nt(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
-            else dma16(bias_src + (size_t)blk * bias_bstep, voff, dst + x * 1024);
+            if (LD && !DENSE) dma16nt(bias_src + (size_t)blk * bias_bstep, bias_fix[x], dst + x * 1024);
+            else dma16(bias_src + (size_t)blk * bias_bstep, (unsigned)(min(bias_var[x], left >> bias_lshift) * bias_pitch) + bias_fix[x], dst + x * 1024);
         }
     };
     // all but the newest block's loads (plus `stores` global stores issued since) may remain
@@ -992,8 +991,7 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
 #pragma unroll
             for (int kk = 0; kk < 2; kk++) dcur[kk] = read_d(0, kk, blk_of(0));
         }
-        // causal: the dkv launch visits whole 128-row tiles; the blocks of a wave past its own are not there
-        const int b_own = CAUSAL ? min(b_end, (rw0 / 128 + 1) * 4) : b_end;
+        static_assert(!CAUSAL || kRows == 128, "the dkv launch leaves dS of whole 128-row tiles on and below the diagonal: the blocks walked here");
         int sl = 0;
         for (int i = 0; i < nIt; i++) {
             const int sln = sl + 1 == NS_ ? 0 : sl + 1, slp = sl == 0 ? NS_ - 1 : sl - 1;
@@ -1004,13 +1002,12 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             issue_block(i + NS_ - 1, slp);
             issue_bias(i + NS_ - 1, slp);
             bf16x8 nxt[LB], dn[2];
-            const bool own = !CAUSAL || i < b_own;      // wave-uniform
 #pragma unroll
             for (int n = 0; n < NO1; n++) {
                 if (n + LB < NO1) opd[(n + LB) % (LB + 1)] = tr_read1(tb0, (n + LB) >> 1, (n + LB) & 1);
                 else nxt[n + LB - NO1] = tr_read1(tbn, (n + LB - NO1) >> 1, (n + LB - NO1) & 1);
                 if (n >= NO1 - 2) dn[n - (NO1 - 2)] = read_d(offn, n - (NO1 - 2), blk_of(i + 1));
-                if (own) acc1[n >> 1] = mfma32(opd[n % (LB + 1)], dcur[n & 1], acc1[n >> 1]);
+                acc1[n >> 1] = mfma32(opd[n % (LB + 1)], dcur[n & 1], acc1[n >> 1]);
             }
 #pragma unroll
             for (int n = 0; n < LB; n++) opd[n] = nxt[n];
@@ -1120,8 +1117,6 @@ FB_DEV void bwd_tile(const BwdParams& p, const MainArgs& a, unsigned char* smem,
             __syncthreads();
             issue_block(i + 3, (i + 3) & (NSLOT - 1));
             issue_bias(i + 3, (i + 3) & (NSLOT - 1));
-
-            store_ds(dsb, sb0);
 
             // ---------------- dBias = dS, issued behind the loads: a store has two blocks' time before anything waits for
             // it (dq, B 8, H 12, N 1024, C 64: 110 -> 100 us) ----------------
@@ -1296,7 +1291,7 @@ int stored_heads(long long heads, int N, int M, bool causal, size_t room) {
 }
 
 // Pre-pass and the two main kernels.  DENSE: the bias is a dense matrix streamed tile by tile
-// (RP = 0) and the dq kernel also writes dBias.
+// (RP = 0) and the dq kernel, or where dBias is read back as dS the dkv kernel, also writes dBias.
 template <int C, int RP, bool CAUSAL, bool DENSE, bool LIMB, int CG>
 int launch(const BwdParams& pin, hipStream_t stream) {
     using K = Cfg<C, RP, LIMB, CG>;

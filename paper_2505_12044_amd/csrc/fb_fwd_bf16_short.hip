@@ -21,7 +21,7 @@
 
 namespace {
 
-constexpr int kMaxWaves = 12;          // three waves per SIMD: 168 registers
+constexpr int kMaxWaves = 12;          // three waves per SIMD: 168 registers, and none saved for a fourth (amdgpu_waves_per_eu)
 constexpr size_t kLdsBytes = 160 * 1024;
 constexpr float kSumLimit = 256.0f;    // see fb_fwd_bf16_impl.h
 
@@ -46,12 +46,13 @@ FB_DEV void dma16(const void* sbase, unsigned voff, unsigned lds_addr) {
 
 // PM: 0 = no factors, 1 = bf16 factors in whole 16-byte pieces (R % 8 == 0), 2 = bf16 factors of any R, 3 = fp32 factors
 template <int CG, int RP, int PM, bool CAUSAL>
-__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_short_kernel(FwdParams p, int units, int upr) {
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(3, 3))) void fwd_short_kernel(FwdParams p, int heads) {
     using K = Cfg<CG, RP>;
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr bool F32 = PM == 3;
     constexpr bool FOLD = score_log2e(CG, F32);
     const float emul = FOLD ? 1.f : kLog2e;
+    // N = M: a wave to every 32 queries and to every 32 keys, so a head's factor pieces are PIT whole rounds of threads
     const int N = p.N, M = p.M, R = p.R;
     const int NT = blockDim.x, nw = NT >> 6;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -76,7 +77,6 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         }
     };
     // ---- factor rows, piece by piece through registers ----
-    const int n_phi = Mp * K::PCH;
     auto phi_piece = [&](int bh, int e) __attribute__((always_inline)) {
         const int b = bh / p.H, h = bh - b * p.H;
         const unsigned row = min((unsigned)e / (K::PCH > 0 ? K::PCH : 1), (unsigned)(M - 1));
@@ -91,14 +91,16 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         const int c8 = (unsigned)e % (K::PCH > 0 ? K::PCH : 1);
         *(u32x4*)(smem + buf + poff0 + row * K::PP + c8 * 16) = PM == 1 ? raw : as_uint4(phi_chunk_finish<false>(raw, c8, F32));
     };
-    constexpr int PIT = K::PCH / 2 > 0 ? K::PCH / 2 : 1;      // pieces a thread keeps in flight: all of them where N >= M
+    constexpr int PIT = K::PCH / 2;      // pieces of a thread, in flight together
+    static_assert(2 * PIT == K::PCH, "whole rounds");
 
     // ---- query rows: raw in registers while they travel ----
     u32x4 qraw[K::KC];
     bf16x8 qphi[RP / 16 > 0 ? RP / 16 : 1];
-    auto load_q = [&](int unit, int bh) __attribute__((always_inline)) {
+    const int qw0 = wave * 32;      // first query row of this wave
+    auto load_q = [&](int bh) __attribute__((always_inline)) {
         const int b = bh / p.H, h = bh - b * p.H;
-        const int qi = min(((unit - bh * upr) * nw + wave) * 32 + l32, N - 1);
+        const int qi = min(qw0 + l32, N - 1);
         const bf16_t* q = (const bf16_t*)p.q + ((size_t)bh * N + qi) * CG + 8 * hf;
 #pragma unroll
         for (int ks = 0; ks < K::KC; ks++) qraw[ks] = *(const u32x4*)(q + ks * 16);
@@ -113,12 +115,12 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         }
     };
 
-    int unit = blockIdx.x;
-    if (unit >= units) return;
-    int bh = unit / upr;
+    int bh = blockIdx.x;
+    if (bh >= heads) return;
     issue_kv(bh, 0);
-    load_q(unit, bh);
-    for (int e = tid; e < n_phi; e += NT) phi_store(0, e, phi_piece(bh, e));
+    load_q(bh);
+#pragma unroll
+    for (int it = 0; it < PIT; it++) phi_store(0, tid + it * NT, phi_piece(bh, tid + it * NT));
     __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
     __syncthreads();
 
@@ -137,11 +139,8 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
     unsigned buf = 0;
     for (;;) {
         const unsigned nbuf = buf_bytes - buf;
-        const int qw0 = ((unit - bh * upr) * nw + wave) * 32;       // first query row of this wave
-        const int next = unit + (int)gridDim.x;
-        const bool more = next < units;                             // workgroup-uniform
-        const int nbh = more ? next / upr : bh;
-        const bool fresh = nbh != bh;                               // another head's rows have to be staged
+        const int next = bh + (int)gridDim.x;
+        const bool more = next < heads;                             // workgroup-uniform
 
         bf16x8 qreg[K::KS];
         const float qscale = FOLD ? p.scale * kLog2e : p.scale;
@@ -155,14 +154,13 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
                 qreg[ks] = qphi[ks - K::KC];
             }
         }
-        // everything the next unit reads is requested here and met at the end of this one
-        u32x4 praw[PIT];
-        if (fresh) issue_kv(nbh, nbuf);
-        if (more) load_q(next, nbh);
-        if (RP > 0 && fresh) {
+        // everything the next head reads is requested here and met at the end of this one
+        u32x4 praw[PIT > 0 ? PIT : 1];
+        if (more) {
+            issue_kv(next, nbuf);
+            load_q(next);
 #pragma unroll
-            for (int it = 0; it < PIT; it++)
-                if (tid + it * NT < n_phi) praw[it] = phi_piece(nbh, tid + it * NT);
+            for (int it = 0; it < PIT; it++) praw[it] = phi_piece(next, tid + it * NT);
         }
 
         f32x16 oacc;
@@ -265,26 +263,19 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         using One = std::integral_constant<int, 1>;
         using Two = std::integral_constant<int, 2>;
 
-        if (qw0 < N) {      // wave-uniform
-            using Yes = std::true_type;
-            using No = std::false_type;
-            using Tail = std::integral_constant<bool, !CAUSAL>;
-            const int diag = min(qw0 >> 5, nkb - 1);
-            const int whole = CAUSAL ? diag : M >> 5, end = CAUSAL ? diag : nkb;      // blocks without masks, all blocks but the first taken
-            step(CAUSAL ? diag : 0, One{}, Yes{}, Yes{});
-            int kb = CAUSAL ? 0 : 1;
-            for (; kb + 2 <= whole; kb += 2) step(kb, Two{}, No{}, No{});
-            for (; kb < end; kb++) step(kb, One{}, No{}, Tail{});
-        }
-        if (fresh) {
+        using Yes = std::true_type;
+        using No = std::false_type;
+        using Tail = std::integral_constant<bool, !CAUSAL>;
+        const int whole = CAUSAL ? wave : M >> 5, end = CAUSAL ? wave : nkb;      // blocks without masks; all blocks but the first one taken
+        step(CAUSAL ? wave : 0, One{}, Yes{}, Yes{});
+        int kb = CAUSAL ? 0 : 1;
+        for (; kb + 2 <= whole; kb += 2) step(kb, Two{}, No{}, No{});
+        for (; kb < end; kb++) step(kb, One{}, No{}, Tail{});
+        if (more) {
             // the next head's rows have landed before anyone reads them; the stores of the results follow behind the
-            // barrier, so nothing waits for them until the next unit ends
-            if (RP > 0) {
+            // barrier, so nothing waits for them until the next head ends
 #pragma unroll
-                for (int it = 0; it < PIT; it++)
-                    if (tid + it * NT < n_phi) phi_store(nbuf, tid + it * NT, praw[it]);
-                for (int e = tid + PIT * NT; e < n_phi; e += NT) phi_store(nbuf, e, phi_piece(nbh, e));
-            }
+            for (int it = 0; it < PIT; it++) phi_store(nbuf, tid + it * NT, praw[it]);
             __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
             __syncthreads();
         }
@@ -305,25 +296,23 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
             if (hf == 0) p.lse[(size_t)bh * N + qi] = (mref + __log2f(ltot)) * kLn2;
         }
         if (!more) break;
-        if (fresh) buf = nbuf;
-        unit = next;
-        bh = nbh;
+        buf = nbuf;
+        bh = next;
     }
 }
 
 template <int CG, int RP, int PM, bool CAUSAL>
-int launch(const FwdParams& pin, int nw, int cus, hipStream_t stream) {
+int launch(const FwdParams& p, int nw, int cus, hipStream_t stream) {
     using K = Cfg<CG, RP>;
     auto kern = fwd_short_kernel<CG, RP, PM, CAUSAL>;
     static FbLdsOnce once;
     if (!fb_raise_lds_limit((const void*)kern, kLdsBytes, once)) return 1;
-    const int upr = (pin.N + 32 * nw - 1) / (32 * nw);
-    const long long units = (long long)pin.B * pin.H * upr;
-    const size_t lds = (size_t)2 * ((pin.M + 31) / 32 * 32) * K::kRow;
+    const int heads = p.B * p.H;
+    const size_t lds = (size_t)2 * (32 * nw) * K::kRow;
     // workgroups that stay resident: by LDS and by the twelve waves that the registers allow
     const long long per_cu = kMaxWaves / nw < (int)(kLdsBytes / lds) ? kMaxWaves / nw : (long long)(kLdsBytes / lds);
     const long long most = (long long)cus * (per_cu < 1 ? 1 : per_cu);
-    hipLaunchKernelGGL(kern, dim3((unsigned)(units < most ? units : most)), dim3(64 * nw), lds, stream, pin, (int)units, upr);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(heads < most ? heads : most)), dim3(64 * nw), lds, stream, p, heads);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

@@ -441,7 +441,8 @@ int dispatch_rp(const BwdParams& p, int rp, int cus, hipStream_t stream) {
 //   six waves only stage rows); up to 192 keys 1.05-1.3 in one round, 1.0-1.18 in full rounds, 0.88-0.97 in others; 224 and
 //   256 keys the same, but no more than 0.92-1.0 from the fourth and fifth round on; beyond 256 keys 1.02-1.25 in full rounds,
 //   0.85-0.98 in others.  Causal: 1.0-1.7, but for 65 to 128 and 224 keys (0.86-1.0 in three rounds and from five on) and 160
-//   and 192 keys in many rounds that are not full (0.95).
+//   and 192 keys in many rounds that are not full (0.95).  (Full enough: the other kernels take 128 rows to a workgroup, three a
+//   CU, so up to 256 keys 1.5 heads a CU are one round of theirs and 1.6 are two: 384 heads 0.91, 400 heads 1.28.)
 //   32 columns: 1.05-1.9 up to 192 keys (65 to 128 in many rounds 0.91-0.95), beyond 1.0-1.4 in rounds that are full enough;
 //   causal 1.0-2.0.
 //   C 16 (two 16-column groups, no dead rows): 1.07-2.4, but for 65 to 96 keys in many rounds (0.87-0.98).
@@ -461,7 +462,8 @@ static bool rounds_pay(int C, int rp, int nkb, bool causal, const FbHeadRounds r
         return (nkb != 5 && nkb != 6) || r.rounds < 6 || r.fill >= 0.9;
     }
     if (nkb <= 4) return false;
-    return r.rounds <= (nkb == 7 ? 3 : nkb == 8 ? 4 : r.rounds) && r.fill >= 1.0 - 0.33 / (double)r.rounds;
+    const double least = r.rounds == 2 ? 0.76 : r.rounds > 3 ? 1.0 - 0.33 / (double)r.rounds : nkb <= 6 || nkb == 8 ? 0.8 : 0.9;
+    return r.rounds <= (nkb == 7 ? 3 : nkb == 8 ? 4 : r.rounds) && r.fill >= least;
 }
 
 bool fb_short_bwd(const BwdParams& p, int C, int rp) {

@@ -372,9 +372,9 @@ bool fb_short_fwd(const FwdParams& p, int C, int rp) {
     if (wide) return BH * 8 >= 5LL * cus && BH <= cus;
     if (C == 32 ? BH * 8 < 5LL * cus : nkb > 8 && BH * 2 < cus) return false;
     if (r.rounds == 1) return true;
-    if (C == 16) return r.fill >= (nkb > 8 ? 0.72 : r.rounds <= 3 ? 0.8 : 0.92);
-    if (nkb <= 6) return r.rounds > 2 || r.fill >= 0.8;
-    if (nkb <= 8) return r.rounds <= 3 && r.fill >= 0.85;
+    if (C == 16) return r.fill >= (nkb > 8 ? 0.72 : r.rounds == 2 ? 0.76 : r.rounds == 3 ? 0.8 : 0.92);
+    if (nkb <= 6) return r.rounds > 2 || r.fill >= 0.76;
+    if (nkb <= 8) return r.rounds <= 3 && r.fill >= (r.rounds == 2 ? 0.76 : 0.85);
     return r.fill >= (r.rounds == 2 ? 0.75 : 0.97);
 }
 

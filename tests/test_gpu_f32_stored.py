@@ -98,8 +98,12 @@ def test_same_bits_with_any_workspace(N, M, causal, C, R, scale):
     for heads in (60, 35, 0):
         room = d + heads * _up(N) * _up(M) * 4
         # (none: the sizes are such that the least workspace leaves no room for it)
-        ws = torch.empty(max(least, room), dtype=torch.uint8, device="cuda")
+        ws = torch.full((max(least, room),), 0xA5, dtype=torch.uint8, device="cuda")
         got.append(bwd(q, k, v, pq, pk, out, lse, do, workspace=ws, **kw))
+        per = _up(N) * _up(M) * 4      # dS of the heads of one launch, nothing behind it; D alone where none fits
+        n = {60: 60, 35: 30 if 30 * min(_up(N), _up(M)) // 32 >= 512 else 0, 0: 0}[heads]      # (two launches have to fill the chip)
+        assert bool((ws[d:d + n * per].view(n, per) != 0xA5).any(1).all()) if n else not bool((ws[d:] != 0xA5).any())
+        assert not bool((ws[d + n * per:] != 0xA5).any())
     if N == M:
         grads = tuple(None if x is None else torch.empty_like(x) for x in got[0])
         got.append(api.fb_lowrank_attn_bwd_noalloc(q, k, v, pq, pk, out, lse, do, grads, **kw))
@@ -108,3 +112,22 @@ def test_same_bits_with_any_workspace(N, M, causal, C, R, scale):
         for name, x, y in zip(NAMES, got[0], other):
             if x is not None:
                 assert torch.equal(x, y), (name, n, float((x - y).abs().max()))
+
+
+@pytest.mark.parametrize("heads,N,causal", [(20000, 1, False), (9000, 5, True), (3000, 33, False)])
+def test_very_many_short_heads(heads, N, causal):
+    """One partial tile (or two) a head, thousands of heads to a launch: against float64, every head."""
+    torch.manual_seed(N)
+    C, R = 32, 3
+    t = lambda *s: torch.randn(*s, device="cuda")
+    q, k, v, do, pq, pk = t(heads, 1, N, C), t(heads, 1, N, C), t(heads, 1, N, C), t(heads, 1, N, C), t(heads, 1, N, R), t(heads, 1, N, R)
+    out, lse = api.fb_lowrank_attn_fwd(q, k, v, pq, pk, causal=causal)
+    got = api.fb_lowrank_attn_bwd(q, k, v, pq, pk, out, lse, do, causal=causal)
+    leaves = [x.double().requires_grad_() for x in (q, k, v, pq, pk)]
+    s = leaves[0] @ leaves[1].transpose(-1, -2) * C ** -0.5 + leaves[3] @ leaves[4].transpose(-1, -2)
+    if causal:
+        s = s.masked_fill(torch.ones(N, N, device="cuda").triu(1).bool(), float("-inf"))
+    ref = torch.autograd.grad(s.softmax(-1) @ leaves[2], leaves, do.double())
+    for name, x, y in zip(NAMES, got, ref):
+        big = max(1.0, float(y.abs().max()))
+        assert float((x.double() - y).abs().max()) <= 1e-4 * big, name

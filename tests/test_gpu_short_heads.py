@@ -132,6 +132,32 @@ def test_recomputes_the_scores_of_the_two_kernel_backward(M, C, R, level):
         assert float((x.float() - y.float()).norm() / y.float().norm()) <= 1e-3, name
 
 
+@pytest.mark.parametrize("N,kept", [(64, 20), (200, 150), (200, 33), (384, 32)])
+@pytest.mark.parametrize("C", [16, 32])
+@pytest.mark.parametrize("causal", [False, True])
+def test_key_padding(N, kept, C, causal):
+    """A factor column that masks the keys from `kept` on: whole blocks of a row hold nothing but the mask, the diagonal one
+    (which gives a causal row its reference maximum) and the last among them."""
+    rng = np.random.default_rng(N + kept + C)
+    rd = lambda *s: W.round_bf16(rng.standard_normal(s).astype(np.float32))
+    B, H, R = 64, 4, 8
+    q, k, v, dout = rd(B, H, N, C), rd(B, H, N, C), rd(B, H, N, C), rd(B, H, N, C)
+    pq, pk = 0.5 * rd(1, H, N, R), 0.5 * rd(1, H, N, R)
+    pq[..., 0], pk[..., 0] = 1.0, np.where(np.arange(N) < kept, 0.0, -2.0 ** 14)
+    d = [dev(x, "bf16") for x in (q, k, v, pq, pk)]
+    out, lse = api.fb_lowrank_attn_fwd(*d, causal=causal)
+    grads = api.fb_lowrank_attn_bwd(*d, out, lse, dev(dout, "bf16"), causal=causal)
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (63, 3)):
+        label = f"padding N{N} kept {kept} C{C} causal={causal} ({b},{h})"
+        ro, rl = O.attention_lowrank(q[b, h], k[b, h], v[b, h], pq[0, h], pk[0, h], causal=causal)
+        check_fwd(label, "out", host(out[b, h]), ro)
+        check_fwd(label, "lse", host(lse[b, h]), rl)
+        ref = O.attention_lowrank_grads(q[b, h], k[b, h], v[b, h], pq[0, h], pk[0, h], dout[b, h], causal=causal)
+        for name, g, r in zip(("dq", "dk", "dv", "dphi_k"), (*grads[:3], grads[4]), (*ref[:3], ref[4])):
+            check_grad(label, name, host(g[b, h]), r, data_scaled=True, gain=max(1.0, float(np.abs(pq).max())))
+
+
 @pytest.mark.parametrize("B", [90, 128])       # two heads to some workgroups (the longer kernels' call), to all
 def test_same_result_on_every_run(B):
     torch.manual_seed(5)

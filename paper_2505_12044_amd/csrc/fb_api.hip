@@ -415,14 +415,21 @@ static size_t bwd_ws_query(int B, int H, int N, int M, int C, int R, fb_dtype dt
     const size_t least = bwd_ws_impl(B, H, N, M, C, R);
     if (least == 0) return 0;
     if (dtype != FB_F32) return least + stored_room(B, H, N, M, C);
-    const size_t f32 = fb_bwd_f32_workspace_bytes((long long)B * H, N, M, C);
-    return f32 > least ? f32 : least;
+    size_t most = least;
+    for (int causal = 0; causal <= (N == M ? 1 : 0); causal++) {
+        const size_t f32 = fb_bwd_f32_workspace_bytes((long long)B * H, N, M, C, causal != 0);
+        if (f32 > most) most = f32;
+    }
+    return most;
 }
 
 size_t fb_attn_bwd_call_workspace_bytes(int B, int H, int N, int M, int C, int R, int causal, fb_dtype dtype) {
-    if (causal < 0 || dtype == FB_F32) return causal < 0 ? bwd_ws_impl(B, H, N, M, C, R) : bwd_ws_query(B, H, N, M, C, R, dtype);
     const size_t least = bwd_ws_impl(B, H, N, M, C, R);
-    return least == 0 ? 0 : least + fb_bwd_stored_bytes((long long)B * H, N, M, C, causal != 0);
+    if (causal < 0 || least == 0) return least;
+    const long long heads = (long long)B * H;
+    if (dtype != FB_F32) return least + fb_bwd_stored_bytes(heads, N, M, C, causal != 0);
+    const size_t f32 = fb_bwd_f32_workspace_bytes(heads, N, M, C, causal != 0);
+    return f32 > least ? f32 : least;
 }
 
 static int lowrank_bwd_impl(const void* q, const void* k, const void* v,

@@ -48,20 +48,29 @@ constexpr size_t kMaxStored = (size_t)1 << 30;
 // Heads whose dS the workspace takes at a time, 0 where the query side recomputes it.  Stored against recomputed,
 // kernel times (us): C 32, R 8 64 heads of N 1024 333 / 290; C 64 16 heads of N 1500 372 / 301; C 128 790 / 553; from
 // the smallest calls on (C 64, 2 heads of 256 34 / 29), where one launch more costs the host what it saves: left to
-// recompute below about 60 us.  Neither the mask nor short heads move the line (backward calls, before / now): causal C 32,
-// 64 heads of 1024 323 / 263; C 64, 262144 heads of one row 13455 / 10948, 4096 of 65 causal 628 / 525, 4096 of 4 x 512
+// recompute below about 60 us.  In one launch neither the mask nor short heads move the line (backward calls, before / now):
+// causal C 32, 64 heads of 1024 323 / 263; C 64, 262144 heads of one row 13455 / 10948, 4096 of 65 causal 628 / 525, 4096 of 4 x 512
 // 1549 / 1218.  Not at 16 channels: a block's recomputation takes 1300 cycles of the matrix pipe, its
 // 8 KB to memory and back more.
-int stored_heads(long long heads, int N, int M, int C, size_t avail) {
+// Several launches (C 32 and 64; at 128 channels 1.06-2.0 throughout): each has a tail of its own.  Of 2048 waves at a time
+// (f32_split) one tile each, a launch of 2204 tiles takes two rounds: C 64, 76 heads of N 3700 9554 / 10385 us, cut smaller 9528 / 8305.
+// Causal tiles differ in length, and a launch's few heads fall unevenly on the XCDs: N 3700, 38 to 120 heads 0.77-0.92, N 8192,
+// 16 heads 0.83, N 2500 and 3000 0.95-1.13, up to N 2000 (4096 tiles a launch) 0.98-1.26: from there on.
+int stored_heads(long long heads, int N, int M, int C, bool causal, size_t avail) {
     if (avail > kMaxStored) avail = kMaxStored;
-    const long long fit = (long long)(avail / ds_head_bytes(N, M));
+    long long fit = (long long)(avail / ds_head_bytes(N, M));
     if (fit <= 0) return 0;
-    const long long parts = (heads + fit - 1) / fit, chunk = (heads + parts - 1) / parts;
-    // several launches have to be worth filling the chip (four waves to a 32-row tile)
-    const long long nq = ((long long)N + 31) / 32, nk = ((long long)M + 31) / 32;
+    const long long nq = ((long long)N + 31) / 32, nk = ((long long)M + 31) / 32, tiles = nq < nk ? nq : nk;
     if ((double)heads * nq * nk * C < 262144.0) return 0;
-    if (parts > 1 && chunk * (nq < nk ? nq : nk) < 512) return 0;
-    return (int)chunk;
+    for (;;) {
+        const long long parts = (heads + fit - 1) / fit, chunk = (heads + parts - 1) / parts;
+        if (parts == 1) return (int)heads;
+        // worth filling the chip (four waves to a 32-row tile)
+        if (chunk * tiles < (causal && C <= 64 ? 4096 : 512)) return 0;
+        const long long whole = chunk * tiles / 2048 * 2048;
+        if (causal || whole == 0 || chunk * tiles * 10 >= (whole + 2048) * 6 || chunk * tiles == whole || whole < tiles) return (int)chunk;
+        fit = whole / tiles;      // fewer heads, full rounds
+    }
 }
 
 template <int C, int RP, bool KEYSIDE>
@@ -505,7 +514,7 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_f32_dq_kernel(BwdParams p, co
 template <int C, bool DENSE>
 long long planned_heads(const BwdParams& p) {
     const long long heads = (long long)p.B * p.H;
-    const int chunk = C < 32 || DENSE ? 0 : stored_heads(heads, p.N, p.M, C, kMaxStored);
+    const int chunk = C < 32 || DENSE ? 0 : stored_heads(heads, p.N, p.M, C, p.causal != 0, kMaxStored);
     return chunk > 0 ? chunk : heads;
 }
 
@@ -558,7 +567,7 @@ int launch(const BwdParams& p, hipStream_t stream) {
         int exponent = 0;
         const bool pow2 = std::frexp(p.scale, &exponent) == 0.5f;
         const size_t off = d_bytes((long long)p.B * p.H * p.N);
-        const int chunk = stored_heads((long long)p.B * p.H, p.N, p.M, C, p.workspace_bytes > off ? p.workspace_bytes - off : 0);
+        const int chunk = stored_heads((long long)p.B * p.H, p.N, p.M, C, p.causal != 0, p.workspace_bytes > off ? p.workspace_bytes - off : 0);
         float* const dS = (float*)((unsigned char*)p.workspace + off);
         if (chunk > 0) return pow2 ? launch_stored<C, RP, false>(p, dS, chunk, stream) : launch_stored<C, RP, true>(p, dS, chunk, stream);
         if (!pow2) {
@@ -583,8 +592,8 @@ int dispatch_c(const BwdParams& p, hipStream_t stream) {
 
 // Workspace with which the query side takes dS from the key side, by the rule and in the parts of the launch; 0 where it
 // recomputes dS in any case.
-size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C) {
-    const int chunk = C < 32 ? 0 : stored_heads(heads, N, M, C, kMaxStored);
+size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C, bool causal) {
+    const int chunk = C < 32 ? 0 : stored_heads(heads, N, M, C, causal, kMaxStored);
     return chunk > 0 ? d_bytes(heads * N) + (size_t)chunk * ds_head_bytes(N, M) : 0;
 }
 

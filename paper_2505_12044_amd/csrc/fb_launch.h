@@ -35,7 +35,7 @@ size_t fb_bwd_workspace_bytes(long long rows_q, long long rows_k, int C, int R);
 size_t fb_bwd_stored_bytes(long long heads, int N, int M, int C, bool causal);
 // fp32 tensors and fp32 factors: p.workspace holds one float per query row (a prefix of the size above) and, where
 // p.workspace_bytes allows it (fb_bwd_f32_workspace_bytes; 0: no use for more), dS of some or all heads behind them.
-size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C);
+size_t fb_bwd_f32_workspace_bytes(long long heads, int N, int M, int C, bool causal);
 int fb_launch_bwd_f32(const BwdParams& p, int C, hipStream_t stream);
 int fb_launch_bwd_dense_f32(const BwdParams& p, int C, hipStream_t stream);
 // Dense-bias backward (p.bias, p.dbias, p.bias_bstride set; p.R = 0; workspace as above with R = 0).

@@ -222,19 +222,29 @@ def _stored_heads_bf16(heads, N, M, causal):
     return best, per
 
 
-def _stored_heads_f32(heads, N, M, C):
+def _stored_heads_f32(heads, N, M, C, causal, room=1 << 30):
+    """Parts of equal size; where a part's tiles spill a little into another round of 2048, parts of full rounds."""
     up = lambda n: -(-n // 32) * 32
     per, nq, nk = up(N) * up(M) * 4, -(-N // 32), -(-M // 32)
-    fit = (1 << 30) // per
+    fit = room // per
     if fit == 0 or heads * nq * nk * C < 262144:
         return 0, per
-    parts = -(-heads // fit)
-    chunk = -(-heads // parts)
-    return (0 if parts > 1 and chunk * min(nq, nk) < 512 else chunk), per
+    while True:
+        parts = -(-heads // fit)
+        chunk = -(-heads // parts)
+        tiles = chunk * min(nq, nk)
+        if parts == 1:
+            return heads, per
+        if tiles < (4096 if causal and C <= 64 else 512):
+            return 0, per
+        rounds = tiles / 2048
+        if causal or rounds < 1 or rounds >= 0.6 * (int(rounds) + 1) or rounds == int(rounds) or int(rounds) * 2048 < min(nq, nk):
+            return chunk, per
+        fit = int(rounds) * 2048 // min(nq, nk)
 
 
 SIZES = [(1, 1, 100), (4, 16, 256), (16, 16, 1000), (4, 16, 1024), (64, 4, 1024), (8, 8, 1100), (64, 4, 1536), (4, 16, 1500), (16, 60, 1100), (1, 16, 2048),
-         (4, 16, 4096), (3, 5, 3000), (40, 40, 800), (100, 50, 900), (33, 33, 1900), (2, 8, 8192), (1, 16, 8800), (2, 8, 10000), (1, 16, 12000), (1, 2, 16000), (2, 8, 16384),
+         (4, 16, 4096), (3, 5, 3000), (40, 40, 800), (100, 50, 900), (33, 33, 1900), (19, 4, 3700), (30, 4, 3716), (24, 3, 3000), (2, 8, 8192), (1, 16, 8800), (2, 8, 10000), (1, 16, 12000), (1, 2, 16000), (2, 8, 16384),
          (1, 1, 23168), (1, 1, 23169), (2, 8, 30000), (1 << 16, 4, 8), (1 << 18, 1, 1)]
 
 
@@ -254,10 +264,14 @@ def test_backward_asks_for_no_room_it_does_not_use(lib, B, H, N):
                 assert call(B, H, N, M, 128, R, causal, api.FB_BF16) == sizes[-1], (M, R, causal)
             assert lib.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, M, 128, R, api.FB_BF16) == (max(sizes) if M == N else sizes[0])
             for C in (32, 64, 128):
-                chunk, per = _stored_heads_f32(B * H, N, M, C)
-                need = max(_least(B, H, N, M, C, R), (B * H * N * 4 + 255 & ~255) + chunk * per if chunk else 0)
-                assert call(B, H, N, M, C, R, 0, api.FB_F32) == call(B, H, N, M, C, R, 1, api.FB_F32) == need
-                assert lib.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, M, C, R, api.FB_F32) == need
+                sizes = []
+                for causal in (0, 1):
+                    chunk, per = _stored_heads_f32(B * H, N, M, C, causal)
+                    # the launch finds the same part in that room
+                    assert chunk == 0 or _stored_heads_f32(B * H, N, M, C, causal, chunk * per)[0] == chunk
+                    sizes.append(max(_least(B, H, N, M, C, R), (B * H * N * 4 + 255 & ~255) + chunk * per if chunk else 0))
+                    assert call(B, H, N, M, C, R, causal, api.FB_F32) == sizes[-1], (C, causal)
+                assert lib.fb_lowrank_xattn_bwd_workspace_bytes(B, H, N, M, C, R, api.FB_F32) == (max(sizes) if M == N else sizes[0])
     assert call(B, H, N, N, 64, 8, 0, api.FB_BF16) == _least(B, H, N, N, 64, 8)
     assert lib.fb_alibi_attn_bwd_workspace_bytes(B, H, N, 128, api.FB_BF16) == lib.fb_lowrank_attn_bwd_workspace_bytes(B, H, N, 128, 2, api.FB_BF16)
     room = lib.fb_lowrank_attn_bwd_workspace_bytes(B, H, N, 128, 0, api.FB_BF16) - _least(B, H, N, N, 128, 0)

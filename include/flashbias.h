@@ -59,7 +59,7 @@ typedef enum {
     FB_ERR_SHAPE = 2,        /* B, H, N <= 0, R < 0, or sizes overflow the indexing */
     FB_ERR_UNSUPPORTED = 3,  /* C / R / dtype combination has no kernel             */
     FB_ERR_ALIGN = 4,        /* a pointer is not 16-byte aligned                    */
-    FB_ERR_WORKSPACE = 5,    /* workspace NULL or smaller than the size query says  */
+    FB_ERR_WORKSPACE = 5,    /* workspace NULL or smaller than the least the call takes */
     FB_ERR_LAUNCH = 6,       /* the HIP runtime rejected a launch                   */
     FB_ERR_TOO_LARGE = 7     /* problem needs more scratch than the allocation-free entry point owns */
 } fb_status;

@@ -349,7 +349,7 @@ int dispatch_rp(const FwdParams& p, int rp, int nw, int cus, hipStream_t stream)
 //   where the second is nearly empty (280 heads), 1.04-1.10 where it is full; then up to 192 keys 0.97-1.12, up to 256 keys
 //   1.0-1.05 in a full third round and 0.91-0.98 after it, beyond 256 keys 1.0-1.13 in full rounds and 0.85-0.97 in others;
 //   C 16: the same shape of line, some 5 % (up to 256 keys) and 15 % (beyond) higher;
-//   32 factor columns at C 32: only where the heads fill one round (1.10-1.35; the last round's spills 0.90-0.94);
+//   32 factor columns at C 32: only where the heads fill one round (1.10-1.35; beyond it 0.90-0.94, some registers spill);
 //   no factors, or C 16 with R 8: 0.95-1.02, not beyond 128 keys (at 128 in many rounds 0.93-0.96).
 //   fp32 factors are split once a head, but only by one workgroup: 0.7-0.95, never.
 // Causal the ring kernel's 128-row tiles do up to twice the work: 1.04-1.9 throughout, but for 32 factor columns at many

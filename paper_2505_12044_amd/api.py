@@ -144,8 +144,8 @@ def _scratch(nbytes: int, device, stream, least: Optional[Callable[[], int]] = N
 
 def _bwd_scratch(lib, B, H, N, M, C, R, causal, dtype_code, device, stream) -> torch.Tensor:
     """Workspace of one low-rank backward: with the room for dS that it uses (up to 1 GiB), without where memory is short."""
-    size = lambda mask: lib.fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, mask, dtype_code)
-    return _scratch(size(int(bool(causal))), device, stream, lambda: size(-1))
+    need = lib.fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, 1 if causal else 0, dtype_code)
+    return _scratch(need, device, stream, lambda: lib.fb_attn_bwd_call_workspace_bytes(B, H, N, M, C, R, -1, dtype_code))
 
 
 def _check(status: int, what: str) -> None:

@@ -82,7 +82,7 @@ def test_outgrown_reference(C, N):
     _run(64, 4, N, N, C, 8, "bf16", False, True, [(0, 0), (63, 3)], offset=30.0)
 
 
-@pytest.mark.parametrize("N", [20, 32, 64, 95, 224, 300, 384])
+@pytest.mark.parametrize("N", [20, 32, 64, 95, 129, 161, 192, 225, 256, 300, 384])
 @pytest.mark.parametrize("C,R,offset", [(16, 0, 0), (16, 12, 0), (32, 4, 0), (32, 16, 0), (32, 32, 0), (16, 12, 30), (32, 16, 30)])
 def test_rounds_as_the_ring_kernel_does(N, C, R, offset):
     """Full attention: the reference maximum comes from the same block and the sums follow in the same order as in the
@@ -107,7 +107,7 @@ def test_rounds_as_the_ring_kernel_does(N, C, R, offset):
     assert float((got[1] - ref[1]).abs().max()) <= 2 ** -21 * max(1.0, float(ref[1].abs().max()))
 
 
-@pytest.mark.parametrize("M", [20, 64, 95, 160, 300, 384])
+@pytest.mark.parametrize("M", [20, 64, 95, 160, 200, 225, 300, 384])
 @pytest.mark.parametrize("C,R", [(16, 8), (16, 28), (32, 4), (32, 16), (32, 32)])
 @pytest.mark.parametrize("level", [0.0, 2.0 ** 14])
 def test_recomputes_the_scores_of_the_two_kernel_backward(M, C, R, level):
